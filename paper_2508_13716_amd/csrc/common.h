@@ -39,17 +39,33 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 static inline int elem_bytes(int dtype) { return dtype == CAPGNN_BF16 ? 2 : 4; }
 static inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// One direction of the sparse operator: output row k sums over entries [ptr[k], ptr[k+1]).
-// Rows of a work list that are too long for one workgroup: the first n_rows positions of the list.  Each is cut
-// into pieces of GIANT_PIECE entries (the last one shorter); piece q belongs to position piece_pos[q], and the
-// pieces of position p are [piece_first[p], piece_first[p+1]).
-struct GiantList {
-    int64_t n_rows = 0;
-    int64_t n_pieces = 0;
-    const int32_t *piece_pos = nullptr;    // device [n_pieces]
-    const int32_t *piece_first = nullptr;  // device [n_rows + 1]
+// What one lane group of the aggregation kernel walks: a whole short row of the output, or a piece of a long one.
+struct alignas(16) RowItem {
+    int32_t row;
+    uint32_t beg, cnt;          // entries [beg, beg + cnt)
+    uint32_t unused;            // one 16-byte load per item
 };
 
+// Work list of one direction.  Rows of at least twice `piece` entries are cut into pieces (the last one shorter), whose
+// partial sums a second kernel adds in piece order; the pieces come first, then the other rows by entry count,
+// descending.  Piece q of cut row k is item piece_first[k] + q.
+struct ItemList {
+    int64_t n_items = 0, n_pieces = 0, n_cut = 0;
+    int64_t max_pieces = 0;                // of one row
+    const RowItem *items = nullptr;        // device [n_items]: n_pieces pieces, then whole rows
+    const RowItem *cut = nullptr;          // device [n_cut]: the cut rows, whole
+    const int32_t *piece_first = nullptr;  // device [n_cut + 1]
+    int64_t below[12] = {};                // below[k]: the first item after the pieces that has fewer than 2^k entries
+
+    // the same for the smallest power of two >= entries (at most 2048)
+    int64_t first_below(int entries) const {
+        int k = 0;
+        while (k < 11 && (1 << k) < entries) ++k;
+        return below[k];
+    }
+};
+
+// One direction of the sparse operator: output row k sums over entries [ptr[k], ptr[k+1]).
 struct SpOp {
     int64_t n_out = 0;          // rows of the output
     int64_t n_in = 0;           // rows of the gathered operand
@@ -64,15 +80,12 @@ struct SpOp {
     bool weights_by_source = false;
     const float *out_scale = nullptr; // device [n_out] or null
     const float *in_scale = nullptr;  // device [n_in]  or null
-    // work lists: output rows by entry count, descending; rows shorter than EXACT_ROW only by power-of-two class,
-    // in index order inside a class
+    // output rows by entry count, descending; rows shorter than EXACT_ROW only by power-of-two class, in index order
+    // inside a class
     const int32_t *order = nullptr;   // device [n_out]
-    int64_t n_long = 0;               // first n_long entries of `order` have >= LONG_ROW entries
-    int64_t n_sub = 0;                // rows [0, n_sub) of the output restricted list (bwd: local columns only)
-    const int32_t *order_sub = nullptr;
-    int64_t n_long_sub = 0;
+    int64_t n_sub = 0;                // rows [0, n_sub) of the output: the restricted list (bwd: local columns only)
     int64_t max_deg = 0;
-    GiantList giant, giant_sub;       // of `order` and of `order_sub`
+    ItemList list, list_sub;          // of all output rows, and of the restricted ones
     // Column-blocked copy of the entries (built for dense-degree operators whose gathered operand does not
     // fit an L2): entries regrouped by (source block cb = idx / CB_ROWS, position p in `order`), original
     // entry order kept inside a group.  Group (cb, p) = entries [b_off[cb*n_out+p], b_off[cb*n_out+p+1]).
@@ -88,9 +101,6 @@ struct SpOp {
 };
 
 constexpr int EXACT_ROW = 256;  // work lists sort rows at least this long by their exact entry count
-constexpr int LONG_ROW = 2048;  // rows at least this long are reduced by a whole workgroup
-constexpr int GIANT_ROW = 16384;  // rows at least this long are cut into pieces when the caller brings scratch
-constexpr int GIANT_PIECE = 4096; // entries per piece: one workgroup each, partial sums combined in piece order
 constexpr int CB_ROWS = 32768;  // source rows per column block: 32768 x 128-byte slices = 4 MB, one XCD's L2 (swept: 8192 .. 49152)
 constexpr int B_LONG_GROUP = 1024; // rows with at least this many entries per source block on average: workgroup per group (swept 256 .. 4096)
 constexpr int B_MID_GROUP = 256;  // ... at least this many: wave per group (swept 64 .. 1024; the eight-rows-per-wave class below is the fastest)

@@ -39,18 +39,26 @@ static int64_t order_key(int64_t len) {
     return k;
 }
 
-// Output rows [lo, hi) ordered by order_key (descending, ties by index); returns how many are "long".
-static int64_t degree_order(const std::vector<int64_t> &ptr, int64_t lo, int64_t hi, std::vector<int32_t> &order) {
+// Output rows [lo, hi) ordered by order_key, descending, ties by index: a counting sort over the keys (at most
+// EXACT_ROW power-of-two classes below, exact counts above).
+static void degree_order(const int64_t *ptr, int64_t lo, int64_t hi, std::vector<int32_t> &order) {
     order.resize(hi - lo);
-    std::iota(order.begin(), order.end(), static_cast<int32_t>(lo));
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        return order_key(ptr[a + 1] - ptr[a]) > order_key(ptr[b + 1] - ptr[b]);
-    });
-    int64_t n_long = 0;
-    while (n_long < static_cast<int64_t>(order.size()) &&
-           ptr[order[n_long] + 1] - ptr[order[n_long]] >= LONG_ROW)
-        ++n_long;
-    return n_long;
+    std::vector<int32_t> longer;
+    std::vector<int64_t> count(EXACT_ROW + 1, 0);
+    for (int64_t r = lo; r < hi; ++r) {
+        const int64_t k = order_key(ptr[r + 1] - ptr[r]);
+        if (k >= EXACT_ROW) longer.push_back(static_cast<int32_t>(r));
+        else ++count[k];
+    }
+    std::stable_sort(longer.begin(), longer.end(), [&](int32_t a, int32_t b) { return ptr[a + 1] - ptr[a] > ptr[b + 1] - ptr[b]; });
+    std::copy(longer.begin(), longer.end(), order.begin());
+    std::vector<int64_t> at(EXACT_ROW + 1, 0);
+    int64_t next = static_cast<int64_t>(longer.size());
+    for (int k = EXACT_ROW - 1; k >= 0; --k) { at[k] = next; next += count[k]; }
+    for (int64_t r = lo; r < hi; ++r) {
+        const int64_t k = order_key(ptr[r + 1] - ptr[r]);
+        if (k < EXACT_ROW) order[at[k]++] = static_cast<int32_t>(r);
+    }
 }
 
 // Per-entry weights val * in_scale[source] (the float product the kernels would otherwise form per entry).
@@ -71,23 +79,45 @@ static int upload_weights(capgnn_graph *g, int64_t nnz, const int32_t *idx, cons
     return upload(g, w.data(), w.size(), dev);
 }
 
-// Cuts the leading rows of a degree-ordered work list that have at least GIANT_ROW entries into pieces.
-static int upload_giant(capgnn_graph *g, const int64_t *ptr, const std::vector<int32_t> &order, GiantList *out) {
-    std::vector<int32_t> pos, first(1, 0);
-    int64_t n = 0;
-    for (; n < static_cast<int64_t>(order.size()); ++n) {
-        const int64_t len = ptr[order[n] + 1] - ptr[order[n]];
-        if (len < GIANT_ROW) break;
-        const int64_t pieces = (len + GIANT_PIECE - 1) / GIANT_PIECE;
-        pos.insert(pos.end(), pieces, static_cast<int32_t>(n));
-        first.push_back(static_cast<int32_t>(pos.size()));
+// Entries per piece of a cut row.  A lane group takes about a microsecond for 8 to 16 entries, so the longest item bounds
+// a small launch: about 4096 items' worth of entries each, between 64 (42 k entries: a row of 1000 entries in one piece
+// alone took 15 us) and 512 (above 2 M entries; the partial rows then cost under half a per cent of the gathered bytes).
+static int64_t piece_entries(int64_t nnz) {
+    int64_t p = 64;
+    while (p < 512 && p * 4096 < nnz) p *= 2;
+    return p;
+}
+
+// The work list (see ItemList) of a degree-ordered row list.
+static int upload_items(capgnn_graph *g, const int64_t *ptr, int64_t nnz, const std::vector<int32_t> &order, ItemList *out) {
+    const int64_t piece = piece_entries(nnz), n = static_cast<int64_t>(order.size());
+    std::vector<RowItem> items, cut;
+    std::vector<int32_t> first(1, 0);
+    items.reserve(n + 16);
+    int64_t k = 0;
+    for (; k < n; ++k) {
+        const int64_t beg = ptr[order[k]], len = ptr[order[k] + 1] - beg;
+        if (len < 2 * piece) break;          // rows this long are in exact descending order (2 * piece <= 1024 may fall
+                                             // into a power-of-two class: the classes are descending as well)
+        cut.push_back({order[k], static_cast<uint32_t>(beg), static_cast<uint32_t>(len), 0u});
+        for (int64_t q = 0; q < len; q += piece)
+            items.push_back({order[k], static_cast<uint32_t>(beg + q), static_cast<uint32_t>(std::min(piece, len - q)), 0u});
+        out->max_pieces = std::max(out->max_pieces, static_cast<int64_t>(items.size()) - first.back());
+        first.push_back(static_cast<int32_t>(items.size()));
     }
-    if (n == 0) return CAPGNN_OK;
-    CG_TRY(upload(g, pos.data(), pos.size(), &out->piece_pos));
-    CG_TRY(upload(g, first.data(), first.size(), &out->piece_first));
-    out->n_rows = n;
-    out->n_pieces = static_cast<int64_t>(pos.size());
-    return CAPGNN_OK;
+    out->n_cut = k;
+    out->n_pieces = static_cast<int64_t>(items.size());
+    int step = 11;                                      // powers of two are class limits: the list descends through them
+    for (; k < n; ++k) {
+        const int64_t beg = ptr[order[k]], len = ptr[order[k] + 1] - beg;
+        for (; step >= 0 && len < (int64_t(1) << step); --step) out->below[step] = static_cast<int64_t>(items.size());
+        items.push_back({order[k], static_cast<uint32_t>(beg), static_cast<uint32_t>(len), 0u});
+    }
+    for (; step >= 0; --step) out->below[step] = static_cast<int64_t>(items.size());
+    out->n_items = static_cast<int64_t>(items.size());
+    CG_TRY(upload(g, items.data(), items.size(), &out->items));
+    CG_TRY(upload(g, cut.data(), cut.size(), &out->cut));
+    return upload(g, first.data(), first.size(), &out->piece_first);
 }
 
 // Column-blocked copy of one direction of the operator (see SpOp).  Worth building only when the gathered
@@ -261,12 +291,11 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     g->n_loc = n_loc; g->n_halo = n_halo; g->n_cols = n_cols; g->nnz = nnz; g->flags = flags;
     auto fail = [&](int rc) { capgnn_graph_destroy(g); return rc; };
 
-    std::vector<int64_t> rp(rowptr, rowptr + n_loc + 1);
     std::vector<int32_t> order_f, order_b, order_bs;
-    int64_t nl_f = degree_order(rp, 0, n_loc, order_f);
+    degree_order(rowptr, 0, n_loc, order_f);
     int rc;
     SpOp &f = g->fwd;
-    f.n_out = n_loc; f.n_in = n_cols; f.nnz = nnz; f.n_long = nl_f; f.n_sub = n_loc; f.n_long_sub = nl_f;
+    f.n_out = n_loc; f.n_in = n_cols; f.nnz = nnz; f.n_sub = n_loc;
     if ((rc = upload(g, rowptr, n_loc + 1, &f.ptr))) return fail(rc);
     if ((rc = upload(g, col, nnz, &f.idx))) return fail(rc);
     if ((rc = upload_weights(g, nnz, col, edge_val, col_scale, &f.wt))) return fail(rc);
@@ -274,9 +303,8 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     if (row_scale && (rc = upload(g, row_scale, n_loc, &f.out_scale))) return fail(rc);
     if (col_scale && (rc = upload(g, col_scale, n_cols, &f.in_scale))) return fail(rc);
     if ((rc = upload(g, order_f.data(), order_f.size(), &f.order))) return fail(rc);
-    f.order_sub = f.order;
-    if ((rc = upload_giant(g, rowptr, order_f, &f.giant))) return fail(rc);
-    f.giant_sub = f.giant;
+    if ((rc = upload_items(g, rowptr, nnz, order_f, &f.list))) return fail(rc);
+    f.list_sub = f.list;
     for (int64_t i = 0; i < n_loc; ++i) f.max_deg = std::max(f.max_deg, rowptr[i + 1] - rowptr[i]);
     BlockedHost bh_f;
     if (build_blocked(rowptr, col, edge_val, col_scale, order_f, n_loc, n_cols, &bh_f) && (rc = upload_blocked(g, bh_f, &f)))
@@ -286,9 +314,8 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     b.n_out = n_cols; b.n_in = n_loc; b.nnz = nnz; b.out_scale = f.in_scale; b.in_scale = f.out_scale;
     b.weights_by_source = !edge_val && row_scale;
     if (share) {
-        b.ptr = f.ptr; b.idx = f.idx; b.order = f.order; b.n_long = f.n_long;
-        b.order_sub = f.order; b.n_sub = n_loc; b.n_long_sub = f.n_long; b.max_deg = f.max_deg;
-        b.giant = f.giant; b.giant_sub = f.giant;
+        b.ptr = f.ptr; b.idx = f.idx; b.order = f.order; b.n_sub = n_loc; b.max_deg = f.max_deg;
+        b.list = f.list; b.list_sub = f.list;
         b.ncb = f.ncb; b.b_off = f.b_off; b.b_ew = f.b_ew; b.b_src = f.b_src; b.b_long = f.b_long; b.b_mid = f.b_mid;
         const bool same_scales = (!row_scale && !col_scale) ||
                                  (row_scale && col_scale && std::memcmp(row_scale, col_scale, n_loc * sizeof(float)) == 0);
@@ -303,16 +330,15 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
             }
         }
     } else {
-        b.n_long = degree_order(colptr, 0, n_cols, order_b);
-        b.n_long_sub = degree_order(colptr, 0, n_loc, order_bs);
+        degree_order(colptr.data(), 0, n_cols, order_b);
+        degree_order(colptr.data(), 0, n_loc, order_bs);
         b.n_sub = n_loc;
         if ((rc = upload(g, colptr.data(), n_cols + 1, &b.ptr))) return fail(rc);
         if ((rc = upload(g, rowidx.data(), nnz, &b.idx))) return fail(rc);
         if ((rc = upload_weights(g, nnz, rowidx.data(), edge_val ? cscval.data() : nullptr, row_scale, &b.wt))) return fail(rc);
         if ((rc = upload(g, order_b.data(), order_b.size(), &b.order))) return fail(rc);
-        if ((rc = upload(g, order_bs.data(), order_bs.size(), &b.order_sub))) return fail(rc);
-        if ((rc = upload_giant(g, colptr.data(), order_b, &b.giant))) return fail(rc);
-        if ((rc = upload_giant(g, colptr.data(), order_bs, &b.giant_sub))) return fail(rc);
+        if ((rc = upload_items(g, colptr.data(), nnz, order_b, &b.list))) return fail(rc);
+        if ((rc = upload_items(g, colptr.data(), nnz, order_bs, &b.list_sub))) return fail(rc);
         for (int64_t j = 0; j < n_cols; ++j) b.max_deg = std::max(b.max_deg, colptr[j + 1] - colptr[j]);
         BlockedHost bh;
         if (build_blocked(colptr.data(), rowidx.data(), edge_val ? cscval.data() : nullptr, row_scale, order_b, n_cols,

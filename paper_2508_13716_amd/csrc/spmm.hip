@@ -1,13 +1,11 @@
 // Normalised sparse aggregation Y = A_hat X (and, over the CSC, dX = A_hat^T dY) for gfx950.
 //
-// One 64-wide wavefront owns one output row.  The row's column indices are read 64 at a time,
-// one per lane (coalesced), together with the per-entry weight (edge_val * in_scale[col], formed at graph creation); the
-// indices are then handed from lane to lane (v_readlane / ds_bpermute) so that every feature-row
-// load is a contiguous, 16-byte-per-lane access with a wave-uniform base address.  Several loads
-// are kept in flight per wave before any is consumed.  Narrow feature rows (fewer than 64 vectors)
-// let a wave work on several edges at once (64/LPR lane groups, combined with a butterfly at the
-// end).  Rows with at least LONG_ROW entries are split over the four waves of a workgroup and
-// combined through LDS in a fixed order, so results are reproducible run to run.
+// LPR lanes (a power of two, as many as a feature row has 16-byte vectors, at most a whole wave) cover one feature row, so a
+// wave gathers the rows of 64 / LPR entries with one instruction.  Short output rows are given to one lane group each, so
+// that a wave works on 64 / LPR of them at a time; longer ones, and pieces of very long ones, to a whole wave, whose groups
+// share the entries.  Either way every lane has eight feature-row loads in flight.  The column indices are read one per
+// lane, together with the per-entry weight (edge_val * in_scale[col], formed at graph creation), and handed from lane to
+// lane.  The pieces of a cut row are summed in a fixed order by a second kernel: results are reproducible run to run.
 #include "common.h"
 
 #include <algorithm>
@@ -15,12 +13,12 @@
 namespace capgnn {
 
 struct SpmmArgs {
-    const int64_t *ptr;
     const int32_t *idx;
     const float *out_scale;
     const float *wt;          // per-entry weights, or null: every weight is 1
-    const int32_t *order;
-    int64_t list_begin, list_end;
+    const RowItem *items;     // [n_items]
+    int64_t n_items, n_pieces;   // the first n_pieces items are pieces of cut rows: raw sums to `part`
+    int64_t n_wave;              // the first n_wave items (pieces among them) are given a whole wave each
     const char *X;
     int64_t ldx_bytes;
     char *Y;
@@ -30,10 +28,7 @@ struct SpmmArgs {
     const float *bias;
     int relu;
     int accumulate;
-    // cut rows: piece lists and the fp32 partial sums [n_pieces][ldp]
-    const int32_t *piece_pos;
-    const int32_t *piece_first;
-    float *part;
+    float *part;              // fp32 partial sums [n_pieces][ldp]
     int64_t ldp;
 };
 
@@ -88,20 +83,22 @@ __device__ __forceinline__ void zero_raw(RawVec<BF16, E> &r) {
     }
 }
 
-template <bool BF16, int E>
+// acc += w * r (W), or acc += r
+template <bool BF16, bool W, int E>
 __device__ __forceinline__ void fma_raw(float w, const RawVec<BF16, E> &r, float (&acc)[E]) {
+    auto add = [w](float x, float &s) { s = W ? fmaf(w, x, s) : s + x; };
     if constexpr (BF16 && E == 8) {
         const uint32_t u[4] = {r.v.x, r.v.y, r.v.z, r.v.w};
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            acc[2 * d] = fmaf(w, __uint_as_float(u[d] << 16), acc[2 * d]);
-            acc[2 * d + 1] = fmaf(w, __uint_as_float(u[d] & 0xffff0000u), acc[2 * d + 1]);
+            add(__uint_as_float(u[d] << 16), acc[2 * d]);
+            add(__uint_as_float(u[d] & 0xffff0000u), acc[2 * d + 1]);
         }
     } else if constexpr (BF16 && E == 1) {
-        acc[0] = fmaf(w, bf16_bits_to_f32(r.v), acc[0]);
+        add(bf16_bits_to_f32(r.v), acc[0]);
     } else {
 #pragma unroll
-        for (int j = 0; j < E; ++j) acc[j] = fmaf(w, r.v[j], acc[j]);
+        for (int j = 0; j < E; ++j) add(r.v[j], acc[j]);
     }
 }
 
@@ -142,184 +139,262 @@ __device__ __forceinline__ void store_elems(char *p, const float (&x)[E]) {
     }
 }
 
-// Adds, for the entries [e_begin, e_end) of one output row, weight * X[source, lane's features] to acc.
-template <bool BF16, int E, int LPR, int NV, int U>
-__device__ __forceinline__ void accumulate_range(const SpmmArgs &a, int64_t e_begin, int64_t e_end, int lane,
-                                                 int elem0, float (&acc)[NV][E]) {
-    constexpr int G = 64 / LPR;
+// Adds, for the entries [e, end) of one output row, weight * X[source, lane's features] to acc.
+//   WAVE   the row belongs to the whole wave: e, end are uniform, lane group `sub` takes every (64 / LPR)-th entry and the
+//          caller adds the groups
+//   !WAVE  it belongs to the lane group: e, end may differ between the groups; all lanes of the wave take part
+// U loads per lane are issued before the first is consumed, also at the end of a row (entries beyond it are masked out, not
+// loaded): a row of 10 entries costs two round trips to memory and not one per entry, which bounds the launches of
+// low-degree graphs.  Lanes beyond the row's last vector load the first one instead (the same line, never stored).
+template <bool BF16, bool W, bool WAVE, int E, int LPR, int NV, int U>
+__device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, uint32_t end, int lane, int elem0,
+                                               float (&acc)[NV][E]) {
     constexpr int ES = BF16 ? 2 : 4;
-    const int sub = lane / LPR;
-    const int c_first = a.idx[e_begin];
-    bool ok[NV];
+    constexpr int G = 64 / LPR;
+    uint32_t off[NV];                               // the lane's place inside a feature row
 #pragma unroll
-    for (int v = 0; v < NV; ++v) ok[v] = elem0 + v * LPR * E < a.F_lim;
-    const char *xbase = a.X + static_cast<int64_t>(elem0) * ES;
+    for (int v = 0; v < NV; ++v) off[v] = elem0 + v * LPR * E < a.F_lim ? static_cast<uint32_t>(elem0 + v * LPR * E) * ES : 0u;
 
-    for (int64_t e0 = e_begin; e0 < e_end; e0 += 64) {
-        const int64_t my = e0 + lane;
-        int c = c_first;
-        float w = 0.f;
-        if (my < e_end) {
-            c = a.idx[my];
-            w = a.wt ? a.wt[my] : 1.f;
+    if constexpr (G == 1) {     // one entry per instruction: its row address is scalar
+        for (; e < end; e += 64) {
+            const int n = static_cast<int>(end - e < 64u ? end - e : 64u);
+            int c = 0, w = 0;
+            if (lane < n) {
+                c = a.idx[e + lane];
+                if constexpr (W) w = __float_as_int(a.wt[e + lane]);
+            }
+            int t = 0;
+            for (; t + U <= n; t += U) {
+                RawVec<BF16, E> x[U][NV];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const char *p = a.X + static_cast<int64_t>(__builtin_amdgcn_readlane(c, t + u)) * a.ldx_bytes;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) load_raw<BF16, E>(p + off[v], x[u][v]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float wu = 1.f;
+                    if constexpr (W) wu = __int_as_float(__builtin_amdgcn_readlane(w, t + u));
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) fma_raw<BF16, W, E>(wu, x[u][v], acc[v]);
+                }
+            }
+            if (t < n) {        // the last U - 1 entries at most, in flight together as well
+                RawVec<BF16, E> x[U - 1][NV];
+#pragma unroll
+                for (int u = 0; u < U - 1; ++u) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) zero_raw<BF16, E>(x[u][v]);
+                    if (t + u < n) {
+                        const char *p = a.X + static_cast<int64_t>(__builtin_amdgcn_readlane(c, t + u)) * a.ldx_bytes;
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) load_raw<BF16, E>(p + off[v], x[u][v]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U - 1; ++u) {
+                    float wu = 1.f;
+                    if constexpr (W) wu = __int_as_float(__builtin_amdgcn_readlane(w, (t + u) & 63));
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) fma_raw<BF16, W, E>(wu, x[u][v], acc[v]);
+                }
+            }
         }
-        const int cnt = static_cast<int>(e_end - e0 < 64 ? e_end - e0 : 64);
-        const int nsteps = (cnt + G - 1) / G;
-        int s = 0;
-        for (; s + U <= nsteps; s += U) {
-            RawVec<BF16, E> x[U][NV];
-            float ws[U];
+        return;
+    }
+
+    static_assert(G == 1 || NV == 1, "rows narrower than a wave are one vector per lane");
+    constexpr int NQ = LPR < U ? U / LPR : 1;       // indices per lane and chunk
+    constexpr int CH = LPR * NQ;                    // entries of a lane group per chunk
+    constexpr uint32_t STEP = WAVE ? CH * G : CH;   // distance of a row's chunks
+    const int sub = lane / LPR;
+    const uint32_t mine = WAVE ? lane : lane % LPR, lanes = WAVE ? 64 : LPR;
+    // entry k of the group: held by lane first + (k % LPR) * (WAVE ? G : 1), index register k / LPR
+    const int first4 = 4 * (WAVE ? sub : sub * LPR);
+    constexpr int STRIDE4 = 4 * (WAVE ? G : 1);
+    const char *xbase = a.X + off[0];
+    const uint32_t ld = static_cast<uint32_t>(a.ldx_bytes);
+    int c[NQ], w[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t i = e + q * lanes + mine;
+        c[q] = i < end ? a.idx[i] : 0;
+        if constexpr (W) w[q] = i < end ? __float_as_int(a.wt[i]) : 0;
+    }
+    while (WAVE ? e < end : __any(e < end)) {
+        // entries the group still has (may exceed a chunk)
+        const int n = e < end ? (WAVE ? (static_cast<int>(end - e) - sub + G - 1) / G : static_cast<int>(end - e)) : 0;
+        e += STEP;
+        int cn[NQ], wn[NQ];
+        auto trip = [&](int t, bool prefetch) __attribute__((always_inline)) {
+            RawVec<BF16, E> x[U];
+            int at = first4 + STRIDE4 * t;
+            asm volatile("" : "+v"(at));    // formed here: the exchanges' constant distances stay immediate offsets
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                int cj;
-                if constexpr (G == 1) {
-                    cj = __builtin_amdgcn_readlane(c, s + u);
-                    ws[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s + u));
-                } else {
-                    cj = __shfl(c, (s + u) * G + sub);
-                    ws[u] = __shfl(w, (s + u) * G + sub);
-                }
-                const char *p = xbase + static_cast<int64_t>(cj) * a.ldx_bytes;
+                const uint32_t cj = __builtin_amdgcn_ds_bpermute(at + STRIDE4 * (u % LPR), c[NQ > 1 ? u / LPR : 0]);
+                zero_raw<BF16, E>(x[u]);
+                if (t + u < n) load_raw<BF16, E>(xbase + static_cast<uint64_t>(cj) * ld, x[u]);
+            }
+            if (prefetch) {             // the next chunk's indices: in flight behind the gathers, needed after them
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    if (ok[v]) load_raw<BF16, E>(p + v * LPR * E * ES, x[u][v]);
-                    else zero_raw<BF16, E>(x[u][v]);
+                for (int q = 0; q < NQ; ++q) {
+                    const uint32_t i = e + q * lanes + mine;
+                    cn[q] = i < end ? a.idx[i] : 0;
+                    if constexpr (W) wn[q] = i < end ? __float_as_int(a.wt[i]) : 0;
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) fma_raw<BF16, E>(ws[u], x[u][v], acc[v]);
+            for (int u = 0; u < U; ++u) {
+                float wu = 1.f;
+                if constexpr (W) wu = __int_as_float(__builtin_amdgcn_ds_bpermute(at + STRIDE4 * (u % LPR), w[NQ > 1 ? u / LPR : 0]));
+                fma_raw<BF16, W, E>(wu, x[u], acc[0]);
+            }
+        };
+        trip(0, true);
+        if constexpr (CH > U) {
+#pragma unroll 1
+            for (int t = U; t < CH; t += U) {
+                if (!__any(t < n)) break;
+                trip(t, false);
+            }
         }
-        for (; s < nsteps; ++s) {
-            int cj;
-            float wj;
-            if constexpr (G == 1) {
-                cj = __builtin_amdgcn_readlane(c, s);
-                wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s));
-            } else {
-                cj = __shfl(c, s * G + sub);
-                wj = __shfl(w, s * G + sub);
-            }
-            const char *p = xbase + static_cast<int64_t>(cj) * a.ldx_bytes;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                if (ok[v]) {
-                    float x[E];
-                    load_elems<BF16, E>(p + v * LPR * E * ES, x);
-#pragma unroll
-                    for (int j = 0; j < E; ++j) acc[v][j] = fmaf(wj, x[j], acc[v][j]);
-                }
-            }
+        for (int q = 0; q < NQ; ++q) {
+            c[q] = cn[q];
+            if constexpr (W) w[q] = wn[q];
         }
     }
 }
 
-// The wave-per-row launches are bound by how many gathers the resident waves keep in flight: at least six waves per
-// SIMD are asked for (the bf16-in / fp32-out variants otherwise settle at four).
-// MODE 0: one single-wave workgroup per output row (rows of one work-list class differ in length, and a wave that
-// shares a workgroup with a longer row would hold its slot until that one ends).  MODE 1: one workgroup per row.  MODE 2: one workgroup per piece of a cut row;
-// the raw fp32 sum of the piece goes to a.part and spmm_pieces_finish_kernel completes the row.
-template <bool BF16, bool OBF16, int E, int LPR, int NV, int MODE>
-__global__ __launch_bounds__(MODE == 0 ? 64 : 256, (MODE == 0 && NV < 3) ? 6 : 1) void spmm_kernel(SpmmArgs a) {
-    constexpr bool LONG = MODE >= 1;
+// adds the lane groups of a wave (a butterfly: the same order in every lane)
+template <int E, int LPR, int NV>
+__device__ __forceinline__ void add_lane_groups(float (&acc)[NV][E]) {
+#pragma unroll
+    for (int d = LPR; d < 64; d <<= 1)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int j = 0; j < E; ++j) acc[v][j] += __shfl_xor(acc[v][j], d);
+}
+
+// Scale, accumulate, bias, ReLU and store of E consecutive features of one output row.
+template <bool OBF16, int E>
+__device__ __forceinline__ void store_row(const SpmmArgs &a, char *yrow, int f0, float oscale, const float (&acc)[E]) {
+    constexpr int ES = OBF16 ? 2 : 4;
+    if (f0 >= a.F) return;
+    float y[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        float t = acc[j] * oscale;
+        if (f0 + j < a.F) {
+            if (a.accumulate) t += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
+            if (a.bias) t += a.bias[f0 + j];
+        }
+        if (a.relu) t = t > 0.f ? t : 0.f;
+        y[j] = t;
+    }
+    if (f0 + E <= a.F) {
+        store_elems<OBF16, E>(yrow + static_cast<int64_t>(f0) * ES, y);
+    } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            if (f0 + j < a.F) store_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES, y[j]);
+    }
+}
+
+// Single-wave workgroups (a wave that shares a workgroup with a longer row would hold its slot until that one ends): the
+// first n_wave of them take one item each, the others 64 / LPR, one per lane group.  The launches are bound by how many
+// gathers the resident waves keep in flight, then by the fabric behind the L2s: at least six waves per SIMD are asked for
+// (the bf16-in / fp32-out variants otherwise settle at four).  W: entries have weights (a.wt), else every weight is 1.
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+__global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void spmm_kernel(SpmmArgs a) {
     constexpr int G = 64 / LPR;
-    constexpr int ES = OBF16 ? 2 : 4;   // element size of the output
     constexpr int U = (NV == 1) ? 8 : 4;
     constexpr int PASS = LPR * E * NV;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int l = lane % LPR;
-    const int64_t slot = a.list_begin + blockIdx.x;
-    if (slot >= a.list_end) return;   // LONG: uniform over the workgroup
-    const int row = a.order[MODE == 2 ? a.piece_pos[slot] : slot];
-    int64_t beg = a.ptr[row], end = a.ptr[row + 1];
-    if constexpr (MODE == 2) {
-        beg += static_cast<int64_t>(slot - a.piece_first[a.piece_pos[slot]]) * GIANT_PIECE;
-        if (beg + GIANT_PIECE < end) end = beg + GIANT_PIECE;
+    const int lane = threadIdx.x;
+    const bool by_wave = G == 1 || blockIdx.x < a.n_wave;
+    int64_t item = blockIdx.x;
+    bool stores = true;
+    if (!by_wave) {
+        item = a.n_wave + (item - a.n_wave) * G + lane / LPR;
+        stores = item < a.n_items;
+    } else if constexpr (G > 1) {
+        stores = lane < LPR;
     }
-    if constexpr (LONG) {
-        const int64_t len = end - beg;
-        const int64_t per = ((len + 3) / 4 + 63) / 64 * 64;
-        beg = beg + wave * per;
-        if (beg > end) beg = end;
-        if (beg + per < end) end = beg + per;
-    }
-    __shared__ float red[LONG ? 3 : 1][NV * E][64];
-    const float oscale = a.out_scale ? a.out_scale[row] : 1.f;
+    RowItem it{0, 0u, 0u, 0u};
+    if (by_wave || stores) it = a.items[item];
 
     for (int pass = 0; pass < a.F_lim; pass += PASS) {
-        const int elem0 = pass + l * E;
+        const int elem0 = pass + lane % LPR * E;
         float acc[NV][E];
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int j = 0; j < E; ++j) acc[v][j] = 0.f;
-        if (beg < end) accumulate_range<BF16, E, LPR, NV, U>(a, beg, end, lane, elem0, acc);
-        if constexpr (G > 1) {
-#pragma unroll
-            for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                    for (int j = 0; j < E; ++j) acc[v][j] += __shfl_xor(acc[v][j], off);
+        if (by_wave) {
+            accumulate_row<BF16, W, true, E, LPR, NV, U>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
+            if constexpr (G > 1) add_lane_groups<E, LPR, NV>(acc);
+        } else if constexpr (G > 1) {
+            accumulate_row<BF16, W, false, E, LPR, NV, U>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
         }
-        if constexpr (LONG) {
-            if (pass > 0) __syncthreads();
-            if (wave > 0) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                    for (int j = 0; j < E; ++j) red[wave - 1][v * E + j][lane] = acc[v][j];
-            }
-            __syncthreads();
-            if (wave == 0) {
-#pragma unroll
-                for (int wv = 0; wv < 3; ++wv)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v)
-#pragma unroll
-                        for (int j = 0; j < E; ++j) acc[v][j] += red[wv][v * E + j][lane];
-            }
-        }
-        if constexpr (MODE == 2) {
-            if (wave == 0 && lane < LPR) {
-                float *prow = a.part + slot * a.ldp;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const int f0 = elem0 + v * LPR * E;
-#pragma unroll
-                    for (int j = 0; j < E; ++j)
-                        if (f0 + j < a.F) prow[f0 + j] = acc[v][j];
-                }
-            }
-            continue;
-        }
-        if ((!LONG || wave == 0) && lane < LPR) {
-            char *yrow = a.Y + static_cast<int64_t>(row) * a.ldy_bytes;
+        if (!stores) continue;
+        if (item < a.n_pieces) {
+            float *prow = a.part + item * a.ldp;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const int f0 = elem0 + v * LPR * E;
-                if (f0 >= a.F) continue;
-                float y[E];
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    float t = acc[v][j] * oscale;
-                    if (f0 + j < a.F) {
-                        if (a.accumulate) t += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
-                        if (a.bias) t += a.bias[f0 + j];
-                    }
-                    if (a.relu) t = t > 0.f ? t : 0.f;
-                    y[j] = t;
-                }
-                if (f0 + E <= a.F) {
-                    store_elems<OBF16, E>(yrow + static_cast<int64_t>(f0) * ES, y);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < E; ++j)
-                        if (f0 + j < a.F) store_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES, y[j]);
-                }
+                const int f0 = elem0 + v * LPR * E;     // ldp covers whole vectors
+                if (f0 < a.F) store_elems<false, E>(reinterpret_cast<char *>(prow + f0), acc[v]);
             }
+        } else {
+            char *yrow = a.Y + static_cast<int64_t>(it.row) * a.ldy_bytes;
+            const float oscale = a.out_scale ? a.out_scale[it.row] : 1.f;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, yrow, elem0 + v * LPR * E, oscale, acc[v]);
+        }
+    }
+}
+
+// The cut rows where the caller brought no scratch for their pieces: a workgroup per row, each wave a quarter of its
+// entries, combined through LDS in a fixed order.
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+__global__ __launch_bounds__(256) void spmm_long_kernel(SpmmArgs a, const RowItem *cut) {
+    constexpr int U = (NV == 1) ? 8 : 4;
+    constexpr int PASS = LPR * E * NV;
+    __shared__ float red[3][NV * E][LPR];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const RowItem it = cut[blockIdx.x];
+    const uint32_t end = it.beg + it.cnt, per = (it.cnt + 3) / 4;
+    const uint32_t e0 = wave * per < it.cnt ? it.beg + wave * per : end, e1 = end - e0 < per ? end : e0 + per;
+    const float oscale = a.out_scale ? a.out_scale[it.row] : 1.f;
+    for (int pass = 0; pass < a.F_lim; pass += PASS) {
+        const int elem0 = pass + lane % LPR * E;
+        float acc[NV][E];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int j = 0; j < E; ++j) acc[v][j] = 0.f;
+        accumulate_row<BF16, W, true, E, LPR, NV, U>(a, e0, e1, lane, elem0, acc);
+        if constexpr (LPR < 64) add_lane_groups<E, LPR, NV>(acc);
+        if (pass > 0) __syncthreads();
+        if (wave > 0 && lane < LPR) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int j = 0; j < E; ++j) red[wave - 1][v * E + j][lane] = acc[v][j];
+        }
+        __syncthreads();
+        if (wave == 0 && lane < LPR) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int j = 0; j < E; ++j) acc[v][j] += red[p][v * E + j][lane];
+            char *yrow = a.Y + static_cast<int64_t>(it.row) * a.ldy_bytes;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, yrow, elem0 + v * LPR * E, oscale, acc[v]);
         }
     }
 }
@@ -701,7 +776,7 @@ static int64_t pieces_ldp(int F) { return (static_cast<int64_t>(F) + 7) / 8 * 8;
 
 size_t spmm_ws_bytes(const SpOp &op, int F, int dtype) {
     const BlockedGeom g = blocked_geom(op, F, dtype);
-    const int64_t pieces = std::max(op.giant.n_pieces, op.giant_sub.n_pieces);
+    const int64_t pieces = std::max(op.list.n_pieces, op.list_sub.n_pieces);
     const size_t cut = F > 0 ? static_cast<size_t>(pieces) * pieces_ldp(F) * sizeof(float) : 0;
     return std::max<size_t>(g.ok ? g.ws : 0, cut);
 }
@@ -727,73 +802,97 @@ static int launch_blocked(const SpOp &op, const BlockedGeom &g, const SpmmArgs &
     return CAPGNN_OK;
 }
 
-// Completes the cut rows: sums the pieces of a row in piece order and applies the same epilogue as spmm_kernel.
+// Completes the cut rows: sums the pieces of a row in a fixed order (blockDim.y strided groups, then the groups in order)
+// and applies the same epilogue as spmm_kernel.  One workgroup per (row, 64 features).
 template <bool OBF16>
-__global__ __launch_bounds__(256) void spmm_pieces_finish_kernel(SpmmArgs a, int64_t n_giant) {
-    constexpr int ES = OBF16 ? 2 : 4;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= n_giant * a.F) return;
-    const int64_t pos = t / a.F;
-    const int f = static_cast<int>(t - pos * a.F);
-    const int row = a.order[pos];
-    float acc = 0.f;
-    for (int q = a.piece_first[pos]; q < a.piece_first[pos + 1]; ++q) acc += a.part[q * a.ldp + f];
-    acc *= a.out_scale ? a.out_scale[row] : 1.f;
-    char *y = a.Y + static_cast<int64_t>(row) * a.ldy_bytes + static_cast<int64_t>(f) * ES;
-    if (a.accumulate) acc += load_one<OBF16>(y);
-    if (a.bias) acc += a.bias[f];
-    if (a.relu) acc = acc > 0.f ? acc : 0.f;
-    store_one<OBF16>(y, acc);
+__global__ void spmm_pieces_finish_kernel(SpmmArgs a, const RowItem *cut, const int32_t *piece_first) {
+    __shared__ float red[16][64];
+    const int k = blockIdx.x, f = blockIdx.y * 64 + threadIdx.x;
+    const int row = cut[k].row, q1 = piece_first[k + 1], step = blockDim.y;
+    float s = 0.f;
+    if (f < a.F) {
+        int q = piece_first[k] + threadIdx.y;
+        for (; q + 7 * step < q1; q += 8 * step) {         // eight loads in flight
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = a.part[static_cast<int64_t>(q + u * step) * a.ldp + f];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; q < q1; q += step) s += a.part[static_cast<int64_t>(q) * a.ldp + f];
+    }
+    red[threadIdx.y][threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.y != 0 || f >= a.F) return;
+    float acc[1] = {0.f};
+    for (int y = 0; y < step; ++y) acc[0] += red[y][threadIdx.x];
+    store_row<OBF16, 1>(a, a.Y + static_cast<int64_t>(row) * a.ldy_bytes, f, a.out_scale ? a.out_scale[row] : 1.f, acc);
 }
 
-template <bool BF16, bool OBF16, int E, int LPR, int NV>
-static int launch_cfg(const SpmmArgs &base, const GiantList *giant, int64_t n_long, int64_t n_rows, hipStream_t st) {
-    int64_t n_giant = 0;
-    if (giant) {
-        n_giant = giant->n_rows;
-        SpmmArgs a = base;
-        a.list_begin = 0;
-        a.list_end = giant->n_pieces;
-        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, E, LPR, NV, 2>), dim3(static_cast<unsigned>(giant->n_pieces)),
-                           dim3(256), 0, st, a);
-        const int64_t threads = n_giant * a.F;
-        hipLaunchKernelGGL((spmm_pieces_finish_kernel<OBF16>), dim3(static_cast<unsigned>((threads + 255) / 256)),
-                           dim3(256), 0, st, a, n_giant);
+// How long a row may be that one lane group walks alone.  A group takes about a microsecond for eight entries, so a row of T
+// entries ends T / 8 us after it began: T follows the time the launch needs anyway (its gathers at 5 TB/s), from 16 (a
+// 40 k-entry launch of 8 features: 4.4 us with 16, 8.0 with 64, 12 with 128) to 128 (6 M entries of 47 bf16 features: 150 us
+// with 16, 110 with 64, 106 with 128).
+static int group_row_entries(int64_t nnz, int64_t row_bytes) {
+    const double us = static_cast<double>(nnz) * row_bytes / 5e6;
+    int t = 16;
+    while (t < 128 && t < us) t *= 2;
+    return t;
+}
+
+// Unused LDS asked for by the launches whose rows average at least CROWDED_ROW entries of at least CROWDED_BYTES: twelve
+// waves per compute unit instead of 20 to 28.  Twelve keep the fabric behind the L2s busy with such rows, and fewer rows
+// under way at a time leave more of the L2s to the hubs: 980 k rows x 50 entries, 256 bf16 features 3.66 -> 3.48 ms, 128
+// features 1.86 -> 1.76, 47 float features 1.77 -> 1.68.  Shorter rows need the waves to hide their start and end (13 entries
+// x 256 float features: 0.60 -> 0.63 ms), narrower ones to keep enough requests in flight (47 bf16 features: 0.10 -> 0.115).
+constexpr int CROWDED_ROW = 32, CROWDED_BYTES = 192, CROWDED_LDS = 13312;
+
+// pieces: the caller brought scratch for the pieces of the cut rows
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
+    constexpr int G = 64 / LPR;
+    a.items = list.items; a.n_items = list.n_items; a.n_pieces = list.n_pieces;
+    const int64_t row_bytes = static_cast<int64_t>(a.F_lim) * (BF16 ? 2 : 4);
+    a.n_wave = G == 1 ? list.n_items : list.first_below(group_row_entries(nnz, row_bytes));
+    const bool long_rows = nnz >= CROWDED_ROW * list.n_items && row_bytes >= CROWDED_BYTES;
+    if (!pieces) {
+        a.items += list.n_pieces; a.n_items -= list.n_pieces; a.n_wave -= list.n_pieces; a.n_pieces = 0;
+        if (list.n_cut > 0)
+            hipLaunchKernelGGL((spmm_long_kernel<BF16, OBF16, W, E, LPR, NV>), dim3(static_cast<unsigned>(list.n_cut)), dim3(256), 0,
+                               st, a, list.cut);
     }
-    if (n_long > n_giant) {
-        SpmmArgs a = base;
-        a.list_begin = n_giant;
-        a.list_end = n_long;
-        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, E, LPR, NV, 1>), dim3(static_cast<unsigned>(n_long - n_giant)),
-                           dim3(256), 0, st, a);
-    }
-    if (n_rows > n_long) {
-        SpmmArgs a = base;
-        a.list_begin = n_long;
-        a.list_end = n_rows;
-        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, E, LPR, NV, 0>), dim3(static_cast<unsigned>(n_rows - n_long)),
-                           dim3(64), 0, st, a);
-    }
+    if (a.n_items > 0)
+        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV>),
+                           dim3(static_cast<unsigned>(a.n_wave + (a.n_items - a.n_wave + G - 1) / G)), dim3(64),
+                           long_rows ? CROWDED_LDS : 0, st, a);
+    if (pieces)
+        hipLaunchKernelGGL((spmm_pieces_finish_kernel<OBF16>), dim3(static_cast<unsigned>(list.n_cut), (a.F + 63) / 64),
+                           dim3(64, list.max_pieces > 64 ? 16 : 4), 0, st, a, list.cut, list.piece_first);
     CG_HIP(hipGetLastError());
     return CAPGNN_OK;
 }
 
-template <bool BF16, bool OBF16>
-static int dispatch(const SpmmArgs &a, bool vec, const GiantList *gl, int64_t n_long, int64_t n_rows, hipStream_t st) {
+template <bool BF16, bool OBF16, bool W>
+static int dispatch_w(const SpmmArgs &a, bool vec, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
     constexpr int EV = BF16 ? 8 : 4;
     if (vec) {
         const int nvec = a.F_lim / EV;
-        if (nvec <= 4) return launch_cfg<BF16, OBF16, EV, 4, 1>(a, gl, n_long, n_rows, st);
-        if (nvec <= 8) return launch_cfg<BF16, OBF16, EV, 8, 1>(a, gl, n_long, n_rows, st);
-        if (nvec <= 16) return launch_cfg<BF16, OBF16, EV, 16, 1>(a, gl, n_long, n_rows, st);
-        if (nvec <= 32) return launch_cfg<BF16, OBF16, EV, 32, 1>(a, gl, n_long, n_rows, st);
-        if (nvec <= 64) return launch_cfg<BF16, OBF16, EV, 64, 1>(a, gl, n_long, n_rows, st);
-        if (nvec <= 128) return launch_cfg<BF16, OBF16, EV, 64, 2>(a, gl, n_long, n_rows, st);
-        return launch_cfg<BF16, OBF16, EV, 64, 3>(a, gl, n_long, n_rows, st);   // wider rows take several passes
+        if (nvec <= 4) return launch_cfg<BF16, OBF16, W, EV, 4, 1>(a, list, pieces, nnz, st);
+        if (nvec <= 8) return launch_cfg<BF16, OBF16, W, EV, 8, 1>(a, list, pieces, nnz, st);
+        if (nvec <= 16) return launch_cfg<BF16, OBF16, W, EV, 16, 1>(a, list, pieces, nnz, st);
+        if (nvec <= 32) return launch_cfg<BF16, OBF16, W, EV, 32, 1>(a, list, pieces, nnz, st);
+        if (nvec <= 64) return launch_cfg<BF16, OBF16, W, EV, 64, 1>(a, list, pieces, nnz, st);
+        if (nvec <= 128) return launch_cfg<BF16, OBF16, W, EV, 64, 2>(a, list, pieces, nnz, st);
+        return launch_cfg<BF16, OBF16, W, EV, 64, 3>(a, list, pieces, nnz, st);   // wider rows take several passes
     }
-    if (a.F <= 64) return launch_cfg<BF16, OBF16, 1, 64, 1>(a, gl, n_long, n_rows, st);
-    if (a.F <= 128) return launch_cfg<BF16, OBF16, 1, 64, 2>(a, gl, n_long, n_rows, st);
-    return launch_cfg<BF16, OBF16, 1, 64, 4>(a, gl, n_long, n_rows, st);
+    if (a.F <= 64) return launch_cfg<BF16, OBF16, W, 1, 64, 1>(a, list, pieces, nnz, st);
+    if (a.F <= 128) return launch_cfg<BF16, OBF16, W, 1, 64, 2>(a, list, pieces, nnz, st);
+    return launch_cfg<BF16, OBF16, W, 1, 64, 4>(a, list, pieces, nnz, st);
+}
+
+template <bool BF16, bool OBF16>
+static int dispatch(const SpmmArgs &a, bool vec, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
+    return a.wt ? dispatch_w<BF16, OBF16, true>(a, vec, list, pieces, nnz, st) : dispatch_w<BF16, OBF16, false>(a, vec, list, pieces, nnz, st);
 }
 
 int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, void *Y, int64_t ldy, int F,
@@ -810,21 +909,20 @@ int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, v
     const int ev = 16 / es;
     const int f_up = (F + ev - 1) / ev * ev;
     const int es_out = elem_bytes(out_dtype);
-    const bool vec = aligned16(X) && aligned16(Y) && (ldx * es) % 16 == 0 && (ldy * es_out) % 16 == 0 && ldx >= f_up;
+    const bool vec = aligned16(X) && aligned16(Y) && (ldx * es) % 16 == 0 && (ldy * es_out) % 16 == 0 && ldx >= f_up &&
+                     ldx * es < (int64_t(1) << 32);
     SpmmArgs a;
-    a.ptr = op.ptr; a.idx = op.idx; a.out_scale = op.out_scale;
+    a.idx = op.idx; a.out_scale = op.out_scale;
     a.wt = op.wt;
     if (ep.operand_scaled) {
         if (!op.weights_by_source) CG_FAIL(CAPGNN_EINVAL, "spmm: operand_scaled asks for an operator whose weights depend on the source alone");
         a.wt = nullptr;             // the rows of X carry the weights
     }
-    a.order = restrict_sub ? op.order_sub : op.order;
-    a.list_begin = 0; a.list_end = n_rows;
+    a.items = nullptr; a.n_items = 0; a.n_pieces = 0; a.n_wave = 0;
     a.X = static_cast<const char *>(X); a.ldx_bytes = ldx * es;
     a.Y = static_cast<char *>(Y); a.ldy_bytes = ldy * es_out;
     a.F = F; a.F_lim = vec ? f_up : F;
     a.bias = ep.bias; a.relu = ep.relu; a.accumulate = ep.accumulate;
-    const int64_t n_long = restrict_sub ? op.n_long_sub : op.n_long;
     if (vec && !restrict_sub && ep.ws) {
         // the blocked kernel runs when the operator has a blocked copy and the caller brought the scratch for it
         const BlockedGeom bg = blocked_geom(op, F, dtype);
@@ -838,18 +936,15 @@ int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, v
             return launch_blocked<true, false>(op, bg, a, part, stream);
         }
     }
-    // rows too long for one workgroup are cut into pieces when the caller brought scratch for their partial sums
-    const GiantList &gl = restrict_sub ? op.giant_sub : op.giant;
-    const GiantList *cut = nullptr;
-    a.piece_pos = gl.piece_pos; a.piece_first = gl.piece_first;
+    // long rows are cut into pieces when the caller brought scratch for their partial sums
+    const ItemList &list = restrict_sub ? op.list_sub : op.list;
     a.part = static_cast<float *>(ep.ws); a.ldp = pieces_ldp(F);
-    if (gl.n_rows > 0 && ep.ws && (reinterpret_cast<uintptr_t>(ep.ws) & 15u) == 0 &&
-        ep.ws_bytes >= static_cast<size_t>(gl.n_pieces) * a.ldp * sizeof(float))
-        cut = &gl;
-    if (dtype == CAPGNN_F32 && out_dtype == CAPGNN_BF16) return dispatch<false, true>(a, vec, cut, n_long, n_rows, stream);
-    if (dtype == CAPGNN_F32) return dispatch<false, false>(a, vec, cut, n_long, n_rows, stream);
-    if (out_dtype == CAPGNN_BF16) return dispatch<true, true>(a, vec, cut, n_long, n_rows, stream);
-    return dispatch<true, false>(a, vec, cut, n_long, n_rows, stream);
+    const bool pieces = list.n_cut > 0 && ep.ws && (reinterpret_cast<uintptr_t>(ep.ws) & 15u) == 0 &&
+                        ep.ws_bytes >= static_cast<size_t>(list.n_pieces) * a.ldp * sizeof(float);
+    if (dtype == CAPGNN_F32 && out_dtype == CAPGNN_BF16) return dispatch<false, true>(a, vec, list, pieces, op.nnz, stream);
+    if (dtype == CAPGNN_F32) return dispatch<false, false>(a, vec, list, pieces, op.nnz, stream);
+    if (out_dtype == CAPGNN_BF16) return dispatch<true, true>(a, vec, list, pieces, op.nnz, stream);
+    return dispatch<true, false>(a, vec, list, pieces, op.nnz, stream);
 }
 
 // Measurement aid for the gather roofline: every 8-lane group fetches 128-byte lines (16 bytes per lane) at

@@ -179,6 +179,47 @@ def test_spmm_exact_on_small_integers(env):
     g.close()
 
 
+@pytest.mark.parametrize("scratch", [True, False])
+@pytest.mark.parametrize("fill", [0, 45000])
+def test_spmm_row_length_classes_exact(env, fill, scratch):
+    """Row lengths on both sides of every limit of the work list: eight entries per trip of a lane group, 16 .. 128 entries
+    for a group alone, pieces of 64 entries (small graph) or 512 (more than 2 M entries), cut from twice that length on.
+    One width per lane-group size and one whose rows are not vectors; small integers, so every order of summation gives the
+    same float and a bf16 result is that float rounded once: equality."""
+    torch, B, H, O, orc = env["torch"], env["B"], env["H"], env["O"], env["orc"]
+    rng = np.random.default_rng(3 + fill)
+    lens = [0, 1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 191, 193, 255, 256, 257, 511, 513, 1023, 1024,
+            1025, 1537, 5000] + [48] * fill
+    n_loc, n_halo = len(lens), 700
+    rowptr = np.zeros(n_loc + 1, np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    col = rng.integers(0, n_loc + n_halo, rowptr[-1]).astype(np.int32)
+    val = rng.integers(-1, 2, rowptr[-1]).astype(np.float32)
+    for F, ld, vals in [(5, 8, False), (30, 32, True), (60, 64, False), (41, 41, True)] + ([] if fill else [
+            (100, 104, True), (250, 256, False), (400, 400, True), (1600, 1600, False)]):
+        for dt in (B.F32, B.BF16):
+            say(f"spmm row classes F={F} ld={ld} dtype={dt} fill={fill} scratch={scratch}")
+            X = rng.integers(-2, 3, (n_loc + n_halo, F)).astype(np.float32)
+            g = B.Graph(n_loc, n_halo, rowptr, col, None, None, val if vals else None)
+            og = orc.Graph(n_loc, n_loc + n_halo, rowptr, col, np.ones(n_loc), np.ones(n_loc + n_halo),
+                           val.astype(np.float64) if vals else None)
+            Xd = H.padded_matrix(X if dt == B.F32 else synth.f32_to_bf16_rne(X).reshape(X.shape), ld)
+            wsb = B.spmm_workspace_bytes(g, F, dt) if scratch else 0
+            ws = torch.empty(wsb, dtype=torch.uint8, device="cuda") if wsb else None
+            assert wsb > 0 or not scratch
+            for back in (False, True):
+                n_out = n_loc + n_halo if back else n_loc
+                ref = (orc.spmm_bwd(og, X[:n_loc].astype(np.float64)) if back else orc.spmm_fwd(og, X.astype(np.float64)))
+                Yd = torch.full((n_out, ld), 7.0, dtype=Xd.dtype, device="cuda")
+                (B.spmm_bwd if back else B.spmm_fwd)(g, Xd, ld, Yd, ld, F, dt, ws=ws, ws_bytes=wsb)
+                torch.cuda.synchronize()
+                Y = O.widen(H.dev_to_np(Yd))
+                want = ref if dt == B.F32 else synth.bf16_to_f32(synth.f32_to_bf16_rne(ref.astype(np.float32))).reshape(ref.shape)
+                assert np.array_equal(Y[:, :F], want), (F, dt, back)
+                assert (Y[:, F:] == 7.0).all(), "padding columns were written"
+            g.close()
+
+
 def test_spmm_on_config1_graph(env):
     cfg = synth.CONFIGS["C1"]
     part = synth.partition_for(cfg)
