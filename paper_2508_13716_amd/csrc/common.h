@@ -157,6 +157,7 @@ struct SpmmEpilogue {
     const float *bias = nullptr;   // [F] added after scaling
     int relu = 0;
     int accumulate = 0;            // add the previous contents of Y
+    int64_t acc_rows = INT64_MAX;  // ... in output rows below this one
     int out_f32 = 0;               // store Y as float although X is bf16
     int out_bf16 = 0;              // store Y as bf16 although X is float (the loss gradient of a bf16 model is gathered unrounded)
     int operand_scaled = 0;        // row s of X already carries in_scale[s] (only for operators with weights_by_source)
@@ -174,10 +175,16 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
                 hipStream_t stream, const float *row_scale = nullptr,    // row_scale: C[i,:] *= row_scale[i] at the very end (fp32 C)
                 int f32_product = CAPGNN_F32_PRODUCT_AUTO);
-// C = A W + A2 W2 (+ bias, ReLU), one launch where the fp32 three-piece form applies, else the two launches it replaces
-int launch_gemm_dual(int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
+// C = A op(W) + A2 op(W2) (+ bias, ReLU), one launch where a kernel forms the sum, else the two launches it replaces
+int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
                      const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product);
+// C = op(A) op(B) (rows scaled) and C2 = op(A2) op(B2), one launch for small and middling sizes
+int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
+                     int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
+                     int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
+                     int f32_product);
+size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K);
 // scratch that lets launch_gemm_dual run as one launch
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2);
 size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K);

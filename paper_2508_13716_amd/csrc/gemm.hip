@@ -11,7 +11,6 @@
 #include "common.h"
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 namespace capgnn {
@@ -1090,6 +1089,313 @@ __global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kerne
     store_tile<TM, 1>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Small products, whose tiles of 128 rows would leave most of the chip idle and pay a round trip to memory per 16 or 32 k:
+// here a workgroup owns 32 x (TN * 32) outputs, its four waves take quarters of the reduction (or, of a sum of two
+// products, two waves each), and every wave loads its operands straight into the registers the matrix instruction reads
+// them from, four units (fp32: 32 k, bf16: 64 k) at a time and one batch ahead: one or two round trips in all.  The four
+// partial tiles are added through LDS in wave order.  No alignment is needed; k may be assigned to the instruction's k slots
+// in any order as long as both operands agree, so a lane takes four (eight) consecutive k of its row.
+struct SmallGemmArgs {
+    GemmArgs g;                     // tile grid, sizes, epilogue; A2 / lda2 / K1 not used
+    // second product of a sum C = A B + A2 B2 (dual), or second problem of the same shape C2 = A2 B2 (pair)
+    const char *A2; int64_t lda2;
+    const char *B2; int64_t ldb2;
+    char *C2; int64_t ldc2;
+    float *part2;
+    const float *rscale2;
+    int64_t K2;                     // of the dual form
+    int64_t M2;                     // rows of the second problem
+    int dual;
+};
+
+// One unit of an operand: 4 fp32 k (of a half wave's 8) or 8 bf16 k (of 16), of one row / column of the result.
+template <bool BF16> struct SmallUnit { float v[4]; };
+template <> struct SmallUnit<true> { uint32_t v[4]; };
+
+// ALONG: the operand is stored along the reduction index.  p: address of its first element at k = 0; step: bytes from one k
+// to the next when not ALONG; the unit starts at k; elements from k_end on are zero (FULL: there are none).
+template <bool BF16, bool ALONG, bool FULL>
+__device__ __forceinline__ void small_load(const char *p, int64_t step, int64_t k, int64_t k_end, bool vec, SmallUnit<BF16> &r) {
+    constexpr int ES = BF16 ? 2 : 4, NE = BF16 ? 8 : 4;
+    if constexpr (ALONG) {
+        if (FULL && vec) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(p + k * ES);
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (BF16) r.v[e] = w[e];
+                else r.v[e] = __uint_as_float(w[e]);
+            }
+            return;
+        }
+    }
+    const int64_t d = ALONG ? ES : step;
+    const char *q = p + k * d;
+#pragma unroll
+    for (int e = 0; e < NE; e += BF16 ? 2 : 1) {
+        if constexpr (BF16) {
+            const uint32_t lo = FULL || k + e < k_end ? *reinterpret_cast<const uint16_t *>(q + e * d) : 0u;
+            const uint32_t hi = FULL || k + e + 1 < k_end ? *reinterpret_cast<const uint16_t *>(q + (e + 1) * d) : 0u;
+            r.v[e / 2] = lo | (hi << 16);
+        } else {
+            r.v[e] = FULL || k + e < k_end ? *reinterpret_cast<const float *>(q + e * d) : 0.f;
+        }
+    }
+}
+
+constexpr int SMALL_UNITS = 4;      // units per batch
+template <bool BF16> constexpr int SMALL_UNIT_K = BF16 ? 16 : 8;
+
+template <bool BF16, bool A_KC, bool B_KC, int TN>
+__global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
+    constexpr int ES = BF16 ? 2 : 4, UK = SMALL_UNIT_K<BF16>, HK = UK / 2, UB = SMALL_UNITS;
+    constexpr int PITCH = TN * 32 + 4;
+    __shared__ __attribute__((aligned(16))) float red[4][32][PITCH];
+    const GemmArgs &g = s.g;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    int bx, by, bz;
+    if (!tile_coords(g, &bx, &by, &bz)) return;      // uniform over the workgroup
+    const bool second = blockIdx.y != 0;             // pair: the other problem
+    const int64_t M = second ? s.M2 : g.M;
+    const int64_t m0 = static_cast<int64_t>(by) * 32, n0 = static_cast<int64_t>(bx) * (TN * 32);
+    // the wave's operands and its range of the reduction
+    const bool alt = second || (s.dual && wave >= 2);
+    const char *A = alt ? s.A2 : g.A, *B = alt ? s.B2 : g.B;
+    const int64_t lda = alt ? s.lda2 : g.lda, ldb = alt ? s.ldb2 : g.ldb;
+    int64_t k_end, k;
+    if (s.dual) {
+        const int64_t K = wave >= 2 ? s.K2 : g.K, per = (K + 2 * UK - 1) / (2 * UK) * UK;
+        k = (wave & 1) * per;
+        k_end = k + per < K ? k + per : K;
+    } else {
+        const int64_t per = g.k_chunk / 4;           // whole units
+        k = bz * g.k_chunk + wave * per;
+        k_end = k + per < g.K ? k + per : g.K;
+    }
+    // rows and columns beyond the matrices repeat the last one: what they give is never stored
+    if (m0 >= M) return;                             // uniform over the workgroup
+    const int64_t row = m0 + l32 < M ? m0 + l32 : M - 1;
+    const char *pa = A + (A_KC ? row * lda : row) * ES;
+    const char *pb[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int64_t c = n0 + j * 32 + l32, col = c < g.N ? c : g.N - 1;
+        pb[j] = B + (B_KC ? col * ldb : col) * ES;
+    }
+    const int64_t sa = lda * ES, sb = ldb * ES;
+    const bool va = (reinterpret_cast<uintptr_t>(A) | static_cast<uintptr_t>(sa)) % 16 == 0;
+    const bool vb = (reinterpret_cast<uintptr_t>(B) | static_cast<uintptr_t>(sb)) % 16 == 0;
+
+    SmallUnit<BF16> a[UB], b[UB][TN];
+    auto fetch = [&](int64_t kb) __attribute__((always_inline)) {
+        if (kb + UB * UK <= k_end) {
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                const int64_t ku = kb + u * UK + half * HK;
+                small_load<BF16, A_KC, true>(pa, sa, ku, k_end, va, a[u]);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, true>(pb[j], sb, ku, k_end, vb, b[u][j]);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                const int64_t ku = kb + u * UK + half * HK;
+                small_load<BF16, A_KC, false>(pa, sa, ku, k_end, va, a[u]);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, false>(pb[j], sb, ku, k_end, vb, b[u][j]);
+            }
+        }
+    };
+    floatx16 acc[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    if (k < k_end) fetch(k);
+    for (; k < k_end; k += UB * UK) {
+        SmallUnit<BF16> ca[UB], cb[UB][TN];
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            ca[u] = a[u];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) cb[u][j] = b[u][j];
+        }
+        if (k + UB * UK < k_end) fetch(k + UB * UK);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (BF16) {
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ca[u]), __builtin_bit_cast(bf16x8, cb[u][j]),
+                                                                     acc[j], 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[u].v[e], cb[u][j].v[e], acc[j], 0, 0, 0);
+                }
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * half + (r & 3)][j * 32 + l32] = acc[j][r];
+    __syncthreads();
+    float *part = second ? s.part2 : g.part;
+    char *C = second ? s.C2 : g.C;
+    const int64_t ldc = second ? s.ldc2 : g.ldc;
+    const float *rscale = second ? s.rscale2 : g.rscale;
+    // four columns per thread
+    for (int i = threadIdx.x; i < 32 * TN * 8; i += 256) {
+        const int r = i / (TN * 8), c4 = i % (TN * 8);
+        const int64_t orow = m0 + r, ocol = n0 + 4 * c4;
+        if (orow >= M || ocol >= g.N) continue;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float4 q = *reinterpret_cast<const float4 *>(&red[w][r][4 * c4]);
+            v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
+        }
+        const int nv = g.N - ocol < 4 ? static_cast<int>(g.N - ocol) : 4;
+        if (part) {
+            float *o = part + (bz * M + orow) * g.N + ocol;
+            for (int e = 0; e < nv; ++e) o[e] = v[e];
+            continue;
+        }
+        for (int e = 0; e < nv; ++e) {
+            const int64_t at = orow * ldc + ocol + e;
+            float x = v[e];
+            if (g.accumulate)
+                x += g.out_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(C)[at]) << 16)
+                                : reinterpret_cast<const float *>(C)[at];
+            if (g.bias) x += g.bias[ocol + e];
+            if (g.relu) x = x > 0.f ? x : 0.f;
+            if (g.mask) {
+                const int64_t am = orow * g.ldm + ocol + e;
+                const float mv = g.mask_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(g.mask)[am]) << 16)
+                                             : reinterpret_cast<const float *>(g.mask)[am];
+                if (!(mv > 0.f)) x = 0.f;
+            }
+            if (rscale) x *= rscale[orow];
+            if (g.out_bf16) reinterpret_cast<uint16_t *>(C)[at] = static_cast<uint16_t>(f32_to_bf16_rne(x));
+            else reinterpret_cast<float *>(C)[at] = x;
+        }
+    }
+}
+
+// Plain fp32 products of middling size (the 128-row tiles of gemm_split_kernel would not fill the chip): 64 x 64 tiles with
+// four waves, a 32 x 32 part each.  Both operands are cut here, the second one as well, which saves the launch that cuts a
+// weight matrix beforehand (4-5 us, a third of such a product).  Two LDS buffers and operands fetched two steps ahead: one
+// barrier per step and no step waits for memory; three workgroups share a compute unit.
+// Also the sum of two products (dual) and two products of one shape (pair), see SmallGemmArgs.
+
+// An operand stored across the reduction index, cut while staged into the same 16-byte units: a thread takes eight k of one
+// column (64 neighbouring columns per wave and load).
+struct SplitUnitLoader {
+    float r[8];
+    uint4 pk[3];
+
+    template <bool FULL>
+    __device__ __forceinline__ void fetch(const char *base, int64_t ld, int64_t t0, int64_t T, int64_t k0, int64_t k_end, int tid) {
+        const int64_t t = t0 + (tid & 63) < T ? t0 + (tid & 63) : T - 1, k = k0 + 8 * (tid >> 6);     // columns beyond T: never stored
+        const float *p = reinterpret_cast<const float *>(base) + k * ld + t;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = FULL || k + e < k_end ? p[e * ld] : 0.f;
+    }
+
+    __device__ __forceinline__ void cut() {
+        uint32_t w[4][3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split3_pair(r[2 * e], r[2 * e + 1], w[e]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) pk[p] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+    }
+
+    __device__ __forceinline__ void put(char *s, int tid) const {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4 *>(s + Units16<64>::at(p, tid >> 6, tid & 63)) = pk[p];
+    }
+};
+
+template <bool B_KC>
+__global__ __launch_bounds__(256, 3) void gemm_split_mid_kernel(SmallGemmArgs s) {
+    constexpr int BT = 64, BYTES = Units16<BT>::BYTES;
+    __shared__ __attribute__((aligned(16))) char smem[2][2][BYTES];
+    const GemmArgs &g = s.g;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, half = lane >> 5;
+    int bx, by, bz;
+    if (!tile_coords(g, &bx, &by, &bz)) return;      // uniform over the workgroup
+    const bool second = blockIdx.y != 0;             // pair: the other second operand and result
+    const int64_t M = second ? s.M2 : g.M;
+    const int64_t m0 = static_cast<int64_t>(by) * BT, n0 = static_cast<int64_t>(bx) * BT;
+    if (m0 >= M) return;                             // uniform over the workgroup
+    const int nk1 = static_cast<int>((g.K + SBK - 1) / SBK);
+    const int nk = nk1 + (s.dual ? static_cast<int>((s.K2 + SBK - 1) / SBK) : 0);
+
+    floatx16 acc[1][1];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+    SplitRowLoader<BT> la;
+    typename std::conditional<B_KC, SplitRowLoader<BT>, SplitUnitLoader>::type lb;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        const bool alt = t >= nk1;                   // uniform over the grid
+        const char *A = (alt || second) ? s.A2 : g.A, *B = (alt || second) ? s.B2 : g.B;
+        const int64_t lda = (alt || second) ? s.lda2 : g.lda, ldb = (alt || second) ? s.ldb2 : g.ldb;
+        const int64_t k0 = static_cast<int64_t>(alt ? t - nk1 : t) * SBK, kend = alt ? s.K2 : g.K;
+        if (m0 + BT <= M && k0 + SBK <= kend && g.a_vec) la.fetch_at(A, lda, m0, k0, tid);
+        else la.fetch(A, lda, m0, M, k0, kend, g.a_vec, tid);
+        if constexpr (B_KC) {
+            if (n0 + BT <= g.N && k0 + SBK <= kend && g.b_vec) lb.fetch_at(B, ldb, n0, k0, tid);
+            else lb.fetch(B, ldb, n0, g.N, k0, kend, g.b_vec, tid);
+        } else {
+            if (k0 + SBK <= kend) lb.template fetch<true>(B, ldb, n0, g.N, k0, kend, tid);
+            else lb.template fetch<false>(B, ldb, n0, g.N, k0, kend, tid);
+        }
+    };
+    fetch(0);
+    la.cut();
+    lb.cut();
+    la.put(smem[0][0], tid);
+    lb.put(smem[0][1], tid);
+    if (nk > 1) fetch(1);
+    __syncthreads();
+    for (int t = 0; t < nk; ++t) {
+        const char *As = smem[t & 1][0], *Bs = smem[t & 1][1];
+        if (t + 1 < nk) {
+            la.cut();
+            lb.cut();
+            if (t + 2 < nk) fetch(t + 2);
+        }
+#pragma unroll
+        for (int ks = 0; ks < SBK / 16; ++ks) {
+            bf16x8 a[3], b[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                a[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(As + Units16<BT>::at(p, 2 * ks + half, wm * 32 + l32)));
+                b[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bs + Units16<BT>::at(p, 2 * ks + half, wn * 32 + l32)));
+            }
+            // the six piece products, smallest first
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc[0][0], 0, 0, 0);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc[0][0], 0, 0, 0);
+        }
+        if (t + 1 < nk) {
+            la.put(smem[(t + 1) & 1][0], tid);
+            lb.put(smem[(t + 1) & 1][1], tid);
+        }
+        __syncthreads();
+    }
+    GemmArgs o = g;
+    if (second) { o.C = s.C2; o.ldc = s.ldc2; o.rscale = s.rscale2; o.M = M; }
+    store_tile<1, 1>(o, acc, m0 + wm * 32, n0 + wn * 32, l32, half, 0);
+}
+
 // Cuts the (small) second operand of a plain product into bf16 pieces laid out in 16-byte units
 // Wt[piece][k / 8][n][k % 8], n_pad rows, ku_total units along k, zero beyond N and K.  kc: the source is [n][k]
 // (pitch ldw), else [k][n].
@@ -1127,7 +1433,9 @@ __global__ __launch_bounds__(256) void repack_bf16_kernel(const uint16_t *W, int
 // Sums the split partials and applies the epilogue.  A workgroup covers 32 consecutive output elements with 8
 // groups of threads; group y adds the partials z = y, y+8, ... in that order, then the 8 group sums are added
 // in group order: a fixed summation order, whatever the launch geometry.
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S) {
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, const float *part2 = nullptr, char *C2 = nullptr,
+                                                          int64_t ldc2 = 0) {
+    if (blockIdx.y != 0) { g.part = const_cast<float *>(part2); g.C = C2; g.ldc = ldc2; }      // the second problem of a pair
     __shared__ float red[8][32];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int64_t total = g.M * g.N;
@@ -1161,7 +1469,9 @@ static int choose_split(int trans_a, int64_t M, int64_t N, int64_t K, int bm, in
     if (!trans_a) return 1;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     int64_t s = 1536 / (tiles > 0 ? tiles : 1);
-    const int64_t max_by_k = K / (bk * 16) > 0 ? K / (bk * 16) : 1;   // at least 16 k-steps per split
+    // at least 16 k-steps per split, down to 4 where that leaves compute units without a workgroup
+    int64_t max_by_k = K / (bk * 16);
+    if (max_by_k * tiles < 256) max_by_k = std::min<int64_t>((256 + tiles - 1) / tiles, K / (bk * 4));
     if (s > max_by_k) s = max_by_k;
     if (s > 1024) s = 1024;
     if (s < 1) s = 1;
@@ -1184,18 +1494,59 @@ static size_t split_b_bytes(int64_t N, int64_t K) {
     return align_up(static_cast<size_t>(3) * split_rows(N) * split_ld(K) * sizeof(uint16_t), 256);
 }
 
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K);
+static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk);
+
 size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
     int bm, bn;
     tile_for(N, &bm, &bn);
     // the larger split of the two kernels (they step through K in 16s and 32s)
     const int s = std::max(choose_split(trans_a, M, N, K, bm, bn, BK), choose_split(trans_a, M, N, K, bm, bn, HBK));
     size_t b = s > 1 ? align_up(static_cast<size_t>(s) * M * N * sizeof(float), 256) : 0;
+    for (const bool bf : {false, true})
+        if (trans_a && small_product(bf, trans_a, M, N, K)) {
+            int tn, z;
+            int64_t chunk;
+            small_geometry(bf, trans_a, M, N, K, &tn, &z, &chunk);
+            if (z > 1) b = std::max(b, align_up(static_cast<size_t>(z) * M * N * sizeof(float), 256));
+        }
     // room to lay a weight matrix out for the bf16 kernel (bf16 operands) or as its three planes (fp32 operands)
     if (!trans_a) b = std::max(b, std::max(transposed_b_bytes(N, K), split_b_bytes(N, K)));
     return b;
 }
 
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2) { return split_b_bytes(N, split_ld(K1) + K2); }
+
+// Which products take gemm_small_kernel (fp32 ones unless their three-piece form was asked for).  Plain products: while its
+// 32-row tiles make at most two workgroups per compute unit and a wave has at most two batches to multiply (4096 x 64 x 128
+// fp32: 13.2 -> 6.7 us; 9973 x 64 x 100: 13.8 -> 9.1; 21557 x 128 x 50, 1348 tiles: 24 us against 14).  Reductions over
+// vertices (trans_a), whose other kernels stage tiles through LDS step by step: up to 2^28.5 multiply-adds in fp32 (128 x 121
+// x 21557: 39 -> 21 us; 256 x 256 x 20000: 46 against 34) and 2^30.5 in bf16 (256 x 256 x 20000: 30 -> 19; 100 x 256 x 70001:
+// 34 against 33), and further where N <= 64 leaves those kernels half idle (256 x 41 x 180000: 106 -> 91 fp32, 42 -> 34
+// bf16; 256 x 47 x 306000: 161 against 148 fp32, 67 -> 56 bf16).
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K) {
+    if (K <= 0) return false;
+    const double macs = static_cast<double>(M) * N * K;
+    if (trans_a) return macs <= (bf16 ? (N <= 64 ? 0x1p32 : 0x1.6p30) : (N <= 64 ? 0x1p31 : 0x1.6p28));
+    return !bf16 && K <= 128 && ((M + 31) / 32) * ((N + 63) / 64) <= 512;
+}
+
+// Tiles and reduction splits of a small product: N tiles of 64 columns (32 where that is all), and for a reduction over
+// vertices enough splits for about two workgroups per compute unit, each wave with at least one batch.
+static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk) {
+    const int64_t unit = bf16 ? SMALL_UNIT_K<true> : SMALL_UNIT_K<false>, batch = unit * SMALL_UNITS;
+    *tn = N <= 32 ? 1 : 2;
+    *S = 1;
+    const int64_t tiles = ((M + 31) / 32) * ((N + *tn * 32 - 1) / (*tn * 32));
+    if (trans_a) {
+        int64_t z = 512 / tiles;
+        if (z > K / (4 * batch)) z = K / (4 * batch);
+        *S = static_cast<int>(z < 1 ? 1 : z);
+    }
+    const int64_t chunk = (K + *S - 1) / *S;
+    *k_chunk = (chunk + 4 * unit - 1) / (4 * unit) * (4 * unit);
+    *S = static_cast<int>((K + *k_chunk - 1) / *k_chunk);
+}
 
 // AUTO: smaller products stay on the fp32 instruction, and so do weight gradients at most 64 columns wide (half of
 // the threads that stage their operands would idle; measured slower)
@@ -1220,9 +1571,21 @@ static void launch_tiles(const GemmArgs &g, int bn, dim3 grid, hipStream_t st) {
 }
 
 template <bool A_KC, bool B_KC>
-static void launch_bf16_tiles(const GemmArgs &g, int bn, dim3 grid, hipStream_t st) {
-    if (bn == 64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
+static void launch_bf16_tiles(const GemmArgs &g, int bn, bool bm64, dim3 grid, hipStream_t st) {
+    if (bn == 64 && bm64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 64, 64>), grid, dim3(256), 0, st, g);
+    else if (bn == 64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
     else hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 128>), grid, dim3(256), 0, st, g);
+}
+
+static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
+#define CG_SMALL_CASE(BF, AK, BK_, TN_)                                                                                        \
+    if (bf16 == BF && akc == AK && bkc == BK_ && tn == TN_)                                                                  \
+        hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, TN_>), grid, dim3(256), 0, st, s);
+#define CG_SMALL_TYPES(AK, BK_)                                                                                                \
+    CG_SMALL_CASE(false, AK, BK_, 1) CG_SMALL_CASE(false, AK, BK_, 2) CG_SMALL_CASE(true, AK, BK_, 1) CG_SMALL_CASE(true, AK, BK_, 2)
+    CG_SMALL_TYPES(true, false) CG_SMALL_TYPES(true, true) CG_SMALL_TYPES(false, false) CG_SMALL_TYPES(false, true)
+#undef CG_SMALL_TYPES
+#undef CG_SMALL_CASE
 }
 
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
@@ -1241,20 +1604,37 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const int es = elem_bytes(dtype);
     int bm, bn;
     tile_for(N, &bm, &bn);
-    // bf16 operands whose rows start on 16-byte boundaries run on the bf16 matrix cores; the second operand of a
-    // product with a plain first operand is a weight matrix, small enough to be repacked into the workspace
-    const bool repack_b = dtype == CAPGNN_BF16 && !trans_a && ws && ws_bytes >= transposed_b_bytes(N, K);
-    const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 &&
-                           (repack_b || (aligned16(B) && (ldb * 2) % 16 == 0));
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    // bf16 operands whose rows start on 16-byte boundaries run on the bf16 matrix cores, in 64 x 64 tiles while tiles of
+    // 128 rows are few (20000 x 256 x 256: 17.5 -> 15.5 us; 306000 x 256 x 256: 133 against 111).  The second operand of a
+    // product with a plain first operand is a weight matrix, repacked into the workspace first unless it is stored along
+    // the reduction index already, or the product so short that the repacking launch is a good part of it (21557 x 128 x 50:
+    // 8.9 -> 7.2 us; 5000 x 256 x 602: 18.6 against 16.6)
+    const bool b_aligned = aligned16(B) && (ldb * 2) % 16 == 0;
+    const bool repack_b = dtype == CAPGNN_BF16 && !trans_a && ws && ws_bytes >= transposed_b_bytes(N, K) &&
+                          !(b_aligned && (trans_b || (tiles64 <= 768 && K <= 256)));
+    const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned);
     // fp32 operands as three bf16 pieces each (see gemm_split_kernel)
     const int mode = f32_product;
-    const bool split_path = dtype == CAPGNN_F32 && mode != CAPGNN_F32_PRODUCT_NATIVE && !(trans_a && trans_b) &&
+    const bool split_form = dtype == CAPGNN_F32 && mode != CAPGNN_F32_PRODUCT_NATIVE && !(trans_a && trans_b);
+    // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
+    const bool mid = split_form && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
+    const bool split_path = split_form &&
                             (mode == CAPGNN_F32_PRODUCT_SPLIT ||
                              (M * N >= SPLIT_MIN_MACS / (K > 0 ? K : 1) && !(trans_a && N <= 64))) &&
                             (trans_a || (ws && ws_bytes >= split_b_bytes(N, K)));
+    const bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && mode != CAPGNN_F32_PRODUCT_SPLIT;
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
-    const int S = choose_split(trans_a, M, N, K, bm, bn, bk);
+    int S = choose_split(trans_a, M, N, K, bm, bn, bk), tn = 0;
+    int64_t small_chunk = 0;
+    if (small_path) {
+        small_geometry(dtype == CAPGNN_BF16, trans_a, M, N, K, &tn, &S, &small_chunk);
+        bm = 32;
+        bn = 32 * tn;
+    }
+    const bool mid_path = !small_path && mid;
+    if (mid_path || (half_path && !trans_a && tiles128 <= 1280)) bm = bn = 64;
     GemmArgs g;
     g.M = M; g.N = N; g.K = K;
     g.A = static_cast<const char *>(A); g.lda = lda;
@@ -1277,6 +1657,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         const int64_t steps = (K + bk - 1) / bk;
         g.k_chunk = (steps + S - 1) / S * bk;
     }
+    if (small_path) g.k_chunk = small_chunk;
     const int64_t gy = (M + bm - 1) / bm, gx = (N + bn - 1) / bn;
     const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     if (n_wg >= (int64_t(1) << 31) || gx >= (int64_t(1) << 24) || gy >= (int64_t(1) << 30))
@@ -1285,7 +1666,18 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     g.c_staged = half_path && g.out_bf16 && !g.part && !g.mask && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0;
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
-    if (split_path) {
+    if (small_path) {
+        SmallGemmArgs sm{};
+        sm.g = g;
+        sm.M2 = M;
+        launch_small(sm, dtype == CAPGNN_BF16, akc, bkc, tn, grid, stream);
+    } else if (mid_path) {
+        SmallGemmArgs sm{};
+        sm.g = g;
+        sm.M2 = M;
+        if (bkc) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, sm);
+        else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, sm);
+    } else if (split_path) {
         if (trans_a) {
             launch_split_tiles(true, g, bn, grid, nullptr, 0, 0, stream);
         } else {
@@ -1303,10 +1695,10 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
             g.B = static_cast<const char *>(ws); g.ldb = ldt;
             bkc = true;
         }
-        if (akc && bkc) launch_bf16_tiles<true, true>(g, bn, grid, stream);
-        else if (akc) launch_bf16_tiles<true, false>(g, bn, grid, stream);
-        else if (bkc) launch_bf16_tiles<false, true>(g, bn, grid, stream);
-        else launch_bf16_tiles<false, false>(g, bn, grid, stream);
+        if (akc && bkc) launch_bf16_tiles<true, true>(g, bn, bm == 64, grid, stream);
+        else if (akc) launch_bf16_tiles<true, false>(g, bn, bm == 64, grid, stream);
+        else if (bkc) launch_bf16_tiles<false, true>(g, bn, bm == 64, grid, stream);
+        else launch_bf16_tiles<false, false>(g, bn, bm == 64, grid, stream);
     } else {
         const bool bf = dtype == CAPGNN_BF16;
 #define CG_GEMM_CASE(BF, AK, BKC_) if (bf == BF && akc == AK && bkc == BKC_) launch_tiles<BF, AK, BKC_>(g, bn, grid, stream);
@@ -1325,52 +1717,131 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     return CAPGNN_OK;
 }
 
-// C = A W + A2 W2 (+ bias, ReLU): the two products of a GraphSAGE layer (neighbour term and self term) into one result.
-// fp32 operands in the three-piece form run as ONE launch whose reduction walks A's columns and then A2's, so C is
-// written once and never read back; every other case is the two launches it replaces (A2 W2 first, then A W accumulated
-// on top with the epilogue).  Plain operands only: A [M x K1], A2 [M x K2], W [K1 x N], W2 [K2 x N], row-major.
-int launch_gemm_dual(int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
+// Two products in one launch of gemm_small_kernel or gemm_split_mid_kernel: their sum C = op(A) op(B) + op(A2) op(B2) (dual), or
+// C = op(A) op(B) and C2 = op(A2) op(B2) of one shape but for the rows (pair).  *done says whether the sizes are such a kernel's;
+// nothing has run otherwise.
+static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, int dtype, int out_f32, void *ws, size_t ws_bytes,
+                            hipStream_t stream, int f32_product, bool *done) {
+    *done = false;
+    SmallGemmArgs s = in;
+    GemmArgs &g = s.g;
+    const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
+    const int64_t Kmax = s.dual ? std::max(g.K, s.K2) : g.K;
+    const bool small = f32_product != CAPGNN_F32_PRODUCT_SPLIT && small_product(bf, trans_a, g.M, g.N, Kmax);
+    const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
+    const bool mid = !small && !bf && !trans_a && f32_product != CAPGNN_F32_PRODUCT_NATIVE && tiles64 * (pair ? 2 : 1) <= 768 &&
+                     std::max(std::max(g.lda, s.lda2), std::max(g.ldb, s.ldb2)) < (1 << 22);
+    if ((!small && !mid) || Kmax <= 0 || (s.dual && (g.K <= 0 || s.K2 <= 0))) return CAPGNN_OK;
+    int tn = 2, S = 1;
+    g.k_chunk = Kmax;
+    if (small) small_geometry(bf, trans_a, g.M, g.N, g.K, &tn, &S, &g.k_chunk);
+    if (s.dual && S > 1) return CAPGNN_OK;           // a sum is formed by the waves of one workgroup
+    if (S > 1) {
+        const size_t one = align_up(static_cast<size_t>(S) * g.M * g.N * sizeof(float), 256);
+        if (g.M != s.M2 || !ws || ws_bytes < 2 * one) return CAPGNN_OK;
+        g.part = static_cast<float *>(ws);
+        s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + one);
+    }
+    const int es = elem_bytes(dtype);
+    auto vec_rows = [&](const void *p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) % (4 * es) == 0 && (ld * es) % (4 * es) == 0; };
+    g.a_vec = vec_rows(g.A, g.lda) && vec_rows(s.A2, s.lda2);
+    g.b_vec = vec_rows(g.B, g.ldb) && vec_rows(s.B2, s.ldb2);
+    g.out_bf16 = bf && !out_f32;
+    const int bm = small ? 32 : 64, bn = small ? 32 * tn : 64;
+    const int64_t gy = (std::max(g.M, s.M2) + bm - 1) / bm, gx = (g.N + bn - 1) / bn;
+    g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
+    const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
+    const dim3 grid(static_cast<unsigned>(n_wg), pair ? 2 : 1, 1);
+    if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
+    else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
+    else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
+    if (S > 1)
+        hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>((g.M * g.N + 31) / 32), 2), dim3(256), 0, stream, g, S,
+                           static_cast<const float *>(s.part2), s.C2, s.ldc2);
+    CG_HIP(hipGetLastError());
+    *done = true;
+    return CAPGNN_OK;
+}
+
+// C = op(A) op(B), C2 = op(A2) op(B2): the neighbour and self products of a GraphSAGE layer's backward pass (weight gradients: one
+// second operand; input gradients: one first operand) or of its forward pass in the transform-first order (M rows and M2 <= M).
+int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
+                     int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
+                     int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
+                     int f32_product) {
+    if (M2 > M) CG_FAIL(CAPGNN_EINVAL, "gemm_pair: the second product has more rows");
+    SmallGemmArgs s{};
+    s.g.M = M; s.g.N = N; s.g.K = K;
+    s.g.A = static_cast<const char *>(A); s.g.lda = lda; s.g.B = static_cast<const char *>(B); s.g.ldb = ldb;
+    s.g.C = static_cast<char *>(C); s.g.ldc = ldc; s.g.rscale = row_scale;
+    s.A2 = static_cast<const char *>(A2); s.lda2 = lda2; s.B2 = static_cast<const char *>(B2); s.ldb2 = ldb2;
+    s.C2 = static_cast<char *>(C2); s.ldc2 = ldc2; s.M2 = M2;
+    bool done = false;
+    if (M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
+        lda2 >= (trans_a ? M : K) && ldb >= (trans_b ? K : N) && ldb2 >= (trans_b ? K : N))
+        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, &done));
+    if (done) return CAPGNN_OK;
+    CG_TRY(launch_gemm(trans_a, trans_b, M, N, K, A, lda, B, ldb, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes, stream,
+                       row_scale, f32_product));
+    return launch_gemm(trans_a, trans_b, M2, N, K, A2, lda2, B2, ldb2, C2, ldc2, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
+                       stream, nullptr, f32_product);
+}
+
+size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return (trans_a ? 2 : 1) * gemm_ws_bytes(trans_a, M, N, K); }
+
+// C = A op(W) + A2 op(W2) (+ bias, ReLU): the two products of a GraphSAGE layer (neighbour term and self term), or of its input
+// gradient, into one result.  Small and middling sizes, and fp32 operands in the three-piece form, run as ONE launch, whose
+// reduction walks both first operands, so C is written once and never read back; every other case is the two launches it
+// replaces (A2 W2 first, then A W accumulated on top with the epilogue).  A [M x K1], A2 [M x K2] row-major; W [K1 x N],
+// W2 [K2 x N], or their transposes when trans_b.
+int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
                      const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product) {
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
+    const bool sane = M > 0 && N > 0 && K1 > 0 && K2 > 0 && A && A2 && W && W2 && C && lda >= K1 && lda2 >= K2 &&
+                      ldw >= (trans_b ? K1 : N) && ldw2 >= (trans_b ? K2 : N) && ldc >= N && N <= (1 << 22) &&
+                      M < (int64_t(1) << 31) * 64;
+    GemmArgs g{};
+    g.M = M; g.N = N;
+    g.A = static_cast<const char *>(A); g.lda = lda;
+    g.B = static_cast<const char *>(W); g.ldb = ldw;
+    g.C = static_cast<char *>(C); g.ldc = ldc;
+    g.relu = relu; g.bias = bias;
+    if (sane) {
+        SmallGemmArgs s{};
+        s.g = g;
+        s.g.K = K1; s.K2 = K2; s.dual = 1; s.M2 = M;
+        s.A2 = static_cast<const char *>(A2); s.lda2 = lda2; s.B2 = static_cast<const char *>(W2); s.ldb2 = ldw2;
+        bool done = false;
+        CG_TRY(launch_two_small(s, 0, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, &done));
+        if (done) return CAPGNN_OK;
+    }
     const int64_t K1p = split_ld(K1 > 0 ? K1 : 0), K = K1p + K2;
-    const bool one_launch = dtype == CAPGNN_F32 && f32_product != CAPGNN_F32_PRODUCT_NATIVE && M > 0 && N > 0 && K1 > 0 && K2 > 0 &&
-                            A && A2 && W && W2 && C && lda >= K1 && lda2 >= K2 && ldw >= N && ldw2 >= N && ldc >= N &&
-                            N <= (1 << 22) && M < (int64_t(1) << 31) * 64 && lda < (1 << 22) && lda2 < (1 << 22) &&
-                            (f32_product == CAPGNN_F32_PRODUCT_SPLIT || M * N >= SPLIT_MIN_MACS / (K1 + K2)) &&
+    const bool one_launch = sane && dtype == CAPGNN_F32 && f32_product != CAPGNN_F32_PRODUCT_NATIVE && lda < (1 << 22) &&
+                            lda2 < (1 << 22) && (f32_product == CAPGNN_F32_PRODUCT_SPLIT || M * N >= SPLIT_MIN_MACS / (K1 + K2)) &&
                             ws && ws_bytes >= split_b_bytes(N, K);
     if (!one_launch) {
-        CG_TRY(launch_gemm(0, 0, M, N, K2, A2, lda2, W2, ldw2, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
+        CG_TRY(launch_gemm(0, trans_b, M, N, K2, A2, lda2, W2, ldw2, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
                            stream, nullptr, f32_product));
-        return launch_gemm(0, 0, M, N, K1, A, lda, W, ldw, C, ldc, dtype, out_f32, 1, bias, relu, nullptr, 0, ws, ws_bytes,
+        return launch_gemm(0, trans_b, M, N, K1, A, lda, W, ldw, C, ldc, dtype, out_f32, 1, bias, relu, nullptr, 0, ws, ws_bytes,
                            stream, nullptr, f32_product);
     }
     int bm, bn;
     tile_for(N, &bm, &bn);
-    GemmArgs g;
-    g.M = M; g.N = N; g.K = K;
-    g.A = static_cast<const char *>(A); g.lda = lda;
-    g.B = static_cast<const char *>(W); g.ldb = ldw;
-    g.C = static_cast<char *>(C); g.ldc = ldc;
-    g.part = nullptr;
+    g.K = K;
     g.k_chunk = K;
     g.a_vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && ((lda * 4) % 16 == 0) && (reinterpret_cast<uintptr_t>(A2) % 16 == 0) &&
               ((lda2 * 4) % 16 == 0);
-    g.b_vec = 0;
-    g.out_bf16 = 0; g.accumulate = 0; g.relu = relu; g.bias = bias;
-    g.mask = nullptr; g.ldm = 0; g.mask_bf16 = 0;
-    g.rscale = nullptr;
     g.A2 = static_cast<const char *>(A2); g.lda2 = lda2; g.K1 = K1; g.K1p = K1p;
     const int64_t gy = (M + bm - 1) / bm, gx = (N + bn - 1) / bn;
     const int64_t n_wg = NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     if (n_wg >= (int64_t(1) << 31) || gx >= (int64_t(1) << 24) || gy >= (int64_t(1) << 30))
         CG_FAIL(CAPGNN_EINVAL, "gemm: %lld x %lld tiles exceed the grid", (long long)gy, (long long)gx);
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = 1;
-    g.c_staged = 0;
     const int64_t n_pad = split_rows(N), ku_total = split_ld(K) / 8;
     hipLaunchKernelGGL(split_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0, stream,
-                       static_cast<const float *>(W), ldw, 0, K1, N, static_cast<uint16_t *>(ws), n_pad, ku_total,
+                       static_cast<const float *>(W), ldw, trans_b ? 1 : 0, K1, N, static_cast<uint16_t *>(ws), n_pad, ku_total,
                        static_cast<const float *>(W2), ldw2, K1p, K2);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     if (bn == 64)

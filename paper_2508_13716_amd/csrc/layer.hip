@@ -128,12 +128,19 @@ static size_t grad_copy_bytes(const capgnn_graph *g, const capgnn_layer *l) {
     return align_up(static_cast<size_t>(g->n_loc) * pad_ld(g, l->f_out, CAPGNN_BF16) * sizeof(uint16_t), 256);
 }
 
+// scratch of the gradient GEMMs; GraphSAGE layers form theirs in pairs
+static size_t bwd_g_bytes(const capgnn_graph *g, const capgnn_layer *l, int64_t red_rows) {
+    const size_t b = std::max(std::max(gemm_ws_bytes(1, l->f_in, l->f_out, red_rows), gemm_ws_bytes(1, l->f_in, l->f_out, g->n_loc)),
+                              gemm_ws_bytes(0, g->n_cols, l->f_in, l->f_out));
+    if (l->kind != CAPGNN_SAGE_MEAN) return b;
+    return std::max(b, std::max(gemm_pair_ws_bytes(1, l->f_in, l->f_out, g->n_loc), gemm_dual_ws_bytes(l->f_in, l->f_out, l->f_out)));
+}
+
 static size_t bwd_ws_bytes(const capgnn_graph *g, const capgnn_layer *l, int order) {
     const int es = elem_bytes(l->dtype);
     size_t b = relu_bias_ws_bytes(g->n_loc, l->f_out);
     const int64_t red_rows = order == CAPGNN_AGG_FIRST ? g->n_loc : g->n_cols;
-    b += std::max(std::max(gemm_ws_bytes(1, l->f_in, l->f_out, red_rows), gemm_ws_bytes(1, l->f_in, l->f_out, g->n_loc)),
-                  gemm_ws_bytes(0, g->n_cols, l->f_in, l->f_out));
+    b += bwd_g_bytes(g, l, red_rows);
     if (order == CAPGNN_AGG_FIRST) b += align_up(static_cast<size_t>(g->n_loc) * pad_ld(g, l->f_in, l->dtype) * es, 256);
     else b += align_up(static_cast<size_t>(g->n_cols) * pad_ld(g, l->f_out, l->dtype) * es, 256);
     b += spmm_ws_bytes(g->bwd, order == CAPGNN_AGG_FIRST ? l->f_in : l->f_out, l->dtype);
@@ -164,7 +171,7 @@ static int layer_fwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
         void *gws = (ws && ws_bytes >= fwd_g_bytes(g, l)) ? ws : nullptr;
         const size_t gwb = gws ? fwd_g_bytes(g, l) : 0;
         if (sage)       // H = act(M W + X_loc W_self + b): one launch where the three-piece fp32 form applies
-            return launch_gemm_dual(g->n_loc, l->f_out, l->f_in, saved, ldm, l->W, l->f_out, l->f_in, X, ldx, l->W_self, l->f_out,
+            return launch_gemm_dual(0, g->n_loc, l->f_out, l->f_in, saved, ldm, l->W, l->f_out, l->f_in, X, ldx, l->W_self, l->f_out,
                                     H, ldh, dt, l->out_f32, l->bias, relu, gws, gwb, st, l->f32_product);
         CG_TRY(launch_gemm(0, 0, g->n_loc, l->f_out, l->f_in, saved, ldm, l->W, l->f_out, H, ldh, dt, l->out_f32, 0, l->bias,
                            relu, nullptr, 0, gws, gwb, st, nullptr, l->f32_product));
@@ -181,9 +188,13 @@ static int layer_fwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     {
         Scope s(CAPGNN_K_GEMM, li, 0, st);
         void *gws = static_cast<char *>(ws) + fwd_t_bytes(g, l, order);
-        CG_TRY(launch_gemm(0, 0, g->n_cols, l->f_out, l->f_in, X, ldx, l->W, l->f_out, ws, ldt, dt, 0, 0, nullptr, 0,
-                           nullptr, 0, gws, fwd_g_bytes(g, l), st, pre ? g->fwd.in_scale : nullptr, l->f32_product));
-        if (sage)
+        if (sage && dt == CAPGNN_F32)
+            CG_TRY(launch_gemm_pair(0, 0, g->n_cols, g->n_loc, l->f_out, l->f_in, X, ldx, X, ldx, l->W, l->f_out, l->W_self, l->f_out, ws,
+                                    ldt, H, ldh, dt, 0, pre ? g->fwd.in_scale : nullptr, gws, fwd_g_bytes(g, l), st, l->f32_product));
+        else
+            CG_TRY(launch_gemm(0, 0, g->n_cols, l->f_out, l->f_in, X, ldx, l->W, l->f_out, ws, ldt, dt, 0, 0, nullptr, 0,
+                               nullptr, 0, gws, fwd_g_bytes(g, l), st, pre ? g->fwd.in_scale : nullptr, l->f32_product));
+        if (sage && dt != CAPGNN_F32)
             CG_TRY(launch_gemm(0, 0, g->n_loc, l->f_out, l->f_in, X, ldx, l->W_self, l->f_out, H, ldh, dt, l->out_f32, 0,
                                nullptr, 0, nullptr, 0, gws, fwd_g_bytes(g, l), st, nullptr, l->f32_product));
     }
@@ -213,8 +224,7 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     const size_t rb = relu_bias_ws_bytes(g->n_loc, l->f_out);
     w += rb;
     const int64_t red_rows = order == CAPGNN_AGG_FIRST ? g->n_loc : g->n_cols;
-    const size_t gw = std::max(std::max(gemm_ws_bytes(1, l->f_in, l->f_out, red_rows), gemm_ws_bytes(1, l->f_in, l->f_out, g->n_loc)),
-                               gemm_ws_bytes(0, g->n_cols, l->f_in, l->f_out));
+    const size_t gw = bwd_g_bytes(g, l, red_rows);
     void *ws_gemm = w;
     w += gw;
     void *tmp = w;   // dM (AGG_FIRST) or dT (XFORM_FIRST)
@@ -260,25 +270,31 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
         const int64_t ldm = pad_ld(g, l->f_in, dt);
         {
             Scope s(CAPGNN_K_GEMM, li, 1, st);
-            if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, saved, ldm, dHb, lddhb, dW, l->f_out, dt, 1, 0,
+            if (sage && dW && dW_self) {
+                CG_TRY(launch_gemm_pair(1, 0, l->f_in, l->f_in, l->f_out, g->n_loc, saved, ldm, X, ldx, dHb, lddhb, dHb, lddhb, dW, l->f_out,
+                                        dW_self, l->f_out, dt, 1, nullptr, ws_gemm, gw, st, l->f32_product));
+            } else {
+                if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, saved, ldm, dHb, lddhb, dW, l->f_out, dt, 1, 0,
+                                           nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                if (sage && dW_self)
+                    CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0,
                                        nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
-            if (sage && dW_self)
-                CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0,
-                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
-            if (dX) CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W, l->f_out, tmp, ldm, dt, 0, 0,
-                                       nullptr, 0, nullptr, 0, ws_gemm, gw, st, pre_b ? g->bwd.in_scale : nullptr, l->f32_product));
+            }
+            // dM = dZ W^T; the self term dZ W_self^T goes to dX, where the transposed aggregation of dM is added to it
+            if (dX && sage)
+                CG_TRY(launch_gemm_pair(0, 1, g->n_loc, g->n_loc, l->f_in, l->f_out, dHb, lddhb, dHb, lddhb, l->W, l->f_out, l->W_self,
+                                        l->f_out, tmp, ldm, dX, lddx, dt, 0, pre_b ? g->bwd.in_scale : nullptr, ws_gemm, gw, st,
+                                        l->f32_product));
+            else if (dX)
+                CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W, l->f_out, tmp, ldm, dt, 0, 0,
+                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, pre_b ? g->bwd.in_scale : nullptr, l->f32_product));
         }
         if (dX) {
-            {
-                Scope s(CAPGNN_K_SPMM_BWD, li, 1, st);
-                sp_ep.operand_scaled = pre_b;
-                CG_TRY(launch_spmm(g->bwd, !need_halo_grad, tmp, ldm, dX, lddx, l->f_in, dt, sp_ep, st));
-            }
-            if (sage) {
-                Scope s(CAPGNN_K_GEMM, li, 1, st);
-                CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX, lddx, dt, 0, 1,
-                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
-            }
+            Scope s(CAPGNN_K_SPMM_BWD, li, 1, st);
+            sp_ep.operand_scaled = pre_b;
+            sp_ep.accumulate = sage ? 1 : 0;
+            sp_ep.acc_rows = g->n_loc;               // halo rows have no self term
+            CG_TRY(launch_spmm(g->bwd, !need_halo_grad, tmp, ldm, dX, lddx, l->f_in, dt, sp_ep, st));
         }
         return CAPGNN_OK;
     }
@@ -299,11 +315,16 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
                            nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
     if (dX) {
         const int64_t rows = need_halo_grad ? g->n_cols : g->n_loc;
-        CG_TRY(launch_gemm(0, 1, rows, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, dX, lddx, dt, 0, 0, nullptr, 0,
-                           nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
-        if (sage)
-            CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX, lddx, dt, 0, 1,
-                               nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+        if (sage && !need_halo_grad) {
+            CG_TRY(launch_gemm_dual(1, g->n_loc, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX,
+                                    lddx, dt, 0, nullptr, 0, ws_gemm, gw, st, l->f32_product));
+        } else {
+            CG_TRY(launch_gemm(0, 1, rows, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, dX, lddx, dt, 0, 0, nullptr, 0,
+                               nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+            if (sage)
+                CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX, lddx, dt, 0, 1,
+                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+        }
     }
     return CAPGNN_OK;
 }

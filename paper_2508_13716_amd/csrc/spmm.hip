@@ -27,7 +27,7 @@ struct SpmmArgs {
     int F_lim;    // elements covered by loads (F rounded up to the vector width)
     const float *bias;
     int relu;
-    int accumulate;
+    int acc_rows;             // output rows below this one are added to what Y holds
     float *part;              // fp32 partial sums [n_pieces][ldp]
     int64_t ldp;
 };
@@ -281,15 +281,18 @@ __device__ __forceinline__ void add_lane_groups(float (&acc)[NV][E]) {
 
 // Scale, accumulate, bias, ReLU and store of E consecutive features of one output row.
 template <bool OBF16, int E>
-__device__ __forceinline__ void store_row(const SpmmArgs &a, char *yrow, int f0, float oscale, const float (&acc)[E]) {
+__device__ __forceinline__ void store_row(const SpmmArgs &a, int row, int f0, const float (&acc)[E]) {
     constexpr int ES = OBF16 ? 2 : 4;
     if (f0 >= a.F) return;
+    char *yrow = a.Y + static_cast<int64_t>(row) * a.ldy_bytes;
+    const float oscale = a.out_scale ? a.out_scale[row] : 1.f;
+    const bool accumulate = row < a.acc_rows;
     float y[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
         float t = acc[j] * oscale;
         if (f0 + j < a.F) {
-            if (a.accumulate) t += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
+            if (accumulate) t += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
             if (a.bias) t += a.bias[f0 + j];
         }
         if (a.relu) t = t > 0.f ? t : 0.f;
@@ -348,10 +351,8 @@ __global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void s
                 if (f0 < a.F) store_elems<false, E>(reinterpret_cast<char *>(prow + f0), acc[v]);
             }
         } else {
-            char *yrow = a.Y + static_cast<int64_t>(it.row) * a.ldy_bytes;
-            const float oscale = a.out_scale ? a.out_scale[it.row] : 1.f;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, yrow, elem0 + v * LPR * E, oscale, acc[v]);
+            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, it.row, elem0 + v * LPR * E, acc[v]);
         }
     }
 }
@@ -367,7 +368,6 @@ __global__ __launch_bounds__(256) void spmm_long_kernel(SpmmArgs a, const RowIte
     const RowItem it = cut[blockIdx.x];
     const uint32_t end = it.beg + it.cnt, per = (it.cnt + 3) / 4;
     const uint32_t e0 = wave * per < it.cnt ? it.beg + wave * per : end, e1 = end - e0 < per ? end : e0 + per;
-    const float oscale = a.out_scale ? a.out_scale[it.row] : 1.f;
     for (int pass = 0; pass < a.F_lim; pass += PASS) {
         const int elem0 = pass + lane % LPR * E;
         float acc[NV][E];
@@ -392,9 +392,8 @@ __global__ __launch_bounds__(256) void spmm_long_kernel(SpmmArgs a, const RowIte
                 for (int v = 0; v < NV; ++v)
 #pragma unroll
                     for (int j = 0; j < E; ++j) acc[v][j] += red[p][v * E + j][lane];
-            char *yrow = a.Y + static_cast<int64_t>(it.row) * a.ldy_bytes;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, yrow, elem0 + v * LPR * E, oscale, acc[v]);
+            for (int v = 0; v < NV; ++v) store_row<OBF16, E>(a, it.row, elem0 + v * LPR * E, acc[v]);
         }
     }
 }
@@ -694,7 +693,7 @@ struct SpmmReduceArgs {
     int64_t ldy_bytes;
     int F;
     const float *bias;
-    int relu, accumulate;
+    int relu, acc_rows;
 };
 
 // one thread per (position, four consecutive features)
@@ -720,7 +719,7 @@ __global__ __launch_bounds__(256) void spmm_blocked_reduce_kernel(SpmmReduceArgs
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         if (f0 + j < a.F) {
-            if (a.accumulate) y[j] += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
+            if (row < a.acc_rows) y[j] += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
             if (a.bias) y[j] += a.bias[f0 + j];
         }
         if (a.relu) y[j] = y[j] > 0.f ? y[j] : 0.f;
@@ -794,7 +793,7 @@ static int launch_blocked(const SpOp &op, const BlockedGeom &g, const SpmmArgs &
     SpmmReduceArgs r;
     r.off = op.b_off; r.order = op.order; r.out_scale = op.out_scale; r.part = part; r.ldp = g.ldp; r.n_out = op.n_out;
     r.ncb = op.ncb; r.Y = a.Y; r.ldy_bytes = a.ldy_bytes; r.F = a.F; r.bias = a.bias; r.relu = a.relu;
-    r.accumulate = a.accumulate;
+    r.acc_rows = a.acc_rows;
     const int64_t threads = op.n_out * ((a.F + 3) / 4);
     hipLaunchKernelGGL((spmm_blocked_reduce_kernel<OBF16>), dim3(static_cast<unsigned>((threads + 255) / 256)), dim3(256),
                        0, st, r);
@@ -826,7 +825,7 @@ __global__ void spmm_pieces_finish_kernel(SpmmArgs a, const RowItem *cut, const 
     if (threadIdx.y != 0 || f >= a.F) return;
     float acc[1] = {0.f};
     for (int y = 0; y < step; ++y) acc[0] += red[y][threadIdx.x];
-    store_row<OBF16, 1>(a, a.Y + static_cast<int64_t>(row) * a.ldy_bytes, f, a.out_scale ? a.out_scale[row] : 1.f, acc);
+    store_row<OBF16, 1>(a, row, f, acc);
 }
 
 // How long a row may be that one lane group walks alone.  A group takes about a microsecond for eight entries, so a row of T
@@ -922,7 +921,8 @@ int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, v
     a.X = static_cast<const char *>(X); a.ldx_bytes = ldx * es;
     a.Y = static_cast<char *>(Y); a.ldy_bytes = ldy * es_out;
     a.F = F; a.F_lim = vec ? f_up : F;
-    a.bias = ep.bias; a.relu = ep.relu; a.accumulate = ep.accumulate;
+    a.bias = ep.bias; a.relu = ep.relu;
+    a.acc_rows = ep.accumulate ? static_cast<int>(std::min<int64_t>(ep.acc_rows, INT32_MAX)) : 0;
     if (vec && !restrict_sub && ep.ws) {
         // the blocked kernel runs when the operator has a blocked copy and the caller brought the scratch for it
         const BlockedGeom bg = blocked_geom(op, F, dtype);

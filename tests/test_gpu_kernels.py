@@ -477,6 +477,44 @@ def test_gemm_bf16_matrix_core_path(env, ta, tb):
             assert (got[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_gemm_size_classes_exact(env, dtype, ta, tb):
+    """Both sides of the limits between the product kernels: single elements, ragged 32- and 64-wide tiles, K around a unit, a
+    batch and 128, 512 and 513 tiles of 32 rows, 768 and 769 tiles of 64 rows, vertex reductions with one and with many
+    splits; rows that are and are not 16-byte aligned.  Small integers: every product and sum is an integer below 2^24
+    (K * 9 at most), so each form of the product gives it exactly."""
+    torch, B, H, O = env["torch"], env["B"], env["H"], env["O"]
+    rng = np.random.default_rng(70 + 2 * ta + tb)
+    sizes = [(1, 1, 1), (31, 33, 7), (32, 32, 8), (33, 64, 9), (65, 65, 31), (64, 63, 33), (97, 130, 127), (96, 128, 128), (40, 40, 129),
+             (70, 256, 300)]
+    sizes += [(130, 121, 2999), (64, 47, 5003), (8, 7, 20000), (257, 200, 1025)] if ta else [
+        (16384, 64, 20), (16385, 64, 20), (49152, 64, 36), (49153, 64, 36), (3000, 300, 100)]
+    for M, N, K in sizes:
+        A = rng.integers(-3, 4, (K, M) if ta else (M, K)).astype(np.float32)
+        Bm = rng.integers(-3, 4, (N, K) if tb else (K, N)).astype(np.float32)
+        ref = (A.T if ta else A).astype(np.float64) @ (Bm.T if tb else Bm).astype(np.float64)
+        st = (lambda x: synth.f32_to_bf16_rne(x).reshape(x.shape)) if dtype == "bf16" else (lambda x: x)
+        dt = B.BF16 if dtype == "bf16" else B.F32
+        for mult, forms in ((8, (0, 1, 2)), (1, (0,))):           # row pitches: whole vectors, or the bare width plus one
+            lda = synth.pad_to(A.shape[1], mult) + (mult == 1)
+            ldb = synth.pad_to(Bm.shape[1], mult) + (mult == 1)
+            ldc = N + 3
+            Ad, Bd = H.padded_matrix(st(A), lda), H.padded_matrix(st(Bm), ldb)
+            Ad[:, A.shape[1]:] = float("nan")                     # what the padding holds never reaches C
+            Bd[:, Bm.shape[1]:] = float("nan")
+            for form in forms if dtype == "f32" else (0,):
+                wsb = B.gemm_workspace_bytes(ta, M, N, K)
+                ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+                Cd = torch.full((M, ldc), 2.0, dtype=torch.float32, device="cuda")
+                say(f"gemm classes {dtype} ta={ta} tb={tb} {M}x{N}x{K} lda={lda} form={form}")
+                B.gemm(ta, tb, M, N, K, Ad, lda, Bd, ldb, Cd, ldc, dt, out_f32=1, ws=ws, ws_bytes=wsb, f32_product=form)
+                torch.cuda.synchronize()
+                got = Cd.cpu().numpy()
+                assert np.array_equal(got[:, :N].astype(np.float64), ref), (M, N, K, form)
+                assert (got[:, N:] == 2.0).all(), "padding columns were written"
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
