@@ -105,6 +105,7 @@ constexpr int CB_ROWS = 32768;  // source rows per column block: 32768 x 128-byt
 constexpr int B_LONG_GROUP = 1024; // rows with at least this many entries per source block on average: workgroup per group (swept 256 .. 4096)
 constexpr int B_MID_GROUP = 256;  // ... at least this many: wave per group (swept 64 .. 1024; the eight-rows-per-wave class below is the fastest)
 constexpr int SLICE_BYTES = 128;  // feature bytes of one source row that one task of the blocked kernel gathers
+constexpr int NUM_CU = 256;       // compute units of the chip
 constexpr int NUM_XCD = 8;        // L2 domains of the chip; workgroup b is dispatched to domain b % NUM_XCD
 
 }  // namespace capgnn
@@ -158,6 +159,8 @@ struct SpmmEpilogue {
     int relu = 0;
     int accumulate = 0;            // add the previous contents of Y
     int64_t acc_rows = INT64_MAX;  // ... in output rows below this one
+    const void *mask = nullptr;    // [rows x ldm] of Y's storage type: Y is zeroed where it is not positive
+    int64_t ldm = 0;
     int out_f32 = 0;               // store Y as float although X is bf16
     int out_bf16 = 0;              // store Y as bf16 although X is float (the loss gradient of a bf16 model is gathered unrounded)
     int operand_scaled = 0;        // row s of X already carries in_scale[s] (only for operators with weights_by_source)
@@ -174,16 +177,18 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
                 hipStream_t stream, const float *row_scale = nullptr,    // row_scale: C[i,:] *= row_scale[i] at the very end (fp32 C)
-                int f32_product = CAPGNN_F32_PRODUCT_AUTO);
+                int f32_product = CAPGNN_F32_PRODUCT_AUTO,
+                float *colsum = nullptr);                                // [N] column sums of B (trans_a && !trans_b only)
 // C = A op(W) + A2 op(W2) (+ bias, ReLU), one launch where a kernel forms the sum, else the two launches it replaces
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
-                     const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product);
+                     const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product,
+                     const void *relu_mask = nullptr, int64_t ldm = 0);
 // C = op(A) op(B) (rows scaled) and C2 = op(A2) op(B2), one launch for small and middling sizes
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product);
+                     int f32_product, float *colsum = nullptr);
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K);
 // scratch that lets launch_gemm_dual run as one launch
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2);
@@ -196,11 +201,21 @@ size_t relu_bias_ws_bytes(int64_t n, int F);
 int launch_relu_mask_dbias(int64_t n, int F, const void *src, int64_t lds, int src_dtype, void *dH, int64_t lddh,
                            const void *H, int64_t ldh, int dtype, int h_dtype, int relu, float *dbias, void *ws,
                            size_t ws_bytes, hipStream_t stream, const float *row_scale = nullptr);
-int launch_sgd(float *W, const float *dW, int64_t n, float lr, hipStream_t stream);
-// capgnn_softmax_ce that also writes the logits as a dense [n x C] matrix to `copy` (NULL: does not)
-int softmax_ce_with_copy(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *mask,
-                         double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, void *ws, size_t ws_bytes,
-                         hipStream_t st, float *copy);
+// tensors of one SGD step (three per layer at most)
+struct SgdList {
+    float *W[48];
+    const float *dW[48];
+    int64_t n[48];
+    unsigned first[48];         // filled by launch_sgd
+    int count = 0;
+};
+int launch_sgd(SgdList s, float lr, hipStream_t stream);
+// the loss of an epoch on labels or targets, with what else can be had on the way (see ops.hip)
+int loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
+               const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy, float *dbias,
+               const float *row_scale, void *ws, size_t ws_bytes, hipStream_t st);
+size_t loss_epoch_ws_bytes(int64_t n, int C);
+bool loss_sums_columns(int C);      // whether loss_epoch can form dbias
 
 uint64_t hash_gid(uint64_t x);
 

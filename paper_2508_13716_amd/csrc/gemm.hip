@@ -23,6 +23,7 @@ struct GemmArgs {
     const char *B; int64_t ldb;
     char *C; int64_t ldc;           // final destination
     float *part;                    // split partials [S][M][N] or null
+    float *colpart;                 // [S][N] column sums of B over the split's k (reductions over vertices), or null
     int64_t k_chunk;                // reduction range per grid.z
     int a_vec, b_vec;               // operand rows allow 4-element vector loads
     int out_bf16, accumulate, relu;
@@ -346,6 +347,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
         la.fast_begin(g.A, g.lda, m0, k_begin + BK, tid);
         lb.fast_begin(g.B, g.ldb, n0, k_begin + BK, tid);
     }
+    // column sums of B (see gemm_small_kernel): a thread's vectors of a step cover the same four columns
+    constexpr bool SUMS = !A_KC && !B_KC;
+    const bool sums = SUMS && g.colpart && by == 0;
+    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
+    auto add_b = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < TileLoader<BF16, B_KC, BN>::NLD; ++q) { bsum[0] += lb.r[q].x; bsum[1] += lb.r[q].y; bsum[2] += lb.r[q].z; bsum[3] += lb.r[q].w; }
+    };
+    if (sums && nk > 0) add_b();
     __syncthreads();
     for (int64_t kt = 0; kt < nk; ++kt) {
         const int buf = static_cast<int>(kt & 1);
@@ -385,12 +395,28 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
             __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
         }
         if (more) {
+            if (sums) add_b();
             la.stash(As[buf ^ 1], tid);
             lb.stash(Bs[buf ^ 1], tid);
         }
         __syncthreads();
     }
 
+    if constexpr (SUMS) {
+        if (sums) {     // the operand tiles are free: [256 / (BN / 4)][BN] partial sums
+            float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+            constexpr int QPR = BN / 4, ROWS = 256 / QPR;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bred[tid / QPR][4 * (tid % QPR) + e] = bsum[e];
+            __syncthreads();
+            if (tid < BN && n0 + tid < g.N) {
+                float t = 0.f;
+                for (int y = 0; y < ROWS; ++y) t += bred[y][tid];
+                g.colpart[bz * g.N + n0 + tid] = t;
+            }
+            __syncthreads();
+        }
+    }
     if constexpr (STAGED) {
         // the last pass through the loop ended with a barrier: every wave is done with the operands
         store_tile_staged(g, acc, smem + wave * (STAGE_BYTES / 4), m0 + wm * WM, n0 + wn * WN, lane, bz);
@@ -515,6 +541,18 @@ struct HalfTileLoader {
     }
 };
 
+__device__ __forceinline__ bool positive_bf16(uint32_t bits) { return __uint_as_float(bits << 16) > 0.f; }
+
+// eight bf16: those of v where m > 0, else zero
+__device__ __forceinline__ uint4 keep_positive(uint4 v, uint4 m) {
+    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t k[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        w[d] &= (positive_bf16(k[d] & 0xffffu) ? 0xffffu : 0u) | (__uint_as_float(k[d] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 template <bool A_KC, bool B_KC, int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
     constexpr int WM = BM / 2, WN = BN / 2;
@@ -565,6 +603,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
             lb.fast_begin(g.B, g.ldb, n0, k_begin + HBK, tid);
         }
     }
+    // column sums of B (see gemm_small_kernel): a staging thread's four rows of a step cover the same eight columns
+    constexpr bool SUMS = !A_KC && !B_KC;
+    const bool sums = SUMS && g.colpart && by == 0;
+    float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto add_b = [&]() __attribute__((always_inline)) {
+        if constexpr (SUMS) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t w[4] = {lb.r[q].x, lb.r[q].y, lb.r[q].z, lb.r[q].w};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    bsum[2 * d] += __uint_as_float(w[d] << 16);
+                    bsum[2 * d + 1] += __uint_as_float(w[d] & 0xffff0000u);
+                }
+            }
+        }
+    };
+    if (sums && nk > 0) add_b();
     __syncthreads();
     for (int64_t kt = 0; kt < nk; ++kt) {
         const int buf = static_cast<int>(kt & 1);
@@ -603,10 +659,28 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
         if (more) {
+            if (sums) add_b();
             la.stash(As[buf ^ 1], tid);
             lb.stash(Bs[buf ^ 1], tid);
         }
         __syncthreads();
+    }
+    if constexpr (SUMS) {
+        if (sums) {     // threads 128 .. 128 + NTH of the workgroup stage B: [HBK / 4][BN] partial sums
+            float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+            constexpr int CPR = BN / 8;
+            const int tt = tid - 128;
+            if (tt >= 0 && tt < (HBK / 4) * CPR)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) bred[tt / CPR][8 * (tt % CPR) + e] = bsum[e];
+            __syncthreads();
+            if (tid < BN && n0 + tid < g.N) {
+                float t = 0.f;
+                for (int y = 0; y < HBK / 4; ++y) t += bred[y][tid];
+                g.colpart[bz * g.N + n0 + tid] = t;
+            }
+            __syncthreads();
+        }
     }
     if (!g.c_staged) {
         store_tile<TM, TN>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
@@ -636,10 +710,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
         const int64_t grow = m0 + row, gcol = n0 + 8 * cq;
         if (grow >= g.M || gcol >= g.N) continue;
         uint16_t *dst = reinterpret_cast<uint16_t *>(g.C) + grow * g.ldc + gcol;
+        uint4 v = *reinterpret_cast<const uint4 *>(&Cs[row][8 * cq]);
         if (gcol + 8 <= g.N) {
-            *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(&Cs[row][8 * cq]);
+            if (g.mask) v = keep_positive(v, *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(g.mask) + grow * g.ldm + gcol));
+            *reinterpret_cast<uint4 *>(dst) = v;
         } else {
-            for (int e = 0; gcol + e < g.N; ++e) dst[e] = Cs[row][8 * cq + e];
+            for (int e = 0; gcol + e < g.N; ++e)
+                dst[e] = g.mask && !positive_bf16(reinterpret_cast<const uint16_t *>(g.mask)[grow * g.ldm + gcol + e]) ? 0 : Cs[row][8 * cq + e];
         }
     }
 }
@@ -1049,6 +1126,13 @@ __global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kerne
         lc.put();
         if (interior) lc.fast_begin(k_begin + SBK);
     }
+    // column sums of B (see gemm_small_kernel): waves 4-7 stage it, a thread's block of a step is four k of four columns
+    const bool sums = g.colpart && by == 0;
+    f32x4 bsum = {0.f, 0.f, 0.f, 0.f};
+    auto add_b = [&]() __attribute__((always_inline)) {
+        if (!lc.idle) bsum += (lc.r[0] + lc.r[1]) + (lc.r[2] + lc.r[3]);
+    };
+    if (sums && nk > 0) add_b();
     __syncthreads();
     const int slot_b = ColUnits8::col_slot(wn * WN + l32);
     auto products = [&]() {
@@ -1081,11 +1165,25 @@ __global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kerne
         else lc.fetch(k_begin + (kt + 1) * SBK, k_end, both_vec);
         products();
         __syncthreads();            // every wave has read this step's operands
+        if (sums) add_b();
         lc.cut();
         lc.put();
         __syncthreads();
     }
     if (nk > 0) products();
+    if (sums) {
+        __syncthreads();            // the operand tiles are free: [8][BN] partial sums
+        float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+        if (tid >= 256 && !lc.idle)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bred[lc.kb][4 * lc.tq + e] = bsum[e];
+        __syncthreads();
+        if (tid < BN && n0 + tid < g.N) {
+            float t = 0.f;
+            for (int y = 0; y < 8; ++y) t += bred[y][tid];
+            g.colpart[bz * g.N + n0 + tid] = t;
+        }
+    }
     store_tile<TM, 1>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
 }
 
@@ -1213,6 +1311,11 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway
+    const bool sums = !A_KC && !B_KC && g.colpart && by == 0 && !second;      // uniform over the workgroup
+    float bsum[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bsum[j] = 0.f;
     if (k < k_end) fetch(k);
     for (; k < k_end; k += UB * UK) {
         SmallUnit<BF16> ca[UB], cb[UB][TN];
@@ -1223,6 +1326,17 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
             for (int j = 0; j < TN; ++j) cb[u][j] = b[u][j];
         }
         if (k + UB * UK < k_end) fetch(k + UB * UK);
+        if (sums) {
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (BF16) bsum[j] += __uint_as_float(cb[u][j].v[e] << 16) + __uint_as_float(cb[u][j].v[e] & 0xffff0000u);
+                        else bsum[j] += cb[u][j].v[e];
+                    }
+        }
 #pragma unroll
         for (int u = 0; u < UB; ++u)
 #pragma unroll
@@ -1240,7 +1354,18 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * half + (r & 3)][j * 32 + l32] = acc[j][r];
+    __shared__ float bred[4][TN * 32];
+    if (sums) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const float t = bsum[j] + __shfl_xor(bsum[j], 32);
+            if (half == 0) bred[wave][j * 32 + l32] = t;
+        }
+    }
     __syncthreads();
+    if (sums)
+        for (int c = threadIdx.x; c < TN * 32; c += 256)
+            if (n0 + c < g.N) g.colpart[bz * g.N + n0 + c] = (bred[0][c] + bred[1][c]) + (bred[2][c] + bred[3][c]);
     float *part = second ? s.part2 : g.part;
     char *C = second ? s.C2 : g.C;
     const int64_t ldc = second ? s.ldc2 : g.ldc;
@@ -1434,12 +1559,28 @@ __global__ __launch_bounds__(256) void repack_bf16_kernel(const uint16_t *W, int
 // groups of threads; group y adds the partials z = y, y+8, ... in that order, then the 8 group sums are added
 // in group order: a fixed summation order, whatever the launch geometry.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, const float *part2 = nullptr, char *C2 = nullptr,
-                                                          int64_t ldc2 = 0) {
+                                                          int64_t ldc2 = 0, float *colsum = nullptr) {
     if (blockIdx.y != 0) { g.part = const_cast<float *>(part2); g.C = C2; g.ldc = ldc2; }      // the second problem of a pair
     __shared__ float red[8][32];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int64_t total = g.M * g.N;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 32 + tx;
+    const int64_t total = g.part ? g.M * g.N : 0;       // (no partials: only the column sums are left to add)
+    int64_t t = static_cast<int64_t>(blockIdx.x) * 32 + tx;
+    const int64_t c_blocks = (total + 31) / 32;
+    if (static_cast<int64_t>(blockIdx.x) >= c_blocks) {     // the workgroups behind C's: column sums, in double precision
+        if (blockIdx.y != 0) return;
+        __shared__ double dred[8][32];
+        t -= c_blocks * 32;
+        double d = 0.0;
+        if (t < g.N)
+            for (int z = ty; z < S; z += 8) d += static_cast<double>(g.colpart[static_cast<int64_t>(z) * g.N + t]);
+        dred[ty][tx] = d;
+        __syncthreads();
+        if (ty != 0 || t >= g.N) return;
+        d = 0.0;
+        for (int y = 0; y < 8; ++y) d += dred[y][tx];
+        colsum[t] = static_cast<float>(d);
+        return;
+    }
     float v = 0.f;
     if (t < total)
         for (int z = ty; z < S; z += 8) v += g.part[static_cast<int64_t>(z) * total + t];
@@ -1502,14 +1643,18 @@ size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
     tile_for(N, &bm, &bn);
     // the larger split of the two kernels (they step through K in 16s and 32s)
     const int s = std::max(choose_split(trans_a, M, N, K, bm, bn, BK), choose_split(trans_a, M, N, K, bm, bn, HBK));
+    // partial results of every split, and the column sums of B
     size_t b = s > 1 ? align_up(static_cast<size_t>(s) * M * N * sizeof(float), 256) : 0;
+    int s_max = s;
     for (const bool bf : {false, true})
         if (trans_a && small_product(bf, trans_a, M, N, K)) {
             int tn, z;
             int64_t chunk;
             small_geometry(bf, trans_a, M, N, K, &tn, &z, &chunk);
             if (z > 1) b = std::max(b, align_up(static_cast<size_t>(z) * M * N * sizeof(float), 256));
+            s_max = std::max(s_max, z);
         }
+    if (trans_a) b += align_up(static_cast<size_t>(s_max) * N * sizeof(float), 256);
     // room to lay a weight matrix out for the bf16 kernel (bf16 operands) or as its three planes (fp32 operands)
     if (!trans_a) b = std::max(b, std::max(transposed_b_bytes(N, K), split_b_bytes(N, K)));
     return b;
@@ -1591,7 +1736,8 @@ static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, 
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
-                hipStream_t stream, const float *row_scale, int f32_product) {
+                hipStream_t stream, const float *row_scale, int f32_product, float *colsum) {
+    if (colsum && (!trans_a || trans_b)) CG_FAIL(CAPGNN_EINVAL, "gemm: column sums are formed by X^T G alone");
     if (dtype != CAPGNN_F32 && dtype != CAPGNN_BF16) CG_FAIL(CAPGNN_EINVAL, "gemm: unknown dtype %d", dtype);
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
@@ -1658,12 +1804,20 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         g.k_chunk = (steps + S - 1) / S * bk;
     }
     if (small_path) g.k_chunk = small_chunk;
+    g.colpart = nullptr;
+    if (colsum) {
+        const size_t at = S > 1 ? align_up(static_cast<size_t>(S) * M * N * sizeof(float), 256) : 0;
+        const size_t need = at + static_cast<size_t>(S) * N * sizeof(float);
+        if (!ws || ws_bytes < need) CG_FAIL(CAPGNN_ENOMEM, "gemm: workspace of %zu bytes needed, %zu given", need, ws_bytes);
+        g.colpart = reinterpret_cast<float *>(static_cast<char *>(ws) + at);
+    }
     const int64_t gy = (M + bm - 1) / bm, gx = (N + bn - 1) / bn;
     const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     if (n_wg >= (int64_t(1) << 31) || gx >= (int64_t(1) << 24) || gy >= (int64_t(1) << 30))
         CG_FAIL(CAPGNN_EINVAL, "gemm: %lld x %lld tiles exceed the grid", (long long)gy, (long long)gx);
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
-    g.c_staged = half_path && g.out_bf16 && !g.part && !g.mask && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0;
+    g.c_staged = half_path && g.out_bf16 && !g.part && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0 &&
+                 (!relu_mask || (aligned16(relu_mask) && (ldm * 2) % 16 == 0));
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
     if (small_path) {
@@ -1709,9 +1863,10 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 #undef CG_GEMM_CASE
     }
     CG_HIP(hipGetLastError());
-    if (S > 1) {
-        const int64_t total = M * N;
-        hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>((total + 31) / 32)), dim3(256), 0, stream, g, S);
+    if (S > 1 || colsum) {
+        const int64_t blocks = (S > 1 ? (M * N + 31) / 32 : 0) + (colsum ? (N + 31) / 32 : 0);
+        hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, g, S,
+                           static_cast<const float *>(nullptr), static_cast<char *>(nullptr), int64_t(0), colsum);
         CG_HIP(hipGetLastError());
     }
     return CAPGNN_OK;
@@ -1721,7 +1876,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 // C = op(A) op(B) and C2 = op(A2) op(B2) of one shape but for the rows (pair).  *done says whether the sizes are such a kernel's;
 // nothing has run otherwise.
 static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, int dtype, int out_f32, void *ws, size_t ws_bytes,
-                            hipStream_t stream, int f32_product, bool *done) {
+                            hipStream_t stream, int f32_product, float *colsum, bool *done) {
     *done = false;
     SmallGemmArgs s = in;
     GemmArgs &g = s.g;
@@ -1738,9 +1893,13 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     if (s.dual && S > 1) return CAPGNN_OK;           // a sum is formed by the waves of one workgroup
     if (S > 1) {
         const size_t one = align_up(static_cast<size_t>(S) * g.M * g.N * sizeof(float), 256);
-        if (g.M != s.M2 || !ws || ws_bytes < 2 * one) return CAPGNN_OK;
+        if (g.M != s.M2 || !ws || ws_bytes < 2 * one + static_cast<size_t>(S) * g.N * sizeof(float)) return CAPGNN_OK;
         g.part = static_cast<float *>(ws);
         s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + one);
+        if (colsum) g.colpart = reinterpret_cast<float *>(static_cast<char *>(ws) + 2 * one);
+    } else if (colsum) {
+        if (!ws || ws_bytes < g.N * sizeof(float)) return CAPGNN_OK;
+        g.colpart = static_cast<float *>(ws);
     }
     const int es = elem_bytes(dtype);
     auto vec_rows = [&](const void *p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) % (4 * es) == 0 && (ld * es) % (4 * es) == 0; };
@@ -1755,9 +1914,10 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
     else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
     else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
-    if (S > 1)
-        hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>((g.M * g.N + 31) / 32), 2), dim3(256), 0, stream, g, S,
-                           static_cast<const float *>(s.part2), s.C2, s.ldc2);
+    if (S > 1 || colsum)
+        hipLaunchKernelGGL(gemm_reduce_kernel,
+                           dim3(static_cast<unsigned>((S > 1 ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), pair ? 2 : 1),
+                           dim3(256), 0, stream, g, S, static_cast<const float *>(s.part2), s.C2, s.ldc2, colsum);
     CG_HIP(hipGetLastError());
     *done = true;
     return CAPGNN_OK;
@@ -1768,7 +1928,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product) {
+                     int f32_product, float *colsum) {
     if (M2 > M) CG_FAIL(CAPGNN_EINVAL, "gemm_pair: the second product has more rows");
     SmallGemmArgs s{};
     s.g.M = M; s.g.N = N; s.g.K = K;
@@ -1779,10 +1939,10 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
     bool done = false;
     if (M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
         lda2 >= (trans_a ? M : K) && ldb >= (trans_b ? K : N) && ldb2 >= (trans_b ? K : N))
-        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, &done));
+        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done));
     if (done) return CAPGNN_OK;
     CG_TRY(launch_gemm(trans_a, trans_b, M, N, K, A, lda, B, ldb, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes, stream,
-                       row_scale, f32_product));
+                       row_scale, f32_product, colsum));
     return launch_gemm(trans_a, trans_b, M2, N, K, A2, lda2, B2, ldb2, C2, ldc2, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
                        stream, nullptr, f32_product);
 }
@@ -1796,7 +1956,8 @@ size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return
 // W2 [K2 x N], or their transposes when trans_b.
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
-                     const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product) {
+                     const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product, const void *relu_mask,
+                     int64_t ldm) {
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
     const bool sane = M > 0 && N > 0 && K1 > 0 && K2 > 0 && A && A2 && W && W2 && C && lda >= K1 && lda2 >= K2 &&
@@ -1808,13 +1969,14 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
     g.B = static_cast<const char *>(W); g.ldb = ldw;
     g.C = static_cast<char *>(C); g.ldc = ldc;
     g.relu = relu; g.bias = bias;
+    g.mask = static_cast<const char *>(relu_mask); g.ldm = ldm; g.mask_bf16 = dtype == CAPGNN_BF16;
     if (sane) {
         SmallGemmArgs s{};
         s.g = g;
         s.g.K = K1; s.K2 = K2; s.dual = 1; s.M2 = M;
         s.A2 = static_cast<const char *>(A2); s.lda2 = lda2; s.B2 = static_cast<const char *>(W2); s.ldb2 = ldw2;
         bool done = false;
-        CG_TRY(launch_two_small(s, 0, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, &done));
+        CG_TRY(launch_two_small(s, 0, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, nullptr, &done));
         if (done) return CAPGNN_OK;
     }
     const int64_t K1p = split_ld(K1 > 0 ? K1 : 0), K = K1p + K2;
@@ -1824,7 +1986,7 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
     if (!one_launch) {
         CG_TRY(launch_gemm(0, trans_b, M, N, K2, A2, lda2, W2, ldw2, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
                            stream, nullptr, f32_product));
-        return launch_gemm(0, trans_b, M, N, K1, A, lda, W, ldw, C, ldc, dtype, out_f32, 1, bias, relu, nullptr, 0, ws, ws_bytes,
+        return launch_gemm(0, trans_b, M, N, K1, A, lda, W, ldw, C, ldc, dtype, out_f32, 1, bias, relu, relu_mask, ldm, ws, ws_bytes,
                            stream, nullptr, f32_product);
     }
     int bm, bn;

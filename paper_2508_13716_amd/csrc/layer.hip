@@ -208,10 +208,25 @@ static int layer_fwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     return CAPGNN_OK;
 }
 
+// What an epoch hands a layer's backward pass, so that no pass over the gradient alone is left: the layer above has applied this
+// layer's sigma' where it produced the gradient, the weight gradient's product sums the columns of dZ for the bias, and this
+// layer applies the sigma' of the layer below where it produces dX.
+struct BwdFusion {
+    bool ready = false;             // dH is dZ already (masked; rows scaled where scaled_dz() says so)
+    bool dbias_done = false;        // dbias is complete
+    const void *dx_mask = nullptr;  // zero dX where this is not positive (storage type of the layer)
+    int64_t ld_mask = 0;
+};
+
+// The transposed aggregation gathers dZ itself and wants its rows multiplied by their scale (layer_bwd_impl).
+static bool scaled_dz(const capgnn_graph *g, const capgnn_layer *l, int order) {
+    return l->dtype == CAPGNN_F32 && g->bwd.weights_by_source && order == CAPGNN_XFORM_FIRST && l->kind != CAPGNN_SAGE_MEAN;
+}
+
 static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int order, int li, const void *X, int64_t ldx,
                           const void *H, int64_t ldh, const void *saved, void *dH, int64_t lddh, float *dW,
                           float *dW_self, float *dbias, void *dX, int64_t lddx, int need_halo_grad, void *ws,
-                          size_t ws_bytes, hipStream_t st) {
+                          size_t ws_bytes, hipStream_t st, const BwdFusion &fuse = BwdFusion()) {
     const int dt = l->dtype;
     const bool sage = l->kind == CAPGNN_SAGE_MEAN;
     const int relu = l->act == CAPGNN_ACT_RELU;
@@ -248,21 +263,29 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     // edge values: the rows it gathers are multiplied by that scale where they are produced (dZ below when it is
     // gathered itself and nothing else reads it; dH W^T in the other order) and it sums unweighted.  fp32 only.
     const bool pre_b = dt == CAPGNN_F32 && g->bwd.weights_by_source;
-    const bool scale_dz = pre_b && order == CAPGNN_XFORM_FIRST && !sage && (dW || dX);
+    const bool scale_dz = scaled_dz(g, l, order) && (dW || dX);
     const bool need_copy = f32grad && (order == CAPGNN_AGG_FIRST || sage);
-    {   // dZ = dH * sigma'(Z) in place; dbias = column sums of dZ
+    // who sums the columns of dZ: the product X^T dZ where dZ is its operand as it is (not rounded, not scaled), else a pass
+    const bool sum_in_gemm = dbias && fuse.ready && !fuse.dbias_done && !f32grad && (order == CAPGNN_AGG_FIRST ? dW != nullptr
+                                                                                                        : sage && dW_self);
+    float *gemm_db = sum_in_gemm ? dbias : nullptr;
+    if (fuse.ready && (sum_in_gemm || fuse.dbias_done || !dbias) && !need_copy) {
+        // nothing left to do here
+    } else {   // dZ = dH * sigma'(Z) in place; dbias = column sums of dZ
         Scope s(CAPGNN_K_ELEMENTWISE, li, 1, st);
         const int h_dt = (l->out_f32 ? CAPGNN_F32 : dt);
         if (f32grad) {
             // mask and bias gradient in float, in place; then the rounded copy where a dense product needs one
-            CG_TRY(launch_relu_mask_dbias(g->n_loc, l->f_out, nullptr, 0, CAPGNN_F32, dH, lddh, H, ldh, CAPGNN_F32, h_dt, relu,
-                                          dbias, ws_rb, rb, st, nullptr));
+            if (!fuse.ready || !fuse.dbias_done)
+                CG_TRY(launch_relu_mask_dbias(g->n_loc, l->f_out, nullptr, 0, CAPGNN_F32, dH, lddh, H, ldh, CAPGNN_F32, h_dt,
+                                              fuse.ready ? 0 : relu, fuse.dbias_done ? nullptr : dbias, ws_rb, rb, st, nullptr));
             if (need_copy)
                 CG_TRY(launch_relu_mask_dbias(g->n_loc, l->f_out, dH, lddh, CAPGNN_F32, dHb, lddhb, nullptr, 0, CAPGNN_BF16,
                                               h_dt, 0, nullptr, ws_rb, rb, st, nullptr));
         } else {
-            CG_TRY(launch_relu_mask_dbias(g->n_loc, l->f_out, nullptr, 0, dt, dH, lddh, H, ldh, dt, h_dt, relu, dbias,
-                                          ws_rb, rb, st, scale_dz ? g->bwd.in_scale : nullptr));
+            CG_TRY(launch_relu_mask_dbias(g->n_loc, l->f_out, nullptr, 0, dt, dH, lddh, H, ldh, dt, h_dt, fuse.ready ? 0 : relu,
+                                          fuse.dbias_done ? nullptr : dbias, ws_rb, rb, st,
+                                          scale_dz && !fuse.ready ? g->bwd.in_scale : nullptr));
         }
     }
     if (order == CAPGNN_AGG_FIRST) {
@@ -272,10 +295,10 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
             Scope s(CAPGNN_K_GEMM, li, 1, st);
             if (sage && dW && dW_self) {
                 CG_TRY(launch_gemm_pair(1, 0, l->f_in, l->f_in, l->f_out, g->n_loc, saved, ldm, X, ldx, dHb, lddhb, dHb, lddhb, dW, l->f_out,
-                                        dW_self, l->f_out, dt, 1, nullptr, ws_gemm, gw, st, l->f32_product));
+                                        dW_self, l->f_out, dt, 1, nullptr, ws_gemm, gw, st, l->f32_product, gemm_db));
             } else {
                 if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, saved, ldm, dHb, lddhb, dW, l->f_out, dt, 1, 0,
-                                           nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                                           nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product, gemm_db));
                 if (sage && dW_self)
                     CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0,
                                        nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
@@ -294,6 +317,8 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
             sp_ep.operand_scaled = pre_b;
             sp_ep.accumulate = sage ? 1 : 0;
             sp_ep.acc_rows = g->n_loc;               // halo rows have no self term
+            sp_ep.mask = fuse.dx_mask;
+            sp_ep.ldm = fuse.ld_mask;
             CG_TRY(launch_spmm(g->bwd, !need_halo_grad, tmp, ldm, dX, lddx, l->f_in, dt, sp_ep, st));
         }
         return CAPGNN_OK;
@@ -312,15 +337,15 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
                                nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
     if (sage && dW_self)
         CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0, nullptr, 0,
-                           nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                           nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product, gemm_db));
     if (dX) {
         const int64_t rows = need_halo_grad ? g->n_cols : g->n_loc;
         if (sage && !need_halo_grad) {
             CG_TRY(launch_gemm_dual(1, g->n_loc, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX,
-                                    lddx, dt, 0, nullptr, 0, ws_gemm, gw, st, l->f32_product));
+                                    lddx, dt, 0, nullptr, 0, ws_gemm, gw, st, l->f32_product, fuse.dx_mask, fuse.ld_mask));
         } else {
             CG_TRY(launch_gemm(0, 1, rows, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, dX, lddx, dt, 0, 0, nullptr, 0,
-                               nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                               fuse.dx_mask, fuse.ld_mask, ws_gemm, gw, st, nullptr, l->f32_product));
             if (sage)
                 CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX, lddx, dt, 0, 1,
                                    nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
@@ -364,7 +389,7 @@ static int plan_epoch(const capgnn_graph *g, const capgnn_cache *c, const capgnn
     p->grad_off[1] = take(static_cast<size_t>(g->n_loc) * max_w * sizeof(float));
     p->layer_ws_bytes = lws;
     p->layer_ws_off = take(lws);
-    p->loss_ws_off = take(capgnn_loss_workspace_bytes(g->n_loc));
+    p->loss_ws_off = take(loss_epoch_ws_bytes(g->n_loc, layers[L - 1].f_out));
     p->loss_val_off = take(256);
     if (c && c->miss_mode != CAPGNN_MISS_ZEROCOPY) {
         size_t hb = 0;
@@ -591,18 +616,23 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
     // loss and its gradient w.r.t. the logits
     float *loss_dev = reinterpret_cast<float *>(w + p.loss_val_off);
     int cur = 0;
+    BwdFusion fuse;
     {
         Scope s(CAPGNN_K_LOSS, L - 1, 0, st);
         // a bf16 model gets the gradient in fp32 first (the bias gradient is summed before rounding)
         void *dz = dt == CAPGNN_BF16 ? static_cast<void *>(w + p.dz32_off) : static_cast<void *>(w + p.grad_off[cur]);
         const int64_t lddz = dt == CAPGNN_BF16 ? ldz : p.ld_grad;
         const int dzt = dt == CAPGNN_BF16 ? CAPGNN_F32 : dt;
-        if (targets)
-            CG_TRY(capgnn_sigmoid_bce(g->n_loc, C, Z, ldz, targets, ldt, mask, loss_norm, loss_dev, dz, lddz, dzt,
-                                      w + p.loss_ws_off, capgnn_loss_workspace_bytes(g->n_loc), st));
-        else    // the loss kernel reads every logit anyway: it also writes the caller's dense copy
-            CG_TRY(softmax_ce_with_copy(g->n_loc, C, Z, ldz, labels, mask, loss_norm, loss_dev, dz, lddz, dzt,
-                                        w + p.loss_ws_off, capgnn_loss_workspace_bytes(g->n_loc), st, logits));
+        // the kernel reads every logit anyway: it also writes the caller's dense copy, sums the columns of dZ for the last bias
+        // and scales the rows of dZ when the last layer's transposed aggregation gathers them
+        const bool linear = layers[L - 1].act == CAPGNN_ACT_NONE && g->n_loc > 0;
+        fuse.ready = linear;
+        fuse.dbias_done = linear && dbias[L - 1] && loss_sums_columns(C);
+        const bool scale = linear && scaled_dz(g, &layers[L - 1], p.order[L - 1]);
+        if (scale && dbias[L - 1] && !fuse.dbias_done) fuse.ready = false;       // the pass that sums the columns scales the rows
+        CG_TRY(loss_epoch(g->n_loc, C, Z, ldz, labels, targets, ldt, mask, loss_norm, loss_dev, dz, lddz, dzt, logits,
+                          fuse.dbias_done ? dbias[L - 1] : nullptr, scale && fuse.ready ? g->bwd.in_scale : nullptr, w + p.loss_ws_off,
+                          loss_epoch_ws_bytes(g->n_loc, C), st));
     }
     // backward
     for (int l = L - 1; l >= 0; --l) {
@@ -612,26 +642,31 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
         void *dX = l > 0 ? static_cast<void *>(w + p.grad_off[cur ^ 1]) : nullptr;
         // the last layer of a bf16 model takes the loss gradient as float (its output is float as well)
         const bool f32grad = last && dt == CAPGNN_BF16;
+        // sigma' of the layer below goes into the kernel that writes dX, unless that layer's own pass is needed to scale the rows
+        const bool below = l > 0 && !scaled_dz(g, &layers[l - 1], p.order[l - 1]);
+        if (below && layers[l - 1].act == CAPGNN_ACT_RELU) { fuse.dx_mask = Xl(l); fuse.ld_mask = p.ldx[l]; }
         CG_TRY(layer_bwd_impl(g, &layers[l], p.order[l], l, Xl(l), p.ldx[l], Hl, ldh, w + p.saved_off[l],
                               f32grad ? static_cast<void *>(w + p.dz32_off) : static_cast<void *>(w + p.grad_off[cur]),
                               f32grad ? ldz : p.ld_grad, dW[l], dW_self ? dW_self[l] : nullptr, dbias[l], dX,
-                              p.ld_grad, 0, w + p.layer_ws_off, p.layer_ws_bytes, st));
+                              p.ld_grad, 0, w + p.layer_ws_off, p.layer_ws_bytes, st, fuse));
+        fuse = BwdFusion();
+        fuse.ready = below;
         cur ^= 1;
     }
     if (lr != 0.f) {
         Scope s(CAPGNN_K_ELEMENTWISE, 0, 1, st);
+        SgdList sgd;
+        auto add = [&](void *w, const float *d, int64_t n) {
+            sgd.W[sgd.count] = static_cast<float *>(w); sgd.dW[sgd.count] = d; sgd.n[sgd.count++] = n;
+        };
         for (int l = 0; l < L; ++l) {
             const int64_t nw = static_cast<int64_t>(layers[l].f_in) * layers[l].f_out;
-            CG_TRY(launch_sgd(static_cast<float *>(layers[l].W), dW[l], nw, lr, st));
-            if (layers[l].kind == CAPGNN_SAGE_MEAN && dW_self && dW_self[l])
-                CG_TRY(launch_sgd(static_cast<float *>(layers[l].W_self), dW_self[l], nw, lr, st));
-            if (layers[l].bias && dbias[l]) CG_TRY(launch_sgd(layers[l].bias, dbias[l], layers[l].f_out, lr, st));
+            add(layers[l].W, dW[l], nw);
+            if (layers[l].kind == CAPGNN_SAGE_MEAN && dW_self && dW_self[l]) add(layers[l].W_self, dW_self[l], nw);
+            if (layers[l].bias && dbias[l]) add(layers[l].bias, dbias[l], layers[l].f_out);
         }
+        CG_TRY(launch_sgd(sgd, lr, st));
     }
-    if (logits && targets)
-        CG_HIP(hipMemcpy2DAsync(logits, static_cast<size_t>(C) * sizeof(float), Z, static_cast<size_t>(ldz) * sizeof(float),
-                                static_cast<size_t>(C) * sizeof(float), static_cast<size_t>(g->n_loc),
-                                hipMemcpyDeviceToDevice, st));
     if (capture && has_miss && side != st) {
         // a recorded epoch ends when its side stream has: the prefetches for the next replay are part of this one
         CG_HIP(hipEventRecord(ev.join, side));

@@ -243,12 +243,12 @@ __global__ __launch_bounds__(256) void relu_mask_dbias_bf16x8_kernel(int64_t n, 
     }
 }
 
-// dbias[f] = sum_b partial[b][f]: 32 features x 32 strided groups per workgroup, doubles, fixed order
+// dbias[f] = sum_b partial[b][f] for 32 features f from 32 * chunk on: 32 strided groups of 32 threads, doubles, fixed order.
+// red: 1024 doubles of LDS.
 constexpr int DBF_GROUPS = 32;
-__global__ __launch_bounds__(1024) void dbias_final_kernel(int64_t nblocks, int F, const float *partial, float *dbias) {
-    __shared__ double red[DBF_GROUPS][32];
+__device__ __forceinline__ void column_sums(int chunk, int64_t nblocks, int F, const float *partial, float *dbias, double *red) {
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int f = blockIdx.x * 32 + tx;
+    const int f = chunk * 32 + tx;
     double s = 0.0;
     if (f < F) {
         int64_t b = ty;
@@ -260,13 +260,18 @@ __global__ __launch_bounds__(1024) void dbias_final_kernel(int64_t nblocks, int 
         }
         for (; b < nblocks; b += DBF_GROUPS) s += static_cast<double>(partial[b * F + f]);
     }
-    red[ty][tx] = s;
+    red[ty * 32 + tx] = s;
     __syncthreads();
     if (ty == 0 && f < F) {
         double t = 0.0;
-        for (int y = 0; y < DBF_GROUPS; ++y) t += red[y][tx];
+        for (int y = 0; y < DBF_GROUPS; ++y) t += red[y * 32 + tx];
         dbias[f] = static_cast<float>(t);
     }
+}
+
+__global__ __launch_bounds__(1024) void dbias_final_kernel(int64_t nblocks, int F, const float *partial, float *dbias) {
+    __shared__ double red[1024];
+    column_sums(blockIdx.x, nblocks, F, partial, dbias, red);
 }
 
 static int64_t rb_blocks(int64_t n) {
@@ -349,54 +354,97 @@ int launch_relu_mask_dbias(int64_t n, int F, const void *src, int64_t lds, int s
 }
 
 // ------------------------------------------------------------------ SGD
-__global__ __launch_bounds__(256) void sgd_kernel(float *W, const float *dW, int64_t n, float lr) {
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * 256)
-        W[i] = W[i] - lr * dW[i];
+// W -= lr * dW for all of a model's tensors in one launch: workgroups [first[t], first[t+1]) walk tensor t.
+__global__ __launch_bounds__(256) void sgd_kernel(SgdList s, float lr) {
+    int t = 0;
+    while (t + 1 < s.count && blockIdx.x >= s.first[t + 1]) ++t;
+    const int64_t blocks = (t + 1 < s.count ? s.first[t + 1] : gridDim.x) - s.first[t], b = blockIdx.x - s.first[t];
+    float *W = s.W[t];
+    const float *dW = s.dW[t];
+    for (int64_t i = b * 256 + threadIdx.x; i < s.n[t]; i += blocks * 256) W[i] = W[i] - lr * dW[i];
 }
 
-int launch_sgd(float *W, const float *dW, int64_t n, float lr, hipStream_t stream) {
-    if (n <= 0) return CAPGNN_OK;
-    if (!W || !dW) CG_FAIL(CAPGNN_EINVAL, "sgd: NULL operand");
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 2048));
-    hipLaunchKernelGGL(sgd_kernel, dim3(blocks), dim3(256), 0, stream, W, dW, n, lr);
+int launch_sgd(SgdList s, float lr, hipStream_t stream) {
+    unsigned blocks = 0;
+    for (int t = 0; t < s.count; ++t) {
+        if (!s.W[t] || !s.dW[t] || s.n[t] <= 0) CG_FAIL(CAPGNN_EINVAL, "sgd: NULL operand");
+        s.first[t] = blocks;
+        blocks += static_cast<unsigned>(std::min<int64_t>((s.n[t] + 255) / 256, 2048));
+    }
+    if (!blocks) return CAPGNN_OK;
+    hipLaunchKernelGGL(sgd_kernel, dim3(blocks), dim3(256), 0, stream, s, lr);
     CG_HIP(hipGetLastError());
     return CAPGNN_OK;
 }
 
-// ------------------------------------------------------------------ masked softmax cross-entropy
-// scratch layout (bytes): [0] normaliser (float); [256, 256 + 8*LOSS_PARTS) per-workgroup partial sums (double);
-// [LOSS_HEADER ..] per-row loss terms (float).  Both reductions are two-level with fixed summation orders.
+// ------------------------------------------------------------------ masked softmax / binary cross-entropy
+// scratch layout (bytes): [0] normaliser (float); [256, LOSS_HEADER) partial counts of the mask (double); [LOSS_HEADER ..]
+// per-workgroup partial sums of the loss (double).  All reductions have fixed summation orders.
 constexpr int LOSS_PARTS = 512;
 constexpr size_t LOSS_HEADER = 8192;
 
-__device__ __forceinline__ double block_sum_1024(double c, double *red) {
+// threads: a power of two
+__device__ __forceinline__ double block_sum(double c, double *red, int threads) {
     red[threadIdx.x] = c;
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    for (int s = threads / 2; s > 0; s >>= 1) {
+        if (static_cast<int>(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
     return red[0];
 }
 
-// part[b] = number of masked rows in workgroup b's contiguous slice
+__device__ __forceinline__ int nonzero_bytes(uint32_t w) {
+    return ((w & 0xffu) != 0) + ((w & 0xff00u) != 0) + ((w & 0xff0000u) != 0) + ((w & 0xff000000u) != 0);
+}
+
+// nonzero bytes of [lo, hi), shared by `threads` threads; 16 at a time when the mask starts on a 16-byte boundary
+__device__ __forceinline__ int count_range(const uint8_t *mask, int64_t lo, int64_t hi, int threads) {
+    int cnt = 0;
+    int64_t i = lo;
+    if (reinterpret_cast<uintptr_t>(mask + lo) % 16 == 0) {
+        const uint4 *m4 = reinterpret_cast<const uint4 *>(mask + lo);
+        const int64_t n16 = (hi - lo) / 16;
+        for (int64_t j = threadIdx.x; j < n16; j += threads) {
+            const uint4 v = m4[j];
+            cnt += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
+        }
+        i = lo + n16 * 16;
+    }
+    for (i += threadIdx.x; i < hi; i += threads) cnt += mask[i] ? 1 : 0;
+    return cnt;
+}
+
+// part[b] = number of masked rows in workgroup b's contiguous slice (a multiple of 16 rows)
 __global__ __launch_bounds__(1024) void count_mask_kernel(int64_t n, const uint8_t *mask, double *part) {
     __shared__ double red[1024];
-    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * per, hi = lo + per < n ? lo + per : n;
-    double c = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 1024) c += mask[i] ? 1.0 : 0.0;
-    c = block_sum_1024(c, red);
+    const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
+    const int64_t lo = blockIdx.x * per < n ? blockIdx.x * per : n, hi = lo + per < n ? lo + per : n;
+    const double c = block_sum(count_range(mask, lo, hi, 1024), red, 1024);
     if (threadIdx.x == 0) part[blockIdx.x] = c;
 }
 
-__global__ __launch_bounds__(64) void count_final_kernel(int parts, const double *part, float times, float *norm_out) {
-    if (threadIdx.x != 0) return;
-    double c = 0.0;
-    for (int b = 0; b < parts; ++b) c += part[b];
-    norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
+// norm_out[0] = max(sum of part, 1) * times
+__global__ __launch_bounds__(LOSS_PARTS) void count_final_kernel(int parts, const double *part, float times, float *norm_out) {
+    __shared__ double red[LOSS_PARTS];
+    const double c = block_sum(static_cast<int>(threadIdx.x) < parts ? part[threadIdx.x] : 0.0, red, LOSS_PARTS);
+    if (threadIdx.x == 0) norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
 }
+
+// Up to this many rows one workgroup counts the mask (the two-level form costs a second launch) ...
+constexpr int64_t COUNT_SMALL_N = int64_t(1) << 18;
+__global__ __launch_bounds__(1024) void count_small_kernel(int64_t n, const uint8_t *mask, float times, float *norm_out) {
+    __shared__ double red[1024];
+    const double c = block_sum(count_range(mask, 0, n, 1024), red, 1024);
+    if (threadIdx.x == 0) norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
+}
+// ... and up to this many every workgroup of the loss kernel counts it for itself: at most 64 bytes per thread, out of
+// the L2, instead of a launch of its own (3-4 us).
+constexpr int64_t COUNT_INLINE_N = int64_t(1) << 14;
+
+// Workgroups of the loss kernel that a compute unit holds at once: the grid is that many on every unit and no more, since all
+// of them walk equally many rows (2048 workgroups where 1792 fit: 980 k rows x 47 classes 240 us, 72 us for 306 k rows).
+template <bool BCE> constexpr int LOSS_WG_PER_CU = BCE ? 5 : 8;
 
 // A group of lpr lanes (a power of two, 4..64, about a quarter of the classes) per row, so that narrow class counts
 // still keep 64/lpr rows in flight per wave; the lanes of a group stride over the classes.
@@ -406,178 +454,219 @@ static int loss_lanes_per_row_host(int C) {
     return lpr;
 }
 
-// One lane group (lpr lanes) per row.  A lane's logits (classes l, l + lpr, ...) are read once and kept: up to four per
-// lane in registers, which covers every C <= 4 * lpr (all C <= 256); beyond that the row is read again from the L1.
-// One exponential per class: the terms of the sum are reused for the gradient, p_k = e_k / s.  copy: when not null, the
-// logits are also written there as a dense [n x C] matrix (what the caller of an epoch asked for as `logits`).
-__global__ __launch_bounds__(256) void softmax_ce_kernel(int64_t n, int C, int lpr, const float *Z, int64_t ldz,
-                                                         const int32_t *labels, const uint8_t *mask, float norm_val,
-                                                         const float *norm_dev, float *row_loss, char *dZ,
-                                                         int64_t lddz, int dz_bf16, float *copy) {
-    const int lane = threadIdx.x & 63;
-    const int l = lane % lpr;
-    const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * (64 / lpr) + lane / lpr;
-    if (row >= n) return;          // whole lane groups leave; the shuffles below stay inside a group
-    const float norm = norm_dev ? norm_dev[0] : norm_val;
-    const bool on = !mask || mask[row];
-    const float *z = Z + row * ldz;
+struct LossArgs {
+    int64_t n;
+    int C, lpr;
+    const float *Z; int64_t ldz;
+    const int32_t *labels;              // softmax: class of every row
+    const uint8_t *targets; int64_t ldt;   // binary: 0/1 matrix
+    const uint8_t *mask;
+    float norm_val; const float *norm_dev;  // the normaliser, or where it is
+    float norm_times;                   // > 0: the normaliser is the mask's count times this, counted by every workgroup
+    double *part;                       // [gridDim.x] sums of the row losses
+    float *norm_out;                    // where workgroup 0 leaves a normaliser counted here, or null
+    char *dZ; int64_t lddz; int dz_bf16;
+    const float *rscale;                // dZ rows are stored times this, or null
+    float *copy;                        // dense [n x C] copy of the logits, or null
+    float *colpart;                     // [gridDim.x][C] column sums of dZ (not scaled), or null; C <= 4 * lpr
+};
+
+// One lane group per row, rows strided over the grid; the next row's logits are on their way while a row is worked on.  A lane
+// keeps up to four logits (classes l, l + lpr, ...), which covers every C <= 4 * lpr (all C <= 256); beyond that the row is
+// read again from the L1.  One exponential per class.  Softmax: p_k = e_k / s.  Binary: the element's loss in the form
+// max(z,0) - z*y + log(1 + exp(-|z|)), which neither overflows nor cancels, and its derivative s(z) - y.
+// The kernel also sums the row losses and, for the layer's bias gradient, the columns of dZ: what were passes of their own
+// over the rows' terms and over dZ (a 4096-vertex epoch: five launches, 35 us, now two).
+template <bool BCE>
+__global__ __launch_bounds__(256, LOSS_WG_PER_CU<BCE>) void loss_kernel(LossArgs a) {
     constexpr int KEEP = 4;
-    float zr[KEEP];
-#pragma unroll
-    for (int j = 0; j < KEEP; ++j) {
-        const int k = l + j * lpr;
-        zr[j] = k < C ? z[k] : -INFINITY;
-        if (copy && k < C) copy[row * C + k] = zr[j];
-    }
+    __shared__ double red[256];
+    __shared__ float cred[4][4 * 64];
+    const int lpr = a.lpr, C = a.C;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l = lane % lpr;
+    const int64_t per = static_cast<int64_t>(gridDim.x) * 4 * (64 / lpr);
+    int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * (64 / lpr) + lane / lpr;
     const bool kept = C <= KEEP * lpr;
-    if (copy && !kept) for (int k = l + KEEP * lpr; k < C; k += lpr) copy[row * C + k] = z[k];
-    if (!on) {
-        if (l == 0) row_loss[row] = 0.f;
-        if (dZ) for (int k = l; k < C; k += lpr) st_elem(dZ, row * lddz + k, 0.f, dz_bf16);
-        return;
-    }
-    float m = fmaxf(fmaxf(zr[0], zr[1]), fmaxf(zr[2], zr[3]));
-    if (!kept) for (int k = l + KEEP * lpr; k < C; k += lpr) m = fmaxf(m, z[k]);
-    for (int off = lpr >> 1; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    float er[KEEP];
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < KEEP; ++j) {
-        er[j] = (l + j * lpr < C) ? expf(zr[j] - m) : 0.f;
-        s += er[j];
-    }
-    if (!kept) for (int k = l + KEEP * lpr; k < C; k += lpr) s += expf(z[k] - m);
-    for (int off = lpr >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    const float lse = m + logf(s);
-    int y = labels[row];
-    y = y < 0 ? 0 : (y >= C ? C - 1 : y);
-    if (l == 0) row_loss[row] = lse - z[y];
-    if (dZ) {
-        const float inv = 1.f / norm, inv_s = 1.f / s;
+    float zn[KEEP], tn[KEEP];
+    bool on_n = false;
+    int y_n = 0;
+    auto fetch = [&](int64_t r) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < KEEP; ++j) {
             const int k = l + j * lpr;
-            if (k < C) st_elem(dZ, row * lddz + k, (er[j] * inv_s - (k == y ? 1.f : 0.f)) * inv, dz_bf16);
+            zn[j] = r < a.n && k < C ? a.Z[r * a.ldz + k] : -INFINITY;
+            if constexpr (BCE) tn[j] = r < a.n && k < C && a.targets[r * a.ldt + k] ? 1.f : 0.f;
         }
-        if (!kept)
-            for (int k = l + KEEP * lpr; k < C; k += lpr)
-                st_elem(dZ, row * lddz + k, (expf(z[k] - m) * inv_s - (k == y ? 1.f : 0.f)) * inv, dz_bf16);
+        on_n = r < a.n && (!a.mask || a.mask[r]);
+        if constexpr (!BCE) y_n = r < a.n ? a.labels[r] : 0;
+    };
+    fetch(row);
+    float norm = a.norm_val;
+    if (a.norm_times > 0.f) {           // uniform over the grid
+        const double c = block_sum(count_range(a.mask, 0, a.n, 256), red, 256);
+        norm = (c > 0.0 ? static_cast<float>(c) : 1.f) * a.norm_times;
+        if (a.norm_out && blockIdx.x == 0 && threadIdx.x == 0) a.norm_out[0] = norm;
+        __syncthreads();
+    } else if (a.norm_dev) {
+        norm = a.norm_dev[0];
     }
+    const float inv = 1.f / norm;
+    double loss = 0.0;
+    float csum[KEEP] = {0.f, 0.f, 0.f, 0.f};
+    for (; __any(row < a.n); row += per) {
+        float z[KEEP], t[KEEP];
+#pragma unroll
+        for (int j = 0; j < KEEP; ++j) {
+            z[j] = zn[j];
+            if constexpr (BCE) t[j] = tn[j];
+        }
+        const bool in = row < a.n, on = on_n;
+        int y = y_n;
+        fetch(row + per);
+        const float *zr = a.Z + row * a.ldz;
+        if (in && a.copy) {
+#pragma unroll
+            for (int j = 0; j < KEEP; ++j)
+                if (l + j * lpr < C) a.copy[row * C + l + j * lpr] = z[j];
+            if (!kept) for (int k = l + KEEP * lpr; k < C; k += lpr) a.copy[row * C + k] = zr[k];
+        }
+        float d[KEEP] = {0.f, 0.f, 0.f, 0.f};
+        float term = 0.f, m = -INFINITY, inv_s = 0.f;
+        if constexpr (BCE) {
+            if (on) {
+#pragma unroll
+                for (int j = 0; j < KEEP; ++j) {
+                    if (l + j * lpr >= C) continue;
+                    const float e = expf(-fabsf(z[j]));
+                    term += fmaxf(z[j], 0.f) - z[j] * t[j] + log1pf(e);
+                    d[j] = ((z[j] >= 0.f ? 1.f / (1.f + e) : e / (1.f + e)) - t[j]) * inv;
+                }
+                if (!kept)
+                    for (int k = l + KEEP * lpr; k < C; k += lpr) {
+                        const float zk = zr[k], yk = a.targets[row * a.ldt + k] ? 1.f : 0.f;
+                        term += fmaxf(zk, 0.f) - zk * yk + log1pf(expf(-fabsf(zk)));
+                    }
+            }
+            for (int off = lpr >> 1; off > 0; off >>= 1) term += __shfl_xor(term, off);
+        } else {
+            y = y < 0 ? 0 : (y >= C ? C - 1 : y);
+            m = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+            if (in && !kept) for (int k = l + KEEP * lpr; k < C; k += lpr) m = fmaxf(m, zr[k]);
+            for (int off = lpr >> 1; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+            float er[KEEP], s = 0.f, zy = 0.f;
+#pragma unroll
+            for (int j = 0; j < KEEP; ++j) {
+                const int k = l + j * lpr;
+                er[j] = in && k < C ? expf(z[j] - m) : 0.f;
+                s += er[j];
+                if (k == y) zy = z[j];
+            }
+            if (in && !kept)
+                for (int k = l + KEEP * lpr; k < C; k += lpr) {
+                    s += expf(zr[k] - m);
+                    if (k == y) zy = zr[k];
+                }
+            for (int off = lpr >> 1; off > 0; off >>= 1) { s += __shfl_xor(s, off); zy += __shfl_xor(zy, off); }
+            inv_s = 1.f / s;
+            if (on) {
+                term = m + logf(s) - zy;
+#pragma unroll
+                for (int j = 0; j < KEEP; ++j) d[j] = (er[j] * inv_s - (l + j * lpr == y ? 1.f : 0.f)) * inv;
+            }
+        }
+        if (on && l == 0) loss += static_cast<double>(term);
+        if (in && a.dZ) {
+            const float rs = a.rscale ? a.rscale[row] : 1.f;
+#pragma unroll
+            for (int j = 0; j < KEEP; ++j) {
+                const int k = l + j * lpr;
+                if (k < C) st_elem(a.dZ, row * a.lddz + k, d[j] * rs, a.dz_bf16);
+            }
+            if (!kept)
+                for (int k = l + KEEP * lpr; k < C; k += lpr) {
+                    float g = 0.f;
+                    if (on) {
+                        if constexpr (BCE) {
+                            const float zk = zr[k], yk = a.targets[row * a.ldt + k] ? 1.f : 0.f, e = expf(-fabsf(zk));
+                            g = ((zk >= 0.f ? 1.f / (1.f + e) : e / (1.f + e)) - yk) * inv;
+                        } else {
+                            g = (expf(zr[k] - m) * inv_s - (k == y ? 1.f : 0.f)) * inv;
+                        }
+                    }
+                    st_elem(a.dZ, row * a.lddz + k, g * rs, a.dz_bf16);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < KEEP; ++j) csum[j] += in ? d[j] : 0.f;
+    }
+    const double c = block_sum(loss, red, 256);
+    if (threadIdx.x == 0) a.part[blockIdx.x] = c;
+    if (!a.colpart) return;
+    for (int off = lpr; off < 64; off <<= 1)
+#pragma unroll
+        for (int j = 0; j < KEEP; ++j) csum[j] += __shfl_xor(csum[j], off);
+    if (lane < lpr)
+#pragma unroll
+        for (int j = 0; j < KEEP; ++j) cred[wave][l + j * lpr] = csum[j];
+    __syncthreads();
+    for (int k = threadIdx.x; k < C; k += 256)
+        a.colpart[static_cast<int64_t>(blockIdx.x) * C + k] = (cred[0][k] + cred[1][k]) + (cred[2][k] + cred[3][k]);
 }
 
-// Binary cross-entropy on logits, one lane group per row like the softmax kernel: the element's loss in the form
-// max(z,0) - z*y + log(1 + exp(-|z|)), which neither overflows nor cancels, and its derivative s(z) - y.
-__global__ __launch_bounds__(256) void sigmoid_bce_kernel(int64_t n, int C, int lpr, const float *Z, int64_t ldz,
-                                                          const uint8_t *targets, int64_t ldt, const uint8_t *mask,
-                                                          float norm_val, const float *norm_dev, float *row_loss, char *dZ,
-                                                          int64_t lddz, int dz_bf16) {
-    const int lane = threadIdx.x & 63;
-    const int l = lane % lpr;
-    const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * (64 / lpr) + lane / lpr;
-    if (row >= n) return;
-    const bool on = !mask || mask[row];
-    if (!on) {
-        if (l == 0) row_loss[row] = 0.f;
-        if (dZ) for (int k = l; k < C; k += lpr) st_elem(dZ, row * lddz + k, 0.f, dz_bf16);
+// workgroup 0: loss = sum of part / normaliser; the others (when there is a bias gradient): 32 columns each, as dbias_final_kernel
+__global__ __launch_bounds__(1024) void loss_final_kernel(int parts, const double *part, float norm_val, const float *norm_dev,
+                                                          float *loss_out, const float *colpart, int C, float *dbias) {
+    __shared__ double red[1024];
+    if (blockIdx.x == 0) {
+        double c = 0.0;
+        for (int b = threadIdx.x; b < parts; b += 1024) c += part[b];
+        c = block_sum(c, red, 1024);
+        if (threadIdx.x == 0) loss_out[0] = static_cast<float>(c / (norm_dev ? static_cast<double>(norm_dev[0]) : static_cast<double>(norm_val)));
         return;
     }
-    const float inv = 1.f / (norm_dev ? norm_dev[0] : norm_val);
-    const float *z = Z + row * ldz;
-    const uint8_t *t = targets + row * ldt;
-    float s = 0.f;
-    for (int k = l; k < C; k += lpr) {
-        const float zk = z[k], y = t[k] ? 1.f : 0.f;
-        const float e = expf(-fabsf(zk));
-        s += fmaxf(zk, 0.f) - zk * y + log1pf(e);
-        if (dZ) {
-            const float sig = zk >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-            st_elem(dZ, row * lddz + k, (sig - y) * inv, dz_bf16);
+    column_sums(blockIdx.x - 1, parts, C, colpart, dbias, red);
+}
+
+static int loss_blocks(int64_t n, int C, bool bce) {
+    const int64_t rows = 4 * (64 / loss_lanes_per_row_host(C));
+    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, NUM_CU * (bce ? LOSS_WG_PER_CU<true> : LOSS_WG_PER_CU<false>))));
+}
+
+// a: everything but the normaliser and `part`.  times: what the mask's count is multiplied with for the normaliser.
+// colpart (loss_colpart_bytes) and dbias: also the layer's bias gradient.
+static int loss_launch(LossArgs a, bool bce, double loss_norm, float times, float *loss_dev, void *ws, float *colpart, float *dbias,
+                       hipStream_t st) {
+    float *norm_dev = static_cast<float *>(ws);
+    double *counts = reinterpret_cast<double *>(static_cast<char *>(ws) + 256);
+    a.part = reinterpret_cast<double *>(static_cast<char *>(ws) + LOSS_HEADER);
+    a.lpr = loss_lanes_per_row_host(a.C);
+    a.norm_val = 1.f; a.norm_dev = nullptr; a.norm_times = 0.f; a.norm_out = nullptr;
+    if (loss_norm > 0.0) {
+        a.norm_val = static_cast<float>(loss_norm);
+    } else if (!a.mask) {
+        a.norm_val = static_cast<float>(a.n) * times;
+    } else if (a.n <= COUNT_INLINE_N) {
+        a.norm_times = times;
+        a.norm_out = norm_dev;
+    } else {
+        a.norm_dev = norm_dev;
+        if (a.n <= COUNT_SMALL_N) {
+            hipLaunchKernelGGL(count_small_kernel, dim3(1), dim3(1024), 0, st, a.n, a.mask, times, norm_dev);
+        } else {
+            const int parts = static_cast<int>(std::min<int64_t>((a.n + 4095) / 4096, LOSS_PARTS));
+            hipLaunchKernelGGL(count_mask_kernel, dim3(parts), dim3(1024), 0, st, a.n, a.mask, counts);
+            hipLaunchKernelGGL(count_final_kernel, dim3(1), dim3(LOSS_PARTS), 0, st, parts, counts, times, norm_dev);
         }
     }
-    for (int off = lpr >> 1; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (l == 0) row_loss[row] = s;
-}
-
-__global__ __launch_bounds__(1024) void loss_partial_kernel(int64_t n, const float *row_loss, double *part) {
-    __shared__ double red[1024];
-    const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * per, hi = lo + per < n ? lo + per : n;
-    double c = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 1024) c += static_cast<double>(row_loss[i]);
-    c = block_sum_1024(c, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = c;
-}
-
-__global__ __launch_bounds__(64) void loss_final_kernel(int parts, const double *part, float norm_val, const float *norm_dev,
-                                                        float *loss_out) {
-    if (threadIdx.x != 0) return;
-    double c = 0.0;
-    for (int b = 0; b < parts; ++b) c += part[b];
-    const double norm = norm_dev ? static_cast<double>(norm_dev[0]) : static_cast<double>(norm_val);
-    loss_out[0] = static_cast<float>(c / norm);
-}
-
-// Up to LOSS_SMALL_N rows: one workgroup does a whole reduction (16-byte loads, fixed order), which saves the second
-// launch of the two-level form; these kernels run for a few microseconds either way.
-constexpr int64_t LOSS_SMALL_N = int64_t(1) << 18;
-
-__device__ __forceinline__ int nonzero_bytes(uint32_t w) {
-    return ((w & 0xffu) != 0) + ((w & 0xff00u) != 0) + ((w & 0xff0000u) != 0) + ((w & 0xff000000u) != 0);
-}
-
-// norm_out[0] = max(number of masked rows, 1) * times; mask must start on a 16-byte boundary
-__global__ __launch_bounds__(1024) void count_small_kernel(int64_t n, const uint8_t *mask, float times, float *norm_out) {
-    __shared__ double red[1024];
-    const int64_t n16 = n / 16;
-    const uint4 *m4 = reinterpret_cast<const uint4 *>(mask);
-    int cnt = 0;
-    for (int64_t i = threadIdx.x; i < n16; i += 1024) {
-        const uint4 v = m4[i];
-        cnt += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
-    }
-    for (int64_t i = n16 * 16 + threadIdx.x; i < n; i += 1024) cnt += mask[i] ? 1 : 0;
-    const double c = block_sum_1024(static_cast<double>(cnt), red);
-    if (threadIdx.x == 0) norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
-}
-
-// loss_out[0] = sum(row_loss) / norm; row_loss must start on a 16-byte boundary
-__global__ __launch_bounds__(1024) void loss_small_kernel(int64_t n, const float *row_loss, float norm_val, const float *norm_dev,
-                                                          float *loss_out) {
-    __shared__ double red[1024];
-    const int64_t n4 = n / 4;
-    const float4 *r4 = reinterpret_cast<const float4 *>(row_loss);
-    double c = 0.0;
-    for (int64_t i = threadIdx.x; i < n4; i += 1024) {
-        const float4 v = r4[i];
-        c += static_cast<double>(v.x); c += static_cast<double>(v.y); c += static_cast<double>(v.z); c += static_cast<double>(v.w);
-    }
-    for (int64_t i = n4 * 4 + threadIdx.x; i < n; i += 1024) c += static_cast<double>(row_loss[i]);
-    c = block_sum_1024(c, red);
-    if (threadIdx.x == 0) {
-        const double norm = norm_dev ? static_cast<double>(norm_dev[0]) : static_cast<double>(norm_val);
-        loss_out[0] = static_cast<float>(c / norm);
-    }
-}
-
-// the two reductions around a loss kernel: the normaliser from the mask, and the loss from the per-row terms
-static void launch_mask_count(int64_t n, const uint8_t *mask, float times, double *part, int parts, float *norm_dev,
-                              hipStream_t st) {
-    if (n <= LOSS_SMALL_N && reinterpret_cast<uintptr_t>(mask) % 16 == 0) {
-        hipLaunchKernelGGL(count_small_kernel, dim3(1), dim3(1024), 0, st, n, mask, times, norm_dev);
-        return;
-    }
-    hipLaunchKernelGGL(count_mask_kernel, dim3(parts), dim3(1024), 0, st, n, mask, part);
-    hipLaunchKernelGGL(count_final_kernel, dim3(1), dim3(64), 0, st, parts, part, times, norm_dev);
-}
-
-static void launch_loss_sum(int64_t n, const float *row_loss, double *part, int parts, float norm_val, const float *norm_dev,
-                            float *loss_dev, hipStream_t st) {
-    if (n <= LOSS_SMALL_N && reinterpret_cast<uintptr_t>(row_loss) % 16 == 0) {
-        hipLaunchKernelGGL(loss_small_kernel, dim3(1), dim3(1024), 0, st, n, row_loss, norm_val, norm_dev, loss_dev);
-        return;
-    }
-    hipLaunchKernelGGL(loss_partial_kernel, dim3(parts), dim3(1024), 0, st, n, row_loss, part);
-    hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(64), 0, st, parts, part, norm_val, norm_dev, loss_dev);
+    const int blocks = loss_blocks(a.n, a.C, bce);
+    a.colpart = dbias ? colpart : nullptr;
+    if (bce) hipLaunchKernelGGL(loss_kernel<true>, dim3(blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(loss_kernel<false>, dim3(blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(loss_final_kernel, dim3(1 + (dbias ? (a.C + 31) / 32 : 0)), dim3(1024), 0, st, blocks, a.part, a.norm_val,
+                       (a.norm_dev || a.norm_out) ? norm_dev : nullptr, loss_dev, a.colpart, a.C, dbias);
+    CG_HIP(hipGetLastError());
+    return CAPGNN_OK;
 }
 
 }  // namespace capgnn
@@ -597,50 +686,19 @@ extern "C" int capgnn_sigmoid_bce(int64_t n, int C, const float *Z, int64_t ldz,
     if (!Z || !targets || !loss_dev) CG_FAIL(CAPGNN_EINVAL, "sigmoid_bce: NULL operand");
     if (ldz < C || ldt < C || (dZ && lddz < C)) CG_FAIL(CAPGNN_EINVAL, "sigmoid_bce: leading dimension smaller than C");
     if (!ws || ws_bytes < capgnn_loss_workspace_bytes(n)) CG_FAIL(CAPGNN_ENOMEM, "sigmoid_bce: workspace too small");
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    float *norm_dev = nullptr;
-    float norm_val = 1.f;
-    double *part = reinterpret_cast<double *>(static_cast<char *>(ws) + 256);
-    const int parts = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, LOSS_PARTS)));
-    if (loss_norm > 0.0) norm_val = static_cast<float>(loss_norm);
-    else if (!mask) norm_val = static_cast<float>(n) * static_cast<float>(C);
-    else {   // masked rows x classes
-        norm_dev = static_cast<float *>(ws);
-        launch_mask_count(n, mask, static_cast<float>(C), part, parts, norm_dev, st);
-    }
-    float *row_loss = reinterpret_cast<float *>(static_cast<char *>(ws) + LOSS_HEADER);
-    const int lpr = loss_lanes_per_row_host(C);
-    const int64_t rows_per_block = 4 * (64 / lpr);
-    hipLaunchKernelGGL(sigmoid_bce_kernel, dim3(static_cast<unsigned>((n + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, n, C, lpr, Z, ldz, targets,
-                       ldt, mask, norm_val, norm_dev, row_loss, static_cast<char *>(dZ), lddz, dz_dtype == CAPGNN_BF16 ? 1 : 0);
-    launch_loss_sum(n, row_loss, part, parts, norm_val, norm_dev, loss_dev, st);
-    CG_HIP(hipGetLastError());
-    return CAPGNN_OK;
+    LossArgs a{};
+    a.n = n; a.C = C; a.Z = Z; a.ldz = ldz; a.targets = targets; a.ldt = ldt; a.mask = mask;
+    a.dZ = static_cast<char *>(dZ); a.lddz = lddz; a.dz_bf16 = dz_dtype == CAPGNN_BF16;
+    return loss_launch(a, true, loss_norm, static_cast<float>(C), loss_dev, ws, nullptr, nullptr, static_cast<hipStream_t>(stream));
 }
 
 // everything capgnn_softmax_ce does after its argument checks; `ws` holds capgnn_loss_workspace_bytes(n) bytes
 static int softmax_ce_launch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *mask,
-                             double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, void *ws,
-                             hipStream_t st, float *copy = nullptr) {
-    float *norm_dev = nullptr;
-    float norm_val = 1.f;
-    float *scratch = static_cast<float *>(ws);
-    double *part = reinterpret_cast<double *>(static_cast<char *>(ws) + 256);
-    const int parts = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, LOSS_PARTS)));
-    if (loss_norm > 0.0) norm_val = static_cast<float>(loss_norm);
-    else if (!mask) norm_val = static_cast<float>(n);
-    else {
-        norm_dev = scratch;
-        launch_mask_count(n, mask, 1.f, part, parts, norm_dev, st);
-    }
-    float *row_loss = reinterpret_cast<float *>(static_cast<char *>(ws) + LOSS_HEADER);
-    const int lpr = loss_lanes_per_row_host(C);
-    const int64_t rows_per_block = 4 * (64 / lpr);
-    hipLaunchKernelGGL(softmax_ce_kernel, dim3(static_cast<unsigned>((n + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, n, C, lpr, Z, ldz,
-                       labels, mask, norm_val, norm_dev, row_loss, static_cast<char *>(dZ), lddz, dz_dtype == CAPGNN_BF16 ? 1 : 0, copy);
-    launch_loss_sum(n, row_loss, part, parts, norm_val, norm_dev, loss_dev, st);
-    CG_HIP(hipGetLastError());
-    return CAPGNN_OK;
+                             double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, void *ws, hipStream_t st) {
+    LossArgs a{};
+    a.n = n; a.C = C; a.Z = Z; a.ldz = ldz; a.labels = labels; a.mask = mask;
+    a.dZ = static_cast<char *>(dZ); a.lddz = lddz; a.dz_bf16 = dz_dtype == CAPGNN_BF16;
+    return loss_launch(a, false, loss_norm, 1.f, loss_dev, ws, nullptr, nullptr, st);
 }
 
 static int softmax_ce_check(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, float *loss_dev,
@@ -663,18 +721,31 @@ extern "C" int capgnn_softmax_ce(int64_t n, int C, const float *Z, int64_t ldz, 
                              static_cast<hipStream_t>(stream));
 }
 
-// capgnn_softmax_ce for the epoch, which also wants the logits as a dense [n x C] copy (or not: copy may be NULL)
-int capgnn::softmax_ce_with_copy(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *mask,
-                         double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, void *ws, size_t ws_bytes,
-                         hipStream_t st, float *copy) {
-    CG_TRY(softmax_ce_check(n, C, Z, ldz, labels, loss_dev, dZ, lddz, dz_dtype));
+size_t capgnn::loss_epoch_ws_bytes(int64_t n, int C) {
+    return capgnn_loss_workspace_bytes(n) + align_up(static_cast<size_t>(loss_blocks(n, C, false)) * C * sizeof(float), 256);
+}
+
+bool capgnn::loss_sums_columns(int C) { return C <= 4 * loss_lanes_per_row_host(C); }
+
+// The loss of an epoch (labels or targets): also writes the logits as a dense [n x C] matrix to `copy`, sums the columns of dZ
+// into dbias, and stores the rows of dZ times row_scale (each may be NULL).
+int capgnn::loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
+                       const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy,
+                       float *dbias, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t st) {
+    CG_TRY(softmax_ce_check(n, C, Z, ldz, targets ? reinterpret_cast<const int32_t *>(targets) : labels, loss_dev, dZ, lddz, dz_dtype));
     if (n == 0) return CAPGNN_OK;
-    if (!ws || ws_bytes < capgnn_loss_workspace_bytes(n)) CG_FAIL(CAPGNN_ENOMEM, "softmax_ce: workspace too small");
-    return softmax_ce_launch(n, C, Z, ldz, labels, mask, loss_norm, loss_dev, dZ, lddz, dz_dtype, ws, st, copy);
+    if (targets && ldt < C) CG_FAIL(CAPGNN_EINVAL, "loss: ldt smaller than the number of classes");
+    if (dbias && !loss_sums_columns(C)) CG_FAIL(CAPGNN_EINVAL, "loss: too many classes for the column sums");
+    if (!ws || ws_bytes < loss_epoch_ws_bytes(n, C)) CG_FAIL(CAPGNN_ENOMEM, "loss: workspace too small");
+    LossArgs a{};
+    a.n = n; a.C = C; a.Z = Z; a.ldz = ldz; a.labels = labels; a.targets = targets; a.ldt = ldt; a.mask = mask;
+    a.dZ = static_cast<char *>(dZ); a.lddz = lddz; a.dz_bf16 = dz_dtype == CAPGNN_BF16; a.copy = copy; a.rscale = row_scale;
+    return loss_launch(a, targets != nullptr, loss_norm, targets ? static_cast<float>(C) : 1.f, loss_dev, ws,
+                       reinterpret_cast<float *>(static_cast<char *>(ws) + capgnn_loss_workspace_bytes(n)), dbias, st);
 }
 
 // ------------------------------------------------------------------ the same loss without any allocation by anyone
-// The scratch of capgnn_softmax_ce (normaliser, per-workgroup partial sums, per-row loss terms) for up to
+// The scratch of capgnn_softmax_ce (normaliser, per-workgroup partial sums) for up to
 // CAPGNN_LOSS_STATIC_MAX_ROWS rows, as a device array that is part of the library image: every GPU the library
 // runs on holds its own copy until the process ends.  Host code never uses the array's name as an address: the
 // address on the current device is asked for once per device and kept.
@@ -710,8 +781,7 @@ extern "C" int capgnn_softmax_ce_static(int64_t n, int C, const float *Z, int64_
     if (n == 0) return CAPGNN_OK;
     void *ws = nullptr;
     CG_TRY(static_scratch(&ws));
-    // nothing in the scratch has to start at zero: the normaliser, parts[0..parts) and row terms [0, n) are all written
-    // before they are read, so what an earlier (larger) call left behind is never seen
+    // nothing in the scratch has to start at zero: the normaliser and the partial sums are all written before they are read, so what an earlier (larger) call left behind is never seen
     return softmax_ce_launch(n, C, Z, ldz, labels, mask, loss_norm, loss_dev, dZ, lddz, dz_dtype, ws,
                              static_cast<hipStream_t>(stream));
 }

@@ -28,6 +28,8 @@ struct SpmmArgs {
     const float *bias;
     int relu;
     int acc_rows;             // output rows below this one are added to what Y holds
+    const char *mask;         // zero where mask <= 0 (storage type of Y), or null
+    int64_t ldm_bytes;
     float *part;              // fp32 partial sums [n_pieces][ldp]
     int64_t ldp;
 };
@@ -287,6 +289,7 @@ __device__ __forceinline__ void store_row(const SpmmArgs &a, int row, int f0, co
     char *yrow = a.Y + static_cast<int64_t>(row) * a.ldy_bytes;
     const float oscale = a.out_scale ? a.out_scale[row] : 1.f;
     const bool accumulate = row < a.acc_rows;
+    const char *mrow = a.mask ? a.mask + static_cast<int64_t>(row) * a.ldm_bytes : nullptr;
     float y[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
@@ -294,6 +297,7 @@ __device__ __forceinline__ void store_row(const SpmmArgs &a, int row, int f0, co
         if (f0 + j < a.F) {
             if (accumulate) t += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
             if (a.bias) t += a.bias[f0 + j];
+            if (mrow && !(load_one<OBF16>(mrow + static_cast<int64_t>(f0 + j) * ES) > 0.f)) t = 0.f;
         }
         if (a.relu) t = t > 0.f ? t : 0.f;
         y[j] = t;
@@ -307,18 +311,14 @@ __device__ __forceinline__ void store_row(const SpmmArgs &a, int row, int f0, co
     }
 }
 
-// Single-wave workgroups (a wave that shares a workgroup with a longer row would hold its slot until that one ends): the
-// first n_wave of them take one item each, the others 64 / LPR, one per lane group.  The launches are bound by how many
-// gathers the resident waves keep in flight, then by the fabric behind the L2s: at least six waves per SIMD are asked for
-// (the bf16-in / fp32-out variants otherwise settle at four).  W: entries have weights (a.wt), else every weight is 1.
+// What wave `w` of a launch works on: one of the first n_wave items, or 64 / LPR of the others, one per lane group.
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
-__global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void spmm_kernel(SpmmArgs a) {
+__device__ __forceinline__ void wave_items(const SpmmArgs &a, int64_t w, int lane) {
     constexpr int G = 64 / LPR;
     constexpr int U = (NV == 1) ? 8 : 4;
     constexpr int PASS = LPR * E * NV;
-    const int lane = threadIdx.x;
-    const bool by_wave = G == 1 || blockIdx.x < a.n_wave;
-    int64_t item = blockIdx.x;
+    const bool by_wave = G == 1 || w < a.n_wave;
+    int64_t item = w;
     bool stores = true;
     if (!by_wave) {
         item = a.n_wave + (item - a.n_wave) * G + lane / LPR;
@@ -357,16 +357,34 @@ __global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void s
     }
 }
 
-// The cut rows where the caller brought no scratch for their pieces: a workgroup per row, each wave a quarter of its
-// entries, combined through LDS in a fixed order.
+// Single-wave workgroups: a wave that shares a workgroup with a longer row would hold its slot until that one ends.  The
+// launches are bound by how many gathers the resident waves keep in flight, then by the fabric behind the L2s: at least
+// five (bf16) or six waves per SIMD are asked for (the bf16-in / fp32-out variants otherwise settle at four; six would spill
+// in the bf16 variants: 7.46 against 7.06 ms for two launches of 980 k rows x 50 entries x 256 features).  W: entries have
+// weights (a.wt), else every weight is 1.
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
-__global__ __launch_bounds__(256) void spmm_long_kernel(SpmmArgs a, const RowItem *cut) {
+__global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void spmm_kernel(SpmmArgs a) {
+    wave_items<BF16, OBF16, W, E, LPR, NV>(a, blockIdx.x, threadIdx.x);
+}
+
+// Workgroups [0, n_cut): one long row each, its entries shared by the waves and the partial sums added through LDS in wave
+// order.  The rest: the short items, one wave after the other.  Serves small graphs, whose launch is over before the pieces
+// of cut rows and the kernel that adds them would be, and the long rows where the caller brought no scratch for pieces.
+template <int NV> constexpr int ROW_WAVES = NV == 1 ? 16 : 4;
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+__global__ __launch_bounds__(64 * ROW_WAVES<NV>) void spmm_rows_kernel(SpmmArgs a, const RowItem *cut, int n_cut, int64_t n_waves) {
     constexpr int U = (NV == 1) ? 8 : 4;
     constexpr int PASS = LPR * E * NV;
-    __shared__ float red[3][NV * E][LPR];
+    constexpr int NW = ROW_WAVES<NV>;
+    __shared__ float red[NW - 1][NV * E][LPR];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (static_cast<int>(blockIdx.x) >= n_cut) {
+        const int64_t w = static_cast<int64_t>(blockIdx.x - n_cut) * NW + wave;
+        if (w < n_waves) wave_items<BF16, OBF16, W, E, LPR, NV>(a, w, lane);
+        return;
+    }
     const RowItem it = cut[blockIdx.x];
-    const uint32_t end = it.beg + it.cnt, per = (it.cnt + 3) / 4;
+    const uint32_t end = it.beg + it.cnt, per = (it.cnt + NW - 1) / NW;
     const uint32_t e0 = wave * per < it.cnt ? it.beg + wave * per : end, e1 = end - e0 < per ? end : e0 + per;
     for (int pass = 0; pass < a.F_lim; pass += PASS) {
         const int elem0 = pass + lane % LPR * E;
@@ -386,8 +404,8 @@ __global__ __launch_bounds__(256) void spmm_long_kernel(SpmmArgs a, const RowIte
         }
         __syncthreads();
         if (wave == 0 && lane < LPR) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
+#pragma unroll 3
+            for (int p = 0; p < NW - 1; ++p)
 #pragma unroll
                 for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -694,6 +712,8 @@ struct SpmmReduceArgs {
     int F;
     const float *bias;
     int relu, acc_rows;
+    const char *mask;
+    int64_t ldm_bytes;
 };
 
 // one thread per (position, four consecutive features)
@@ -721,6 +741,7 @@ __global__ __launch_bounds__(256) void spmm_blocked_reduce_kernel(SpmmReduceArgs
         if (f0 + j < a.F) {
             if (row < a.acc_rows) y[j] += load_one<OBF16>(yrow + static_cast<int64_t>(f0 + j) * ES);
             if (a.bias) y[j] += a.bias[f0 + j];
+            if (a.mask && !(load_one<OBF16>(a.mask + row * a.ldm_bytes + static_cast<int64_t>(f0 + j) * ES) > 0.f)) y[j] = 0.f;
         }
         if (a.relu) y[j] = y[j] > 0.f ? y[j] : 0.f;
     }
@@ -793,7 +814,7 @@ static int launch_blocked(const SpOp &op, const BlockedGeom &g, const SpmmArgs &
     SpmmReduceArgs r;
     r.off = op.b_off; r.order = op.order; r.out_scale = op.out_scale; r.part = part; r.ldp = g.ldp; r.n_out = op.n_out;
     r.ncb = op.ncb; r.Y = a.Y; r.ldy_bytes = a.ldy_bytes; r.F = a.F; r.bias = a.bias; r.relu = a.relu;
-    r.acc_rows = a.acc_rows;
+    r.acc_rows = a.acc_rows; r.mask = a.mask; r.ldm_bytes = a.ldm_bytes;
     const int64_t threads = op.n_out * ((a.F + 3) / 4);
     hipLaunchKernelGGL((spmm_blocked_reduce_kernel<OBF16>), dim3(static_cast<unsigned>((threads + 255) / 256)), dim3(256),
                        0, st, r);
@@ -846,23 +867,29 @@ static int group_row_entries(int64_t nnz, int64_t row_bytes) {
 // x 256 float features: 0.60 -> 0.63 ms), narrower ones to keep enough requests in flight (47 bf16 features: 0.10 -> 0.115).
 constexpr int CROWDED_ROW = 32, CROWDED_BYTES = 192, CROWDED_LDS = 13312;
 
+// Graphs of at most ROWS_NNZ entries with rows to cut run as one launch of spmm_rows_kernel: the second launch costs more than
+// what the finer cut saves (the three aggregations of a 10 k-vertex GraphSAGE epoch 37 -> 31 us, of a 22 k-vertex GIN epoch
+// 65 -> 61, besides three launch gaps of 1-2 us).
+constexpr int64_t ROWS_NNZ = int64_t(1) << 20;
+
 // pieces: the caller brought scratch for the pieces of the cut rows
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
 static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
-    constexpr int G = 64 / LPR;
+    constexpr int G = 64 / LPR, NW = ROW_WAVES<NV>;
     a.items = list.items; a.n_items = list.n_items; a.n_pieces = list.n_pieces;
     const int64_t row_bytes = static_cast<int64_t>(a.F_lim) * (BF16 ? 2 : 4);
     a.n_wave = G == 1 ? list.n_items : list.first_below(group_row_entries(nnz, row_bytes));
     const bool long_rows = nnz >= CROWDED_ROW * list.n_items && row_bytes >= CROWDED_BYTES;
-    if (!pieces) {
-        a.items += list.n_pieces; a.n_items -= list.n_pieces; a.n_wave -= list.n_pieces; a.n_pieces = 0;
-        if (list.n_cut > 0)
-            hipLaunchKernelGGL((spmm_long_kernel<BF16, OBF16, W, E, LPR, NV>), dim3(static_cast<unsigned>(list.n_cut)), dim3(256), 0,
-                               st, a, list.cut);
-    }
-    if (a.n_items > 0)
-        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV>),
-                           dim3(static_cast<unsigned>(a.n_wave + (a.n_items - a.n_wave + G - 1) / G)), dim3(64),
+    const bool one_launch = list.n_cut > 0 && nnz <= ROWS_NNZ;
+    pieces = pieces && !one_launch;
+    if (!pieces) { a.items += list.n_pieces; a.n_items -= list.n_pieces; a.n_wave -= list.n_pieces; a.n_pieces = 0; }
+    const int64_t waves = a.n_wave + (a.n_items - a.n_wave + G - 1) / G;
+    if (!pieces && list.n_cut > 0)
+        hipLaunchKernelGGL((spmm_rows_kernel<BF16, OBF16, W, E, LPR, NV>),
+                           dim3(static_cast<unsigned>(list.n_cut + (one_launch ? (waves + NW - 1) / NW : 0))), dim3(64 * NW), 0, st, a,
+                           list.cut, static_cast<int>(list.n_cut), waves);
+    if (!one_launch && waves > 0)
+        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV>), dim3(static_cast<unsigned>(waves)), dim3(64),
                            long_rows ? CROWDED_LDS : 0, st, a);
     if (pieces)
         hipLaunchKernelGGL((spmm_pieces_finish_kernel<OBF16>), dim3(static_cast<unsigned>(list.n_cut), (a.F + 63) / 64),
@@ -922,6 +949,7 @@ int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, v
     a.Y = static_cast<char *>(Y); a.ldy_bytes = ldy * es_out;
     a.F = F; a.F_lim = vec ? f_up : F;
     a.bias = ep.bias; a.relu = ep.relu;
+    a.mask = static_cast<const char *>(ep.mask); a.ldm_bytes = ep.ldm * es_out;
     a.acc_rows = ep.accumulate ? static_cast<int>(std::min<int64_t>(ep.acc_rows, INT32_MAX)) : 0;
     if (vec && !restrict_sub && ep.ws) {
         // the blocked kernel runs when the operator has a blocked copy and the caller brought the scratch for it

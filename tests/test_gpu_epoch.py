@@ -84,6 +84,30 @@ def test_epoch_scaled_configs_match_oracle(env, name, scale):
     dp2.close()
 
 
+@pytest.mark.parametrize("kind,dtype,loss", [("gcn", "f32", "ce"), ("sage", "f32", "bce"), ("gin", "f32", "ce"), ("sage", "bf16", "ce"),
+                                             ("gcn", "bf16", "bce")])
+@pytest.mark.parametrize("dims,n_loc", [([40, 33, 48, 1], 500), ([24, 64, 130, 7], 20000), ([16, 50, 256], 3000), ([16, 50, 257], 3000)])
+def test_epoch_fused_gradients(env, kind, dtype, loss, dims, n_loc):
+    """What the gradient path forms on the way: the last bias gradient in the loss kernel (up to 256 classes; 257 take a pass
+    of their own), the other ones in the weight gradients' products, sigma' where an input gradient is written (aggregation and
+    product epilogues: both associations of every layer), the mask counted inside the loss kernel or before it (16384 rows).
+    The tolerances are those of every epoch test: the fusion changes orders of summation, not what is rounded."""
+    B, H, O = env["B"], env["H"], env["O"]
+    cfg = synth.Config(f"fuse-{kind}-{dtype}", kind, n_loc, n_loc // 3, 8 * n_loc, dims, dtype, 1.0, max_deg=300,
+                       seed=synth.BASE_SEED * 10 + 9, extra={"loss": loss, "gin_eps": 0.1})
+    prob = H.make_problem(cfg, mask_frac=0.5)
+    if kind == "gin":       # sums over up to 300 neighbours: keep the activations O(1)
+        for p in prob.model:
+            p.W *= np.float32(0.125)
+    L = len(dims) - 1
+    ref = O.oracle_epoch(prob)
+    for orders in (None, [B.AGG_FIRST] * L, [B.XFORM_FIRST] * L):
+        dp = H.DeviceProblem(prob, orders=orders)
+        got, _ = dp.run_epoch()
+        compare_epoch(env, prob, dp, ref, got, TOL[dtype], f"{cfg.name} {dims} {loss} orders={orders}")
+        dp.close()
+
+
 def test_epoch_pipelined_host_tier_sees_refilled_tables(env):
     """Pipelined mode copies the host tier for the next epoch while the current one runs.  Every epoch must
     still consume exactly the tables last loaded: after capgnn_cache_fill the prefetched rows are dropped."""
