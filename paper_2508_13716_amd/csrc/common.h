@@ -78,6 +78,7 @@ struct SpOp {
     // no edge values: the weight of an entry is in_scale[source] alone, so a caller that multiplies row s of the
     // operand by in_scale[s] first may ask for the unweighted sum (SpmmEpilogue::operand_scaled)
     bool weights_by_source = false;
+    bool finite_weights = false;      // no weight is infinite or NaN: an all-zero row adds nothing, whatever its weight
     const float *out_scale = nullptr; // device [n_out] or null
     const float *in_scale = nullptr;  // device [n_in]  or null
     // output rows by entry count, descending; rows shorter than EXACT_ROW only by power-of-two class, in index order
@@ -153,6 +154,13 @@ struct capgnn_cache {
 
 namespace capgnn {
 
+// Which rows of a matrix may differ from zero: row r if bit r % 32 of bits[r / 32] is set (whole words of 32 rows, the rest of the
+// last one unset or not there), *count of them in all; both on the device.  No bits: any row.
+struct LiveRows {
+    const uint32_t *bits = nullptr;
+    const float *count = nullptr;
+};
+
 // ---- kernels' host-side launchers (each validates what its kernel assumes) ----
 struct SpmmEpilogue {
     const float *bias = nullptr;   // [F] added after scaling
@@ -163,12 +171,16 @@ struct SpmmEpilogue {
     int64_t ldm = 0;
     int out_f32 = 0;               // store Y as float although X is bf16
     int out_bf16 = 0;              // store Y as bf16 although X is float (the loss gradient of a bf16 model is gathered unrounded)
+    LiveRows live;                 // rows of X that need not be read, being zero throughout
     int operand_scaled = 0;        // row s of X already carries in_scale[s] (only for operators with weights_by_source)
     void *ws = nullptr;            // scratch for the column-blocked kernel or for cut rows (spmm_ws_bytes), may be null
     size_t ws_bytes = 0;
 };
 
 size_t spmm_ws_bytes(const SpOp &op, int F, int dtype);
+
+// whether an aggregation of float rows (F elements at a pitch of ldx) makes use of SpmmEpilogue::live
+bool spmm_uses_live(const SpOp &op, int F, int64_t ldx);
 
 int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, void *Y, int64_t ldy, int F,
                 int dtype, const SpmmEpilogue &ep, hipStream_t stream);
@@ -213,7 +225,7 @@ int launch_sgd(SgdList s, float lr, hipStream_t stream);
 // the loss of an epoch on labels or targets, with what else can be had on the way (see ops.hip)
 int loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
                const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy, float *dbias,
-               const float *row_scale, void *ws, size_t ws_bytes, hipStream_t st);
+               const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st);
 size_t loss_epoch_ws_bytes(int64_t n, int C);
 bool loss_sums_columns(int C);      // whether loss_epoch can form dbias
 

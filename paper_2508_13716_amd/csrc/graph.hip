@@ -64,8 +64,9 @@ static void degree_order(const int64_t *ptr, int64_t lo, int64_t hi, std::vector
 // Per-entry weights val * in_scale[source] (the float product the kernels would otherwise form per entry).
 // Leaves *dev null when every weight is 1.
 static int upload_weights(capgnn_graph *g, int64_t nnz, const int32_t *idx, const float *val, const float *in_scale,
-                          const float **dev) {
+                          const float **dev, bool *finite) {
     *dev = nullptr;
+    *finite = true;
     if (nnz == 0 || (!val && !in_scale)) return CAPGNN_OK;
     std::vector<float> w(nnz);
     bool all_one = true;
@@ -74,6 +75,7 @@ static int upload_weights(capgnn_graph *g, int64_t nnz, const int32_t *idx, cons
         if (val) x *= val[e];
         w[e] = x;
         all_one = all_one && x == 1.f;
+        *finite = *finite && std::isfinite(x);
     }
     if (all_one) return CAPGNN_OK;
     return upload(g, w.data(), w.size(), dev);
@@ -298,7 +300,7 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     f.n_out = n_loc; f.n_in = n_cols; f.nnz = nnz; f.n_sub = n_loc;
     if ((rc = upload(g, rowptr, n_loc + 1, &f.ptr))) return fail(rc);
     if ((rc = upload(g, col, nnz, &f.idx))) return fail(rc);
-    if ((rc = upload_weights(g, nnz, col, edge_val, col_scale, &f.wt))) return fail(rc);
+    if ((rc = upload_weights(g, nnz, col, edge_val, col_scale, &f.wt, &f.finite_weights))) return fail(rc);
     f.weights_by_source = !edge_val && col_scale;
     if (row_scale && (rc = upload(g, row_scale, n_loc, &f.out_scale))) return fail(rc);
     if (col_scale && (rc = upload(g, col_scale, n_cols, &f.in_scale))) return fail(rc);
@@ -320,7 +322,8 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
         const bool same_scales = (!row_scale && !col_scale) ||
                                  (row_scale && col_scale && std::memcmp(row_scale, col_scale, n_loc * sizeof(float)) == 0);
         b.wt = f.wt;
-        if (!same_scales && (rc = upload_weights(g, nnz, col, edge_val, row_scale, &b.wt))) return fail(rc);
+        b.finite_weights = f.finite_weights;
+        if (!same_scales && (rc = upload_weights(g, nnz, col, edge_val, row_scale, &b.wt, &b.finite_weights))) return fail(rc);
         if (f.ncb && !same_scales) {   // the transposed product weighs an entry by the other side's scale
             if (edge_val) {
                 b.ncb = 0;             // rare combination: the transposed product takes the unblocked kernel
@@ -335,7 +338,7 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
         b.n_sub = n_loc;
         if ((rc = upload(g, colptr.data(), n_cols + 1, &b.ptr))) return fail(rc);
         if ((rc = upload(g, rowidx.data(), nnz, &b.idx))) return fail(rc);
-        if ((rc = upload_weights(g, nnz, rowidx.data(), edge_val ? cscval.data() : nullptr, row_scale, &b.wt))) return fail(rc);
+        if ((rc = upload_weights(g, nnz, rowidx.data(), edge_val ? cscval.data() : nullptr, row_scale, &b.wt, &b.finite_weights))) return fail(rc);
         if ((rc = upload(g, order_b.data(), order_b.size(), &b.order))) return fail(rc);
         if ((rc = upload_items(g, colptr.data(), nnz, order_b, &b.list))) return fail(rc);
         if ((rc = upload_items(g, colptr.data(), nnz, order_bs, &b.list_sub))) return fail(rc);

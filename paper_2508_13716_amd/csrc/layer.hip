@@ -216,6 +216,7 @@ struct BwdFusion {
     bool dbias_done = false;        // dbias is complete
     const void *dx_mask = nullptr;  // zero dX where this is not positive (storage type of the layer)
     int64_t ld_mask = 0;
+    LiveRows live;                  // rows of dH that may differ from zero
 };
 
 // The transposed aggregation gathers dZ itself and wants its rows multiplied by their scale (layer_bwd_impl).
@@ -329,6 +330,7 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
         Scope s(CAPGNN_K_SPMM_BWD, li, 1, st);
         const bool sub = !dW && !need_halo_grad;
         sp_ep.operand_scaled = scale_dz;
+        sp_ep.live = fuse.live;
         sp_ep.out_bf16 = f32grad;       // float rows in, one rounding on the way out
         CG_TRY(launch_spmm(g->bwd, sub, dH, lddh, tmp, ldt, l->f_out, f32grad ? CAPGNN_F32 : dt, sp_ep, st));
     }
@@ -630,8 +632,11 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
         fuse.dbias_done = linear && dbias[L - 1] && loss_sums_columns(C);
         const bool scale = linear && scaled_dz(g, &layers[L - 1], p.order[L - 1]);
         if (scale && dbias[L - 1] && !fuse.dbias_done) fuse.ready = false;       // the pass that sums the columns scales the rows
+        // rows outside the loss have no gradient: the aggregation that gathers dZ itself need not read them
+        const bool skip = mask && dzt == CAPGNN_F32 && p.order[L - 1] == CAPGNN_XFORM_FIRST && spmm_uses_live(g->bwd, C, lddz);
         CG_TRY(loss_epoch(g->n_loc, C, Z, ldz, labels, targets, ldt, mask, loss_norm, loss_dev, dz, lddz, dzt, logits,
-                          fuse.dbias_done ? dbias[L - 1] : nullptr, scale && fuse.ready ? g->bwd.in_scale : nullptr, w + p.loss_ws_off,
+                          fuse.dbias_done ? dbias[L - 1] : nullptr, scale && fuse.ready ? g->bwd.in_scale : nullptr,
+                          skip ? &fuse.live : nullptr, w + p.loss_ws_off,
                           loss_epoch_ws_bytes(g->n_loc, C), st));
     }
     // backward

@@ -415,20 +415,29 @@ __device__ __forceinline__ int count_range(const uint8_t *mask, int64_t lo, int6
     return cnt;
 }
 
-// part[b] = number of masked rows in workgroup b's contiguous slice (a multiple of 16 rows)
-__global__ __launch_bounds__(1024) void count_mask_kernel(int64_t n, const uint8_t *mask, double *part) {
+// part[b] = number of masked rows in workgroup b's contiguous slice (a multiple of 16 rows); bits (optional): one bit per row
+__global__ __launch_bounds__(1024) void count_mask_kernel(int64_t n, const uint8_t *mask, double *part, uint16_t *bits) {
     __shared__ double red[1024];
     const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
     const int64_t lo = blockIdx.x * per < n ? blockIdx.x * per : n, hi = lo + per < n ? lo + per : n;
+    if (bits)
+        for (int64_t i = lo + 16 * static_cast<int64_t>(threadIdx.x); i < hi; i += 16 * 1024) {
+            uint32_t m = 0;
+            for (int j = 0; j < 16 && i + j < hi; ++j) m |= mask[i + j] ? 1u << j : 0u;
+            bits[i / 16] = static_cast<uint16_t>(m);
+        }
     const double c = block_sum(count_range(mask, lo, hi, 1024), red, 1024);
     if (threadIdx.x == 0) part[blockIdx.x] = c;
 }
 
-// norm_out[0] = max(sum of part, 1) * times
+// norm_out[0] = max(sum of part, 1) * times, norm_out[1] = the sum itself
 __global__ __launch_bounds__(LOSS_PARTS) void count_final_kernel(int parts, const double *part, float times, float *norm_out) {
     __shared__ double red[LOSS_PARTS];
     const double c = block_sum(static_cast<int>(threadIdx.x) < parts ? part[threadIdx.x] : 0.0, red, LOSS_PARTS);
-    if (threadIdx.x == 0) norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
+    if (threadIdx.x == 0) {
+        norm_out[0] = (c > 0.0 ? static_cast<float>(c) : 1.f) * times;
+        norm_out[1] = static_cast<float>(c);
+    }
 }
 
 // Up to this many rows one workgroup counts the mask (the two-level form costs a second launch) ...
@@ -635,29 +644,32 @@ static int loss_blocks(int64_t n, int C, bool bce) {
 
 // a: everything but the normaliser and `part`.  times: what the mask's count is multiplied with for the normaliser.
 // colpart (loss_colpart_bytes) and dbias: also the layer's bias gradient.
+// bits (with a mask): one bit per row of the mask is left there, and the number of set ones in norm_dev[1].
 static int loss_launch(LossArgs a, bool bce, double loss_norm, float times, float *loss_dev, void *ws, float *colpart, float *dbias,
-                       hipStream_t st) {
+                       hipStream_t st, uint16_t *bits = nullptr) {
     float *norm_dev = static_cast<float *>(ws);
     double *counts = reinterpret_cast<double *>(static_cast<char *>(ws) + 256);
     a.part = reinterpret_cast<double *>(static_cast<char *>(ws) + LOSS_HEADER);
     a.lpr = loss_lanes_per_row_host(a.C);
     a.norm_val = 1.f; a.norm_dev = nullptr; a.norm_times = 0.f; a.norm_out = nullptr;
+    if (a.mask && (bits || (loss_norm <= 0.0 && a.n > COUNT_SMALL_N))) {
+        const int parts = static_cast<int>(std::min<int64_t>((a.n + 4095) / 4096, LOSS_PARTS));
+        hipLaunchKernelGGL(count_mask_kernel, dim3(parts), dim3(1024), 0, st, a.n, a.mask, counts, bits);
+        hipLaunchKernelGGL(count_final_kernel, dim3(1), dim3(LOSS_PARTS), 0, st, parts, counts, times, norm_dev);
+        if (loss_norm <= 0.0) a.norm_dev = norm_dev;
+    }
     if (loss_norm > 0.0) {
         a.norm_val = static_cast<float>(loss_norm);
     } else if (!a.mask) {
         a.norm_val = static_cast<float>(a.n) * times;
+    } else if (a.norm_dev) {
+        // counted above
     } else if (a.n <= COUNT_INLINE_N) {
         a.norm_times = times;
         a.norm_out = norm_dev;
     } else {
         a.norm_dev = norm_dev;
-        if (a.n <= COUNT_SMALL_N) {
-            hipLaunchKernelGGL(count_small_kernel, dim3(1), dim3(1024), 0, st, a.n, a.mask, times, norm_dev);
-        } else {
-            const int parts = static_cast<int>(std::min<int64_t>((a.n + 4095) / 4096, LOSS_PARTS));
-            hipLaunchKernelGGL(count_mask_kernel, dim3(parts), dim3(1024), 0, st, a.n, a.mask, counts);
-            hipLaunchKernelGGL(count_final_kernel, dim3(1), dim3(LOSS_PARTS), 0, st, parts, counts, times, norm_dev);
-        }
+        hipLaunchKernelGGL(count_small_kernel, dim3(1), dim3(1024), 0, st, a.n, a.mask, times, norm_dev);
     }
     const int blocks = loss_blocks(a.n, a.C, bce);
     a.colpart = dbias ? colpart : nullptr;
@@ -722,16 +734,18 @@ extern "C" int capgnn_softmax_ce(int64_t n, int C, const float *Z, int64_t ldz, 
 }
 
 size_t capgnn::loss_epoch_ws_bytes(int64_t n, int C) {
-    return capgnn_loss_workspace_bytes(n) + align_up(static_cast<size_t>(loss_blocks(n, C, false)) * C * sizeof(float), 256);
+    return capgnn_loss_workspace_bytes(n) + align_up(static_cast<size_t>(loss_blocks(n, C, false)) * C * sizeof(float), 256) +
+           align_up(static_cast<size_t>(n > 0 ? (n + 31) / 32 : 0) * sizeof(uint32_t), 256);
 }
 
 bool capgnn::loss_sums_columns(int C) { return C <= 4 * loss_lanes_per_row_host(C); }
 
 // The loss of an epoch (labels or targets): also writes the logits as a dense [n x C] matrix to `copy`, sums the columns of dZ
-// into dbias, and stores the rows of dZ times row_scale (each may be NULL).
+// into dbias, and stores the rows of dZ times row_scale (each may be NULL).  live (with a mask): where the rows are that have a
+// gradient, in `ws`.
 int capgnn::loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
                        const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy,
-                       float *dbias, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t st) {
+                       float *dbias, const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st) {
     CG_TRY(softmax_ce_check(n, C, Z, ldz, targets ? reinterpret_cast<const int32_t *>(targets) : labels, loss_dev, dZ, lddz, dz_dtype));
     if (n == 0) return CAPGNN_OK;
     if (targets && ldt < C) CG_FAIL(CAPGNN_EINVAL, "loss: ldt smaller than the number of classes");
@@ -740,8 +754,15 @@ int capgnn::loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int3
     LossArgs a{};
     a.n = n; a.C = C; a.Z = Z; a.ldz = ldz; a.labels = labels; a.targets = targets; a.ldt = ldt; a.mask = mask;
     a.dZ = static_cast<char *>(dZ); a.lddz = lddz; a.dz_bf16 = dz_dtype == CAPGNN_BF16; a.copy = copy; a.rscale = row_scale;
+    char *colpart = static_cast<char *>(ws) + capgnn_loss_workspace_bytes(n);
+    uint16_t *bits = nullptr;
+    if (live && mask) {
+        bits = reinterpret_cast<uint16_t *>(colpart + align_up(static_cast<size_t>(loss_blocks(n, C, false)) * C * sizeof(float), 256));
+        live->bits = reinterpret_cast<const uint32_t *>(bits);
+        live->count = static_cast<const float *>(ws) + 1;
+    }
     return loss_launch(a, targets != nullptr, loss_norm, targets ? static_cast<float>(C) : 1.f, loss_dev, ws,
-                       reinterpret_cast<float *>(static_cast<char *>(ws) + capgnn_loss_workspace_bytes(n)), dbias, st);
+                       reinterpret_cast<float *>(colpart), dbias, st, bits);
 }
 
 // ------------------------------------------------------------------ the same loss without any allocation by anyone

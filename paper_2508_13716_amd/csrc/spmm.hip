@@ -30,6 +30,8 @@ struct SpmmArgs {
     int acc_rows;             // output rows below this one are added to what Y holds
     const char *mask;         // zero where mask <= 0 (storage type of Y), or null
     int64_t ldm_bytes;
+    LiveRows live;            // rows of X that may differ from zero (LIVE kernels)
+    int64_t n_in;
     float *part;              // fp32 partial sums [n_pieces][ldp]
     int64_t ldp;
 };
@@ -148,7 +150,11 @@ __device__ __forceinline__ void store_elems(char *p, const float (&x)[E]) {
 // U loads per lane are issued before the first is consumed, also at the end of a row (entries beyond it are masked out, not
 // loaded): a row of 10 entries costs two round trips to memory and not one per entry, which bounds the launches of
 // low-degree graphs.  Lanes beyond the row's last vector load the first one instead (the same line, never stored).
-template <bool BF16, bool W, bool WAVE, int E, int LPR, int NV, int U>
+//   LIVE   rows of X that a.live does not name are zero and not read (see LIVE_BYTES below).  The bit of an entry is looked up one
+//          chunk ahead and its index two, so that no trip waits for them.
+__device__ __forceinline__ bool row_live(const SpmmArgs &a, int r) { return (a.live.bits[r >> 5] >> (r & 31)) & 1u; }
+
+template <bool BF16, bool W, bool WAVE, int E, int LPR, int NV, int U, bool LIVE>
 __device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, uint32_t end, int lane, int elem0,
                                                float (&acc)[NV][E]) {
     constexpr int ES = BF16 ? 2 : 4;
@@ -159,11 +165,21 @@ __device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, ui
 
     if constexpr (G == 1) {     // one entry per instruction: its row address is scalar
         for (; e < end; e += 64) {
-            const int n = static_cast<int>(end - e < 64u ? end - e : 64u);
+            int n = static_cast<int>(end - e < 64u ? end - e : 64u);
             int c = 0, w = 0;
+            bool on = false;
             if (lane < n) {
                 c = a.idx[e + lane];
                 if constexpr (W) w = __float_as_int(a.wt[e + lane]);
+                if constexpr (LIVE) on = row_live(a, c);
+            }
+            if constexpr (LIVE) {       // the live entries first, in their order
+                const uint64_t m = __ballot(on);
+                const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+                n = __popcll(m);
+                const int to = 4 * (on ? before : n + lane - before);       // a permutation of the wave
+                c = __builtin_amdgcn_ds_permute(to, c);
+                if constexpr (W) w = __builtin_amdgcn_ds_permute(to, w);
             }
             int t = 0;
             for (; t + U <= n; t += U) {
@@ -218,17 +234,23 @@ __device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, ui
     const char *xbase = a.X + off[0];
     const uint32_t ld = static_cast<uint32_t>(a.ldx_bytes);
     int c[NQ], w[NQ];
+    int cr[NQ];                     // LIVE: the next chunk's indices, not yet looked up
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const uint32_t i = e + q * lanes + mine;
-        c[q] = i < end ? a.idx[i] : 0;
+        c[q] = i < end ? a.idx[i] : (LIVE ? -1 : 0);
         if constexpr (W) w[q] = i < end ? __float_as_int(a.wt[i]) : 0;
+        if constexpr (LIVE) {
+            cr[q] = i + STEP < end ? a.idx[i + STEP] : -1;
+            if (c[q] >= 0 && !row_live(a, c[q])) c[q] = -1;
+        }
     }
     while (WAVE ? e < end : __any(e < end)) {
         // entries the group still has (may exceed a chunk)
         const int n = e < end ? (WAVE ? (static_cast<int>(end - e) - sub + G - 1) / G : static_cast<int>(end - e)) : 0;
         e += STEP;
         int cn[NQ], wn[NQ];
+        uint32_t ln[NQ];            // the word with the bit of cr
         auto trip = [&](int t, bool prefetch) __attribute__((always_inline)) {
             RawVec<BF16, E> x[U];
             int at = first4 + STRIDE4 * t;
@@ -237,13 +259,14 @@ __device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, ui
             for (int u = 0; u < U; ++u) {
                 const uint32_t cj = __builtin_amdgcn_ds_bpermute(at + STRIDE4 * (u % LPR), c[NQ > 1 ? u / LPR : 0]);
                 zero_raw<BF16, E>(x[u]);
-                if (t + u < n) load_raw<BF16, E>(xbase + static_cast<uint64_t>(cj) * ld, x[u]);
+                if (t + u < n && (!LIVE || static_cast<int>(cj) >= 0)) load_raw<BF16, E>(xbase + static_cast<uint64_t>(cj) * ld, x[u]);
             }
             if (prefetch) {             // the next chunk's indices: in flight behind the gathers, needed after them
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
-                    const uint32_t i = e + q * lanes + mine;
-                    cn[q] = i < end ? a.idx[i] : 0;
+                    const uint32_t i = e + q * lanes + mine, i2 = LIVE ? i + STEP : i;
+                    if constexpr (LIVE) ln[q] = cr[q] >= 0 ? a.live.bits[cr[q] >> 5] : 0u;
+                    cn[q] = i2 < end ? a.idx[i2] : (LIVE ? -1 : 0);
                     if constexpr (W) wn[q] = i < end ? __float_as_int(a.wt[i]) : 0;
                 }
             }
@@ -264,7 +287,12 @@ __device__ __forceinline__ void accumulate_row(const SpmmArgs &a, uint32_t e, ui
         }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            c[q] = cn[q];
+            if constexpr (LIVE) {
+                c[q] = (ln[q] >> (cr[q] & 31)) & 1u ? cr[q] : -1;
+                cr[q] = cn[q];
+            } else {
+                c[q] = cn[q];
+            }
             if constexpr (W) w[q] = wn[q];
         }
     }
@@ -280,6 +308,15 @@ __device__ __forceinline__ void add_lane_groups(float (&acc)[NV][E]) {
 #pragma unroll
             for (int j = 0; j < E; ++j) acc[v][j] += __shfl_xor(acc[v][j], d);
 }
+
+// Rows of the gathered matrix that are known to be zero (the loss gradient outside the training mask) are not read where the
+// launch is bound by the fabric behind the L2s: rows of CROWDED_ROW entries and more on average, gathered from a matrix that the
+// L2s do not keep.  980 k rows x 50 entries, 47 floats, 60 % of the rows live: 1630 -> 1133 us.  Not taken: 306 k rows x 13 entries
+// (271 against 264 us), and the column-blocked kernel, which the L2s feed (60 k x 500 entries, 41 floats: 364 against 361).
+// Above LIVE_SHARE of live rows the look-up costs more than the rows it saves (all of them live: 1920 us) and the launch reads
+// every row.
+constexpr int64_t LIVE_BYTES = int64_t(16) << 20;
+constexpr float LIVE_SHARE = 0.85f;
 
 // Scale, accumulate, bias, ReLU and store of E consecutive features of one output row.
 template <bool OBF16, int E>
@@ -312,7 +349,7 @@ __device__ __forceinline__ void store_row(const SpmmArgs &a, int row, int f0, co
 }
 
 // What wave `w` of a launch works on: one of the first n_wave items, or 64 / LPR of the others, one per lane group.
-template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV, bool LIVE = false>
 __device__ __forceinline__ void wave_items(const SpmmArgs &a, int64_t w, int lane) {
     constexpr int G = 64 / LPR;
     constexpr int U = (NV == 1) ? 8 : 4;
@@ -337,10 +374,10 @@ __device__ __forceinline__ void wave_items(const SpmmArgs &a, int64_t w, int lan
 #pragma unroll
             for (int j = 0; j < E; ++j) acc[v][j] = 0.f;
         if (by_wave) {
-            accumulate_row<BF16, W, true, E, LPR, NV, U>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
+            accumulate_row<BF16, W, true, E, LPR, NV, U, LIVE>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
             if constexpr (G > 1) add_lane_groups<E, LPR, NV>(acc);
         } else if constexpr (G > 1) {
-            accumulate_row<BF16, W, false, E, LPR, NV, U>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
+            accumulate_row<BF16, W, false, E, LPR, NV, U, LIVE>(a, it.beg, it.beg + it.cnt, lane, elem0, acc);
         }
         if (!stores) continue;
         if (item < a.n_pieces) {
@@ -362,9 +399,10 @@ __device__ __forceinline__ void wave_items(const SpmmArgs &a, int64_t w, int lan
 // five (bf16) or six waves per SIMD are asked for (the bf16-in / fp32-out variants otherwise settle at four; six would spill
 // in the bf16 variants: 7.46 against 7.06 ms for two launches of 980 k rows x 50 entries x 256 features).  W: entries have
 // weights (a.wt), else every weight is 1.
-template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
+template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV, bool LIVE = false>
 __global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void spmm_kernel(SpmmArgs a) {
-    wave_items<BF16, OBF16, W, E, LPR, NV>(a, blockIdx.x, threadIdx.x);
+    if (LIVE && a.live.count[0] <= LIVE_SHARE * static_cast<float>(a.n_in)) wave_items<BF16, OBF16, W, E, LPR, NV, LIVE>(a, blockIdx.x, threadIdx.x);
+    else wave_items<BF16, OBF16, W, E, LPR, NV>(a, blockIdx.x, threadIdx.x);
 }
 
 // Workgroups [0, n_cut): one long row each, its entries shared by the waves and the partial sums added through LDS in wave
@@ -393,7 +431,7 @@ __global__ __launch_bounds__(64 * ROW_WAVES<NV>) void spmm_rows_kernel(SpmmArgs 
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int j = 0; j < E; ++j) acc[v][j] = 0.f;
-        accumulate_row<BF16, W, true, E, LPR, NV, U>(a, e0, e1, lane, elem0, acc);
+        accumulate_row<BF16, W, true, E, LPR, NV, U, false>(a, e0, e1, lane, elem0, acc);
         if constexpr (LPR < 64) add_lane_groups<E, LPR, NV>(acc);
         if (pass > 0) __syncthreads();
         if (wave > 0 && lane < LPR) {
@@ -888,9 +926,18 @@ static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz
         hipLaunchKernelGGL((spmm_rows_kernel<BF16, OBF16, W, E, LPR, NV>),
                            dim3(static_cast<unsigned>(list.n_cut + (one_launch ? (waves + NW - 1) / NW : 0))), dim3(64 * NW), 0, st, a,
                            list.cut, static_cast<int>(list.n_cut), waves);
-    if (!one_launch && waves > 0)
-        hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV>), dim3(static_cast<unsigned>(waves)), dim3(64),
-                           long_rows ? CROWDED_LDS : 0, st, a);
+    if (!one_launch && waves > 0) {
+        bool done = false;
+        if constexpr (!BF16 && E > 1 && LPR > 4) {
+            if (a.live.bits) {
+                hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV, true>), dim3(static_cast<unsigned>(waves)), dim3(64), 0, st, a);
+                done = true;
+            }
+        }
+        if (!done)
+            hipLaunchKernelGGL((spmm_kernel<BF16, OBF16, W, E, LPR, NV>), dim3(static_cast<unsigned>(waves)), dim3(64),
+                               long_rows ? CROWDED_LDS : 0, st, a);
+    }
     if (pieces)
         hipLaunchKernelGGL((spmm_pieces_finish_kernel<OBF16>), dim3(static_cast<unsigned>(list.n_cut), (a.F + 63) / 64),
                            dim3(64, list.max_pieces > 64 ? 16 : 4), 0, st, a, list.cut, list.piece_first);
@@ -919,6 +966,11 @@ static int dispatch_w(const SpmmArgs &a, bool vec, const ItemList &list, bool pi
 template <bool BF16, bool OBF16>
 static int dispatch(const SpmmArgs &a, bool vec, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
     return a.wt ? dispatch_w<BF16, OBF16, true>(a, vec, list, pieces, nnz, st) : dispatch_w<BF16, OBF16, false>(a, vec, list, pieces, nnz, st);
+}
+
+bool spmm_uses_live(const SpOp &op, int F, int64_t ldx) {
+    return op.finite_weights && op.ncb == 0 && F > 16 && op.nnz > ROWS_NNZ && op.nnz >= CROWDED_ROW * op.n_in &&
+           op.n_in * ldx * 4 >= LIVE_BYTES;
 }
 
 int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, void *Y, int64_t ldy, int F,
@@ -950,6 +1002,8 @@ int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, v
     a.F = F; a.F_lim = vec ? f_up : F;
     a.bias = ep.bias; a.relu = ep.relu;
     a.mask = static_cast<const char *>(ep.mask); a.ldm_bytes = ep.ldm * es_out;
+    if (ep.live.bits && dtype == CAPGNN_F32 && spmm_uses_live(op, F, ldx)) a.live = ep.live;
+    a.n_in = op.n_in;
     a.acc_rows = ep.accumulate ? static_cast<int>(std::min<int64_t>(ep.acc_rows, INT32_MAX)) : 0;
     if (vec && !restrict_sub && ep.ws) {
         // the blocked kernel runs when the operator has a blocked copy and the caller brought the scratch for it

@@ -466,3 +466,52 @@ def test_epoch_graph_with_side_stream_matches_eager_epochs(env, miss_mode):
             assert np.array_equal(a, b), f"replay {it} after refill differs"
     eg.close()
     dp.close()
+
+
+@pytest.mark.parametrize("kind,dtype", [("gcn", "f32"), ("gin", "f32"), ("gcn", "bf16")])
+@pytest.mark.parametrize("n,classes,share", [(210_007, 17, 0.5), (110_003, 40, 0.0), (110_003, 47, 0.1), (110_003, 100, 0.8), (110_003, 130, 0.5),
+                                             (110_003, 47, 0.9), (110_003, 47, 1.0)])
+def test_epoch_gradient_rows_outside_the_loss_are_skipped(env, kind, dtype, n, classes, share):
+    """A graph large enough for the last layer's transposed aggregation to skip the rows of dZ outside the training mask (one and
+    several vectors per row, pieces of long rows, rows without entries, a mask that ends inside a word; above 85 % live rows every
+    row is read).  dW of a linear one-layer model against X^T A^T dZ in float64 from the logits that the epoch itself returned:
+    float32 sums of 34-entry rows and of n products of either sign (1e-5 of the norm), and for bf16 one more rounding of each
+    element of A^T dZ (2^-9 at most)."""
+    import scipy.sparse as sp
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(7)
+    deg = rng.integers(0, 69, n)
+    deg[rng.integers(0, n, 5)] = 30_000
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    nnz = int(rowptr[-1])
+    assert nnz >= 32 * n
+    col = rng.integers(0, n, nnz).astype(np.int32)
+    val = rng.uniform(0.5, 1.5, nnz).astype(np.float32) if kind == "gin" else None
+    r, c = (None, None) if kind == "gin" else (rng.uniform(0.1, 0.3, n).astype(np.float32), rng.uniform(0.5, 1.5, n).astype(np.float32))
+    g = B.Graph(n, 0, rowptr, col, r, c, val, 0)
+    f_in, dt = 24, torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn(n, f_in, device="cuda").to(dt)
+    w = (0.05 * torch.randn(f_in, classes, device="cuda")).to(dt)
+    layer = B.make_layer(B.GCN, f_in, classes, B.ACT_NONE, B.BF16 if dtype == "bf16" else B.F32, w, None, None, B.XFORM_FIRST,
+                         out_f32=int(dtype == "bf16"))
+    labels = torch.randint(0, classes, (n,), device="cuda", dtype=torch.int32)
+    mask = torch.from_numpy((rng.random(n) < share).astype(np.uint8)).cuda()
+    logits, dw = torch.zeros(n, classes, device="cuda"), torch.zeros(f_in, classes, device="cuda")
+    db = torch.zeros(classes, device="cuda")
+    size = B.epoch_workspace_bytes(g, None, [layer])
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    for norm in (0.0, 1000.0):      # the normaliser counted, and given
+        B.epoch(g, None, [layer], x, f_in, labels, mask, norm, logits, [dw], None, [db], 0.0, ws, size)
+        torch.cuda.synchronize()
+        z = logits.cpu().double()
+        on = mask.cpu().double()
+        dz = (torch.softmax(z, 1) - torch.nn.functional.one_hot(labels.cpu().long(), classes)) * on[:, None] / (norm or max(float(on.sum()), 1.0))
+        a = sp.csr_matrix((np.ones(nnz) if val is None else val.astype(np.float64), col, rowptr), shape=(n, n))
+        t = dz.numpy() if r is None else dz.numpy() * r[:, None].astype(np.float64)
+        t = a.T @ t
+        if c is not None:
+            t *= c[:, None].astype(np.float64)
+        ref = x.cpu().double().numpy().T @ t
+        err = np.linalg.norm(dw.cpu().double().numpy() - ref) / max(np.linalg.norm(ref), 1e-30)
+        say(f"rows skipped: {kind} {dtype} {n}x{classes} share {share} norm {norm}: {err:.2e}")
+        assert err <= (1e-5 if dtype == "f32" else 2.0 ** -9) if share else not dw.any()
