@@ -90,10 +90,15 @@ __device__ __forceinline__ void zero_row(char *d, int row_bytes, int l, int lpr,
 }
 
 // out[dst_list[k]] = table[k]  (full-batch gather of one tier; dst_list = halo-local index of slot k).
-// A lane group moves SCATTER_ROWS rows at a time: their destination indices are fetched together, then one 16-byte
-// load per row is issued before the first store, so that a wave keeps several kilobytes in flight even when a row
-// is a single load wide (the copy is latency-bound otherwise: index, row, store are three dependent round trips).
+// The copy is bound by latency unless enough is in flight, so a lane group moves R rows at a time and every load of a trip is
+// issued before the first is waited for: the destination indices, then, since they decide only where a row goes, the first
+// 16 bytes per lane of all R rows.  No load stands under a lane condition (which the compiler waits for where it is issued, one
+// row after the other): rows beyond the end repeat the last one and are not stored.
+// Four rows per group; one while that makes fewer than two workgroups per compute unit.  us: 4096 rows of 128 and of 64 floats 15.1
+// -> 3.8 and 10.2 -> 2.8; 8011 rows of 128 and of 50 floats 19.4 -> 4.6 and 14.9 -> 3.4 (so many: one row); 300 k rows of 512
+// bf16 107 -> 104, 350 k rows of 256 floats 122 -> 120 (four rows).
 constexpr int SCATTER_ROWS = 4;
+constexpr unsigned SCATTER_FEW = 2 * NUM_CU;
 
 // One tier's rows and where they go; `blocks` workgroups of the launch work on it.
 struct TierRows {
@@ -105,6 +110,7 @@ struct TierRows {
 
 // One launch serves up to two tiers of the same layer (same pitch and row geometry): workgroups [0, a.blocks) take
 // tier a, the rest tier b.
+template <int R>
 __global__ __launch_bounds__(256) void scatter_tier_kernel(TierRows a, TierRows b, int64_t pitch, char *out,
                                                            int64_t out_pitch, int row_bytes, int lpr, int vec16, int es) {
     const bool second = blockIdx.x >= a.blocks;            // uniform over the workgroup
@@ -117,49 +123,61 @@ __global__ __launch_bounds__(256) void scatter_tier_kernel(TierRows a, TierRows 
     const int l = lane % lpr;
     const int rows_per_wave = 64 / lpr;
     const int64_t wave = static_cast<int64_t>(bx) * 4 + (threadIdx.x >> 6);
-    const int64_t per_wave = static_cast<int64_t>(rows_per_wave) * SCATTER_ROWS;
+    const int64_t per_wave = static_cast<int64_t>(rows_per_wave) * R;
     const int64_t stride = static_cast<int64_t>(blocks) * 4 * per_wave;   // a capped grid walks the list in strides
+    const int nfull = vec16 ? row_bytes >> 4 : 0;
     for (int64_t base = wave * per_wave; base < n; base += stride) {
         const int64_t k0 = base + lane / lpr;
-        const char *src[SCATTER_ROWS];
-        char *dst[SCATTER_ROWS];
-        int32_t di[SCATTER_ROWS];
+        const char *src[R];
+        char *dst[R];
+        int32_t di[R];
+        bool on[R];
+        uint4 v[R];
 #pragma unroll
-        for (int u = 0; u < SCATTER_ROWS; ++u) {
-            const int64_t k = k0 + static_cast<int64_t>(u) * rows_per_wave;
-            di[u] = k < n ? dst_list[k] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < SCATTER_ROWS; ++u) {
-            const int64_t k = k0 + static_cast<int64_t>(u) * rows_per_wave;
+        for (int u = 0; u < R; ++u) {
+            int64_t k = k0 + static_cast<int64_t>(u) * rows_per_wave;
+            on[u] = k < n;
+            k = on[u] ? k : n - 1;
+            di[u] = dst_list[k];
             src[u] = table + k * pitch;
-            dst[u] = out + static_cast<int64_t>(di[u]) * out_pitch;
         }
-        int done = 0;
-        if (vec16) {
-            const int nfull = row_bytes >> 4;
-            for (int c = l; c < nfull; c += lpr) {
-                uint4 a[SCATTER_ROWS];
+        if (nfull > 0) {
+            const int c = l < nfull ? l : nfull - 1;
 #pragma unroll
-                for (int u = 0; u < SCATTER_ROWS; ++u)
-                    if (di[u] >= 0) a[u] = reinterpret_cast<const uint4 *>(src[u])[c];
+            for (int u = 0; u < R; ++u) v[u] = reinterpret_cast<const uint4 *>(src[u])[c];
+        }
 #pragma unroll
-                for (int u = 0; u < SCATTER_ROWS; ++u)
-                    if (di[u] >= 0) reinterpret_cast<uint4 *>(dst[u])[c] = a[u];
+        for (int u = 0; u < R; ++u) dst[u] = out + static_cast<int64_t>(di[u]) * out_pitch;
+        if (l < nfull) {
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (on[u]) reinterpret_cast<uint4 *>(dst[u])[l] = v[u];
+            for (int c = l + lpr; c < nfull; c += lpr) {
+#pragma unroll
+                for (int u = 0; u < R; ++u) v[u] = reinterpret_cast<const uint4 *>(src[u])[c];
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (on[u]) reinterpret_cast<uint4 *>(dst[u])[c] = v[u];
             }
-            done = nfull << 4;
         }
-        if (done < row_bytes) {   // the last few elements of a row, or rows that are not 16-byte aligned
+        // the last few elements of a row, or rows that are not 16-byte aligned
+        if (es == 4) {
+            for (int b = (nfull << 4) + l * 4; b < row_bytes; b += lpr * 4) {
+                uint32_t w[R];
 #pragma unroll
-            for (int u = 0; u < SCATTER_ROWS; ++u) {
-                if (di[u] < 0) continue;
-                if (es == 4) {
-                    for (int b = done + l * 4; b < row_bytes; b += lpr * 4)
-                        *reinterpret_cast<uint32_t *>(dst[u] + b) = *reinterpret_cast<const uint32_t *>(src[u] + b);
-                } else {
-                    for (int b = done + l * 2; b < row_bytes; b += lpr * 2)
-                        *reinterpret_cast<uint16_t *>(dst[u] + b) = *reinterpret_cast<const uint16_t *>(src[u] + b);
-                }
+                for (int u = 0; u < R; ++u) w[u] = *reinterpret_cast<const uint32_t *>(src[u] + b);
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (on[u]) *reinterpret_cast<uint32_t *>(dst[u] + b) = w[u];
+            }
+        } else {
+            for (int b = (nfull << 4) + l * 2; b < row_bytes; b += lpr * 2) {
+                uint16_t w[R];
+#pragma unroll
+                for (int u = 0; u < R; ++u) w[u] = *reinterpret_cast<const uint16_t *>(src[u] + b);
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (on[u]) *reinterpret_cast<uint16_t *>(dst[u] + b) = w[u];
             }
         }
     }
@@ -360,9 +378,25 @@ static unsigned blocks_for(int64_t n, int lpr) {
     return static_cast<unsigned>((n + rows_per_block - 1) / rows_per_block);
 }
 
-static unsigned scatter_blocks_for(int64_t n, int lpr) {
-    const int64_t rows_per_block = 4 * (64 / lpr) * SCATTER_ROWS;
+static unsigned scatter_blocks_for(int64_t n, int lpr, int rows) {
+    const int64_t rows_per_block = 4 * (64 / lpr) * rows;
     return static_cast<unsigned>((n + rows_per_block - 1) / rows_per_block);
+}
+
+// One launch for the rows of up to two tiers; cap: most workgroups (0: no limit)
+static int launch_scatter(const CopyGeom &g, int64_t pitch, TierRows a, TierRows b, unsigned cap, void *out, hipStream_t st) {
+    const bool few = cap == 0 && scatter_blocks_for(a.n, g.lpr, SCATTER_ROWS) + scatter_blocks_for(b.n, g.lpr, SCATTER_ROWS) < SCATTER_FEW;
+    const int rows = few ? 1 : SCATTER_ROWS;
+    a.blocks = scatter_blocks_for(a.n, g.lpr, rows);
+    b.blocks = scatter_blocks_for(b.n, g.lpr, rows);
+    if (cap && a.blocks > cap) a.blocks = cap;
+    const dim3 grid(a.blocks + b.blocks);
+    if (few) hipLaunchKernelGGL(scatter_tier_kernel<1>, grid, dim3(256), 0, st, a, b, pitch, static_cast<char *>(out), g.out_pitch,
+                                g.row_bytes, g.lpr, g.vec16, g.es);
+    else hipLaunchKernelGGL(scatter_tier_kernel<SCATTER_ROWS>, grid, dim3(256), 0, st, a, b, pitch, static_cast<char *>(out), g.out_pitch,
+                            g.row_bytes, g.lpr, g.vec16, g.es);
+    CG_HIP(hipGetLastError());
+    return CAPGNN_OK;
 }
 
 // GPU-tier part of the full-batch gather of one layer, on `st`.
@@ -371,11 +405,7 @@ int gather_all_hits(const capgnn_cache *c, int layer, void *out, int64_t ld, hip
     CopyGeom g;
     const char *tab = c->gpu_tier + c->gpu_off[layer];
     CG_TRY(copy_geom(c, layer, out, ld, tab, &g));
-    const TierRows a{tab, c->gpu_list_d, c->cap_gpu, scatter_blocks_for(c->cap_gpu, g.lpr)}, none{nullptr, nullptr, 0, 0};
-    hipLaunchKernelGGL(scatter_tier_kernel, dim3(a.blocks), dim3(256), 0, st, a, none, c->pitch[layer],
-                       static_cast<char *>(out), g.out_pitch, g.row_bytes, g.lpr, g.vec16, g.es);
-    CG_HIP(hipGetLastError());
-    return CAPGNN_OK;
+    return launch_scatter(g, c->pitch[layer], {tab, c->gpu_list_d, c->cap_gpu, 0}, {nullptr, nullptr, 0, 0}, 0, out, st);
 }
 
 // Both device-resident sources of one layer's halo rows in one launch: the GPU tier and the staged copy of the host
@@ -393,12 +423,7 @@ int gather_hits_and_staged(const capgnn_cache *c, int layer, void *out, int64_t 
         CG_TRY(gather_all_hits(c, layer, out, ld, st));
         return scatter_staged(c, layer, out, ld, staging, st);
     }
-    const TierRows a{tab, c->gpu_list_d, c->cap_gpu, scatter_blocks_for(c->cap_gpu, g.lpr)};
-    const TierRows b{stab, c->host_list_d, c->n_host, scatter_blocks_for(c->n_host, g.lpr)};
-    hipLaunchKernelGGL(scatter_tier_kernel, dim3(a.blocks + b.blocks), dim3(256), 0, st, a, b, c->pitch[layer],
-                       static_cast<char *>(out), g.out_pitch, g.row_bytes, g.lpr, g.vec16, g.es);
-    CG_HIP(hipGetLastError());
-    return CAPGNN_OK;
+    return launch_scatter(g, c->pitch[layer], {tab, c->gpu_list_d, c->cap_gpu, 0}, {stab, c->host_list_d, c->n_host, 0}, 0, out, st);
 }
 
 // DMA of layer `layer`'s host tier into its slot of the staging area.
@@ -416,13 +441,8 @@ static int scatter_host_rows(const capgnn_cache *c, int layer, const char *tab, 
     CG_TRY(copy_geom(c, layer, out, ld, tab, &g));
     // A kernel that reads pinned memory is bound by the host link, not by the CUs: a small grid keeps enough
     // requests in flight and leaves the compute units to the kernels of the main stream.
-    unsigned blocks = scatter_blocks_for(c->n_host, g.lpr);
-    if (pinned && blocks > HOST_READ_BLOCKS) blocks = HOST_READ_BLOCKS;
-    const TierRows a{tab, c->host_list_d, c->n_host, blocks}, none{nullptr, nullptr, 0, 0};
-    hipLaunchKernelGGL(scatter_tier_kernel, dim3(blocks), dim3(256), 0, st, a, none, c->pitch[layer],
-                       static_cast<char *>(out), g.out_pitch, g.row_bytes, g.lpr, g.vec16, g.es);
-    CG_HIP(hipGetLastError());
-    return CAPGNN_OK;
+    return launch_scatter(g, c->pitch[layer], {tab, c->host_list_d, c->n_host, 0}, {nullptr, nullptr, 0, 0}, pinned ? HOST_READ_BLOCKS : 0,
+                          out, st);
 }
 
 // Scatter of a staged host tier into the halo rows it belongs to.

@@ -240,6 +240,39 @@ def test_graph_create_rejects_malformed_input(env):
         B.Graph(2, 0, np.array([0, 1, 1]), np.array([1], np.int32), flags=B.GRAPH_SYMMETRIC)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,cap", [(1, 1), (3, 0), (67, 30), (8191, 4000), (8193, 8193), (70_001, 35_003)])
+def test_full_gather_row_counts_and_widths_bit_exact(env, n, cap, dtype):
+    """Both launch forms of the full-batch gather (few rows: one per lane group, else four), with one and two tiers, at widths
+    whose rows are shorter than a vector, end in the middle of one, or are wider than a lane group; destinations that are and
+    are not 16-byte aligned.  Bit copies: no tolerance."""
+    torch, B = env["torch"], env["B"]
+    dims = [1, 7, 50, 128, 301]
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(n)
+    c = B.Cache(rng.permutation(n).astype(np.int64) + 17, rng.integers(1, 100, n).astype(np.int64), cap, dims, B.BF16 if dtype == "bf16" else B.F32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    ids = torch.arange(n, device="cuda")
+    stage = torch.empty(max(c.staging_bytes, 256), dtype=torch.uint8, device="cuda")
+    main, side = torch.cuda.Stream(), torch.cuda.Stream()
+    for l, d in enumerate(dims):
+        rows = torch.randn(n, d, generator=gen, device="cuda").to(dt)
+        B.cache_update(c, l, ids, n, rows, d, 0)
+        for ld in (d, (d + 15) // 16 * 16 + 16):
+            for two_streams in (False, True):
+                say(f"full gather n={n} cap={cap} width={d} ld={ld} two_streams={two_streams}")
+                out = torch.full((n + 1, ld), -3.0, dtype=dt, device="cuda")
+                torch.cuda.synchronize()
+                if two_streams:
+                    B.halo_gather(c, l, None, n, out, ld, stream=main, side_stream=side, staging=stage)
+                else:
+                    B.halo_gather(c, l, None, n, out, ld, stream=main)
+                torch.cuda.synchronize()
+                assert torch.equal(out[:n, :d], rows)
+                assert (out[n] == -3).all() and (out[:, d:] == -3).all()      # nothing beyond the rows is written
+
+
 # ----------------------------------------------------------------------------- cache
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cap_frac", [0.0, 0.37, 1.0])
