@@ -94,9 +94,10 @@ __device__ __forceinline__ void zero_row(char *d, int row_bytes, int l, int lpr,
 // issued before the first is waited for: the destination indices, then, since they decide only where a row goes, the first
 // 16 bytes per lane of all R rows.  No load stands under a lane condition (which the compiler waits for where it is issued, one
 // row after the other): rows beyond the end repeat the last one and are not stored.
-// Four rows per group; one while that makes fewer than two workgroups per compute unit.  us: 4096 rows of 128 and of 64 floats 15.1
-// -> 3.8 and 10.2 -> 2.8; 8011 rows of 128 and of 50 floats 19.4 -> 4.6 and 14.9 -> 3.4 (so many: one row); 300 k rows of 512
-// bf16 107 -> 104, 350 k rows of 256 floats 122 -> 120 (four rows).
+// One row per group while that is one load per lane, or while groups of four make fewer than two workgroups per compute unit: more
+// waves hide more than more rows per wave do (us with four -> one: 4096 rows of 128 floats 12.6 -> 3.8, 8011 of 128 18.5 -> 4.7,
+// 300 k of 512 bf16 104 -> 93, 350 k of 256 floats 120 -> 107).  Wider rows, and rows read over the host link by a capped grid,
+// go four at a time.
 constexpr int SCATTER_ROWS = 4;
 constexpr unsigned SCATTER_FEW = 2 * NUM_CU;
 
@@ -385,13 +386,14 @@ static unsigned scatter_blocks_for(int64_t n, int lpr, int rows) {
 
 // One launch for the rows of up to two tiers; cap: most workgroups (0: no limit)
 static int launch_scatter(const CopyGeom &g, int64_t pitch, TierRows a, TierRows b, unsigned cap, void *out, hipStream_t st) {
-    const bool few = cap == 0 && scatter_blocks_for(a.n, g.lpr, SCATTER_ROWS) + scatter_blocks_for(b.n, g.lpr, SCATTER_ROWS) < SCATTER_FEW;
-    const int rows = few ? 1 : SCATTER_ROWS;
+    const bool one = cap == 0 && (g.row_bytes <= 16 * g.lpr || scatter_blocks_for(a.n, g.lpr, SCATTER_ROWS) +
+                                                                   scatter_blocks_for(b.n, g.lpr, SCATTER_ROWS) < SCATTER_FEW);
+    const int rows = one ? 1 : SCATTER_ROWS;
     a.blocks = scatter_blocks_for(a.n, g.lpr, rows);
     b.blocks = scatter_blocks_for(b.n, g.lpr, rows);
     if (cap && a.blocks > cap) a.blocks = cap;
     const dim3 grid(a.blocks + b.blocks);
-    if (few) hipLaunchKernelGGL(scatter_tier_kernel<1>, grid, dim3(256), 0, st, a, b, pitch, static_cast<char *>(out), g.out_pitch,
+    if (one) hipLaunchKernelGGL(scatter_tier_kernel<1>, grid, dim3(256), 0, st, a, b, pitch, static_cast<char *>(out), g.out_pitch,
                                 g.row_bytes, g.lpr, g.vec16, g.es);
     else hipLaunchKernelGGL(scatter_tier_kernel<SCATTER_ROWS>, grid, dim3(256), 0, st, a, b, pitch, static_cast<char *>(out), g.out_pitch,
                             g.row_bytes, g.lpr, g.vec16, g.es);
