@@ -213,7 +213,7 @@ size_t relu_bias_ws_bytes(int64_t n, int F);
 int launch_relu_mask_dbias(int64_t n, int F, const void *src, int64_t lds, int src_dtype, void *dH, int64_t lddh,
                            const void *H, int64_t ldh, int dtype, int h_dtype, int relu, float *dbias, void *ws,
                            size_t ws_bytes, hipStream_t stream, const float *row_scale = nullptr);
-// tensors of one SGD step (three per layer at most)
+// tensors of one SGD step (three per layer at most), in the order in which they are updated
 struct SgdList {
     float *W[48];
     const float *dW[48];
@@ -221,7 +221,7 @@ struct SgdList {
     unsigned first[48];         // filled by launch_sgd
     int count = 0;
 };
-int launch_sgd(SgdList s, float lr, hipStream_t stream);
+int launch_sgd(const SgdList &all, float lr, hipStream_t stream);
 // the loss of an epoch on labels or targets, with what else can be had on the way (see ops.hip)
 int loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
                const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy, float *dbias,

@@ -364,16 +364,33 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdList s, float lr) {
     for (int64_t i = b * 256 + threadIdx.x; i < s.n[t]; i += blocks * 256) W[i] = W[i] - lr * dW[i];
 }
 
-int launch_sgd(SgdList s, float lr, hipStream_t stream) {
-    unsigned blocks = 0;
-    for (int t = 0; t < s.count; ++t) {
-        if (!s.W[t] || !s.dW[t] || s.n[t] <= 0) CG_FAIL(CAPGNN_EINVAL, "sgd: NULL operand");
-        s.first[t] = blocks;
-        blocks += static_cast<unsigned>(std::min<int64_t>((s.n[t] + 255) / 256, 2048));
+static bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + nb * sizeof(float) && y < x + na * sizeof(float);
+}
+
+// The tensors of one launch are updated side by side, so a tensor that shares memory with one before it (layers with tied
+// weights or a common bias) starts the next launch: updates of one element follow each other in the order of the list.
+int launch_sgd(const SgdList &all, float lr, hipStream_t stream) {
+    for (int t0 = 0; t0 < all.count;) {
+        SgdList s;
+        unsigned blocks = 0;
+        int t = t0;
+        for (; t < all.count; ++t) {
+            if (!all.W[t] || !all.dW[t] || all.n[t] <= 0) CG_FAIL(CAPGNN_EINVAL, "sgd: NULL operand");
+            bool shared = false;
+            for (int u = 0; u < s.count && !shared; ++u)
+                shared = overlap(all.W[t], all.n[t], s.W[u], s.n[u]) || overlap(all.W[t], all.n[t], s.dW[u], s.n[u]) ||
+                         overlap(all.dW[t], all.n[t], s.W[u], s.n[u]);
+            if (shared) break;
+            s.W[s.count] = all.W[t]; s.dW[s.count] = all.dW[t]; s.n[s.count] = all.n[t];
+            s.first[s.count++] = blocks;
+            blocks += static_cast<unsigned>(std::min<int64_t>((all.n[t] + 255) / 256, 2048));
+        }
+        hipLaunchKernelGGL(sgd_kernel, dim3(blocks), dim3(256), 0, stream, s, lr);
+        CG_HIP(hipGetLastError());
+        t0 = t;
     }
-    if (!blocks) return CAPGNN_OK;
-    hipLaunchKernelGGL(sgd_kernel, dim3(blocks), dim3(256), 0, stream, s, lr);
-    CG_HIP(hipGetLastError());
     return CAPGNN_OK;
 }
 

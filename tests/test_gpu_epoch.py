@@ -515,3 +515,60 @@ def test_epoch_gradient_rows_outside_the_loss_are_skipped(env, kind, dtype, n, c
         err = np.linalg.norm(dw.cpu().double().numpy() - ref) / max(np.linalg.norm(ref), 1e-30)
         say(f"rows skipped: {kind} {dtype} {n}x{classes} share {share} norm {norm}: {err:.2e}")
         assert err <= (1e-5 if dtype == "f32" else 2.0 ** -9) if share else not dw.any()
+
+
+@pytest.mark.parametrize("recorded", [False, True])
+@pytest.mark.parametrize("tie", ["layers", "self", "all", "bias", "overlap"])
+def test_sgd_step_adds_every_gradient_of_a_shared_tensor(env, tie, recorded):
+    """Layers that share a tensor (tied weights, W_self == W, one bias, a matrix that starts inside another one) get the updates of all
+    of them, one after the other: W - lr (dW_0 + dW_1 + ..) in the order of the layers.  Each update of an element rounds its product
+    and its difference at most: 2^-23 of the largest magnitude per update, a hundredth of what a lost update would leave out."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(11)
+    n, D, L, lr = 300, 256, 3, 30.0
+    rowptr = np.arange(0, 4 * n + 1, 4, dtype=np.int64)
+    g = B.Graph(n, 0, rowptr, rng.integers(0, n, 4 * n).astype(np.int32), np.full(n, 0.25, np.float32), None)
+    buf = torch.from_numpy((rng.standard_normal((2 * L, D * D)) / 16).astype(np.float32)).cuda()
+    bias = torch.from_numpy((rng.standard_normal((L, D)) / 16).astype(np.float32)).cuda()
+    w_at = {"layers": [0] * L, "all": [0] * L, "overlap": [0, D * D // 2, D * D]}.get(tie, [l * D * D for l in range(L)])
+    s_at = {"self": w_at, "all": w_at}.get(tie, [(L + l) * D * D for l in range(L)])
+    b_at = [0] * L if tie in ("bias", "all") else list(range(L))
+    flat = buf.view(-1)
+    layers = [B.make_layer(B.SAGE_MEAN, D, D, B.ACT_RELU if l < L - 1 else B.ACT_NONE, B.F32, flat[w_at[l]:], flat[s_at[l]:], bias[b_at[l]], B.AGG_FIRST)
+              for l in range(L)]
+    x = torch.randn(n, D, device="cuda")
+    labels = torch.randint(0, D, (n,), device="cuda", dtype=torch.int32)
+    mk = lambda *s: [torch.zeros(*s, device="cuda") for _ in range(L)]  # noqa: E731
+    dw, ds, db = mk(D, D), mk(D, D), mk(D)
+    size = B.epoch_workspace_bytes(g, None, layers)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.Stream()
+    start = buf.clone(), bias.clone()
+    flat_0, bias_0 = flat.double().cpu().numpy(), bias.double().cpu().numpy()
+    torch.cuda.synchronize()
+    if recorded:
+        eg = B.EpochGraph(g, None, layers, x, D, labels, None, 0.0, None, dw, ds, db, lr, None, ws, size, st)
+    for it in range(3):
+        say(f"shared tensors {tie} recorded={recorded} step {it}")
+        buf.copy_(start[0])
+        bias.copy_(start[1])
+        torch.cuda.synchronize()
+        if recorded:
+            eg.launch(st)
+        else:
+            B.epoch(g, None, layers, x, D, labels, None, 0.0, None, dw, ds, db, lr, ws, size, stream=st, want_loss=False)
+        torch.cuda.synchronize()
+        want_w, want_b = flat_0.copy(), bias_0.copy()
+        least = np.inf
+        for l in range(L):
+            for at, d in ((w_at[l], dw[l]), (s_at[l], ds[l])):
+                step = lr * d.double().cpu().numpy().ravel()
+                want_w[at:at + D * D] -= step
+                least = min(least, np.abs(step).max())
+            step = lr * db[l].double().cpu().numpy()
+            want_b[b_at[l]] -= step
+            least = min(least, np.abs(step).max())
+        bound = 2 * L * 2.0 ** -23 * max(np.abs(flat_0).max(), np.abs(want_w).max(), np.abs(bias_0).max(), np.abs(want_b).max())
+        assert least > 100 * bound, "a lost update would not be seen"
+        assert np.abs(flat.double().cpu().numpy() - want_w).max() <= bound
+        assert np.abs(bias.double().cpu().numpy() - want_b).max() <= bound
