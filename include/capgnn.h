@@ -366,15 +366,15 @@ size_t capgnn_gemm_workspace_bytes(int trans_a, int64_t M, int64_t N, int64_t K)
 
 /* How a product of fp32 operands is formed: an argument of capgnn_gemm and a field of capgnn_layer (nothing is
  * process-wide, so distinct handles and calls stay independent).
- *   CAPGNN_F32_PRODUCT_AUTO    (0, what a zeroed field means) the faster of the two by size: NATIVE for small products and
- *                              for trans_a products with N <= 64, SPLIT otherwise.
+ *   CAPGNN_F32_PRODUCT_AUTO    (0, what a zeroed field means) SPLIT for products of 2^28 multiply-adds and more (trans_a: of
+ *                              1.375 * 2^28 and more, and N > 64; the two forward products of a GraphSAGE layer in the
+ *                              AGG_FIRST order count as one); NATIVE otherwise.
  *   CAPGNN_F32_PRODUCT_NATIVE  the fp32 matrix instruction (v_mfma_f32_32x32x2_f32).
  *   CAPGNN_F32_PRODUCT_SPLIT   each fp32 operand is cut, exactly, into three bf16 numbers and the six largest of the nine
  *                              piece products are accumulated in fp32 on the bf16 matrix cores; what is dropped is
- *                              2^-23 of a product at most, the size of the fp32 instruction's own rounding.  A large
- *                              product needs the workspace of capgnn_gemm_workspace_bytes() also when !trans_a (the
- *                              weight matrix is cut there); without it, and for trans_a && trans_b, the native
- *                              instruction runs.
+ *                              2^-23 of a product at most, the size of the fp32 instruction's own rounding.  Needs the
+ *                              workspace of capgnn_gemm_workspace_bytes() also when !trans_a (the weight matrix is cut
+ *                              there); without it, and for trans_a && trans_b, the native instruction runs.
  *                              Non-finite operands give NaN where the native instruction may give an infinity.
  * bf16 operands are not affected.  Any other value: CAPGNN_EINVAL. */
 #define CAPGNN_F32_PRODUCT_AUTO 0

@@ -1635,7 +1635,7 @@ static size_t split_b_bytes(int64_t N, int64_t K) {
     return align_up(static_cast<size_t>(3) * split_rows(N) * split_ld(K) * sizeof(uint16_t), 256);
 }
 
-static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K);
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches = 1);
 static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk);
 
 size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
@@ -1662,18 +1662,24 @@ size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
 
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2) { return split_b_bytes(N, split_ld(K1) + K2); }
 
-// Which products take gemm_small_kernel (fp32 ones unless their three-piece form was asked for).  Plain products: while its
-// 32-row tiles make at most two workgroups per compute unit and a wave has at most two batches to multiply (4096 x 64 x 128
-// fp32: 13.2 -> 6.7 us; 9973 x 64 x 100: 13.8 -> 9.1; 21557 x 128 x 50, 1348 tiles: 24 us against 14).  Reductions over
-// vertices (trans_a), whose other kernels stage tiles through LDS step by step: up to 2^28.5 multiply-adds in fp32 (128 x 121
-// x 21557: 39 -> 21 us; 256 x 256 x 20000: 46 against 34) and 2^30.5 in bf16 (256 x 256 x 20000: 30 -> 19; 100 x 256 x 70001:
-// 34 against 33), and further where N <= 64 leaves those kernels half idle (256 x 41 x 180000: 106 -> 91 fp32, 42 -> 34
-// bf16; 256 x 47 x 306000: 161 against 148 fp32, 67 -> 56 bf16).
-static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K) {
+constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piece form from here on (see split_form)
+
+// Which products take gemm_small_kernel (fp32 ones unless their three-piece form was asked for).  Plain fp32 products, all of those
+// that AUTO leaves to the fp32 instruction are candidates (gemm_kernel is the other choice): the launch grows with its 32 x 32
+// tiles once they are about four per compute unit, and what it saves, the round trips of a step-by-step reduction, with K.  us
+// against gemm_kernel: 10000 x 41 x 16 (626 tiles) 8.4 / 8.1, 4096 x 256 x 16 (1024) 8.6 / 8.7, 10000 x 128 x 16 (1252) 13.7 / 8.9;
+// 10000 x 128 x 50 (1252) 14.1 / 14.0, 21557 x 41 x 50 (1348) 13.8 / 11.8; 21557 x 41 x 100 (1348) 14.1 / 14.4, 10000 x 256 x 100
+// (2504) 22 / 17; 21557 x 64 x 128 (1348) 13.0 / 13.8, 50000 x 41 x 128 (3126) 25 / 21; 21557 x 41 x 256 17 / 24; 10000 x 41 x
+// 602 26 / 54.  A sum of two products replaces two launches of gemm_kernel, so it may have twice the tiles (launches = 2).
+// Reductions over vertices (trans_a), whose other kernels stage tiles through LDS step by step: up to 2^28.5
+// multiply-adds in fp32 (128 x 121 x 21557: 39 -> 21 us; 256 x 256 x 20000: 46 against 34) and 2^30.5 in bf16 (256 x 256 x 20000: 30
+// -> 19; 100 x 256 x 70001: 34 against 33), and further where N <= 64 leaves those kernels half idle (256 x 41 x 180000: 106 -> 91
+// fp32, 42 -> 34 bf16; 256 x 47 x 306000: 161 against 148 fp32, 67 -> 56 bf16).
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches) {
     if (K <= 0) return false;
     const double macs = static_cast<double>(M) * N * K;
     if (trans_a) return macs <= (bf16 ? (N <= 64 ? 0x1p32 : 0x1.6p30) : (N <= 64 ? 0x1p31 : 0x1.6p28));
-    return !bf16 && K <= 128 && ((M + 31) / 32) * ((N + 63) / 64) <= 512;
+    return !bf16 && macs < SPLIT_MIN_MACS && ((M + 31) / 32) * ((N + 31) / 32) <= launches * (1024 + 8 * std::max<int64_t>(K - 50, 0));
 }
 
 // Tiles and reduction splits of a small product: N tiles of 64 columns (32 where that is all), and for a reduction over
@@ -1693,9 +1699,18 @@ static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t
     *S = static_cast<int>((K + *k_chunk - 1) / *k_chunk);
 }
 
-// AUTO: smaller products stay on the fp32 instruction, and so do weight gradients at most 64 columns wide (half of
-// the threads that stage their operands would idle; measured slower)
-constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;
+// AUTO: smaller products stay on the fp32 instruction (the caller is told the limit), and so do weight gradients at most 64
+// columns wide (half of the threads that stage their operands would idle; measured slower)
+static bool split_form(int mode, int trans_a, int64_t M, int64_t N, int64_t K) {
+    if (mode != CAPGNN_F32_PRODUCT_AUTO) return mode == CAPGNN_F32_PRODUCT_SPLIT;
+    return M * N >= SPLIT_MIN_MACS / (K > 0 ? K : 1) && !(trans_a && N <= 64);
+}
+
+// the sum of two products: a layer's forward products count as one, those of its input gradient each for itself
+static bool split_sum(int mode, int trans_b, int64_t M, int64_t N, int64_t K1, int64_t K2) {
+    if (trans_b) return split_form(mode, 0, M, N, K1) && split_form(mode, 0, M, N, K2);
+    return split_form(mode, 0, M, N, K1 + K2);
+}
 
 // tiles 64 columns wide keep four waves; 128-column tiles run eight (both forms of the product)
 static void launch_split_tiles(bool trans, const GemmArgs &g, int bn, dim3 grid, const uint16_t *Wt, int64_t ku_total,
@@ -1762,14 +1777,11 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned);
     // fp32 operands as three bf16 pieces each (see gemm_split_kernel)
     const int mode = f32_product;
-    const bool split_form = dtype == CAPGNN_F32 && mode != CAPGNN_F32_PRODUCT_NATIVE && !(trans_a && trans_b);
-    // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
-    const bool mid = split_form && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
-    const bool split_path = split_form &&
-                            (mode == CAPGNN_F32_PRODUCT_SPLIT ||
-                             (M * N >= SPLIT_MIN_MACS / (K > 0 ? K : 1) && !(trans_a && N <= 64))) &&
+    const bool split_path = dtype == CAPGNN_F32 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
                             (trans_a || (ws && ws_bytes >= split_b_bytes(N, K)));
-    const bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && mode != CAPGNN_F32_PRODUCT_SPLIT;
+    // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
+    const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
+    const bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
     int S = choose_split(trans_a, M, N, K, bm, bn, bk), tn = 0;
@@ -1881,14 +1893,18 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     SmallGemmArgs s = in;
     GemmArgs &g = s.g;
     const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
-    const int64_t Kmax = s.dual ? std::max(g.K, s.K2) : g.K;
-    const bool small = f32_product != CAPGNN_F32_PRODUCT_SPLIT && small_product(bf, trans_a, g.M, g.N, Kmax);
+    const int64_t Ksum = g.K + (s.dual ? s.K2 : 0);       // (the waves of a workgroup share it)
+    const bool small = f32_product != CAPGNN_F32_PRODUCT_SPLIT && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
-    const bool mid = !small && !bf && !trans_a && f32_product != CAPGNN_F32_PRODUCT_NATIVE && tiles64 * (pair ? 2 : 1) <= 768 &&
+    // the three-piece form on the terms of launch_gemm and launch_gemm_dual
+    const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&
+                       (s.dual ? split_sum(f32_product, trans_b, g.M, g.N, g.K, s.K2)
+                               : split_form(f32_product, 0, g.M, g.N, g.K) && split_form(f32_product, 0, s.M2, g.N, g.K));
+    const bool mid = !small && split && tiles64 * (pair ? 2 : 1) <= 768 &&
                      std::max(std::max(g.lda, s.lda2), std::max(g.ldb, s.ldb2)) < (1 << 22);
-    if ((!small && !mid) || Kmax <= 0 || (s.dual && (g.K <= 0 || s.K2 <= 0))) return CAPGNN_OK;
+    if ((!small && !mid) || g.K <= 0 || (s.dual && s.K2 <= 0)) return CAPGNN_OK;
     int tn = 2, S = 1;
-    g.k_chunk = Kmax;
+    g.k_chunk = Ksum;
     if (small) small_geometry(bf, trans_a, g.M, g.N, g.K, &tn, &S, &g.k_chunk);
     if (s.dual && S > 1) return CAPGNN_OK;           // a sum is formed by the waves of one workgroup
     if (S > 1) {
@@ -1980,9 +1996,8 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
         if (done) return CAPGNN_OK;
     }
     const int64_t K1p = split_ld(K1 > 0 ? K1 : 0), K = K1p + K2;
-    const bool one_launch = sane && dtype == CAPGNN_F32 && f32_product != CAPGNN_F32_PRODUCT_NATIVE && lda < (1 << 22) &&
-                            lda2 < (1 << 22) && (f32_product == CAPGNN_F32_PRODUCT_SPLIT || M * N >= SPLIT_MIN_MACS / (K1 + K2)) &&
-                            ws && ws_bytes >= split_b_bytes(N, K);
+    const bool one_launch = sane && dtype == CAPGNN_F32 && lda < (1 << 22) && lda2 < (1 << 22) &&
+                            split_sum(f32_product, trans_b, M, N, K1, K2) && ws && ws_bytes >= split_b_bytes(N, K);
     if (!one_launch) {
         CG_TRY(launch_gemm(0, trans_b, M, N, K2, A2, lda2, W2, ldw2, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
                            stream, nullptr, f32_product));

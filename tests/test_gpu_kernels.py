@@ -606,6 +606,85 @@ def test_gemm_f32_split_product(env, ta, tb):
         B.gemm(0, 0, 1, 1, 1, one, 1, one, 1, one, 1, B.F32, f32_product=7)
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+def test_gemm_f32_auto_form_is_the_documented_one(env, tb):
+    """AUTO is the fp32 instruction below 2^28 multiply-adds and without a workspace, the three-piece form from there on: bit for bit
+    what the caller gets who asks for that form.  On the fp32 instruction an infinite operand gives an infinity, and one above the
+    largest bf16 number stays finite."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5 + tb)
+
+    def run(form, M, N, K, A, W, with_ws):
+        wsb = B.gemm_workspace_bytes(0, M, N, K) if with_ws else 0
+        ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+        Cd = torch.zeros(M, N, device="cuda")
+        B.gemm(0, tb, M, N, K, A, K, W, K if tb else N, Cd, N, B.F32, ws=ws if with_ws else None, ws_bytes=wsb, f32_product=form)
+        torch.cuda.synchronize()
+        return Cd
+
+    for M, N, K in [(21557, 64, 8), (4096, 256, 200), (8000, 128, 250), (200, 60, 602), (32767, 64, 128), (32768, 64, 128), (10875, 41, 602),
+                    (10876, 41, 602), (49200, 64, 100), (30000, 300, 40)]:
+        say(f"gemm f32 auto form tb={tb} {M}x{N}x{K}")
+        below = M * N * K < 2 ** 28
+        A = torch.randn(M, K, generator=gen, device="cuda")
+        W = torch.rand((N, K) if tb else (K, N), generator=gen, device="cuda") + 0.25
+        if below:
+            A[0, 0], A[1, 0], A[1, 1:] = float("inf"), 3.4e38, 0.0
+            W[0, 0] = 0.5                           # the weight of k = 0 in column 0, either way it is stored
+        auto = run(B.F32_PRODUCT_AUTO, M, N, K, A, W, True)
+        same = run(B.F32_PRODUCT_NATIVE if below else B.F32_PRODUCT_SPLIT, M, N, K, A, W, True)
+        assert torch.equal(auto, same)
+        if below:
+            assert torch.isinf(auto[0]).all() and float(auto[1, 0]) == float(np.float32(3.4e38) * np.float32(0.5))
+        nat = run(B.F32_PRODUCT_NATIVE, M, N, K, A, W, True)
+        for form in (B.F32_PRODUCT_AUTO, B.F32_PRODUCT_SPLIT):
+            assert torch.equal(run(form, M, N, K, A, W, False), nat), "without a workspace the fp32 instruction runs"
+
+
+@pytest.mark.parametrize("kind", ["gcn", "sage"])
+@pytest.mark.parametrize("n,f_in,f_out,split_fwd", [(3000, 200, 64, False), (20000, 100, 100, True), (12000, 128, 128, True)])
+def test_layer_f32_auto_form_is_the_documented_one(env, kind, n, f_in, f_out, split_fwd):
+    """A layer's products under AUTO, each below 2^28 multiply-adds: bit for bit those of NATIVE, forward and backward, both orders.
+    The two forward products of a GraphSAGE layer in the AGG_FIRST order count as one: above 2^28 together (split_fwd) that launch
+    is SPLIT's, and so is nothing else."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(n)
+    n_halo = n // 5
+    assert n * 6 // 5 * f_in * f_out < 2 ** 28 and (2 * n * f_in * f_out >= 2 ** 28) == split_fwd
+    g = B.Graph(n, n_halo, np.arange(0, 3 * n + 1, 3, dtype=np.int64), rng.integers(0, n + n_halo, 3 * n).astype(np.int32),
+                rng.uniform(0.2, 0.5, n).astype(np.float32), rng.uniform(0.5, 1.5, n + n_halo).astype(np.float32))
+    sage = kind == "sage"
+    x = torch.randn(n + n_halo, f_in, device="cuda")
+    w, w_self = (torch.randn(f_in, f_out, device="cuda") / 8 for _ in range(2))
+    dh0 = torch.randn(n, f_out, device="cuda")
+    bias = torch.randn(f_out, device="cuda")
+
+    def run(order, form):
+        l = B.make_layer(B.SAGE_MEAN if sage else B.GCN, f_in, f_out, B.ACT_NONE, B.F32, w, w_self if sage else None, bias, order, f32_product=form)
+        size = B.layer_workspace_bytes(g, l)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        saved = torch.empty(max(B.layer_saved_bytes(g, l), 256), dtype=torch.uint8, device="cuda")
+        out = dict(h=torch.zeros(n, f_out, device="cuda"))
+        B.layer_fwd(g, l, x, f_in, out["h"], f_out, saved, ws, size)
+        for halo in (0, 1):
+            dh = dh0.clone()
+            dw, ds, db = torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_out, device="cuda")
+            dx = torch.zeros(n + n_halo if halo else n, f_in, device="cuda")
+            B.layer_bwd(g, l, x, f_in, out["h"], f_out, saved, dh, f_out, dw, ds if sage else None, db, dx, f_in, halo, ws, size)
+            out.update({f"dw{halo}": dw, f"ds{halo}": ds, f"db{halo}": db, f"dx{halo}": dx})
+        torch.cuda.synchronize()
+        return out
+
+    for order in (B.AGG_FIRST, B.XFORM_FIRST):
+        say(f"layer auto form {kind} n={n} {f_in}-{f_out} order={order}")
+        auto, nat, spl = (run(order, f) for f in (B.F32_PRODUCT_AUTO, B.F32_PRODUCT_NATIVE, B.F32_PRODUCT_SPLIT))
+        for k in auto:
+            as_split = k == "h" and sage and order == B.AGG_FIRST and split_fwd
+            assert torch.equal(auto[k], (spl if as_split else nat)[k]), (order, k)
+    g.close()
+
+
 def test_mfma_peak_loop_runs_and_counts_its_work(env):
     """The register-resident matrix-instruction loop: the reported work is 4 tiles x 4 waves x iterations x workgroups x
     the instruction's 2 * 32 * 32 * k FLOPs, and every thread writes a finite, positive checksum (its operands are
