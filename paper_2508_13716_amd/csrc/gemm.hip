@@ -350,10 +350,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     // column sums of B (see gemm_small_kernel): a thread's vectors of a step cover the same four columns
     constexpr bool SUMS = !A_KC && !B_KC;
     const bool sums = SUMS && g.colpart && by == 0;
-    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
+    double bsum[4] = {0.0, 0.0, 0.0, 0.0};
     auto add_b = [&]() __attribute__((always_inline)) {
+        float t[4] = {lb.r[0].x, lb.r[0].y, lb.r[0].z, lb.r[0].w};
 #pragma unroll
-        for (int q = 0; q < TileLoader<BF16, B_KC, BN>::NLD; ++q) { bsum[0] += lb.r[q].x; bsum[1] += lb.r[q].y; bsum[2] += lb.r[q].z; bsum[3] += lb.r[q].w; }
+        for (int q = 1; q < TileLoader<BF16, B_KC, BN>::NLD; ++q) { t[0] += lb.r[q].x; t[1] += lb.r[q].y; t[2] += lb.r[q].z; t[3] += lb.r[q].w; }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bsum[e] += static_cast<double>(t[e]);
     };
     if (sums && nk > 0) add_b();
     __syncthreads();
@@ -404,15 +407,16 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 
     if constexpr (SUMS) {
         if (sums) {     // the operand tiles are free: [256 / (BN / 4)][BN] partial sums
-            float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+            double (*bred)[BN] = reinterpret_cast<double (*)[BN]>(smem);
             constexpr int QPR = BN / 4, ROWS = 256 / QPR;
+            static_assert(ROWS * BN * sizeof(double) <= sizeof(smem), "the partial sums must fit the operand tiles");
 #pragma unroll
             for (int e = 0; e < 4; ++e) bred[tid / QPR][4 * (tid % QPR) + e] = bsum[e];
             __syncthreads();
             if (tid < BN && n0 + tid < g.N) {
-                float t = 0.f;
+                double t = 0.0;
                 for (int y = 0; y < ROWS; ++y) t += bred[y][tid];
-                g.colpart[bz * g.N + n0 + tid] = t;
+                g.colpart[bz * g.N + n0 + tid] = static_cast<float>(t);
             }
             __syncthreads();
         }
@@ -553,8 +557,9 @@ __device__ __forceinline__ uint4 keep_positive(uint4 v, uint4 m) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// (second launch bound: X^T G on full tiles keeps three workgroups per compute unit beside its column sums)
 template <bool A_KC, bool B_KC, int BM, int BN>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm_bf16_kernel(GemmArgs g) {
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int LDSROW = HBK + HPAD;
@@ -606,18 +611,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
     // column sums of B (see gemm_small_kernel): a staging thread's four rows of a step cover the same eight columns
     constexpr bool SUMS = !A_KC && !B_KC;
     const bool sums = SUMS && g.colpart && by == 0;
-    float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    double bsum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     auto add_b = [&]() __attribute__((always_inline)) {
         if constexpr (SUMS) {
+            float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint32_t w[4] = {lb.r[q].x, lb.r[q].y, lb.r[q].z, lb.r[q].w};
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    bsum[2 * d] += __uint_as_float(w[d] << 16);
-                    bsum[2 * d + 1] += __uint_as_float(w[d] & 0xffff0000u);
+                    t[2 * d] += __uint_as_float(w[d] << 16);
+                    t[2 * d + 1] += __uint_as_float(w[d] & 0xffff0000u);
                 }
             }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bsum[e] += static_cast<double>(t[e]);
         }
     };
     if (sums && nk > 0) add_b();
@@ -667,7 +675,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
     }
     if constexpr (SUMS) {
         if (sums) {     // threads 128 .. 128 + NTH of the workgroup stage B: [HBK / 4][BN] partial sums
-            float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+            double (*bred)[BN] = reinterpret_cast<double (*)[BN]>(smem);
+            static_assert(HBK / 4 * BN * sizeof(double) <= sizeof(smem), "the partial sums must fit the operand tiles");
             constexpr int CPR = BN / 8;
             const int tt = tid - 128;
             if (tt >= 0 && tt < (HBK / 4) * CPR)
@@ -675,9 +684,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
                 for (int e = 0; e < 8; ++e) bred[tt / CPR][8 * (tt % CPR) + e] = bsum[e];
             __syncthreads();
             if (tid < BN && n0 + tid < g.N) {
-                float t = 0.f;
+                double t = 0.0;
                 for (int y = 0; y < HBK / 4; ++y) t += bred[y][tid];
-                g.colpart[bz * g.N + n0 + tid] = t;
+                g.colpart[bz * g.N + n0 + tid] = static_cast<float>(t);
             }
             __syncthreads();
         }
@@ -1128,9 +1137,12 @@ __global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kerne
     }
     // column sums of B (see gemm_small_kernel): waves 4-7 stage it, a thread's block of a step is four k of four columns
     const bool sums = g.colpart && by == 0;
-    f32x4 bsum = {0.f, 0.f, 0.f, 0.f};
+    double bsum[4] = {0.0, 0.0, 0.0, 0.0};
     auto add_b = [&]() __attribute__((always_inline)) {
-        if (!lc.idle) bsum += (lc.r[0] + lc.r[1]) + (lc.r[2] + lc.r[3]);
+        if (lc.idle) return;
+        const f32x4 t = (lc.r[0] + lc.r[1]) + (lc.r[2] + lc.r[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bsum[e] += static_cast<double>(t[e]);
     };
     if (sums && nk > 0) add_b();
     __syncthreads();
@@ -1173,15 +1185,16 @@ __global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kerne
     if (nk > 0) products();
     if (sums) {
         __syncthreads();            // the operand tiles are free: [8][BN] partial sums
-        float (*bred)[BN] = reinterpret_cast<float (*)[BN]>(smem);
+        double (*bred)[BN] = reinterpret_cast<double (*)[BN]>(smem);
+        static_assert(8 * BN * sizeof(double) <= A_BYTES + B_BYTES, "the partial sums must fit the operand tiles");
         if (tid >= 256 && !lc.idle)
 #pragma unroll
             for (int e = 0; e < 4; ++e) bred[lc.kb][4 * lc.tq + e] = bsum[e];
         __syncthreads();
         if (tid < BN && n0 + tid < g.N) {
-            float t = 0.f;
+            double t = 0.0;
             for (int y = 0; y < 8; ++y) t += bred[y][tid];
-            g.colpart[bz * g.N + n0 + tid] = t;
+            g.colpart[bz * g.N + n0 + tid] = static_cast<float>(t);
         }
     }
     store_tile<TM, 1>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
@@ -1311,11 +1324,12 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-    // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway
+    // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway.  However long a split is, a thread
+    // adds no more than the 16 .. 32 terms of a step in fp32; its running sum and those of the workgroup are doubles.
     const bool sums = !A_KC && !B_KC && g.colpart && by == 0 && !second;      // uniform over the workgroup
-    float bsum[TN];
+    double bsum[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) bsum[j] = 0.f;
+    for (int j = 0; j < TN; ++j) bsum[j] = 0.0;
     if (k < k_end) fetch(k);
     for (; k < k_end; k += UB * UK) {
         SmallUnit<BF16> ca[UB], cb[UB][TN];
@@ -1328,14 +1342,17 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
         if (k + UB * UK < k_end) fetch(k + UB * UK);
         if (sums) {
 #pragma unroll
-            for (int u = 0; u < UB; ++u)
+            for (int j = 0; j < TN; ++j) {
+                float t = 0.f;
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
+                for (int u = 0; u < UB; ++u)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        if constexpr (BF16) bsum[j] += __uint_as_float(cb[u][j].v[e] << 16) + __uint_as_float(cb[u][j].v[e] & 0xffff0000u);
-                        else bsum[j] += cb[u][j].v[e];
+                        if constexpr (BF16) t += __uint_as_float(cb[u][j].v[e] << 16) + __uint_as_float(cb[u][j].v[e] & 0xffff0000u);
+                        else t += cb[u][j].v[e];
                     }
+                bsum[j] += static_cast<double>(t);
+            }
         }
 #pragma unroll
         for (int u = 0; u < UB; ++u)
@@ -1354,18 +1371,18 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * half + (r & 3)][j * 32 + l32] = acc[j][r];
-    __shared__ float bred[4][TN * 32];
+    __shared__ double bred[4][TN * 32];
     if (sums) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const float t = bsum[j] + __shfl_xor(bsum[j], 32);
+            const double t = bsum[j] + __shfl_xor(bsum[j], 32);
             if (half == 0) bred[wave][j * 32 + l32] = t;
         }
     }
     __syncthreads();
     if (sums)
         for (int c = threadIdx.x; c < TN * 32; c += 256)
-            if (n0 + c < g.N) g.colpart[bz * g.N + n0 + c] = (bred[0][c] + bred[1][c]) + (bred[2][c] + bred[3][c]);
+            if (n0 + c < g.N) g.colpart[bz * g.N + n0 + c] = static_cast<float>((bred[0][c] + bred[1][c]) + (bred[2][c] + bred[3][c]));
     float *part = second ? s.part2 : g.part;
     char *C = second ? s.C2 : g.C;
     const int64_t ldc = second ? s.ldc2 : g.ldc;

@@ -572,3 +572,50 @@ def test_sgd_step_adds_every_gradient_of_a_shared_tensor(env, tie, recorded):
         assert least > 100 * bound, "a lost update would not be seen"
         assert np.abs(flat.double().cpu().numpy() - want_w).max() <= bound
         assert np.abs(bias.double().cpu().numpy() - want_b).max() <= bound
+
+
+@pytest.mark.parametrize("dtype,form,width,n", [("f32", 0, 4096, 150_001), ("f32", 1, 2048, 150_001), ("f32", 2, 2048, 150_001), ("f32", 0, 64, 520_007),
+                                                ("f32", 2, 64, 520_007), ("bf16", 0, 4096, 150_001), ("bf16", 0, 64, 520_007), ("bf16", 0, 320, 520_007)])
+def test_epoch_bias_gradient_of_many_equal_rows(env, dtype, form, width, n):
+    """The hidden layers' bias gradients are column sums that the weight gradients' products form on the way.  Every row of dZ is the
+    same here (self loops, equal rows and labels) and its elements are known: the last weight matrix holds one power of two per row, so
+    dZ of the layer below is an element of the loss gradient times that.  A running fp32 sum of n equal terms drifts by up to n 2^-25,
+    all in one direction: wide layers have few reduction splits and would add thousands of terms in a row.  Bound: the loss gradient's
+    element (exponential, sum, quotient and product, 8 roundings) plus 32 fp32 additions in a row (2^-20) plus two roundings of the
+    partial and the whole sum: 2^-19; with bf16 storage the element is rounded to bf16 before, which is repeated here."""
+    torch, B = env["torch"], env["B"]
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = B.BF16 if dtype == "bf16" else B.F32
+    C, dims = 4, [8, width, width, 4]
+    g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), None, None)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(width + n)
+    x = (torch.rand(1, 8, generator=gen, device="cuda") + 0.5).to(dt).repeat(n, 1)
+    at = torch.arange(width, device="cuda") % C
+    power = torch.exp2(-(torch.arange(width, device="cuda") % 3).float())
+    w = [(torch.rand(8, width, generator=gen, device="cuda") / 8).to(dt), (torch.rand(width, width, generator=gen, device="cuda") * (2.0 / width)).to(dt),
+         torch.zeros(width, C, device="cuda")]
+    w[2][torch.arange(width, device="cuda"), at] = power * 2.0 ** (2 - width.bit_length())
+    w[2] = w[2].to(dt)
+    layers = [B.make_layer(B.GCN, dims[l], dims[l + 1], B.ACT_RELU if l < 2 else B.ACT_NONE, code, w[l], None, None, B.AGG_FIRST, out_f32=int(dtype == "bf16" and l == 2),
+                           f32_product=form) for l in range(3)]
+    labels = torch.ones(n, device="cuda", dtype=torch.int32)
+    logits = torch.zeros(n, C, device="cuda")
+    dw = [torch.zeros(dims[l], dims[l + 1], device="cuda") for l in range(3)]
+    db = [torch.zeros(d, device="cuda") for d in dims[1:]]
+    size = B.epoch_workspace_bytes(g, None, layers)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    say(f"bias gradient of equal rows {dtype} form={form} {width} wide, {n} rows")
+    B.epoch(g, None, layers, x, 8, labels, None, 0.0, logits, dw, None, db, 0.0, ws, size)
+    torch.cuda.synchronize()
+    assert torch.equal(logits, logits[:1].expand(n, C))
+    z = logits[0].double()
+    dz = (torch.softmax(z, 0) - torch.tensor([0.0, 1.0, 0.0, 0.0], device="cuda", dtype=torch.float64)) / n
+    err = ((db[2].double() - n * dz).abs() / (n * dz).abs()).max().item()
+    if dtype == "bf16":
+        dz = dz.to(torch.bfloat16).double()
+    ref = n * dz[at] * w[2][torch.arange(width, device="cuda"), at].double()
+    got = db[1].double()
+    rel = ((got - ref).abs() / ref.abs()).max().item()
+    say(f"   largest relative error: last bias {err:.2e}, hidden bias {rel:.2e}")
+    assert err <= 2.0 ** -19 and rel <= 2.0 ** -19
