@@ -52,6 +52,7 @@ struct alignas(16) RowItem {
 struct ItemList {
     int64_t n_items = 0, n_pieces = 0, n_cut = 0;
     int64_t max_pieces = 0;                // of one row
+    int64_t longest = 0;                   // entries of the longest cut row
     const RowItem *items = nullptr;        // device [n_items]: n_pieces pieces, then whole rows
     const RowItem *cut = nullptr;          // device [n_cut]: the cut rows, whole
     const int32_t *piece_first = nullptr;  // device [n_cut + 1]
@@ -85,7 +86,6 @@ struct SpOp {
     // inside a class
     const int32_t *order = nullptr;   // device [n_out]
     int64_t n_sub = 0;                // rows [0, n_sub) of the output: the restricted list (bwd: local columns only)
-    int64_t max_deg = 0;
     ItemList list, list_sub;          // of all output rows, and of the restricted ones
     // Column-blocked copy of the entries (built for dense-degree operators whose gathered operand does not
     // fit an L2): entries regrouped by (source block cb = idx / CB_ROWS, position p in `order`), original

@@ -81,9 +81,10 @@ static int upload_weights(capgnn_graph *g, int64_t nnz, const int32_t *idx, cons
     return upload(g, w.data(), w.size(), dev);
 }
 
-// Entries per piece of a cut row.  A lane group takes about a microsecond for 8 to 16 entries, so the longest item bounds
-// a small launch: about 4096 items' worth of entries each, between 64 (42 k entries: a row of 1000 entries in one piece
-// alone took 15 us) and 512 (above 2 M entries; the partial rows then cost under half a per cent of the gathered bytes).
+// Entries per piece of a cut row, which also says from where on rows count as long (two pieces).  A lane group takes about a
+// microsecond for 8 to 16 entries, so the longest item bounds a small launch: about 4096 items' worth of entries each, between
+// 64 (up to 2^18 entries; 42 k entries: a row of 1000 entries in one piece alone took 15 us) and 512 (above 2^20 entries; the
+// partial rows then cost under half a per cent of the gathered bytes).
 static int64_t piece_entries(int64_t nnz) {
     int64_t p = 64;
     while (p < 512 && p * 4096 < nnz) p *= 2;
@@ -105,6 +106,7 @@ static int upload_items(capgnn_graph *g, const int64_t *ptr, int64_t nnz, const 
         for (int64_t q = 0; q < len; q += piece)
             items.push_back({order[k], static_cast<uint32_t>(beg + q), static_cast<uint32_t>(std::min(piece, len - q)), 0u});
         out->max_pieces = std::max(out->max_pieces, static_cast<int64_t>(items.size()) - first.back());
+        out->longest = std::max(out->longest, len);
         first.push_back(static_cast<int32_t>(items.size()));
     }
     out->n_cut = k;
@@ -307,7 +309,6 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     if ((rc = upload(g, order_f.data(), order_f.size(), &f.order))) return fail(rc);
     if ((rc = upload_items(g, rowptr, nnz, order_f, &f.list))) return fail(rc);
     f.list_sub = f.list;
-    for (int64_t i = 0; i < n_loc; ++i) f.max_deg = std::max(f.max_deg, rowptr[i + 1] - rowptr[i]);
     BlockedHost bh_f;
     if (build_blocked(rowptr, col, edge_val, col_scale, order_f, n_loc, n_cols, &bh_f) && (rc = upload_blocked(g, bh_f, &f)))
         return fail(rc);
@@ -316,7 +317,7 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
     b.n_out = n_cols; b.n_in = n_loc; b.nnz = nnz; b.out_scale = f.in_scale; b.in_scale = f.out_scale;
     b.weights_by_source = !edge_val && row_scale;
     if (share) {
-        b.ptr = f.ptr; b.idx = f.idx; b.order = f.order; b.n_sub = n_loc; b.max_deg = f.max_deg;
+        b.ptr = f.ptr; b.idx = f.idx; b.order = f.order; b.n_sub = n_loc;
         b.list = f.list; b.list_sub = f.list;
         b.ncb = f.ncb; b.b_off = f.b_off; b.b_ew = f.b_ew; b.b_src = f.b_src; b.b_long = f.b_long; b.b_mid = f.b_mid;
         const bool same_scales = (!row_scale && !col_scale) ||
@@ -342,7 +343,6 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
         if ((rc = upload(g, order_b.data(), order_b.size(), &b.order))) return fail(rc);
         if ((rc = upload_items(g, colptr.data(), nnz, order_b, &b.list))) return fail(rc);
         if ((rc = upload_items(g, colptr.data(), nnz, order_bs, &b.list_sub))) return fail(rc);
-        for (int64_t j = 0; j < n_cols; ++j) b.max_deg = std::max(b.max_deg, colptr[j + 1] - colptr[j]);
         BlockedHost bh;
         if (build_blocked(colptr.data(), rowidx.data(), edge_val ? cscval.data() : nullptr, row_scale, order_b, n_cols,
                           n_loc, &bh) && (rc = upload_blocked(g, bh, &b)))

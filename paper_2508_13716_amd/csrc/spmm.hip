@@ -907,8 +907,17 @@ constexpr int CROWDED_ROW = 32, CROWDED_BYTES = 192, CROWDED_LDS = 13312;
 
 // Graphs of at most ROWS_NNZ entries with rows to cut run as one launch of spmm_rows_kernel: the second launch costs more than
 // what the finer cut saves (the three aggregations of a 10 k-vertex GraphSAGE epoch 37 -> 31 us, of a 22 k-vertex GIN epoch
-// 65 -> 61, besides three launch gaps of 1-2 us).
+// 65 -> 61, besides three launch gaps of 1-2 us).  That holds while the longest row, which one workgroup walks, ends with the
+// launch.  A compute unit that has other rows as well gathers 50 GB/s for it (four waves, rows of several vectors per lane: 30);
+// the rest of the launch takes its bytes at about 8.5 TB/s (short rows, cached) and the pieces' two launches about 5 us more.
+// us as one launch and as pieces, 200 k entries x 41 floats: longest row of 1024 entries 8.2 / 9.5, 2048 9.1 / 8.7, 4096 14.6 /
+// 9.1, 65536 182 / 13; x 256 floats: 1024 28 / 33, 2048 37 / 32, 16384 180 / 33; 900 k entries x 256: 4096 130 / 139, 8192 164 /
+// 140, 200 k 2076 / 144.
 constexpr int64_t ROWS_NNZ = int64_t(1) << 20;
+static bool rows_in_one_launch(int64_t nnz, int64_t longest, int64_t row_bytes, int row_waves) {
+    const double row_us = static_cast<double>(longest) * row_bytes / (row_waves >= 16 ? 5e4 : 3e4);
+    return nnz <= ROWS_NNZ && row_us <= 5.0 + static_cast<double>(nnz) * row_bytes / 8.5e6;
+}
 
 // pieces: the caller brought scratch for the pieces of the cut rows
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
@@ -918,7 +927,7 @@ static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz
     const int64_t row_bytes = static_cast<int64_t>(a.F_lim) * (BF16 ? 2 : 4);
     a.n_wave = G == 1 ? list.n_items : list.first_below(group_row_entries(nnz, row_bytes));
     const bool long_rows = nnz >= CROWDED_ROW * list.n_items && row_bytes >= CROWDED_BYTES;
-    const bool one_launch = list.n_cut > 0 && nnz <= ROWS_NNZ;
+    const bool one_launch = list.n_cut > 0 && (pieces ? rows_in_one_launch(nnz, list.longest, row_bytes, NW) : nnz <= ROWS_NNZ);
     pieces = pieces && !one_launch;
     if (!pieces) { a.items += list.n_pieces; a.n_items -= list.n_pieces; a.n_wave -= list.n_pieces; a.n_pieces = 0; }
     const int64_t waves = a.n_wave + (a.n_items - a.n_wave + G - 1) / G;

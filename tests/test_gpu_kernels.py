@@ -220,6 +220,43 @@ def test_spmm_row_length_classes_exact(env, fill, scratch):
             g.close()
 
 
+@pytest.mark.parametrize("scratch", [True, False])
+@pytest.mark.parametrize("hub,others", [(500_000, 350_000), (60_000, 90_000), (2_100, 6_000)])
+def test_spmm_hub_of_a_small_graph_exact(env, hub, others, scratch):
+    """Graphs below 2^20 entries whose longest row, and in the transposed product whose longest column, holds a large part of them: with
+    scratch it is cut over many workgroups (pieces of 64, 128 and 256 entries) unless it ends with the launch anyway (the narrow rows
+    here), without it one workgroup walks it.  Small integers, sums below 2^24: equality, and a bf16 result is the sum rounded once."""
+    torch, B, H, O, orc = env["torch"], env["B"], env["H"], env["O"], env["orc"]
+    rng = np.random.default_rng(hub)
+    n_loc, n_halo = others // 6, 300
+    n_cols = n_loc + n_halo
+    rowptr = np.concatenate([[0, 2, 2 + hub], 2 + hub + 3 * np.arange(1, n_loc - 1)]).astype(np.int64)
+    col = rng.integers(0, n_cols, rowptr[-1]).astype(np.int32)
+    col[2 + hub::3] = n_loc + 7                   # the first entry of every short row
+    val = rng.integers(-1, 2, rowptr[-1]).astype(np.float32)
+    assert rowptr[-1] < 2 ** 20
+    for F, ld, vals in [(5, 8, True), (41, 44, False), (64, 64, True), (260, 264, False)] + ([(700, 704, False), (41, 41, True)] if hub < 10_000 else []):
+        for dt in (B.F32, B.BF16):
+            say(f"spmm hub of {hub} entries, {rowptr[-1]} in all, F={F} ld={ld} dtype={dt} scratch={scratch}")
+            X = rng.integers(-2, 3, (n_cols, F)).astype(np.float32)
+            g = B.Graph(n_loc, n_halo, rowptr, col, None, None, val if vals else None)
+            og = orc.Graph(n_loc, n_cols, rowptr, col, np.ones(n_loc), np.ones(n_cols), val.astype(np.float64) if vals else None)
+            Xd = H.padded_matrix(X if dt == B.F32 else synth.f32_to_bf16_rne(X).reshape(X.shape), ld)
+            wsb = B.spmm_workspace_bytes(g, F, dt) if scratch else 0
+            ws = torch.empty(wsb, dtype=torch.uint8, device="cuda") if wsb else None
+            assert wsb > 0 or not scratch
+            for back in (False, True):
+                ref = orc.spmm_bwd(og, X[:n_loc].astype(np.float64)) if back else orc.spmm_fwd(og, X.astype(np.float64))
+                Yd = torch.full((n_cols if back else n_loc, ld), 7.0, dtype=Xd.dtype, device="cuda")
+                (B.spmm_bwd if back else B.spmm_fwd)(g, Xd, ld, Yd, ld, F, dt, ws=ws, ws_bytes=wsb)
+                torch.cuda.synchronize()
+                Y = O.widen(H.dev_to_np(Yd))
+                want = ref if dt == B.F32 else synth.bf16_to_f32(synth.f32_to_bf16_rne(ref.astype(np.float32))).reshape(ref.shape)
+                assert np.array_equal(Y[:, :F], want), (F, dt, back)
+                assert (Y[:, F:] == 7.0).all(), "padding columns were written"
+            g.close()
+
+
 def test_spmm_on_config1_graph(env):
     cfg = synth.CONFIGS["C1"]
     part = synth.partition_for(cfg)
