@@ -1623,13 +1623,13 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, con
     else reinterpret_cast<float *>(g.C)[row * g.ldc + col] = v;
 }
 
-static int choose_split(int trans_a, int64_t M, int64_t N, int64_t K, int bm, int bn, int bk) {
+static int choose_split(int trans_a, int64_t M, int64_t N, int64_t K, int bm, int bn, int bk, bool coarse = false) {
     if (!trans_a) return 1;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     int64_t s = 1536 / (tiles > 0 ? tiles : 1);
-    // at least 16 k-steps per split, down to 4 where that leaves compute units without a workgroup
+    // at least 16 k-steps per split, down to 4 where that leaves compute units without a workgroup (coarse: never)
     int64_t max_by_k = K / (bk * 16);
-    if (max_by_k * tiles < 256) max_by_k = std::min<int64_t>((256 + tiles - 1) / tiles, K / (bk * 4));
+    if (!coarse && max_by_k * tiles < 256) max_by_k = std::min<int64_t>((256 + tiles - 1) / tiles, K / (bk * 4));
     if (s > max_by_k) s = max_by_k;
     if (s > 1024) s = 1024;
     if (s < 1) s = 1;
@@ -1798,13 +1798,18 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                             (trans_a || (ws && ws_bytes >= split_b_bytes(N, K)));
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
     const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
-    const bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
+    bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
     int S = choose_split(trans_a, M, N, K, bm, bn, bk), tn = 0;
     int64_t small_chunk = 0;
+    if (small_path) small_geometry(dtype == CAPGNN_BF16, trans_a, M, N, K, &tn, &S, &small_chunk);
+    if (S > 1 && (!ws || ws_bytes < static_cast<size_t>(S) * M * N * sizeof(float))) {
+        // too little room for that many splits: a reduction of few steps needs none at all on the tiled kernels
+        small_path = false;
+        S = choose_split(trans_a, M, N, K, bm, bn, bk, true);
+    }
     if (small_path) {
-        small_geometry(dtype == CAPGNN_BF16, trans_a, M, N, K, &tn, &S, &small_chunk);
         bm = 32;
         bn = 32 * tn;
     }

@@ -585,6 +585,39 @@ def test_gemm_size_classes_exact(env, dtype, ta, tb):
                 assert (got[:, N:] == 2.0).all(), "padding columns were written"
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tb", [0, 1])
+def test_gemm_vertex_reduction_with_little_workspace(env, dtype, tb):
+    """X^T G splits its reduction as far as the workspace goes: at most 31 steps of 16 need none, longer ones as many splits as have 16
+    steps each; with no room at all those are CAPGNN_ENOMEM, C untouched.  Small integers: exact with any number of splits."""
+    torch, B, H = env["torch"], env["B"], env["H"]
+    rng = np.random.default_rng(tb)
+    for M, N, K, form in [(64, 64, 256, 0), (33, 70, 300, 0), (100, 256, 511, 0), (8, 5, 511, 2), (64, 64, 20000, 0), (130, 121, 6000, 1), (64, 200, 2999, 2)]:
+        A, Bm = rng.integers(-3, 4, (K, M)).astype(np.float32), rng.integers(-3, 4, (N, K) if tb else (K, N)).astype(np.float32)
+        ref = A.T.astype(np.float64) @ (Bm.T if tb else Bm).astype(np.float64)
+        bf = dtype == "bf16"
+        st = (lambda x: synth.f32_to_bf16_rne(x).reshape(x.shape)) if bf else (lambda x: x)
+        lda, ldb = synth.pad_to(M, 8) + 1, synth.pad_to(Bm.shape[1], 8) + 1         # unaligned bf16 rows: steps of 16
+        Ad, Bd = H.padded_matrix(st(A), lda), H.padded_matrix(st(Bm), ldb)
+        step = 32 if not bf and not tb and form == 2 else 16
+        splits = min(1536 // (-(-M // 128) * -(-N // (64 if N <= 64 else 128))), K // (16 * step))
+        need = splits * M * N * 4 if splits > 1 else 0
+        for room in ([need, 0] if need else [0]):
+            say(f"gemm X^T G {dtype} tb={tb} {M}x{N}x{K} form={form}: {room} bytes of workspace")
+            ws = torch.empty(room, dtype=torch.uint8, device="cuda") if room else None
+            Cd = torch.full((M, N), 2.0, device="cuda")
+            call = lambda: B.gemm(1, tb, M, N, K, Ad, lda, Bd, ldb, Cd, N, B.BF16 if bf else B.F32, out_f32=1, ws=ws, ws_bytes=room, f32_product=form)  # noqa: E731
+            if room < need:
+                with pytest.raises(B.CapgnnError) as e:
+                    call()
+                assert e.value.code == B.ENOMEM
+            else:
+                call()
+            torch.cuda.synchronize()
+            got = Cd.cpu().numpy()
+            assert (got == 2.0).all() if room < need else np.array_equal(got.astype(np.float64), ref), (M, N, K, room)
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
