@@ -1916,7 +1916,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     GemmArgs &g = s.g;
     const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
     const int64_t Ksum = g.K + (s.dual ? s.K2 : 0);       // (the waves of a workgroup share it)
-    const bool small = f32_product != CAPGNN_F32_PRODUCT_SPLIT && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
+    const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     // the three-piece form on the terms of launch_gemm and launch_gemm_dual
     const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&

@@ -755,6 +755,56 @@ def test_layer_f32_auto_form_is_the_documented_one(env, kind, n, f_in, f_out, sp
     g.close()
 
 
+def sage_layer(env, dtype, form, n=2500, f_in=100, f_out=72, order=None, dw_is_self=False):
+    """One GraphSAGE layer without halo, forward and backward, on inputs made from a fixed seed: every output."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(3)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    dt, code = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    mk = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(dt)  # noqa: E731
+    g = B.Graph(n, 0, np.arange(0, 5 * n + 1, 5, dtype=np.int64), rng.integers(0, n, 5 * n).astype(np.int32), np.full(n, 0.2, np.float32), None)
+    pad = lambda x: torch.nn.functional.pad(x, (0, -x.shape[1] % 8)).contiguous()  # noqa: E731
+    x, dh, w, w_self = pad(mk(n, f_in)), pad(mk(n, f_out)), mk(f_in, f_out), mk(f_in, f_out)
+    l = B.make_layer(B.SAGE_MEAN, f_in, f_out, B.ACT_RELU, code, w, w_self, None, order or B.AGG_FIRST, f32_product=form)
+    size = B.layer_workspace_bytes(g, l)
+    ws, saved = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty(B.layer_saved_bytes(g, l) + 256, dtype=torch.uint8, device="cuda")
+    h, dx = torch.zeros_like(dh), torch.zeros_like(x)
+    dw, ds, db = torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_out, device="cuda")
+    B.layer_fwd(g, l, x, x.shape[1], h, h.shape[1], saved, ws, size)
+    h0 = h.clone()
+    B.layer_bwd(g, l, x, x.shape[1], h, h.shape[1], saved, dh, dh.shape[1], ds if dw_is_self else dw, ds, db, dx, x.shape[1], 0, ws, size)
+    torch.cuda.synchronize()
+    g.close()
+    return dict(h=h0, dw=dw, dw_self=ds, db=db, dx=dx)
+
+
+@pytest.mark.parametrize("order", [1, 2])
+def test_bf16_products_do_not_depend_on_the_fp32_form(env, order):
+    """f32_product says how products of fp32 operands are formed: bf16 results are the same bits for every value, of a single product
+    in each orientation (below and above the sizes that the small kernel takes) and of a layer's products in pairs."""
+    torch, B = env["torch"], env["B"]
+    forms = (B.F32_PRODUCT_AUTO, B.F32_PRODUCT_NATIVE, B.F32_PRODUCT_SPLIT)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(order)
+    for ta, tb, M, N, K in [(1, 0, 100, 64, 4000), (1, 1, 72, 130, 2000), (0, 0, 3000, 64, 100), (0, 1, 500, 300, 72), (1, 0, 512, 256, 16000)]:
+        A = torch.randn(*((K, M) if ta else (M, K)), generator=gen, device="cuda").bfloat16()
+        W = torch.randn(*((N, K) if tb else (K, N)), generator=gen, device="cuda").bfloat16()
+        wsb = B.gemm_workspace_bytes(ta, M, N, K)
+        ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+        out = []
+        for form in forms:
+            say(f"bf16 product ta={ta} tb={tb} {M}x{N}x{K} form={form}")
+            out.append(torch.zeros(M, N, device="cuda"))
+            B.gemm(ta, tb, M, N, K, A, A.shape[1], W, W.shape[1], out[-1], N, B.BF16, out_f32=1, ws=ws, ws_bytes=wsb, f32_product=form)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+    say(f"bf16 layer order={order}")
+    a, b, c = (sage_layer(env, "bf16", f, order=order) for f in forms)
+    for k in a:
+        assert torch.equal(a[k], b[k]) and torch.equal(a[k], c[k]), k
+
+
 def test_mfma_peak_loop_runs_and_counts_its_work(env):
     """The register-resident matrix-instruction loop: the reported work is 4 tiles x 4 waves x iterations x workgroups x
     the instruction's 2 * 32 * 32 * k FLOPs, and every thread writes a finite, positive checksum (its operands are
