@@ -1968,6 +1968,8 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
                      int f32_product, float *colsum) {
     if (M2 > M) CG_FAIL(CAPGNN_EINVAL, "gemm_pair: the second product has more rows");
+    if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
+        CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
     SmallGemmArgs s{};
     s.g.M = M; s.g.N = N; s.g.K = K;
     s.g.A = static_cast<const char *>(A); s.g.lda = lda; s.g.B = static_cast<const char *>(B); s.g.ldb = ldb;

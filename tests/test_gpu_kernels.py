@@ -805,6 +805,29 @@ def test_bf16_products_do_not_depend_on_the_fp32_form(env, order):
         assert torch.equal(a[k], b[k]) and torch.equal(a[k], c[k]), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("order", [1, 2])
+def test_layer_refuses_an_unknown_fp32_form(env, dtype, order):
+    """Forward and backward of a GraphSAGE layer, whose products run in pairs: any other value of f32_product is CAPGNN_EINVAL."""
+    torch, B = env["torch"], env["B"]
+    n, f = 300, 40
+    g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.ones(n, np.float32), None)
+    dt, code = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    x, w, dw = (torch.zeros(n, f, device="cuda", dtype=t) for t in (dt, dt, torch.float32))
+    for form in (-1, 3, 7):
+        l = B.make_layer(B.SAGE_MEAN, f, f, B.ACT_NONE, code, w, w, None, order, f32_product=form)
+        size = B.layer_workspace_bytes(g, l)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        for call in (lambda: B.layer_fwd(g, l, x, f, x.clone(), f, ws.clone(), ws, size),
+                     lambda: B.layer_bwd(g, l, x, f, x.clone(), f, ws.clone(), x.clone(), f, dw, dw.clone(), None, x.clone(), f, 0, ws, size)):
+            say(f"unknown form {form} {dtype} order={order}")
+            with pytest.raises(B.CapgnnError) as e:
+                call()
+            torch.cuda.synchronize()
+            assert e.value.code == B.EINVAL
+    g.close()
+
+
 def test_mfma_peak_loop_runs_and_counts_its_work(env):
     """The register-resident matrix-instruction loop: the reported work is 4 tiles x 4 waves x iterations x workgroups x
     the instruction's 2 * 32 * 32 * k FLOPs, and every thread writes a finite, positive checksum (its operands are
