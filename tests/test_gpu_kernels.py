@@ -828,6 +828,22 @@ def test_layer_refuses_an_unknown_fp32_form(env, dtype, order):
     g.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [300, 6000])
+def test_layer_bwd_with_one_buffer_for_both_weight_gradients(env, dtype, n):
+    """dW == dW_self: the self gradient is written last, as by two calls one after the other (with one and with several reduction
+    splits); everything else as with two buffers."""
+    torch, B = env["torch"], env["B"]
+    for order in (B.AGG_FIRST, B.XFORM_FIRST):
+        say(f"one weight gradient buffer {dtype} n={n} order={order}")
+        two, one = (sage_layer(env, dtype, 0, n=n, order=order, dw_is_self=s) for s in (False, True))
+        rel = (one["dw_self"].double() - two["dw_self"].double()).norm() / two["dw_self"].double().norm()
+        other = (two["dw"].double() - two["dw_self"].double()).norm() / two["dw_self"].double().norm()
+        assert rel <= 1e-5 < other       # fp32 sums of n products, possibly split another way
+        for k in ("h", "db", "dx"):
+            assert torch.equal(one[k], two[k]), k
+
+
 def test_mfma_peak_loop_runs_and_counts_its_work(env):
     """The register-resident matrix-instruction loop: the reported work is 4 tiles x 4 waves x iterations x workgroups x
     the instruction's 2 * 32 * 32 * k FLOPs, and every thread writes a finite, positive checksum (its operands are
