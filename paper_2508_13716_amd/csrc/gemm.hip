@@ -30,7 +30,7 @@ struct GemmArgs {
     const float *bias;
     const char *mask; int64_t ldm; int mask_bf16;
     int gx, gy, S;                  // tiles along N, along M, reduction splits
-    int c_staged;                   // bf16 kernel: write C through LDS in 16-byte pieces (no mask / accumulate / split)
+    int c_staged;                   // bf16 kernel: write C through LDS in 16-byte pieces (no accumulate / split / row scale)
     const float *rscale;            // C[i,:] *= rscale[i] after everything else (fp32 C), or null
     // two products into one result, C = A W + A2 W2 (gemm_split_kernel<..., DUAL>): the reduction index runs over A's K1
     // columns, padded to K1p (whole steps), and then over A2's K - K1p columns; the cut weights lie one after the other
@@ -1747,21 +1747,28 @@ static void launch_tiles(const GemmArgs &g, int bn, dim3 grid, hipStream_t st) {
     else hipLaunchKernelGGL((gemm_kernel<BF16, A_KC, B_KC, 128, 128>), grid, dim3(256), 0, st, g);
 }
 
+// bm64: tiles of 64 rows (plain products only)
 template <bool A_KC, bool B_KC>
 static void launch_bf16_tiles(const GemmArgs &g, int bn, bool bm64, dim3 grid, hipStream_t st) {
-    if (bn == 64 && bm64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 64, 64>), grid, dim3(256), 0, st, g);
-    else if (bn == 64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
+    if constexpr (A_KC) {
+        if (bm64) {
+            hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 64, 64>), grid, dim3(256), 0, st, g);
+            return;
+        }
+    }
+    if (bn == 64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
     else hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 128>), grid, dim3(256), 0, st, g);
 }
 
+// (bf16 operands take the small kernel in reductions over vertices only, see small_product)
 static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
-#define CG_SMALL_CASE(BF, AK, BK_, TN_)                                                                                        \
-    if (bf16 == BF && akc == AK && bkc == BK_ && tn == TN_)                                                                  \
-        hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, TN_>), grid, dim3(256), 0, st, s);
-#define CG_SMALL_TYPES(AK, BK_)                                                                                                \
-    CG_SMALL_CASE(false, AK, BK_, 1) CG_SMALL_CASE(false, AK, BK_, 2) CG_SMALL_CASE(true, AK, BK_, 1) CG_SMALL_CASE(true, AK, BK_, 2)
-    CG_SMALL_TYPES(true, false) CG_SMALL_TYPES(true, true) CG_SMALL_TYPES(false, false) CG_SMALL_TYPES(false, true)
-#undef CG_SMALL_TYPES
+#define CG_SMALL_CASE(BF, AK, BK_)                                                                                             \
+    if (bf16 == BF && akc == AK && bkc == BK_) {                                                                               \
+        if (tn == 1) hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, 1>), grid, dim3(256), 0, st, s);                       \
+        else hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, 2>), grid, dim3(256), 0, st, s);                               \
+    }
+    CG_SMALL_CASE(false, true, false) CG_SMALL_CASE(false, true, true) CG_SMALL_CASE(false, false, false) CG_SMALL_CASE(false, false, true)
+    CG_SMALL_CASE(true, false, false) CG_SMALL_CASE(true, false, true)
 #undef CG_SMALL_CASE
 }
 
