@@ -183,7 +183,8 @@ def test_spmm_exact_on_small_integers(env):
 @pytest.mark.parametrize("fill", [0, 45000])
 def test_spmm_row_length_classes_exact(env, fill, scratch):
     """Row lengths on both sides of every limit of the work list: eight entries per trip of a lane group, 16 .. 128 entries
-    for a group alone, pieces of 64 entries (small graph) or 512 (more than 2 M entries), cut from twice that length on.
+    for a group alone, pieces of 64 entries (small graph: its longest row ends after the launch but for the narrowest rows,
+    which take one launch) or 512 (more than 2 M entries), cut from twice that length on.
     One width per lane-group size and one whose rows are not vectors; small integers, so every order of summation gives the
     same float and a bf16 result is that float rounded once: equality."""
     torch, B, H, O, orc = env["torch"], env["B"], env["H"], env["O"], env["orc"]
@@ -280,11 +281,12 @@ def test_graph_create_rejects_malformed_input(env):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n,cap", [(1, 1), (3, 0), (67, 30), (8191, 4000), (8193, 8193), (70_001, 35_003)])
 def test_full_gather_row_counts_and_widths_bit_exact(env, n, cap, dtype):
-    """Both launch forms of the full-batch gather (few rows: one per lane group, else four), with one and two tiers, at widths
+    """Both launch forms of the full-batch gather (four rows per lane group where there are many rows of more than one load per lane,
+    else one: the widest rows here are more than one load in either type), with one and two tiers, at widths
     whose rows are shorter than a vector, end in the middle of one, or are wider than a lane group; destinations that are and
     are not 16-byte aligned.  Bit copies: no tolerance."""
     torch, B = env["torch"], env["B"]
-    dims = [1, 7, 50, 128, 301]
+    dims = [1, 7, 50, 128, 301, 701]
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     rng = np.random.default_rng(n)
     c = B.Cache(rng.permutation(n).astype(np.int64) + 17, rng.integers(1, 100, n).astype(np.int64), cap, dims, B.BF16 if dtype == "bf16" else B.F32)
@@ -622,8 +624,9 @@ def test_gemm_vertex_reduction_with_little_workspace(env, dtype, tb):
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
     selection matrix (one +-2^e entry per output column / row) every output is a single product that fp32 holds exactly, so
-    all 24 bits of the other operand must come through: bit-exact, which pins the cut, the piece order and both LDS
-    layouts.  (2) Random operands: within the fp32 tolerance of the fp64 oracle, and no further from it than four times
+    all 24 bits of the other operand must come through: bit-exact, which pins the cut, the piece order and the LDS
+    layouts.  The last three plain shapes have more than 768 tiles of 64 x 64 and run gemm_split_kernel, in both of its widths; the
+    others run gemm_split_mid_kernel.  (2) Random operands: within the fp32 tolerance of the fp64 oracle, and no further from it than four times
     the distance of the fp32 matrix instruction plus 2^-23, the bound on the three piece products that are dropped (both
     distances are rounding noise of the fp32 accumulation, a hundred times below the tolerance)."""
     torch, B, H, O, orc = env["torch"], env["B"], env["H"], env["O"], env["orc"]
@@ -641,7 +644,8 @@ def test_gemm_f32_split_product(env, ta, tb):
         assert (got[:, N:] == 2.0).all()
         return got[:, :N]
 
-    for (M, N, K) in [(1, 1, 1), (130, 41, 602), (257, 256, 100), (300, 130, 1000), (602, 256, 5000), (64, 200, 33)]:
+    for (M, N, K) in [(1, 1, 1), (130, 41, 602), (257, 256, 100), (300, 130, 1000), (602, 256, 5000), (64, 200, 33)] + ([] if ta else [
+            (49217, 64, 37), (50000, 41, 66), (16500, 200, 70)]):
         shapeA, shapeB = ((K, M) if ta else (M, K)), ((N, K) if tb else (K, N))
         for which in ("select_b", "select_a", "random"):
             say(f"gemm f32 split ta={ta} tb={tb} M={M} N={N} K={K} {which}")
@@ -842,6 +846,38 @@ def test_layer_bwd_with_one_buffer_for_both_weight_gradients(env, dtype, n):
         assert rel <= 1e-5 < other       # fp32 sums of n products, possibly split another way
         for k in ("h", "db", "dx"):
             assert torch.equal(one[k], two[k]), k
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("n,f_in,f_out", [(50_000, 40, 60), (17_000, 150, 130), (50_000, 61, 37)])
+def test_sage_layer_products_over_two_weight_matrices(env, order, n, f_in, f_out):
+    """The sum of a GraphSAGE layer's two products as one launch of gemm_split_kernel over both weight matrices, 64 and 128 columns wide
+    (more than 768 tiles of 64 x 64): the forward product of the AGG_FIRST order and the input gradient of XFORM_FIRST, with widths that
+    fill their last step of 32 and that do not.  Self loops only, so both products read the layer's input itself.  Distance from float64
+    no more than four times that of the fp32 instruction plus 2^-23 (see test_gemm_f32_split_product)."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + f_in)
+    mk = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+    assert (n + 63) // 64 * ((min(f_in, f_out) + 63) // 64) > 768
+    g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.ones(n, np.float32), None)
+    x, dh, w, w_self, bias = mk(n, f_in), mk(n, f_out), mk(f_in, f_out), mk(f_in, f_out), mk(f_out)
+    ref = dict(h=x.double() @ (w.double() + w_self.double()) + bias.double(), dx=dh.double() @ (w.double() + w_self.double()).T)
+    err = {}
+    for form in (B.F32_PRODUCT_NATIVE, B.F32_PRODUCT_SPLIT):
+        l = B.make_layer(B.SAGE_MEAN, f_in, f_out, B.ACT_NONE, B.F32, w, w_self, bias, order, f32_product=form)
+        size = B.layer_workspace_bytes(g, l)
+        ws, saved = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty(B.layer_saved_bytes(g, l) + 256, dtype=torch.uint8, device="cuda")
+        out = dict(h=torch.zeros(n, f_out, device="cuda"), dx=torch.zeros(n, f_in, device="cuda"))
+        B.layer_fwd(g, l, x, f_in, out["h"], f_out, saved, ws, size)
+        B.layer_bwd(g, l, x, f_in, out["h"], f_out, saved, dh.clone(), f_out, None, None, None, out["dx"], f_in, 0, ws, size)
+        torch.cuda.synchronize()
+        for k in out:
+            err[k, form] = ((out[k].double() - ref[k]).abs().max() / ref[k].abs().max()).item()
+    say(f"two weight matrices n={n} {f_in}-{f_out} order={order}: {err}")
+    for k in ("h", "dx"):
+        assert err[k, B.F32_PRODUCT_SPLIT] <= 4.0 * err[k, B.F32_PRODUCT_NATIVE] + 2.0 ** -23 and err[k, B.F32_PRODUCT_NATIVE] <= TOL_F32
+    g.close()
 
 
 def test_mfma_peak_loop_runs_and_counts_its_work(env):
