@@ -574,9 +574,11 @@ def test_sgd_step_adds_every_gradient_of_a_shared_tensor(env, tie, recorded):
         assert np.abs(bias.double().cpu().numpy() - want_b).max() <= bound
 
 
-@pytest.mark.parametrize("dtype,form,width,n", [("f32", 0, 4096, 150_001), ("f32", 1, 2048, 150_001), ("f32", 2, 2048, 150_001), ("f32", 0, 64, 520_007),
-                                                ("f32", 2, 64, 520_007), ("bf16", 0, 4096, 150_001), ("bf16", 0, 64, 520_007), ("bf16", 0, 320, 520_007)])
-def test_epoch_bias_gradient_of_many_equal_rows(env, dtype, form, width, n):
+@pytest.mark.parametrize("dtype,form,inner,width,n", [("f32", 0, 4096, 4096, 150_001), ("f32", 1, 2048, 2048, 150_001), ("f32", 2, 2048, 2048, 150_001),
+                                                      ("f32", 0, 64, 64, 520_007), ("f32", 2, 64, 64, 520_007), ("f32", 1, 1024, 64, 40_001),
+                                                      ("bf16", 0, 4096, 4096, 150_001), ("bf16", 0, 64, 64, 520_007), ("bf16", 0, 320, 320, 520_007),
+                                                      ("bf16", 0, 640, 64, 120_001)])
+def test_epoch_bias_gradient_of_many_equal_rows(env, dtype, form, inner, width, n):
     """The hidden layers' bias gradients are column sums that the weight gradients' products form on the way.  Every row of dZ is the
     same here (self loops, equal rows and labels) and its elements are known: the last weight matrix holds one power of two per row, so
     dZ of the layer below is an element of the loss gradient times that.  A running fp32 sum of n equal terms drifts by up to n 2^-25,
@@ -586,14 +588,14 @@ def test_epoch_bias_gradient_of_many_equal_rows(env, dtype, form, width, n):
     torch, B = env["torch"], env["B"]
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     code = B.BF16 if dtype == "bf16" else B.F32
-    C, dims = 4, [8, width, width, 4]
+    C, dims = 4, [8, inner, width, 4]
     g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), None, None)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(width + n)
     x = (torch.rand(1, 8, generator=gen, device="cuda") + 0.5).to(dt).repeat(n, 1)
     at = torch.arange(width, device="cuda") % C
     power = torch.exp2(-(torch.arange(width, device="cuda") % 3).float())
-    w = [(torch.rand(8, width, generator=gen, device="cuda") / 8).to(dt), (torch.rand(width, width, generator=gen, device="cuda") * (2.0 / width)).to(dt),
+    w = [(torch.rand(8, inner, generator=gen, device="cuda") / 8).to(dt), (torch.rand(inner, width, generator=gen, device="cuda") * (2.0 / inner)).to(dt),
          torch.zeros(width, C, device="cuda")]
     w[2][torch.arange(width, device="cuda"), at] = power * 2.0 ** (2 - width.bit_length())
     w[2] = w[2].to(dt)
@@ -605,7 +607,7 @@ def test_epoch_bias_gradient_of_many_equal_rows(env, dtype, form, width, n):
     db = [torch.zeros(d, device="cuda") for d in dims[1:]]
     size = B.epoch_workspace_bytes(g, None, layers)
     ws = torch.empty(size, dtype=torch.uint8, device="cuda")
-    say(f"bias gradient of equal rows {dtype} form={form} {width} wide, {n} rows")
+    say(f"bias gradient of equal rows {dtype} form={form} {inner} x {width}, {n} rows")
     B.epoch(g, None, layers, x, 8, labels, None, 0.0, logits, dw, None, db, 0.0, ws, size)
     torch.cuda.synchronize()
     assert torch.equal(logits, logits[:1].expand(n, C))

@@ -620,6 +620,29 @@ def test_gemm_vertex_reduction_with_little_workspace(env, dtype, tb):
             assert (got == 2.0).all() if room < need else np.array_equal(got.astype(np.float64), ref), (M, N, K, room)
 
 
+@pytest.mark.parametrize("ta,tb,M,N,K", [(0, 0, 164_001, 47, 40), (0, 1, 164_001, 64, 72), (0, 0, 82_100, 130, 24), (0, 1, 82_100, 200, 33), (1, 0, 513, 64, 131_100),
+                                         (1, 1, 600, 41, 180_001), (1, 0, 300, 130, 38_400), (1, 1, 257, 250, 25_000)])
+def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
+    """The 128-row tiles of the bf16 kernel, 64 and 128 columns wide, at sizes that the 64-row tiles and the small kernel leave to them.
+    Small integers (sums below 2^24): equality, which pins the operands' lane layout and the ragged edges."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+    mk = lambda r, c: torch.randint(-2, 3, (r, c), generator=gen, device="cuda")  # noqa: E731
+    A, W = mk(*((K, M) if ta else (M, K))), mk(*((N, K) if tb else (K, N)))
+    ref = (A.T if ta else A).double() @ (W.T if tb else W).double()
+    pad = lambda x: torch.nn.functional.pad(x.bfloat16(), (0, -x.shape[1] % 8), value=float("nan")).contiguous()  # noqa: E731
+    Ad, Wd = pad(A), pad(W)
+    wsb = B.gemm_workspace_bytes(ta, M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for room in (wsb,) if ta else (wsb, 0):         # a plain product without one reads the weights as they are
+        Cd = torch.full((M, N + 3), 2.0, device="cuda")
+        say(f"gemm bf16 full-size tiles ta={ta} tb={tb} {M}x{N}x{K} workspace {room}")
+        B.gemm(ta, tb, M, N, K, Ad, Ad.shape[1], Wd, Wd.shape[1], Cd, N + 3, B.BF16, out_f32=1, ws=ws if room else None, ws_bytes=room)
+        torch.cuda.synchronize()
+        assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
