@@ -1688,28 +1688,46 @@ constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piec
 // 10000 x 128 x 50 (1252) 14.1 / 14.0, 21557 x 41 x 50 (1348) 13.8 / 11.8; 21557 x 41 x 100 (1348) 14.1 / 14.4, 10000 x 256 x 100
 // (2504) 22 / 17; 21557 x 64 x 128 (1348) 13.0 / 13.8, 50000 x 41 x 128 (3126) 25 / 21; 21557 x 41 x 256 17 / 24; 10000 x 41 x
 // 602 26 / 54.  A sum of two products replaces two launches of gemm_kernel, so it may have twice the tiles (launches = 2).
-// Reductions over vertices (trans_a), whose other kernels stage tiles through LDS step by step: up to 2^28.5
-// multiply-adds in fp32 (128 x 121 x 21557: 39 -> 21 us; 256 x 256 x 20000: 46 against 34) and 2^30.5 in bf16 (256 x 256 x 20000: 30
-// -> 19; 100 x 256 x 70001: 34 against 33), and further where N <= 64 leaves those kernels half idle (256 x 41 x 180000: 106 -> 91
-// fp32, 42 -> 34 bf16; 256 x 47 x 306000: 161 against 148 fp32, 67 -> 56 bf16).
+// Reductions over vertices (trans_a), whose other kernels stage tiles through LDS step by step: about as far as the small kernel is
+// the faster one for every M, with the splits of small_geometry (us small / other, M x N at 2^e multiply-adds, medians over five
+// placements of the operands).  fp32, N > 64, up to 2^28.46: 200 x 256 14 / 20 at 2^27, 602 x 256 22 / 26 at 2^28, 100 x 256 23 / 23
+// and 602 x 256 26 / 23 at 2^28.4.  fp32, N <= 64 (the other kernel half idle), up to 2^31: 100 x 41 81 / 86 at 2^30, 200 x 41 124 /
+// 130, 320 x 64 79 / 81, 602 x 41 118 / 111, 512 x 64 70 / 63 at 2^31, 602 x 41 232 / 197 at 2^32.  bf16, N > 64, up to 2^30.46:
+// 200 x 256 21 / 26, 602 x 256 28 / 27, 100 x 100 31 / 33 at 2^30.  bf16, 32 < N <= 64, up to 2^32: 200 x 41 42 / 57, 602 x 64 30 / 32
+// at 2^31, 512 x 64 44 / 51, 602 x 41 69 / 64 at 2^32.  bf16, N <= 32, up to 2^30: 100 x 16 60 / 83, 602 x 16 54 / 51 at 2^30, 320 x 16
+// 117 / 95 at 2^31.
 static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches) {
     if (K <= 0) return false;
     const double macs = static_cast<double>(M) * N * K;
-    if (trans_a) return macs <= (bf16 ? (N <= 64 ? 0x1p32 : 0x1.6p30) : (N <= 64 ? 0x1p31 : 0x1.6p28));
+    if (trans_a) return macs <= (bf16 ? (N <= 32 ? 0x1p30 : N <= 64 ? 0x1p32 : 0x1.6p30) : (N <= 64 ? 0x1p31 : 0x1.6p28));
     return !bf16 && macs < SPLIT_MIN_MACS && ((M + 31) / 32) * ((N + 31) / 32) <= launches * (1024 + 8 * std::max<int64_t>(K - 50, 0));
 }
 
 // Tiles and reduction splits of a small product: N tiles of 64 columns (32 where that is all), and for a reduction over
-// vertices enough splits for about two workgroups per compute unit, each wave with at least one batch.
+// vertices splits for the two workgroups that a compute unit holds, each wave with at least one batch.  The tiles of a split run on
+// one L2 domain (tile_coords), which holds 64 workgroups, so the splits are dealt in eights, and as many eights are taken as give
+// the shortest sweep over two loads of the domains at most (more splits cost more to add up).  512 / tiles splits left one domain
+// of a 602-row result with 76 workgroups and another with 57 (us, 602 x 41: fp32 2^31 143 -> 118, bf16 2^30 44 -> 25; 320 x 41 fp32
+// 2^31 141 -> 112), and two domains without any where the tiles are more than 64 (bf16 602 x 256 2^30 32 -> 28).
 static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk) {
     const int64_t unit = bf16 ? SMALL_UNIT_K<true> : SMALL_UNIT_K<false>, batch = unit * SMALL_UNITS;
     *tn = N <= 32 ? 1 : 2;
     *S = 1;
     const int64_t tiles = ((M + 31) / 32) * ((N + *tn * 32 - 1) / (*tn * 32));
     if (trans_a) {
-        int64_t z = 512 / tiles;
-        if (z > K / (4 * batch)) z = K / (4 * batch);
-        *S = static_cast<int>(z < 1 ? 1 : z);
+        constexpr int64_t HELD = 2 * NUM_CU / NUM_XCD;       // workgroups an L2 domain holds
+        const int64_t most = K / (4 * batch);                // splits with at least one batch per wave
+        auto sweep = [&](int64_t eights) { return static_cast<double>((eights * tiles + HELD - 1) / HELD) / eights; };
+        const int64_t e_most = std::min<int64_t>(most / NUM_XCD, std::max<int64_t>(2 * HELD / tiles, 1));
+        if (e_most < 1) {
+            *S = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(2 * NUM_CU / tiles, most)));
+        } else {
+            double best = sweep(1);
+            for (int64_t e = 2; e <= e_most; ++e) best = std::min(best, sweep(e));
+            int64_t e = 1;
+            while (sweep(e) > 1.03 * best) ++e;
+            *S = static_cast<int>(NUM_XCD * e);
+        }
     }
     const int64_t chunk = (K + *S - 1) / *S;
     *k_chunk = (chunk + 4 * unit - 1) / (4 * unit) * (4 * unit);
