@@ -560,7 +560,7 @@ def test_gemm_size_classes_exact(env, dtype, ta, tb):
     rng = np.random.default_rng(70 + 2 * ta + tb)
     sizes = [(1, 1, 1), (31, 33, 7), (32, 32, 8), (33, 64, 9), (65, 65, 31), (64, 63, 33), (97, 130, 127), (96, 128, 128), (40, 40, 129),
              (70, 256, 300)]
-    sizes += [(130, 121, 2999), (64, 47, 5003), (8, 7, 20000), (257, 200, 1025)] if ta else [
+    sizes += [(130, 121, 2999), (64, 47, 5003), (8, 7, 20000), (257, 200, 1025), (602, 41, 6001), (602, 200, 3500), (320, 16, 5000)] if ta else [
         (16384, 64, 20), (16385, 64, 20), (49152, 64, 36), (49153, 64, 36), (3000, 300, 100)]
     for M, N, K in sizes:
         A = rng.integers(-3, 4, (K, M) if ta else (M, K)).astype(np.float32)
