@@ -355,9 +355,10 @@ int capgnn_relabel_csr(int64_t n_loc, int64_t n_halo, const int64_t *rowptr, con
  * trans_a: A is stored [K x M];  trans_b: B is stored [N x K].  bias: device float[N] or NULL.
  * relu_mask: device [M x ldm] of `dtype` or NULL; when given, C[i,j] is zeroed where
  * relu_mask[i,j] <= 0 (the sigma' factor of the backward recursion).
- * ws is required when trans_a (reduction over the vertex dimension is split over workgroups and
- * reduced in a fixed order) and optional otherwise (room to lay the weight matrix out for the bf16
- * matrix cores; without it a slower kernel runs): capgnn_gemm_workspace_bytes().
+ * ws is required when trans_a and K >= 512 (reduction over the vertex dimension is split over workgroups
+ * and reduced in a fixed order; with less than capgnn_gemm_workspace_bytes() in fewer splits, and
+ * CAPGNN_ENOMEM if it is too little for those) and optional otherwise (room to lay the weight matrix out
+ * for the bf16 matrix cores; without it a slower kernel runs).
  * out_f32 != 0 stores C as float even when dtype is BF16 (weight gradients, logits).
  * The padding of operand rows (columns beyond the operand's width, inside its ld) may be read, whatever it holds, but
  * never reaches C; nothing is read beyond the last row's width.  Padding columns of C are not written.

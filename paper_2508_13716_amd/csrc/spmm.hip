@@ -900,9 +900,11 @@ static int group_row_entries(int64_t nnz, int64_t row_bytes) {
 
 // Unused LDS asked for by the launches whose rows average at least CROWDED_ROW entries of at least CROWDED_BYTES: twelve
 // waves per compute unit instead of 20 to 28.  Twelve keep the fabric behind the L2s busy with such rows, and fewer rows
-// under way at a time leave more of the L2s to the hubs: 980 k rows x 50 entries, 256 bf16 features 3.66 -> 3.48 ms, 128
-// features 1.86 -> 1.76, 47 float features 1.77 -> 1.68.  Shorter rows need the waves to hide their start and end (13 entries
-// x 256 float features: 0.60 -> 0.63 ms), narrower ones to keep enough requests in flight (47 bf16 features: 0.10 -> 0.115).
+// under way at a time leave more of the L2s to the hubs: 980 k rows x 50 entries, 256 bf16 features 3.61 -> 3.46 ms, 128
+// features 1.81 -> 1.70, 64 float features 1.88 -> 1.79; 400 k rows x 35 entries 2 to 3 %, 200 k rows x 100 entries 4 to 10 %.
+// Shorter rows need the waves to hide their start and end (13 entries x 256 float features: 0.60 -> 0.63 ms), narrower ones to
+// keep enough requests in flight (47 bf16 features: 0.10 -> 0.115).  It costs where most gathers hit the L2s anyway: Zipf halo
+// columns, 300 k rows x 50 entries x 256 bf16 features 0.73 -> 0.755 ms, 1 M rows x 40 entries x 512 4.66 -> 4.86.
 constexpr int CROWDED_ROW = 32, CROWDED_BYTES = 192, CROWDED_LDS = 13312;
 
 // Graphs of at most ROWS_NNZ entries with rows to cut run as one launch of spmm_rows_kernel: the second launch costs more than
