@@ -707,17 +707,15 @@ def main():
 def traffic_for(key):
     """(bytes per launch beyond L2, where it comes from) for a launch key of profiles/traffic_per_launch.txt, or (None, None):
     a PROFILED CONSTANT (two rocprofv3 --pmc runs, FETCH_SIZE and WRITE_SIZE, scaled by a copy kernel of known size), not
-    measured in this run; the file names the commit the counters were taken at."""
+    measured in this run; each line names the commit the counters were taken at."""
     tpath = os.path.join(ROOT, "profiles", "traffic_per_launch.txt")
     if not os.path.exists(tpath):
         return None, None
-    taken_at = None
     for line in open(tpath):
-        if line.startswith("# taken at"):
-            taken_at = line[2:].strip()
         parts = line.split()
         if len(parts) >= 2 and parts[0] == key:
-            return float(parts[1]), f"profiled constant from profiles/traffic_per_launch.txt ({taken_at or 'commit not recorded'}); not measured in this run"
+            taken_at = f"taken at commit {parts[2]}" if len(parts) > 2 else "commit not recorded"
+            return float(parts[1]), f"profiled constant from profiles/traffic_per_launch.txt ({taken_at}); not measured in this run"
     return None, None
 
 
@@ -788,7 +786,7 @@ def epoch_record(name, args, peaks, headline):
     pipelined_mode = miss_mode == B.MISS_PIPELINED
     copy_rate = ((hit_bytes + (2 * miss_bytes if (staged_ms or pipelined_mode) else 0)) / ((hit_ms + staged_ms) * 1e-3) / 1e9
                  if hit_ms + staged_ms else None)
-    # which memory level serves the gather: the column-blocked kernel walks 4 MB panels (an L2); the one-wave-per-row
+    # which memory level serves the gather: the column-blocked kernel walks 4 MB panels (an L2); the lane-group
     # kernel gathers from the whole operand
     operand_bytes = touched * F * es
     blocked = bool(B.spmm_workspace_bytes(dp.graph, F, dp.dtype) > operand_bytes)     # partial rows for every source block
@@ -834,7 +832,7 @@ def epoch_record(name, args, peaks, headline):
                             "achieved": gather_rate, "peak": peaks[level], "unit": "GB/s", "frac": gather_rate / peaks[level],
                             "peak_is": f"capgnn_gather_peak on a {level.split('_')[-1]} table, this run",
                             "frac_of_published_l2_peak": gather_rate / L2_PEAK_GBPS,
-                            "kernel_form": "column-blocked (4 MB source panels)" if blocked else "one wave per row"},
+                            "kernel_form": "column-blocked (4 MB source panels)" if blocked else "lane groups and waves"},
     }
     if headline:
         out["env"] = {"device": torch.cuda.get_device_name(0), "hip": torch.version.hip, "torch": torch.__version__,
