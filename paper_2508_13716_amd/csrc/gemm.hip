@@ -439,6 +439,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 // its rows, four consecutive k per thread, transposed in registers (byte permutes pair up the values of two k)
 // and stored as 8-byte pieces: no 2-byte LDS traffic.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// two fp32 numbers rounded to bf16 (nearest even), the first in the low half: one v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t bf16_pair(float x0, float x1) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
+}
 constexpr int HBK = 32;            // k per step of the bf16 kernel
 constexpr int HPAD = 8;            // bf16 elements of row padding
 
@@ -731,6 +739,181 @@ __global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm
 }
 
 // ---------------------------------------------------------------------------------------------------
+// bf16 products of many rows with a small weight matrix (C = A W or A W^T, at most 512 k, more than 64 columns), which move far
+// more bytes than they compute: memory bounds them.  A workgroup of NS waves walks tiles of 32 rows and all its life holds its
+// columns of W in registers, 32 per wave, in the layout the matrix instruction reads (KS units of 16 k): a tile costs its rows of A
+// and of C and nothing else, A is read once per 256 columns, and all of a tile's loads go out at once, two tiles ahead.  One barrier
+// per tile: rows of A and rounded results have two LDS buffers each.  Loads and stores of a wave complete in order, so every tile
+// issues the same ones, unconditionally (the last row's tile comes apart, at the end; stores beyond the matrix go to an offset that
+// the buffer's bounds drop): nothing waits for a store.  Results are stored past the caches (they are read once, by a later
+// kernel, and mostly larger than what the caches hold): 980 k x 256 x 128 153 -> 125 us, 980 k x 256 x 47 124 -> 99.
+// The operands of the instruction are exchanged (W first): a lane then holds four neighbouring columns of a row of C.
+// us, gemm_bf16_kernel's tiles of 128 columns -> here, TB/s of operand and result: 980 k x 256 x 256 322 -> 195 (5.1), x 128 231 ->
+// 123 (6.1), x 47 261 -> 96 (6.2), 150 k x 256 x 512 82 -> 50 (4.6), 200 k x 128 x 128 36 -> 21 (5.0).
+constexpr int stream_lds(int KS, int NS) { return 2 * (2 * KS * 34 * 16) + 2 * (32 * (NS * 32 + 8) * 2) + NS * 128; }
+// workgroups per compute unit: what its LDS holds, and at most 16 waves with their weights
+constexpr int stream_held(int KS, int NS) { return std::min(160 * 1024 / stream_lds(KS, NS), std::max(1, (KS == 32 ? 8 : 16) / NS)); }
+
+template <int KS, int NS, bool MASK>
+__global__ __launch_bounds__(NS * 64, std::max(1, stream_held(KS, NS) * NS / 4)) void gemm_bf16_stream_kernel(GemmArgs g, const uint16_t *Wt, uint32_t n_pad) {
+    constexpr int NT = NS * 64, NU = 2 * KS, PLANE = 34, A_BYTES = NU * PLANE * 16;     // 16-byte units (k / 8, row), see Units16
+    constexpr int NLD = 32 * NU / NT, RPP = NT / NU;                                    // loads per thread and tile, rows per pass
+    constexpr int CPITCH = NS * 32 + 8, C_BYTES = 32 * CPITCH * 2;
+    static_assert(NT % NU == 0 && 32 * NU % NT == 0, "whole rows per pass");
+    __shared__ __attribute__((aligned(16))) char smem[2 * A_BYTES + 2 * C_BYTES + NS * 128];
+    static_assert(sizeof(smem) == stream_lds(KS, NS), "LDS of a workgroup");
+    float *bias = reinterpret_cast<float *>(smem + 2 * A_BYTES + 2 * C_BYTES);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int n0 = static_cast<int>(blockIdx.y) * (NS * 32);
+    const int64_t full = (g.M - 1) / 32;                // tiles before the one that holds the last row
+
+    for (int c = tid; c < NS * 32; c += NT) bias[c] = (g.bias && n0 + c < g.N) ? g.bias[n0 + c] : 0.f;
+    bf16x8 w[KS];       // (a wave beyond the last column of the image holds its last columns: never stored)
+    {
+        const uint32_t n = static_cast<uint32_t>(n0 + wave * 32) + 32 <= n_pad ? n0 + wave * 32 : n_pad - 32;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            w[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Wt + (static_cast<size_t>(2 * s + half) * n_pad + n + l32) * 8));
+    }
+    const int v = tid % NU, r0 = tid / NU;              // the thread's vector of a row of A, its first row
+    const int K = static_cast<int>(g.K), have = K - 8 * v;                    // elements of that vector that exist
+    const uint32_t a_off = static_cast<uint32_t>(r0) * static_cast<uint32_t>(g.lda) * 2 +
+                           16u * (have > 0 ? v : (K - 1) / 8);                // (vectors beyond the width read the last one and are cleared)
+    const uint32_t a_step = static_cast<uint32_t>(g.lda) * 2 * RPP;
+    typedef uint4 Rows[NLD];
+    auto load = [&](int64_t t, Rows &r) __attribute__((always_inline)) {
+        const char *base = g.A + (t < full ? t : full - 1) * 64 * g.lda;
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) r[q] = *reinterpret_cast<const uint4 *>(base + (a_off + q * a_step));
+    };
+    auto load_last = [&](Rows &r) __attribute__((always_inline)) {            // the rows that exist, no further than their width
+        const int rows = static_cast<int>(g.M - full * 32);
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) {
+            const int row = r0 + q * RPP;
+            r[q] = HalfTileLoader<true, 128, 0>::load8(g.A, (full * 32 + row) * g.lda + 8 * v, row < rows ? (have < 8 ? have : 8) : 0);
+        }
+    };
+    auto put = [&](Rows &r, char *As) __attribute__((always_inline)) {
+        if (K < KS * 16) {
+#pragma unroll
+            for (int q = 0; q < NLD; ++q) {
+                uint32_t x[4] = {r[q].x, r[q].y, r[q].z, r[q].w};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) x[d] = 2 * d + 1 < have ? x[d] : 2 * d < have ? x[d] & 0xffffu : 0u;
+                r[q] = make_uint4(x[0], x[1], x[2], x[3]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) *reinterpret_cast<uint4 *>(As + (v * PLANE + r0 + q * RPP) * 16) = r[q];
+    };
+    // the thread's two pieces of a finished tile: 8 columns of rows cr and cr + 16
+    const int cr = tid / (NS * 4), cc = 8 * (tid % (NS * 4));
+    const uint32_t ldc2 = static_cast<uint32_t>(g.ldc) * 2, ldm2 = static_cast<uint32_t>(g.ldm) * 2;
+    const bool whole = n0 + cc + 8 <= g.N;
+    const bool cut = n0 + NS * 32 > g.N && g.N % 8 != 0;                      // a group of eight columns ends inside the matrix (uniform)
+
+    // mid: what becomes of the A registers between the products and the barrier
+    auto tile = [&](int64_t t, int rows, int buf, auto mid) __attribute__((always_inline)) {
+        const char *As = smem + buf * A_BYTES;
+        uint16_t *Cs = reinterpret_cast<uint16_t *>(smem + 2 * A_BYTES + buf * C_BYTES);
+        const int64_t m0 = t * 32;
+        uint4 mk[2];
+        if constexpr (MASK) {
+            const char *mbase = g.mask + m0 * g.ldm * 2;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int row = cr + 16 * p < rows ? cr + 16 * p : rows - 1;
+                mk[p] = *reinterpret_cast<const uint4 *>(mbase + (static_cast<uint32_t>(row) * ldm2 + (whole ? 2u * (n0 + cc) : 0u)));
+            }
+        }
+        floatx16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8 x = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(As + ((2 * s + half) * PLANE + l32) * 16));
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s], x, acc, 0, 0, 0);
+        }
+        // four operand reads ahead of the matrix instructions
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int s = 0; s < KS - 4; ++s) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {                    // registers 4 q ..: columns 8 q + 4 half .. of row l32
+            const float4 b4 = *reinterpret_cast<const float4 *>(&bias[wave * 32 + 8 * q + 4 * half]);
+            float x[4] = {acc[4 * q] + b4.x, acc[4 * q + 1] + b4.y, acc[4 * q + 2] + b4.z, acc[4 * q + 3] + b4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = g.relu && !(x[e] > 0.f) ? 0.f : x[e];
+            uint2 o;
+            o.x = bf16_pair(x[0], x[1]);
+            o.y = bf16_pair(x[2], x[3]);
+            *reinterpret_cast<uint2 *>(&Cs[l32 * CPITCH + wave * 32 + 8 * q + 4 * half]) = o;
+        }
+        mid();
+        __syncthreads();
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.C + (m0 * g.ldc + n0) * 2, 0, 0x7fffffff, 0x00027000);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            uint4 o = *reinterpret_cast<const uint4 *>(&Cs[(cr + 16 * p) * CPITCH + cc]);
+            if constexpr (MASK) o = keep_positive(o, mk[p]);
+            const uint32_t at = cr + 16 * p < rows && whole ? (cr + 16 * p) * ldc2 + 2u * cc : 0xfffffff0u;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc, at, 0, 2);
+        }
+        if (cut) {
+            auto msrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(g.mask) + (m0 * g.ldm + n0) * 2, 0, 0x7fffffff, 0x00027000);
+#pragma unroll 1
+            for (int e = 0; e < 16; ++e) {
+                const int row = cr + 2 * (e & 8), col = cc + (e & 7);
+                const bool in = !whole && row < rows && n0 + col < g.N;
+                uint16_t x = Cs[row * CPITCH + col];
+                if constexpr (MASK)
+                    if (!positive_bf16(__builtin_amdgcn_raw_buffer_load_b16(msrc, in ? row * ldm2 + 2u * col : 0xfffffff0u, 0, 0))) x = 0;
+                __builtin_amdgcn_raw_buffer_store_b16(x, rsrc, in ? row * ldc2 + 2u * col : 0xfffffff0u, 0, 0);
+            }
+        }
+    };
+    // as many dropped stores as the tiles before would have issued, so that the waits of the loop can allow for them
+    auto dropped = [&](uint32_t at) __attribute__((always_inline)) {
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.C, 0, 0x7fffffff, 0x00027000);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, at, 0, 2);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, at + 16, 0, 0);
+    };
+    Rows ra, rb;
+    const int64_t step = gridDim.x;
+    int64_t t = blockIdx.x;
+    if (t < full) {                                      // uniform over the workgroup
+        load(t, ra);
+        load(t + step, rb);
+        dropped(0xffffff00u);
+        put(ra, smem);
+        load(t + 2 * step, ra);
+        dropped(0xffffff40u);
+        __syncthreads();
+        for (; t + step < full; t += 2 * step) {         // (one way out: the waits are counted over every path)
+            tile(t, 32, 0, [&]() { put(rb, smem + A_BYTES); load(t + 3 * step, rb); });
+            tile(t + step, 32, 1, [&]() { put(ra, smem); load(t + 4 * step, ra); });
+        }
+        if (t < full) {
+            tile(t, 32, 0, []() {});
+            t += step;
+        }
+        __syncthreads();                                 // both buffers of A are free
+    }
+    if (t == full) {                                     // the tile with the last row (t went through every residue: one workgroup's)
+        load_last(ra);
+        put(ra, smem);
+        __syncthreads();
+        tile(t, static_cast<int>(g.M - full * 32), 0, []() {});
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
 // fp32 operands on the bf16 matrix cores.  An fp32 number is the exact sum of three bf16 numbers (its 24 significant
 // bits cut into 8 + 8 + 8, with signs), so a product a * b is the sum of nine bf16 products, each exact in fp32.  The
 // three smallest (together at most 2^-23 of the product: the size of fp32's own rounding) are dropped, the other six
@@ -747,14 +930,6 @@ __global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm
 // and kept in 8-byte units S[piece][k / 4][row], which makes both the staging stores (32 bytes per thread and piece)
 // and the operand reads (two 8-byte reads) run over consecutive LDS addresses.
 constexpr int SBK = 32;
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// two fp32 numbers rounded to bf16 (nearest even), the first in the low half: one v_cvt_pk_bf16_f32
-__device__ __forceinline__ uint32_t bf16_pair(float x0, float x1) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
-}
 
 // x = piece 0 + piece 1 + piece 2 exactly, for two numbers at once; p[i] holds piece i of x0 in its low half and of
 // x1 in its high half.  Rounding to nearest bounds the second piece by 2^-8 |x| and the third by 2^-16 |x|; the
@@ -848,7 +1023,6 @@ struct SplitRowLoader {
 };
 
 // second operand already cut into units Wt[piece][k / 8][n] (n padded to whole tiles, k to whole steps): plain copies
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int BT, int NT = 256>
 struct SplitPlaneLoader {
@@ -1572,6 +1746,15 @@ __global__ __launch_bounds__(256) void repack_bf16_kernel(const uint16_t *W, int
     Wt[t] = k < K ? (kc ? W[n * ldw + k] : W[k * ldw + n]) : static_cast<uint16_t>(0);
 }
 
+// The same operand in the units of gemm_bf16_stream_kernel: Wt[k / 8][n][k % 8], n_pad rows, zero beyond N and K.
+__global__ __launch_bounds__(256) void unit_repack_kernel(const uint16_t *W, int64_t ldw, int kc, int64_t K, int64_t N, uint16_t *Wt,
+                                                          int64_t n_pad, int64_t ku_total) {
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (t >= ku_total * n_pad * 8) return;
+    const int64_t ku = t / (n_pad * 8), n = (t / 8) % n_pad, k = 8 * ku + (t % 8);
+    Wt[t] = (n < N && k < K) ? (kc ? W[n * ldw + k] : W[k * ldw + n]) : static_cast<uint16_t>(0);
+}
+
 // Sums the split partials and applies the epilogue.  A workgroup covers 32 consecutive output elements with 8
 // groups of threads; group y adds the partials z = y, y+8, ... in that order, then the 8 group sums are added
 // in group order: a fixed summation order, whatever the launch geometry.
@@ -1778,6 +1961,26 @@ static void launch_bf16_tiles(const GemmArgs &g, int bn, bool bm64, dim3 grid, h
     else hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 128>), grid, dim3(256), 0, st, g);
 }
 
+// Units of 16 k that a wave of gemm_bf16_stream_kernel holds, or 0 where it does not apply
+static int stream_units(int64_t K) { return K <= 0 || K > 512 ? 0 : K <= 128 ? 8 : K <= 256 ? 16 : 32; }
+
+template <int KS, int NS>
+static void launch_stream_cfg(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad, hipStream_t st) {
+    constexpr int HELD = NUM_CU * stream_held(KS, NS);
+    const int64_t tiles = (g.M + 31) / 32, gy = (g.N + NS * 32 - 1) / (NS * 32);
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>(tiles, std::max<int64_t>(HELD / gy, 1))), static_cast<unsigned>(gy));
+    if (g.mask) hipLaunchKernelGGL((gemm_bf16_stream_kernel<KS, NS, true>), grid, dim3(NS * 64), 0, st, g, Wt, n_pad);
+    else hipLaunchKernelGGL((gemm_bf16_stream_kernel<KS, NS, false>), grid, dim3(NS * 64), 0, st, g, Wt, n_pad);
+}
+
+static void launch_stream(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad, hipStream_t st) {
+    const int ks = stream_units(g.K);
+#define CG_STREAM(KS_) if (ks == KS_) { if (g.N <= 128) launch_stream_cfg<KS_, 4>(g, Wt, n_pad, st); \
+        else launch_stream_cfg<KS_, 8>(g, Wt, n_pad, st); }
+    CG_STREAM(8) CG_STREAM(16) CG_STREAM(32)
+#undef CG_STREAM
+}
+
 // (bf16 operands take the small kernel in reductions over vertices only, see small_product)
 static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
 #define CG_SMALL_CASE(BF, AK, BK_)                                                                                             \
@@ -1877,6 +2080,11 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
     g.c_staged = half_path && g.out_bf16 && !g.part && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0 &&
                  (!relu_mask || (aligned16(relu_mask) && (ldm * 2) % 16 == 0));
+    // gemm_bf16_stream_kernel from about one tile per workgroup on, where the load of W into registers is paid back (us against the
+    // tiled kernel, 10000 x 256 x 128 9.7 / 8.0, 20000 x 256 x 256 11.8 / 14.2, 30000 x 256 x 256 13.3 / 18.5, 60000 x 128 x 128 10.1 /
+    // 14.2), and above 64 columns (980 k x 47 x 128 104 / 91, 980 k x 47 x 256 146 / 149)
+    const bool stream_path = g.c_staged && !trans_a && stream_units(K) && N > 64 && M >= 16384 && ws &&
+                             ws_bytes >= static_cast<size_t>(split_rows(N)) * stream_units(K) * 32 && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
     if (small_path) {
@@ -1900,6 +2108,11 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                                ku_total);
             launch_split_tiles(false, g, bn, grid, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream);
         }
+    } else if (stream_path) {
+        const int64_t n_pad = split_rows(N), ku_total = 2 * stream_units(K);
+        hipLaunchKernelGGL(unit_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0, stream,
+                           static_cast<const uint16_t *>(B), ldb, bkc ? 1 : 0, K, N, static_cast<uint16_t *>(ws), n_pad, ku_total);
+        launch_stream(g, static_cast<const uint16_t *>(ws), static_cast<uint32_t>(n_pad), stream);
     } else if (half_path) {
         if (repack_b) {
             const int64_t ldt = (K + 7) / 8 * 8;

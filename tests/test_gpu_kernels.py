@@ -643,6 +643,39 @@ def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
         assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(16384, 128, 128), (16385, 65, 7), (16415, 100, 129), (20000, 130, 200), (16399, 256, 256), (50001, 257, 47),
+                                   (16386, 300, 256), (17003, 200, 257), (16384, 72, 511), (16417, 256, 512), (16383, 256, 64), (16390, 256, 520)])
+def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
+    """bf16 products of many rows whose result is stored as bf16 (weights held in registers from 16384 rows on): the last tile of
+    rows whole, short and of one row, K around a unit and around 128, 256 and 512, N not a multiple of eight, of a wave's 32 and of a
+    workgroup's columns; with and without bias, ReLU and mask.  Integers of at most 8 bits: equality.  Padding of every operand is NaN
+    and C's own stays as it is."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    mk = lambda r, c: torch.randint(-1, 2, (r, c), generator=gen, device="cuda").float()  # noqa: E731
+    A, W = mk(M, K), mk(*((N, K) if tb else (K, N))) * (torch.rand((N, K) if tb else (K, N), generator=gen, device="cuda") < 0.1)
+    bias, mask = mk(1, N)[0].contiguous(), mk(M, N)
+    pad = lambda x: torch.nn.functional.pad(x.bfloat16(), (0, -x.shape[1] % 8 + 8), value=float("nan")).contiguous()  # noqa: E731
+    Ad, Wd, Md = pad(A), pad(W), pad(mask)
+    plain = A @ (W.T if tb else W)
+    assert float(plain.abs().max()) < 250
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    ldc = (N + 7) // 8 * 8 + 8
+    for use_bias, relu, use_mask in ((False, 0, False), (True, 1, False), (False, 0, True)):
+        say(f"gemm bf16 many rows tb={tb} {M}x{N}x{K} bias={use_bias} relu={relu} mask={use_mask}")
+        Cd = torch.full((M, ldc), 2.0, device="cuda", dtype=torch.bfloat16)
+        B.gemm(0, tb, M, N, K, Ad, Ad.shape[1], Wd, Wd.shape[1], Cd, ldc, B.BF16, bias=bias if use_bias else None, relu=relu,
+               relu_mask=Md if use_mask else None, ldm=Md.shape[1] if use_mask else 0, ws=ws, ws_bytes=wsb)
+        torch.cuda.synchronize()
+        ref = plain + bias if use_bias else plain
+        ref = ref.clamp(min=0) if relu else ref
+        ref = ref * (mask > 0) if use_mask else ref
+        assert torch.equal(Cd[:, :N].float(), ref) and (Cd[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
