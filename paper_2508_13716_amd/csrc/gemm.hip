@@ -1599,6 +1599,157 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     }
 }
 
+// Reductions over vertices with a narrow second operand, C = A^T B, A [K x M] and B [K x N <= 64] in float, on the fp32 instruction
+// (v_mfma_f32_16x16x4_f32): many more bytes than products, so memory bounds it.  An operand stored across the reduction index already
+// lies as the instruction wants it when rows of the result are dealt to tiles in steps of four: a lane's 16-byte load of A, four
+// neighbouring columns of row k, is its operand of four tiles.  So nothing is staged: a wave owns 128 x 16 NT results, loads four k
+// at a time, NARROW_AHEAD batches ahead, and multiplies; the four waves of a workgroup take turns at the k of its split and are summed
+// through LDS in wave order, splits by gemm_reduce_kernel.  Rows need no alignment.
+constexpr int NARROW_AHEAD = 4;
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
+
+// A pair of problems of one shape (A2, B2, part2) runs as the second row of the grid.
+template <int NT>
+__global__ __launch_bounds__(256, NT <= 2 ? 3 : 2) void gemm_narrow_kernel(SmallGemmArgs p2) {
+    GemmArgs &g = p2.g;
+    const bool second = blockIdx.y != 0;
+    if (second) { g.A = p2.A2; g.lda = p2.lda2; g.B = p2.B2; g.ldb = p2.ldb2; g.part = p2.part2; }
+    constexpr int AHEAD = NARROW_AHEAD;
+    __shared__ __attribute__((aligned(16))) f32x4 red[4][4 * NT][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quarter = lane >> 4;      // the lane's row / column of a tile, its k of a batch
+    int bx, by, bz;
+    if (!tile_coords(g, &bx, &by, &bz)) return;          // uniform over the workgroup
+    const int64_t m0 = static_cast<int64_t>(by) * 128;
+    const int64_t k_begin = static_cast<int64_t>(bz) * g.k_chunk;
+    const int64_t k_end = k_begin + g.k_chunk < g.K ? k_begin + g.k_chunk : g.K;
+    const float *A = reinterpret_cast<const float *>(g.A), *B = reinterpret_cast<const float *>(g.B);
+    // columns beyond the matrices read others: what they give is never stored
+    int64_t am[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int64_t m = m0 + 64 * u + 4 * l16;
+        am[u] = m < g.M ? m : g.M - 1;
+    }
+    int bn[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) bn[j] = 16 * j + l16 < g.N ? 16 * j + l16 : static_cast<int>(g.N) - 1;
+
+    f32x4 acc[2][4][NT];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[u][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // column sums of B (see gemm_small_kernel): a lane adds AHEAD terms in fp32
+    const bool sums = g.colpart && by == 0 && !second;
+    double bsum[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) bsum[j] = 0.0;
+    auto multiply = [&](const f32x4 (&a)[2], const float (&b)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[u][c][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][c], b[j], acc[u][c][j], 0, 0, 0);
+    };
+    // batches whose loads may run past the width of a row: 16 bytes of a row before the last three stay inside the matrix
+    const int64_t first = k_begin + 4 * wave, limit = k_end < g.K - 3 ? k_end : g.K - 3;
+    const int n = limit >= first + 4 ? static_cast<int>((limit - 4 - first) / 16 + 1) : 0;
+    if (n > 0) {
+        f32x4 a[AHEAD][2];
+        float b[AHEAD][NT];
+        const float *pa = A + (first + quarter) * g.lda, *pb = B + (first + quarter) * g.ldb;
+        auto fetch = [&](int s, int p) __attribute__((always_inline)) {      // (after the last batch: that one again)
+            const int64_t t = 16 * static_cast<int64_t>(s < n ? s : n - 1);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) a[p][u] = *reinterpret_cast<const f32x4_dword *>(pa + t * g.lda + am[u]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[p][j] = pb[t * g.ldb + bn[j]];
+        };
+#pragma unroll
+        for (int p = 0; p < AHEAD; ++p) fetch(p, p);
+        int s = 0;
+        for (; s + AHEAD <= n; s += AHEAD) {
+            float t[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) t[j] = 0.f;
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) {
+                multiply(a[p], b[p]);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) t[j] += b[p][j];
+                fetch(s + p + AHEAD, p);
+            }
+            if (sums)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) bsum[j] += static_cast<double>(t[j]);
+        }
+#pragma unroll
+        for (int p = 0; p < AHEAD; ++p)
+            if (s + p < n) {
+                multiply(a[p], b[p]);
+                if (sums)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) bsum[j] += static_cast<double>(b[p][j]);
+            }
+    }
+    for (int64_t k = first + 16 * static_cast<int64_t>(n); k < k_end; k += 16) {      // what is left, element by element
+        const int64_t row = k + quarter;
+        f32x4 a[2];
+        float b[NT];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int64_t m = m0 + 64 * u + 4 * l16 + c;
+                a[u][c] = row < k_end && m < g.M ? A[row * g.lda + m] : 0.f;
+            }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[j] = row < k_end && 16 * j + l16 < g.N ? B[row * g.ldb + 16 * j + l16] : 0.f;
+        multiply(a, b);
+        if (sums)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) bsum[j] += static_cast<double>(b[j]);
+    }
+    if (sums) {
+        double (*bred)[NT * 16] = reinterpret_cast<double (*)[NT * 16]>(red);        // [16 groups of lanes][columns]
+#pragma unroll
+        for (int j = 0; j < NT; ++j) bred[4 * wave + quarter][16 * j + l16] = bsum[j];
+        __syncthreads();
+        const int c = threadIdx.x;
+        if (c < NT * 16 && c < g.N) {
+            double t = 0.0;
+            for (int y = 0; y < 16; ++y) t += bred[y][c];
+            g.colpart[bz * g.N + c] = static_cast<float>(t);
+        }
+    }
+    // every wave adds up the tiles (u, wave, j) of all four, in wave order.  Register r of tile (u, c, j): row 64 u + 16 quarter +
+    // 4 r + c, column 16 j + l16
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) red[wave][c * NT + j][lane] = acc[u][c][j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            f32x4 t = red[0][wave * NT + j][lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) t += red[w][wave * NT + j][lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t m = m0 + 64 * u + 16 * quarter + 4 * r + wave;
+                if (m < g.M && 16 * j + l16 < g.N) g.part[(static_cast<int64_t>(bz) * g.M + m) * g.N + 16 * j + l16] = t[r];
+            }
+        }
+    }
+}
+
 // Plain fp32 products of middling size (the 128-row tiles of gemm_split_kernel would not fill the chip): 64 x 64 tiles with
 // four waves, a 32 x 32 part each.  Both operands are cut here, the second one as well, which saves the launch that cuts a
 // weight matrix beforehand (4-5 us, a third of such a product).  Two LDS buffers and operands fetched two steps ahead: one
@@ -1782,8 +1933,17 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, con
         return;
     }
     float v = 0.f;
-    if (t < total)
-        for (int z = ty; z < S; z += 8) v += g.part[static_cast<int64_t>(z) * total + t];
+    if (t < total) {
+        int z = ty;
+        for (; z + 56 < S; z += 64) {                   // eight loads on their way, added in order
+            float q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = g.part[static_cast<int64_t>(z + 8 * u) * total + t];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += q[u];
+        }
+        for (; z < S; z += 8) v += g.part[static_cast<int64_t>(z) * total + t];
+    }
     red[ty][tx] = v;
     __syncthreads();
     if (ty != 0 || t >= total) return;
@@ -1917,6 +2077,26 @@ static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t
     *S = static_cast<int>((K + *k_chunk - 1) / *k_chunk);
 }
 
+// Which reductions over vertices take gemm_narrow_kernel: those of 16384 vertices and more.  us, gemm_small_kernel (up to 2^31
+// multiply-adds) or gemm_kernel -> here: 128 x 32 x 21557 13.7 -> 13.0, 50 x 41 x 21557 17.8 -> 13.9, 128 x 47 x 50000 26 -> 18, 256 x
+// 41 x 180000 97 -> 57, 602 x 41 x 60000 88 -> 52, 200 x 16 x 250000 66 -> 42, 256 x 47 x 306000 164 -> 100 (3.7 TB/s), 602 x 64 x
+// 250000 276 -> 219; below, where few batches leave most of the time to the start: 100 x 64 x 9973 12.9 -> 13.2, 128 x 64 x 8192
+// 11.2 -> 14.2, 64 x 7 x 9973 10.0 -> 9.9.
+static bool narrow_product(int dtype, int mode, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K) {
+    return dtype == CAPGNN_F32 && trans_a && !trans_b && N <= 64 && mode != CAPGNN_F32_PRODUCT_SPLIT && K >= 16384;
+}
+
+// Its splits: the workgroups that the chip holds (two or three per compute unit), each wave with NARROW_AHEAD batches at least, in eights, as far as
+// the workspace goes (0: not even one split)
+static int narrow_splits(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+    const int64_t gy = (M + 127) / 128;
+    int64_t s = std::min<int64_t>((N <= 32 ? 3 : 2) * NUM_CU / gy, K / 64);
+    if (s > 8) s = s / 8 * 8;
+    s = std::max<int64_t>(s, 1);
+    const size_t one = static_cast<size_t>(M * N + N) * sizeof(float) + 256;
+    return static_cast<int>(std::min<int64_t>(s, static_cast<int64_t>(ws_bytes / one)));
+}
+
 // AUTO: smaller products stay on the fp32 instruction (the caller is told the limit), and so do weight gradients at most 64
 // columns wide (half of the threads that stage their operands would idle; measured slower)
 static bool split_form(int mode, int trans_a, int64_t M, int64_t N, int64_t K) {
@@ -1993,6 +2173,13 @@ static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, 
 #undef CG_SMALL_CASE
 }
 
+static void launch_narrow(const SmallGemmArgs &s, dim3 grid, hipStream_t st) {
+    if (s.g.N <= 16) hipLaunchKernelGGL(gemm_narrow_kernel<1>, grid, dim3(256), 0, st, s);
+    else if (s.g.N <= 32) hipLaunchKernelGGL(gemm_narrow_kernel<2>, grid, dim3(256), 0, st, s);
+    else if (s.g.N <= 48) hipLaunchKernelGGL(gemm_narrow_kernel<3>, grid, dim3(256), 0, st, s);
+    else hipLaunchKernelGGL(gemm_narrow_kernel<4>, grid, dim3(256), 0, st, s);
+}
+
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
@@ -2037,6 +2224,12 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         small_path = false;
         S = choose_split(trans_a, M, N, K, bm, bn, bk, true);
     }
+    const bool narrow = narrow_product(dtype, mode, trans_a, trans_b, M, N, K) && ws && narrow_splits(M, N, K, ws_bytes) > 0;
+    if (narrow) {
+        small_path = false;
+        S = narrow_splits(M, N, K, ws_bytes);
+        bn = 64;
+    }
     if (small_path) {
         bm = 32;
         bn = 32 * tn;
@@ -2066,9 +2259,13 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         g.k_chunk = (steps + S - 1) / S * bk;
     }
     if (small_path) g.k_chunk = small_chunk;
+    if (narrow) {
+        g.part = static_cast<float *>(ws);
+        g.k_chunk = ((K + S - 1) / S + 15) / 16 * 16;      // (the last splits may be empty: zeros)
+    }
     g.colpart = nullptr;
     if (colsum) {
-        const size_t at = S > 1 ? align_up(static_cast<size_t>(S) * M * N * sizeof(float), 256) : 0;
+        const size_t at = S > 1 || narrow ? align_up(static_cast<size_t>(S) * M * N * sizeof(float), 256) : 0;
         const size_t need = at + static_cast<size_t>(S) * N * sizeof(float);
         if (!ws || ws_bytes < need) CG_FAIL(CAPGNN_ENOMEM, "gemm: workspace of %zu bytes needed, %zu given", need, ws_bytes);
         g.colpart = reinterpret_cast<float *>(static_cast<char *>(ws) + at);
@@ -2087,7 +2284,11 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                              ws_bytes >= static_cast<size_t>(split_rows(N)) * stream_units(K) * 32 && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
-    if (small_path) {
+    if (narrow) {
+        SmallGemmArgs sm{};
+        sm.g = g;
+        launch_narrow(sm, grid, stream);
+    } else if (small_path) {
         SmallGemmArgs sm{};
         sm.g = g;
         sm.M2 = M;
@@ -2135,8 +2336,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 #undef CG_GEMM_CASE
     }
     CG_HIP(hipGetLastError());
-    if (S > 1 || colsum) {
-        const int64_t blocks = (S > 1 ? (M * N + 31) / 32 : 0) + (colsum ? (N + 31) / 32 : 0);
+    if (S > 1 || colsum || narrow) {
+        const int64_t blocks = (S > 1 || narrow ? (M * N + 31) / 32 : 0) + (colsum ? (N + 31) / 32 : 0);
         hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, g, S,
                            static_cast<const float *>(nullptr), static_cast<char *>(nullptr), int64_t(0), colsum);
         CG_HIP(hipGetLastError());
@@ -2155,6 +2356,10 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
     const int64_t Ksum = g.K + (s.dual ? s.K2 : 0);       // (the waves of a workgroup share it)
     const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
+    // two narrow reductions over vertices
+    const size_t half_ws = ws_bytes / 2 / 256 * 256;
+    const int narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K)
+                           ? narrow_splits(g.M, g.N, g.K, half_ws) : 0;
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     // the three-piece form on the terms of launch_gemm and launch_gemm_dual
     const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&
@@ -2162,12 +2367,19 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
                                : split_form(f32_product, 0, g.M, g.N, g.K) && split_form(f32_product, 0, s.M2, g.N, g.K));
     const bool mid = !small && split && tiles64 * (pair ? 2 : 1) <= 768 &&
                      std::max(std::max(g.lda, s.lda2), std::max(g.ldb, s.ldb2)) < (1 << 22);
-    if ((!small && !mid) || g.K <= 0 || (s.dual && s.K2 <= 0)) return CAPGNN_OK;
+    if ((!small && !mid && !narrow) || g.K <= 0 || (s.dual && s.K2 <= 0)) return CAPGNN_OK;
     int tn = 2, S = 1;
     g.k_chunk = Ksum;
-    if (small) small_geometry(bf, trans_a, g.M, g.N, g.K, &tn, &S, &g.k_chunk);
+    if (narrow) {
+        S = narrow;
+        g.k_chunk = ((g.K + S - 1) / S + 15) / 16 * 16;
+        g.part = static_cast<float *>(ws);
+        s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + half_ws);
+        if (colsum) g.colpart = g.part + static_cast<size_t>(S) * g.M * g.N;
+    } else if (small) small_geometry(bf, trans_a, g.M, g.N, g.K, &tn, &S, &g.k_chunk);
     if (s.dual && S > 1) return CAPGNN_OK;           // a sum is formed by the waves of one workgroup
-    if (S > 1) {
+    if (narrow) {
+    } else if (S > 1) {
         const size_t one = align_up(static_cast<size_t>(S) * g.M * g.N * sizeof(float), 256);
         if (g.M != s.M2 || !ws || ws_bytes < 2 * one + static_cast<size_t>(S) * g.N * sizeof(float)) return CAPGNN_OK;
         g.part = static_cast<float *>(ws);
@@ -2182,17 +2394,18 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     g.a_vec = vec_rows(g.A, g.lda) && vec_rows(s.A2, s.lda2);
     g.b_vec = vec_rows(g.B, g.ldb) && vec_rows(s.B2, s.ldb2);
     g.out_bf16 = bf && !out_f32;
-    const int bm = small ? 32 : 64, bn = small ? 32 * tn : 64;
+    const int bm = narrow ? 128 : small ? 32 : 64, bn = narrow || !small ? 64 : 32 * tn;
     const int64_t gy = (std::max(g.M, s.M2) + bm - 1) / bm, gx = (g.N + bn - 1) / bn;
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
     const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     const dim3 grid(static_cast<unsigned>(n_wg), pair ? 2 : 1, 1);
-    if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
+    if (narrow) launch_narrow(s, grid, stream);
+    else if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
     else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
     else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
-    if (S > 1 || colsum)
+    if (S > 1 || colsum || narrow)
         hipLaunchKernelGGL(gemm_reduce_kernel,
-                           dim3(static_cast<unsigned>((S > 1 ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), pair ? 2 : 1),
+                           dim3(static_cast<unsigned>((S > 1 || narrow ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), pair ? 2 : 1),
                            dim3(256), 0, stream, g, S, static_cast<const float *>(s.part2), s.C2, s.ldc2, colsum);
     CG_HIP(hipGetLastError());
     *done = true;

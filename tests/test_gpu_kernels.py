@@ -676,6 +676,59 @@ def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
         assert torch.equal(Cd[:, :N].float(), ref) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 16384), (3, 7, 16385), (64, 16, 16387), (100, 17, 20003), (127, 32, 16447), (128, 33, 16449), (130, 41, 30001),
+                                   (257, 48, 16400), (602, 49, 17000), (255, 64, 65537)])
+def test_gemm_f32_narrow_vertex_reduction_exact(env, M, N, K):
+    """X^T G in float with at most 64 columns over 16384 vertices and more: tiles of 16 columns and of 128 rows whole and ragged, K around
+    batches and splits, rows aligned and not, workspace as asked for and for two splits only, accumulating and with bias and ReLU.
+    Small integers (sums below 2^24): equality.  Padding is NaN; the last rows end with the allocation."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    A, G = (torch.randint(-3, 4, (K, w), generator=gen, device="cuda").float() for w in (M, N))
+    ref = A.double().T @ G.double()
+    bias = torch.randint(-9, 9, (N,), generator=gen, device="cuda").float()
+    wsb = B.gemm_workspace_bytes(1, M, N, K)
+    for pad in (0, 1, 4):
+        flat = lambda x: torch.cat([torch.nn.functional.pad(x[:-1], (0, pad), value=float("nan")).reshape(-1), x[-1]])  # noqa: E731
+        Ad, Gd = flat(A), flat(G)
+        for room, accumulate, relu in ((wsb, 0, 0), (wsb, 1, 1), (2 * (M * N + N) * 4 + 512, 0, 0)):
+            say(f"gemm narrow X^T G {M}x{N}x{K} pad={pad} workspace={room} accumulate={accumulate}")
+            ws = torch.empty(room, dtype=torch.uint8, device="cuda")
+            Cd = torch.full((M, N + 3), 2.0, device="cuda")
+            B.gemm(1, 0, M, N, K, Ad, M + pad, Gd, N + pad, Cd, N + 3, B.F32, accumulate=accumulate, bias=bias if relu else None, relu=relu,
+                   ws=ws, ws_bytes=room)
+            torch.cuda.synchronize()
+            want = (ref + 2.0 + bias).clamp(min=0) if accumulate else ref
+            assert torch.equal(Cd[:, :N].double(), want) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("n,f_in,f_out", [(16384, 100, 41), (20001, 130, 64), (40000, 64, 8)])
+def test_layer_narrow_weight_gradients_exact(env, n, f_in, f_out):
+    """Both weight gradients and the bias gradient of a GraphSAGE layer with at most 64 outputs, over 16384 vertices and more, one entry
+    of weight one per row.  Small integers: equality."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(n)
+    col = rng.integers(0, n, n).astype(np.int32)
+    g = B.Graph(n, 0, np.arange(0, n + 1, dtype=np.int64), col, np.ones(n, np.float32), np.ones(n, np.float32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    x, dh = (torch.randint(-3, 4, (n, w), generator=gen, device="cuda").float() for w in (f_in, f_out))
+    w, w_self = (torch.zeros(f_in, f_out, device="cuda") for _ in range(2))
+    l = B.make_layer(B.SAGE_MEAN, f_in, f_out, B.ACT_NONE, B.F32, w, w_self, torch.zeros(f_out, device="cuda"), B.AGG_FIRST)
+    saved = torch.empty(B.layer_saved_bytes(g, l), dtype=torch.uint8, device="cuda")
+    wsb = B.layer_workspace_bytes(g, l)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    h, dw, dws, db = torch.zeros(n, f_out, device="cuda"), torch.zeros_like(w), torch.zeros_like(w), torch.zeros(f_out, device="cuda")
+    say(f"narrow weight gradients of a layer {n} {f_in}->{f_out}")
+    B.layer_fwd(g, l, x, f_in, h, f_out, saved, ws, wsb, None)
+    B.layer_bwd(g, l, x, f_in, h, f_out, saved, dh.clone(), f_out, dw, dws, db, None, 0, False, ws, wsb, None)
+    torch.cuda.synchronize()
+    m = x[torch.from_numpy(col).long().cuda()]
+    assert torch.equal(dw.double(), m.double().T @ dh.double()) and torch.equal(dws.double(), x.double().T @ dh.double())
+    assert torch.equal(db.double(), dh.double().sum(0))
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
