@@ -109,17 +109,9 @@ struct TierRows {
     unsigned blocks;
 };
 
-// One launch serves up to two tiers of the same layer (same pitch and row geometry): workgroups [0, a.blocks) take
-// tier a, the rest tier b.
 template <int R>
-__global__ __launch_bounds__(256) void scatter_tier_kernel(TierRows a, TierRows b, int64_t pitch, char *out,
-                                                           int64_t out_pitch, int row_bytes, int lpr, int vec16, int es) {
-    const bool second = blockIdx.x >= a.blocks;            // uniform over the workgroup
-    const char *table = second ? b.table : a.table;
-    const int32_t *dst_list = second ? b.dst_list : a.dst_list;
-    const int64_t n = second ? b.n : a.n;
-    const unsigned blocks = second ? b.blocks : a.blocks;
-    const unsigned bx = second ? blockIdx.x - a.blocks : blockIdx.x;
+__device__ __forceinline__ void scatter_rows(const char *table, const int32_t *dst_list, int64_t n, unsigned blocks, unsigned bx, int64_t pitch,
+                                             char *out, int64_t out_pitch, int row_bytes, int lpr, int vec16, int es) {
     const int lane = threadIdx.x & 63;
     const int l = lane % lpr;
     const int rows_per_wave = 64 / lpr;
@@ -182,6 +174,36 @@ __global__ __launch_bounds__(256) void scatter_tier_kernel(TierRows a, TierRows 
             }
         }
     }
+}
+
+// One launch serves up to two tiers of the same layer (same pitch and row geometry): workgroups [0, a.blocks) take
+// tier a, the rest tier b.
+template <int R>
+__global__ __launch_bounds__(256) void scatter_tier_kernel(TierRows a, TierRows b, int64_t pitch, char *out,
+                                                           int64_t out_pitch, int row_bytes, int lpr, int vec16, int es) {
+    const bool second = blockIdx.x >= a.blocks;            // uniform over the workgroup
+    scatter_rows<R>(second ? b.table : a.table, second ? b.dst_list : a.dst_list, second ? b.n : a.n, second ? b.blocks : a.blocks,
+                    second ? blockIdx.x - a.blocks : blockIdx.x, pitch, out, out_pitch, row_bytes, lpr, vec16, es);
+}
+
+// The GPU tier's rows of several layers, one row per lane group: workgroups [first, first + blocks) work on a layer.
+struct LayerRows {
+    const char *table;
+    char *out;
+    int64_t pitch, out_pitch;
+    unsigned first, blocks;
+    int row_bytes, lpr, vec16;
+};
+constexpr int SCATTER_LAYERS = 4;
+struct LayerList {
+    LayerRows l[SCATTER_LAYERS];
+    int count;
+};
+__global__ __launch_bounds__(256) void scatter_layers_kernel(LayerList s, const int32_t *dst_list, int64_t n, int es) {
+    int t = 0;
+    while (t + 1 < s.count && blockIdx.x >= s.l[t + 1].first) ++t;
+    const LayerRows &l = s.l[t];
+    scatter_rows<1>(l.table, dst_list, n, l.blocks, blockIdx.x - l.first, l.pitch, l.out, l.out_pitch, l.row_bytes, l.lpr, l.vec16, es);
 }
 
 // request-list gather with lookup; which: bit0 = serve GPU-tier rows (and absent ids), bit1 = serve host-tier rows
@@ -408,6 +430,31 @@ int gather_all_hits(const capgnn_cache *c, int layer, void *out, int64_t ld, hip
     const char *tab = c->gpu_tier + c->gpu_off[layer];
     CG_TRY(copy_geom(c, layer, out, ld, tab, &g));
     return launch_scatter(g, c->pitch[layer], {tab, c->gpu_list_d, c->cap_gpu, 0}, {nullptr, nullptr, 0, 0}, 0, out, st);
+}
+
+// Up to SCATTER_ALL bytes the layers' rows go in one launch at the start: copies this small are mostly their launches (a 4096-vertex
+// epoch: two of 3-4 us).  Larger ones keep to their layer, which then finds the rows in the caches.
+constexpr int64_t SCATTER_ALL = int64_t(8) << 20;
+int gather_all_hits_of_layers(const capgnn_cache *c, int L, char *const *out, const int64_t *ld, hipStream_t st, bool *done) {
+    *done = false;
+    if (c->cap_gpu == 0 || L < 2 || L > SCATTER_LAYERS) return CAPGNN_OK;
+    LayerList s{};
+    int64_t bytes = 0;
+    unsigned blocks = 0;
+    for (int l = 0; l < L; ++l) {
+        CopyGeom g;
+        const char *tab = c->gpu_tier + c->gpu_off[l];
+        CG_TRY(copy_geom(c, l, out[l], ld[l], tab, &g));
+        const unsigned nb = scatter_blocks_for(c->cap_gpu, g.lpr, 1);
+        s.l[s.count++] = {tab, out[l], c->pitch[l], g.out_pitch, blocks, nb, g.row_bytes, g.lpr, g.vec16};
+        blocks += nb;
+        bytes += c->cap_gpu * g.row_bytes;
+    }
+    if (bytes > SCATTER_ALL) return CAPGNN_OK;
+    hipLaunchKernelGGL(scatter_layers_kernel, dim3(blocks), dim3(256), 0, st, s, c->gpu_list_d, c->cap_gpu, elem_bytes(c->dtype));
+    CG_HIP(hipGetLastError());
+    *done = true;
+    return CAPGNN_OK;
 }
 
 // Both device-resident sources of one layer's halo rows in one launch: the GPU tier and the staged copy of the host

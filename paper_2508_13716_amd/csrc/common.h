@@ -162,6 +162,28 @@ struct LiveRows {
 };
 
 // ---- kernels' host-side launchers (each validates what its kernel assumes) ----
+// What is left to add up at the end of an epoch, and the SGD step, for one launch (see epoch_finish_kernel in ops.hip).
+struct FinishTask {
+    enum Kind : int { SUM, COLUMNS, LOSS_COLUMNS, LOSS, UPDATE };
+    int kind, S;                // S partial results ...
+    int64_t n;                  // ... of n numbers each
+    const void *part;           // [S][n] float; LOSS: [S] double, UPDATE: [n] float, the gradient
+    float *out, *out2;          // their sums; LOSS: the loss, and where else it goes, or null
+    float *W;                   // W -= lr * sum, or null
+    const float *norm_dev;      // LOSS: the normaliser (norm_dev, or norm_val where that is null)
+    float norm_val;
+    unsigned first;             // filled by launch_finish
+};
+struct FinishList {
+    static constexpr int MOST = 48;
+    FinishTask task[MOST];
+    int count = 0;
+    bool full() const { return count >= MOST; }
+};
+// lr != 0: also the tensors of `sgd`, in their order where some share memory
+struct SgdList;
+int launch_finish(FinishList *list, const SgdList *sgd, float lr, hipStream_t stream);
+
 struct SpmmEpilogue {
     const float *bias = nullptr;   // [F] added after scaling
     int relu = 0;
@@ -190,7 +212,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
                 hipStream_t stream, const float *row_scale = nullptr,    // row_scale: C[i,:] *= row_scale[i] at the very end (fp32 C)
                 int f32_product = CAPGNN_F32_PRODUCT_AUTO,
-                float *colsum = nullptr);                                // [N] column sums of B (trans_a && !trans_b only)
+                float *colsum = nullptr,                                 // [N] column sums of B (trans_a && !trans_b only)
+                FinishList *later = nullptr);                            // takes the sum over splits, whose parts stay in ws, if it can
 // C = A op(W) + A2 op(W2) (+ bias, ReLU), one launch where a kernel forms the sum, else the two launches it replaces
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
@@ -200,7 +223,7 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product, float *colsum = nullptr);
+                     int f32_product, float *colsum = nullptr, FinishList *later = nullptr);
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K);
 // scratch that lets launch_gemm_dual run as one launch
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2);
@@ -225,7 +248,7 @@ int launch_sgd(const SgdList &all, float lr, hipStream_t stream);
 // the loss of an epoch on labels or targets, with what else can be had on the way (see ops.hip)
 int loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
                const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy, float *dbias,
-               const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st);
+               const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st, FinishList *later = nullptr);
 size_t loss_epoch_ws_bytes(int64_t n, int C);
 bool loss_sums_columns(int C);      // whether loss_epoch can form dbias
 
@@ -233,6 +256,8 @@ uint64_t hash_gid(uint64_t x);
 
 // full-batch gather of one layer's halo rows, one tier at a time (used by the epoch's two-stream schedule)
 int gather_all_hits(const capgnn_cache *c, int layer, void *out, int64_t ld, hipStream_t st);
+// the same for the first L layers in one launch, where that is a few small copies; *done says whether it was
+int gather_all_hits_of_layers(const capgnn_cache *c, int L, char *const *out, const int64_t *ld, hipStream_t st, bool *done);
 int gather_all_misses(const capgnn_cache *c, int layer, void *out, int64_t ld, void *staging, hipStream_t st);
 // the two halves of the staged path: DMA of the layer's host tier into the staging area, scatter from there
 int stage_misses(const capgnn_cache *c, int layer, void *staging, hipStream_t st);

@@ -1966,6 +1966,22 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, con
     else reinterpret_cast<float *>(g.C)[row * g.ldc + col] = v;
 }
 
+// Leaves the sums of gemm_reduce_kernel (and of a pair's second problem) to the end of the epoch; false where it does more than sum.
+static bool reduce_later(FinishList *later, const GemmArgs &g, int S, const float *part2, char *C2, int64_t ldc2, float *colsum) {
+    if (g.accumulate || g.bias || g.relu || g.mask || g.rscale || g.out_bf16 || (g.part && g.ldc != g.N) || (part2 && ldc2 != g.N) ||
+        later->count + 3 > FinishList::MOST)
+        return false;
+    auto add = [&](FinishTask::Kind kind, const float *part, int64_t n, void *out) {
+        FinishTask t{};
+        t.kind = kind; t.S = S; t.n = n; t.part = part; t.out = static_cast<float *>(out);
+        later->task[later->count++] = t;
+    };
+    if (g.part) add(FinishTask::SUM, g.part, g.M * g.N, g.C);
+    if (part2) add(FinishTask::SUM, part2, g.M * g.N, C2);
+    if (colsum) add(FinishTask::COLUMNS, g.colpart, g.N, colsum);
+    return true;
+}
+
 static int choose_split(int trans_a, int64_t M, int64_t N, int64_t K, int bm, int bn, int bk, bool coarse = false) {
     if (!trans_a) return 1;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -2183,7 +2199,7 @@ static void launch_narrow(const SmallGemmArgs &s, dim3 grid, hipStream_t st) {
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
-                hipStream_t stream, const float *row_scale, int f32_product, float *colsum) {
+                hipStream_t stream, const float *row_scale, int f32_product, float *colsum, FinishList *later) {
     if (colsum && (!trans_a || trans_b)) CG_FAIL(CAPGNN_EINVAL, "gemm: column sums are formed by X^T G alone");
     if (dtype != CAPGNN_F32 && dtype != CAPGNN_BF16) CG_FAIL(CAPGNN_EINVAL, "gemm: unknown dtype %d", dtype);
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
@@ -2336,7 +2352,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 #undef CG_GEMM_CASE
     }
     CG_HIP(hipGetLastError());
-    if (S > 1 || colsum || narrow) {
+    if ((S > 1 || colsum || narrow) && !(later && reduce_later(later, g, S, nullptr, nullptr, 0, colsum))) {
         const int64_t blocks = (S > 1 || narrow ? (M * N + 31) / 32 : 0) + (colsum ? (N + 31) / 32 : 0);
         hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, g, S,
                            static_cast<const float *>(nullptr), static_cast<char *>(nullptr), int64_t(0), colsum);
@@ -2349,7 +2365,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 // C = op(A) op(B) and C2 = op(A2) op(B2) of one shape but for the rows (pair).  *done says whether the sizes are such a kernel's;
 // nothing has run otherwise.
 static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, int dtype, int out_f32, void *ws, size_t ws_bytes,
-                            hipStream_t stream, int f32_product, float *colsum, bool *done) {
+                            hipStream_t stream, int f32_product, float *colsum, bool *done, FinishList *later = nullptr) {
     *done = false;
     SmallGemmArgs s = in;
     GemmArgs &g = s.g;
@@ -2403,7 +2419,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     else if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
     else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
     else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
-    if (S > 1 || colsum || narrow)
+    if ((S > 1 || colsum || narrow) && !(later && reduce_later(later, g, S, pair ? s.part2 : nullptr, s.C2, s.ldc2, colsum)))
         hipLaunchKernelGGL(gemm_reduce_kernel,
                            dim3(static_cast<unsigned>((S > 1 || narrow ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), pair ? 2 : 1),
                            dim3(256), 0, stream, g, S, static_cast<const float *>(s.part2), s.C2, s.ldc2, colsum);
@@ -2417,7 +2433,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product, float *colsum) {
+                     int f32_product, float *colsum, FinishList *later) {
     if (M2 > M) CG_FAIL(CAPGNN_EINVAL, "gemm_pair: the second product has more rows");
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
@@ -2434,12 +2450,14 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
     const bool apart = c1 + ((M - 1) * ldc + N) * es_c <= c2 || c2 + ((M2 - 1) * ldc2 + N) * es_c <= c1;
     if (apart && M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
         lda2 >= (trans_a ? M : K) && ldb >= (trans_b ? K : N) && ldb2 >= (trans_b ? K : N))
-        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done));
+        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done, later));
     if (done) return CAPGNN_OK;
-    CG_TRY(launch_gemm(trans_a, trans_b, M, N, K, A, lda, B, ldb, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes, stream,
-                       row_scale, f32_product, colsum));
-    return launch_gemm(trans_a, trans_b, M2, N, K, A2, lda2, B2, ldb2, C2, ldc2, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws, ws_bytes,
-                       stream, nullptr, f32_product);
+    // (parts that are added up later keep half of the workspace each)
+    const size_t half = later ? ws_bytes / 2 / 256 * 256 : 0;
+    CG_TRY(launch_gemm(trans_a, trans_b, M, N, K, A, lda, B, ldb, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws,
+                       later ? half : ws_bytes, stream, row_scale, f32_product, colsum, later));
+    return launch_gemm(trans_a, trans_b, M2, N, K, A2, lda2, B2, ldb2, C2, ldc2, dtype, out_f32, 0, nullptr, 0, nullptr, 0,
+                       ws ? static_cast<char *>(ws) + half : nullptr, ws_bytes - half, stream, nullptr, f32_product, nullptr, later);
 }
 
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return (trans_a ? 2 : 1) * gemm_ws_bytes(trans_a, M, N, K); }

@@ -217,6 +217,9 @@ struct BwdFusion {
     const void *dx_mask = nullptr;  // zero dX where this is not positive (storage type of the layer)
     int64_t ld_mask = 0;
     LiveRows live;                  // rows of dH that may differ from zero
+    FinishList *later = nullptr;    // takes the sums over the splits of the weight gradients, whose parts stay in later_ws until then
+    char *later_ws = nullptr;
+    size_t later_bytes = 0;
 };
 
 // The transposed aggregation gathers dZ itself and wants its rows multiplied by their scale (layer_bwd_impl).
@@ -289,6 +292,11 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
                                           scale_dz && !fuse.ready ? g->bwd.in_scale : nullptr));
         }
     }
+    // workspace of the weight gradients: two halves where they are formed apart and added up later
+    FinishList *later = fuse.later && fuse.later_bytes ? fuse.later : nullptr;
+    const size_t w_half = later && sage ? fuse.later_bytes / 2 / 256 * 256 : 0;
+    void *ws_w[2] = {later ? fuse.later_ws : ws_gemm, later ? fuse.later_ws + w_half : ws_gemm};
+    const size_t wb[2] = {later ? (sage ? w_half : fuse.later_bytes) : gw, later ? w_half : gw};
     if (order == CAPGNN_AGG_FIRST) {
         if (!saved) CG_FAIL(CAPGNN_EINVAL, "layer_bwd: saved is NULL");
         const int64_t ldm = pad_ld(g, l->f_in, dt);
@@ -296,13 +304,14 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
             Scope s(CAPGNN_K_GEMM, li, 1, st);
             if (sage && dW && dW_self) {
                 CG_TRY(launch_gemm_pair(1, 0, l->f_in, l->f_in, l->f_out, g->n_loc, saved, ldm, X, ldx, dHb, lddhb, dHb, lddhb, dW, l->f_out,
-                                        dW_self, l->f_out, dt, 1, nullptr, ws_gemm, gw, st, l->f32_product, gemm_db));
+                                        dW_self, l->f_out, dt, 1, nullptr, ws_w[0], later ? fuse.later_bytes : gw, st, l->f32_product,
+                                        gemm_db, later));
             } else {
                 if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, saved, ldm, dHb, lddhb, dW, l->f_out, dt, 1, 0,
-                                           nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product, gemm_db));
+                                           nullptr, 0, nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, gemm_db, later));
                 if (sage && dW_self)
                     CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0,
-                                       nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                                       nullptr, 0, nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, nullptr, later));
             }
             // dM = dZ W^T; the self term dZ W_self^T goes to dX, where the transposed aggregation of dM is added to it
             if (dX && sage)
@@ -336,10 +345,10 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     }
     Scope s(CAPGNN_K_GEMM, li, 1, st);
     if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_cols, X, ldx, tmp, ldt, dW, l->f_out, dt, 1, 0, nullptr, 0,
-                               nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
+                               nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, nullptr, later));
     if (sage && dW_self)
         CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0, nullptr, 0,
-                           nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product, gemm_db));
+                           nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, gemm_db, later));
     if (dX) {
         const int64_t rows = need_halo_grad ? g->n_cols : g->n_loc;
         if (sage && !need_halo_grad) {
@@ -360,11 +369,14 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
 struct EpochPlan {
     std::vector<int> order;
     std::vector<int64_t> ldx;          // leading dimension of layer l's input
-    std::vector<size_t> x_off, saved_off;
+    std::vector<size_t> x_off, saved_off, later_off, later_bytes;     // later: parts of weight gradients kept to the epoch's end
     size_t logits_off = 0, dz32_off = 0, grad_off[2] = {0, 0}, layer_ws_off = 0, layer_ws_bytes = 0, loss_ws_off = 0,
            loss_val_off = 0, staging_off = 0, total = 0;
     int64_t ld_grad = 0, ldz = 0;
 };
+
+// Most bytes of parts for that: beyond, a sum of its own follows each product, which finds the parts in the caches.
+constexpr size_t LATER_BYTES = size_t(64) << 20;
 
 static int plan_epoch(const capgnn_graph *g, const capgnn_cache *c, const capgnn_layer *layers, int L, int64_t ld0,
                       EpochPlan *p) {
@@ -393,6 +405,21 @@ static int plan_epoch(const capgnn_graph *g, const capgnn_cache *c, const capgnn
     p->layer_ws_off = take(lws);
     p->loss_ws_off = take(loss_epoch_ws_bytes(g->n_loc, layers[L - 1].f_out));
     p->loss_val_off = take(256);
+    // few bytes of parts: their sums wait for the epoch's last launch, so each layer keeps its own
+    p->later_off.assign(L, 0); p->later_bytes.assign(L, 0);
+    size_t later = 0;
+    for (int l = 0; l < L; ++l) {
+        const capgnn_layer *ly = &layers[l];
+        const bool sage = ly->kind == CAPGNN_SAGE_MEAN;
+        const int64_t red_rows = p->order[l] == CAPGNN_AGG_FIRST ? g->n_loc : g->n_cols;
+        p->later_bytes[l] = (sage ? 2 : 1) * align_up(std::max(gemm_ws_bytes(1, ly->f_in, ly->f_out, red_rows),
+                                                               gemm_ws_bytes(1, ly->f_in, ly->f_out, g->n_loc)), 256);
+        later += p->later_bytes[l];
+    }
+    for (int l = 0; l < L; ++l) {
+        if (later > LATER_BYTES) p->later_bytes[l] = 0;
+        p->later_off[l] = take(p->later_bytes[l]);
+    }
     if (c && c->miss_mode != CAPGNN_MISS_ZEROCOPY) {
         size_t hb = 0;
         for (int l = 0; l < c->n_layers; ++l) hb += align_up(static_cast<size_t>(c->n_host) * c->pitch[l], 256);
@@ -495,11 +522,29 @@ struct EpochEvents {
     bool capture = false;
 };
 
+// No two gradients share memory: those that do are written in the order of the backward pass, none at the epoch's end.
+static bool gradients_apart(const capgnn_layer *layers, int L, float **dW, float **dW_self, float **dbias) {
+    const float *p[48];
+    int64_t n[48];
+    int count = 0;
+    auto add = [&](const float *q, int64_t m) { if (q) { p[count] = q; n[count++] = m; } };
+    for (int l = 0; l < L; ++l) {
+        const int64_t nw = static_cast<int64_t>(layers[l].f_in) * layers[l].f_out;
+        add(dW[l], nw);
+        add(dW_self && layers[l].kind == CAPGNN_SAGE_MEAN ? dW_self[l] : nullptr, nw);
+        add(dbias[l], layers[l].f_out);
+    }
+    for (int i = 0; i < count; ++i)
+        for (int j = 0; j < i; ++j)
+            if (p[i] < p[j] + n[j] && p[j] < p[i] + n[i]) return false;
+    return true;
+}
+
 static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer *layers, int L, void *X0,
                       int64_t ld0, const int32_t *labels, const uint8_t *targets, int64_t ldt, const uint8_t *mask,
                       double loss_norm, float *logits, float **dW, float **dW_self, float **dbias, float lr, float *loss_out,
                       capgnn_epoch_times *times, void *ws, size_t ws_bytes, void *stream, void *side_stream,
-                      const EpochEvents *own_events = nullptr) {
+                      const EpochEvents *own_events = nullptr, float *loss_copy = nullptr) {
     CG_TRY(check_epoch_args(g, c, layers, L));
     if (!X0 || (!labels && !targets) || !dW || !dbias) CG_FAIL(CAPGNN_EINVAL, "epoch: NULL argument");
     if (targets && ldt < layers[L - 1].f_out) CG_FAIL(CAPGNN_EINVAL, "epoch: ldt smaller than the number of classes");
@@ -572,11 +617,18 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
             }
         }
     }
+    // all layers' rows of the GPU tier at once where they are few (the recorder wants them layer by layer)
+    bool gathered = false;
+    if (c && c->n_host == 0 && !g_rec.on) {
+        std::vector<char *> rows(L);
+        for (int l = 0; l < L; ++l) rows[l] = halo_rows(l);
+        CG_TRY(gather_all_hits_of_layers(c, L, rows.data(), p.ldx.data(), st, &gathered));
+    }
     // forward
     for (int l = 0; l < L; ++l) {
         char *X = Xl(l);
         char *halo = halo_rows(l);
-        if (c) {
+        if (c && !gathered) {
             if (pipelined) {
                 // the staged rows landed while the previous epoch ran: both device-resident sources in one launch.  (In a
                 // recorded epoch the replay before this one ended only after its prefetches had: nothing to wait for.)
@@ -619,6 +671,8 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
     float *loss_dev = reinterpret_cast<float *>(w + p.loss_val_off);
     int cur = 0;
     BwdFusion fuse;
+    FinishList finish;
+    FinishList *later = gradients_apart(layers, L, dW, dW_self, dbias) ? &finish : nullptr;
     {
         Scope s(CAPGNN_K_LOSS, L - 1, 0, st);
         // a bf16 model gets the gradient in fp32 first (the bias gradient is summed before rounding)
@@ -637,7 +691,8 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
         CG_TRY(loss_epoch(g->n_loc, C, Z, ldz, labels, targets, ldt, mask, loss_norm, loss_dev, dz, lddz, dzt, logits,
                           fuse.dbias_done ? dbias[L - 1] : nullptr, scale && fuse.ready ? g->bwd.in_scale : nullptr,
                           skip ? &fuse.live : nullptr, w + p.loss_ws_off,
-                          loss_epoch_ws_bytes(g->n_loc, C), st));
+                          loss_epoch_ws_bytes(g->n_loc, C), st, later));
+        if (finish.count) finish.task[0].out2 = loss_copy;       // (the first task is the loss)
     }
     // backward
     for (int l = L - 1; l >= 0; --l) {
@@ -649,6 +704,7 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
         const bool f32grad = last && dt == CAPGNN_BF16;
         // sigma' of the layer below goes into the kernel that writes dX, unless that layer's own pass is needed to scale the rows
         const bool below = l > 0 && !scaled_dz(g, &layers[l - 1], p.order[l - 1]);
+        fuse.later = later; fuse.later_ws = w + p.later_off[l]; fuse.later_bytes = p.later_bytes[l];
         if (below && layers[l - 1].act == CAPGNN_ACT_RELU) { fuse.dx_mask = Xl(l); fuse.ld_mask = p.ldx[l]; }
         CG_TRY(layer_bwd_impl(g, &layers[l], p.order[l], l, Xl(l), p.ldx[l], Hl, ldh, w + p.saved_off[l],
                               f32grad ? static_cast<void *>(w + p.dz32_off) : static_cast<void *>(w + p.grad_off[cur]),
@@ -658,9 +714,8 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
         fuse.ready = below;
         cur ^= 1;
     }
+    SgdList sgd;
     if (lr != 0.f) {
-        Scope s(CAPGNN_K_ELEMENTWISE, 0, 1, st);
-        SgdList sgd;
         auto add = [&](void *w, const float *d, int64_t n) {
             sgd.W[sgd.count] = static_cast<float *>(w); sgd.dW[sgd.count] = d; sgd.n[sgd.count++] = n;
         };
@@ -670,7 +725,11 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
             if (layers[l].kind == CAPGNN_SAGE_MEAN && dW_self && dW_self[l]) add(layers[l].W_self, dW_self[l], nw);
             if (layers[l].bias && dbias[l]) add(layers[l].bias, dbias[l], layers[l].f_out);
         }
-        CG_TRY(launch_sgd(sgd, lr, st));
+    }
+    if (loss_copy && !finish.count) CG_HIP(hipMemcpyAsync(loss_copy, loss_dev, sizeof(float), hipMemcpyDeviceToDevice, st));
+    if (finish.count || sgd.count) {
+        Scope s(CAPGNN_K_ELEMENTWISE, 0, 1, st);
+        CG_TRY(launch_finish(&finish, &sgd, lr, st));
     }
     if (capture && has_miss && side != st) {
         // a recorded epoch ends when its side stream has: the prefetches for the next replay are part of this one
@@ -747,8 +806,6 @@ struct capgnn_epoch_graph {
     }
 };
 
-__global__ void copy_loss_kernel(const float *src, float *dst) { *dst = *src; }
-
 extern "C" int capgnn_epoch_graph_create(capgnn_epoch_graph **out, const capgnn_graph *g, capgnn_cache *c,
                                          const capgnn_layer *layers, int L, void *X0, int64_t ld0, const int32_t *labels,
                                          const uint8_t *mask, double loss_norm, float *logits, float **dW, float **dW_self,
@@ -775,13 +832,7 @@ extern "C" int capgnn_epoch_graph_create(capgnn_epoch_graph **out, const capgnn_
     CG_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     // the side stream joins the recording when it waits for the epoch's first event and is joined back at the end
     int rc = epoch_impl(g, c, layers, L, X0, ld0, labels, nullptr, 0, mask, loss_norm, logits, dW, dW_self, dbias, lr, nullptr,
-                        nullptr, ws, ws_bytes, stream, side_stream, &eg->ev);
-    if (rc == CAPGNN_OK && loss_dev) {
-        EpochPlan p;
-        plan_epoch(g, c, layers, L, ld0, &p);
-        hipLaunchKernelGGL(copy_loss_kernel, dim3(1), dim3(1), 0, st,
-                           reinterpret_cast<const float *>(static_cast<char *>(ws) + p.loss_val_off), loss_dev);
-    }
+                        nullptr, ws, ws_bytes, stream, side_stream, &eg->ev, loss_dev);
     const hipError_t e_end = hipStreamEndCapture(st, &eg->graph);       // always: the stream must leave capture mode
     if (rc != CAPGNN_OK) return rc;
     if (e_end != hipSuccess || !eg->graph) CG_FAIL(CAPGNN_EHIP, "epoch_graph_create: hipStreamEndCapture: %s", hipGetErrorString(e_end));

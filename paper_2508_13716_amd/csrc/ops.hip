@@ -654,6 +654,138 @@ __global__ __launch_bounds__(1024) void loss_final_kernel(int parts, const doubl
     column_sums(blockIdx.x - 1, parts, C, colpart, dbias, red);
 }
 
+// The end of an epoch in one launch: sums over the splits of every weight gradient (as gemm_reduce_kernel adds them), over the
+// loss's workgroups, and the SGD step, which the thread that has a sum applies.  They were a launch each (a 4096-vertex epoch: four
+// of fifteen, 3-4 us apiece; 81 -> 72 us with the gathers of all layers in one launch).  A workgroup takes 4 x 32 sums with eight
+// threads each, or 32 columns of the loss's with 32 threads each, or the loss, or 4096 elements of an update.
+constexpr int FINISH_UPDATES = 4096;
+__global__ __launch_bounds__(1024) void epoch_finish_kernel(FinishList list, float lr) {
+    __shared__ double red[1024];
+    int i = 0;
+    while (i + 1 < list.count && blockIdx.x >= list.task[i + 1].first) ++i;
+    const FinishTask &t = list.task[i];
+    const int64_t b = blockIdx.x - t.first;
+    if (t.kind == FinishTask::SUM || t.kind == FinishTask::COLUMNS) {
+        const int tx = threadIdx.x & 31, ty = (threadIdx.x >> 5) & 7, quarter = threadIdx.x >> 8;
+        const int64_t e = b * 128 + quarter * 32 + tx;
+        const float *part = static_cast<const float *>(t.part);
+        double v = 0.0;
+        if (e < t.n && t.kind == FinishTask::SUM) {
+            float f = 0.f;
+            int z = ty;
+            for (; z + 56 < t.S; z += 64) {
+                float q[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) q[u] = part[static_cast<int64_t>(z + 8 * u) * t.n + e];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f += q[u];
+            }
+            for (; z < t.S; z += 8) f += part[static_cast<int64_t>(z) * t.n + e];
+            v = f;
+        } else if (e < t.n) {
+            for (int z = ty; z < t.S; z += 8) v += static_cast<double>(part[static_cast<int64_t>(z) * t.n + e]);
+        }
+        double *r = red + quarter * 256;
+        r[ty * 32 + tx] = v;
+        __syncthreads();
+        if (ty != 0 || e >= t.n) return;
+        float sum;
+        if (t.kind == FinishTask::SUM) {
+            sum = 0.f;
+            for (int y = 0; y < 8; ++y) sum += static_cast<float>(r[y * 32 + tx]);
+        } else {
+            v = 0.0;
+            for (int y = 0; y < 8; ++y) v += r[y * 32 + tx];
+            sum = static_cast<float>(v);
+        }
+        t.out[e] = sum;
+        if (t.W) t.W[e] = t.W[e] - lr * sum;
+    } else if (t.kind == FinishTask::LOSS_COLUMNS) {
+        column_sums(static_cast<unsigned>(b), t.S, static_cast<int>(t.n), static_cast<const float *>(t.part), t.out, red);
+        const int64_t e = b * 32 + threadIdx.x;
+        if (threadIdx.x < 32 && e < t.n && t.W) t.W[e] = t.W[e] - lr * t.out[e];      // (the thread that wrote it)
+    } else if (t.kind == FinishTask::LOSS) {
+        const double *part = static_cast<const double *>(t.part);
+        double c = 0.0;
+        for (int k = threadIdx.x; k < t.S; k += 1024) c += part[k];
+        c = block_sum(c, red, 1024);
+        if (threadIdx.x == 0) {
+            const float loss = static_cast<float>(c / (t.norm_dev ? static_cast<double>(t.norm_dev[0]) : static_cast<double>(t.norm_val)));
+            t.out[0] = loss;
+            if (t.out2) t.out2[0] = loss;
+        }
+    } else {
+        const float *dW = static_cast<const float *>(t.part);
+        for (int64_t e = b * FINISH_UPDATES + threadIdx.x; e < t.n && e < (b + 1) * FINISH_UPDATES; e += 1024) t.W[e] = t.W[e] - lr * dW[e];
+    }
+}
+
+static int64_t finish_blocks(const FinishTask &t) {
+    switch (t.kind) {
+        case FinishTask::SUM: case FinishTask::COLUMNS: return (t.n + 127) / 128;
+        case FinishTask::LOSS_COLUMNS: return (t.n + 31) / 32;
+        case FinishTask::LOSS: return 1;
+        default: return (t.n + FINISH_UPDATES - 1) / FINISH_UPDATES;
+    }
+}
+
+static int launch_tasks(FinishList *l, float lr, hipStream_t stream) {
+    int64_t blocks = 0;
+    for (int i = 0; i < l->count; ++i) {
+        l->task[i].first = static_cast<unsigned>(blocks);
+        blocks += finish_blocks(l->task[i]);
+    }
+    if (blocks == 0) return CAPGNN_OK;
+    hipLaunchKernelGGL(epoch_finish_kernel, dim3(static_cast<unsigned>(blocks)), dim3(1024), 0, stream, *l, lr);
+    CG_HIP(hipGetLastError());
+    return CAPGNN_OK;
+}
+
+// Tasks of one launch run side by side.  Where tensors share memory (tied weights, a common bias, one buffer for two gradients) the
+// sums are written by one launch each, in their order, and launch_sgd follows, which keeps to the order of its own list.
+int launch_finish(FinishList *list, const SgdList *sgd, float lr, hipStream_t stream) {
+    FinishList l = *list;
+    bool apart = true;
+    if (lr != 0.f && sgd) {
+        for (int u = 0; u < sgd->count; ++u) {
+            if (!sgd->W[u] || !sgd->dW[u] || sgd->n[u] <= 0) CG_FAIL(CAPGNN_EINVAL, "sgd: NULL operand");
+            FinishTask *own = nullptr;
+            for (int i = 0; i < list->count && !own; ++i)
+                if (l.task[i].kind != FinishTask::LOSS && l.task[i].out == sgd->dW[u] && l.task[i].n == sgd->n[u] && !l.task[i].W) own = &l.task[i];
+            if (own) { own->W = sgd->W[u]; continue; }
+            if (l.full()) { apart = false; break; }
+            FinishTask t{};
+            t.kind = FinishTask::UPDATE; t.n = sgd->n[u]; t.part = sgd->dW[u]; t.W = sgd->W[u];
+            l.task[l.count++] = t;
+        }
+    }
+    // the memory a task writes, against everything that another reads or writes of the caller's
+    auto spans = [](const FinishTask &t, const float *(&p)[4], int64_t (&n)[4]) {
+        p[0] = t.out; n[0] = t.out ? (t.kind == FinishTask::LOSS ? 1 : t.n) : 0;
+        p[1] = t.W; n[1] = t.W ? t.n : 0;
+        p[2] = t.out2; n[2] = t.out2 ? 1 : 0;
+        p[3] = t.kind == FinishTask::UPDATE ? static_cast<const float *>(t.part) : nullptr; n[3] = p[3] ? t.n : 0;
+    };
+    for (int i = 0; i < l.count && apart; ++i) {
+        const float *p[4]; int64_t n[4];
+        spans(l.task[i], p, n);
+        for (int j = 0; j <= i && apart; ++j) {
+            const float *q[4]; int64_t m[4];
+            spans(l.task[j], q, m);
+            for (int x = 0; x < 4; ++x)
+                for (int y = 0; y < 4; ++y)
+                    if ((x != 3 || y != 3) && (i != j || x < y) && n[x] && m[y] && overlap(p[x], n[x], q[y], m[y])) apart = false;
+        }
+    }
+    if (apart) return launch_tasks(&l, lr, stream);
+    for (int i = 0; i < list->count; ++i) {
+        FinishList one;
+        one.task[one.count++] = list->task[i];
+        CG_TRY(launch_tasks(&one, lr, stream));
+    }
+    return lr != 0.f && sgd ? launch_sgd(*sgd, lr, stream) : CAPGNN_OK;
+}
+
 static int loss_blocks(int64_t n, int C, bool bce) {
     const int64_t rows = 4 * (64 / loss_lanes_per_row_host(C));
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, NUM_CU * (bce ? LOSS_WG_PER_CU<true> : LOSS_WG_PER_CU<false>))));
@@ -663,7 +795,7 @@ static int loss_blocks(int64_t n, int C, bool bce) {
 // colpart (loss_colpart_bytes) and dbias: also the layer's bias gradient.
 // bits (with a mask): one bit per row of the mask is left there, and the number of set ones in norm_dev[1].
 static int loss_launch(LossArgs a, bool bce, double loss_norm, float times, float *loss_dev, void *ws, float *colpart, float *dbias,
-                       hipStream_t st, uint16_t *bits = nullptr) {
+                       hipStream_t st, uint16_t *bits = nullptr, FinishList *later = nullptr) {
     float *norm_dev = static_cast<float *>(ws);
     double *counts = reinterpret_cast<double *>(static_cast<char *>(ws) + 256);
     a.part = reinterpret_cast<double *>(static_cast<char *>(ws) + LOSS_HEADER);
@@ -692,6 +824,19 @@ static int loss_launch(LossArgs a, bool bce, double loss_norm, float times, floa
     a.colpart = dbias ? colpart : nullptr;
     if (bce) hipLaunchKernelGGL(loss_kernel<true>, dim3(blocks), dim3(256), 0, st, a);
     else hipLaunchKernelGGL(loss_kernel<false>, dim3(blocks), dim3(256), 0, st, a);
+    if (later && later->count + 2 <= FinishList::MOST) {
+        FinishTask t{};
+        t.kind = FinishTask::LOSS; t.S = blocks; t.n = 1; t.part = a.part; t.out = loss_dev;
+        t.norm_val = a.norm_val; t.norm_dev = (a.norm_dev || a.norm_out) ? norm_dev : nullptr;
+        later->task[later->count++] = t;
+        if (dbias) {
+            t = FinishTask{};
+            t.kind = FinishTask::LOSS_COLUMNS; t.S = blocks; t.n = a.C; t.part = a.colpart; t.out = dbias;
+            later->task[later->count++] = t;
+        }
+        CG_HIP(hipGetLastError());
+        return CAPGNN_OK;
+    }
     hipLaunchKernelGGL(loss_final_kernel, dim3(1 + (dbias ? (a.C + 31) / 32 : 0)), dim3(1024), 0, st, blocks, a.part, a.norm_val,
                        (a.norm_dev || a.norm_out) ? norm_dev : nullptr, loss_dev, a.colpart, a.C, dbias);
     CG_HIP(hipGetLastError());
@@ -762,7 +907,7 @@ bool capgnn::loss_sums_columns(int C) { return C <= 4 * loss_lanes_per_row_host(
 // gradient, in `ws`.
 int capgnn::loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int32_t *labels, const uint8_t *targets, int64_t ldt,
                        const uint8_t *mask, double loss_norm, float *loss_dev, void *dZ, int64_t lddz, int dz_dtype, float *copy,
-                       float *dbias, const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st) {
+                       float *dbias, const float *row_scale, LiveRows *live, void *ws, size_t ws_bytes, hipStream_t st, FinishList *later) {
     CG_TRY(softmax_ce_check(n, C, Z, ldz, targets ? reinterpret_cast<const int32_t *>(targets) : labels, loss_dev, dZ, lddz, dz_dtype));
     if (n == 0) return CAPGNN_OK;
     if (targets && ldt < C) CG_FAIL(CAPGNN_EINVAL, "loss: ldt smaller than the number of classes");
@@ -779,7 +924,7 @@ int capgnn::loss_epoch(int64_t n, int C, const float *Z, int64_t ldz, const int3
         live->count = static_cast<const float *>(ws) + 1;
     }
     return loss_launch(a, targets != nullptr, loss_norm, targets ? static_cast<float>(C) : 1.f, loss_dev, ws,
-                       reinterpret_cast<float *>(colpart), dbias, st, bits);
+                       reinterpret_cast<float *>(colpart), dbias, st, bits, later);
 }
 
 // ------------------------------------------------------------------ the same loss without any allocation by anyone

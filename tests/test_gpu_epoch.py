@@ -518,6 +518,53 @@ def test_epoch_gradient_rows_outside_the_loss_are_skipped(env, kind, dtype, n, c
 
 
 @pytest.mark.parametrize("recorded", [False, True])
+@pytest.mark.parametrize("L,shared", [(2, "none"), (3, "dw"), (3, "bias"), (16, "none"), (16, "dw")])
+def test_epoch_end_adds_up_every_gradient(env, L, shared, recorded):
+    """What an epoch leaves to its last launch: the loss, every gradient and the SGD step, with up to 16 GraphSAGE layers (more sums than
+    one launch takes), and with gradient buffers that layers share, which hold the first layer's in the end, as the backward pass
+    writes it last.  Three passes with eager work between them; each equals the separate layer calls' order of writes: the step is W - lr dW
+    with the gradients as returned, bit for bit, and the gradients equal those of a run with buffers of their own."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(L)
+    n, D, lr = 700, 24, 0.5
+    g = B.Graph(n, 0, np.arange(0, 3 * n + 1, 3, dtype=np.int64), rng.integers(0, n, 3 * n).astype(np.int32), np.full(n, 1 / 3, np.float32), None)
+    mk = lambda *s: [torch.randn(*s, device="cuda") / 5 for _ in range(L)]  # noqa: E731
+    w, w_self, b = mk(D, D), mk(D, D), mk(D)
+    start = [t.clone() for t in w + w_self + b]
+    layers = [B.make_layer(B.SAGE_MEAN, D, D, B.ACT_RELU if l < L - 1 else B.ACT_NONE, B.F32, w[l], w_self[l], b[l], B.AGG_FIRST) for l in range(L)]
+    x = torch.randn(n, D, device="cuda")
+    labels = torch.randint(0, D, (n,), device="cuda", dtype=torch.int32)
+    size = B.epoch_workspace_bytes(g, None, layers)
+    st = torch.cuda.Stream()
+
+    def run(share):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        zero = lambda *s: [torch.full(s, 7.0, device="cuda") for _ in range(L)]  # noqa: E731
+        dw, ds, db = zero(D, D), zero(D, D), zero(D)
+        if share == "dw": dw = [dw[0]] * L
+        if share == "bias": db = [db[0]] * L
+        loss = torch.zeros(1, device="cuda")
+        torch.cuda.synchronize()
+        eg = B.EpochGraph(g, None, layers, x, D, labels, None, 0.0, None, dw, ds, db, lr, loss, ws, size, st) if recorded else None
+        for it in range(3):
+            say(f"epoch end L={L} shared={share} recorded={recorded} pass {it}")
+            for t, s in zip(w + w_self + b, start): t.copy_(s)
+            torch.cuda.synchronize()
+            if recorded: eg.launch(st)
+            else: loss.fill_(B.epoch(g, None, layers, x, D, labels, None, 0.0, None, dw, ds, db, lr, ws, size, stream=st, want_loss=True)[0])
+            torch.cuda.synchronize()
+            for t, s, d in zip(w + w_self + b, start, dw + ds + db):
+                assert torch.equal(t, s - lr * d)
+        assert np.isfinite(float(loss)) and float(loss) > 0
+        return dw, ds, db, float(loss)
+
+    own, got = run("none"), run(shared)
+    assert got[3] == own[3] and torch.equal(got[0][0], own[0][0]) and torch.equal(got[2][0], own[2][0])
+    assert all(torch.equal(p, q) for p, q in zip(got[1], own[1]))
+    assert all(float(t.abs().max()) > 0 for t in own[0] + own[1] + own[2])
+
+
+@pytest.mark.parametrize("recorded", [False, True])
 @pytest.mark.parametrize("tie", ["layers", "self", "all", "bias", "overlap"])
 def test_sgd_step_adds_every_gradient_of_a_shared_tensor(env, tie, recorded):
     """Layers that share a tensor (tied weights, W_self == W, one bias, a matrix that starts inside another one) get the updates of all
