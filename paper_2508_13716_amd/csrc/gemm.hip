@@ -98,6 +98,10 @@ __device__ __forceinline__ float4 load4(const char *base, int64_t off, int nvali
     return r;
 }
 
+__device__ __forceinline__ float epilogue_load(const char *p, int64_t at, int bf16) {
+    return bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(p)[at]) << 16) : reinterpret_cast<const float *>(p)[at];
+}
+
 // Writes one wave's TM x TN grid of 32x32 accumulator tiles (top-left corner (row0, col0)) with the epilogue.
 // D layout of the 32x32 MFMAs: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
 template <int TM, int TN>
@@ -162,6 +166,32 @@ __device__ __forceinline__ void store_tile_staged(const GemmArgs &g, const float
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (col + e < g.N) bv[e] = g.bias[col + e];
+    // what the epilogue reads of C, the mask and the row scales, before the first store, behind which it would wait; whole vectors from
+    // clamped places (a wave's part of 32 columns: twice that takes the registers that the kernel's other waves need)
+    constexpr bool EARLY = TN == 1;
+    constexpr int NT_ = 32 / RPP;
+    const bool whole = vec && col + 4 <= g.N;
+    const bool mvec = g.mask && reinterpret_cast<uintptr_t>(g.mask) % 16 == 0 && g.ldm % 4 == 0;      // uniform over the grid
+    auto clamped = [&](int i, int t) { const int64_t row = row0 + i * 32 + RPP * t + rq; return row < g.M ? row : g.M - 1; };
+    const int64_t vcol = col + 4 <= g.N ? col : 0;      // (columns 0 .. 3: there where any vector is whole)
+    float4 mk[2][NT_], ck[2][NT_];
+    float rs[2][NT_];
+    if (EARLY && !plain && mvec && g.N >= 4)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT_; ++t)
+                mk[i][t] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(g.mask) + clamped(i, t) * g.ldm + vcol);
+    if (EARLY && !plain && g.accumulate && vec && g.N >= 4)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT_; ++t) ck[i][t] = *reinterpret_cast<const float4 *>(dst + clamped(i, t) * ld + vcol);
+    if (EARLY && !plain && g.rscale)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT_; ++t) rs[i][t] = g.rscale[clamped(i, t)];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -171,19 +201,18 @@ __device__ __forceinline__ void store_tile_staged(const GemmArgs &g, const float
         __builtin_amdgcn_wave_barrier();
         if (col < g.N) {
 #pragma unroll
-            for (int t = 0; t < 32 / RPP; ++t) {
+            for (int t = 0; t < NT_; ++t) {
                 const int lr = RPP * t + rq;
                 const int64_t row = row0 + i * 32 + lr;
                 if (row >= g.M) continue;
                 const float4 v4 = *reinterpret_cast<const float4 *>(&lds[lr * STAGE_PITCH + 4 * cg]);
                 float v[4] = {v4.x, v4.y, v4.z, v4.w};
                 float *out = dst + row * ld + col;
-                const bool whole = vec && col + 4 <= g.N;
                 if (!plain) {
                     if (g.accumulate) {
                         if (whole) {
-                            const float4 c4 = *reinterpret_cast<const float4 *>(out);
-                            v[0] += c4.x; v[1] += c4.y; v[2] += c4.z; v[3] += c4.w;
+                            if (!EARLY) ck[i][t] = *reinterpret_cast<const float4 *>(out);
+                            v[0] += ck[i][t].x; v[1] += ck[i][t].y; v[2] += ck[i][t].z; v[3] += ck[i][t].w;
                         } else {
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
@@ -196,15 +225,22 @@ __device__ __forceinline__ void store_tile_staged(const GemmArgs &g, const float
                         if (g.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
                     }
                     if (g.mask) {
-                        const float *mk = reinterpret_cast<const float *>(g.mask) + row * g.ldm + col;
+                        if (mvec && col + 4 <= g.N) {
+                            if (!EARLY) mk[i][t] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(g.mask) + row * g.ldm + col);
+                            const float m[4] = {mk[i][t].x, mk[i][t].y, mk[i][t].z, mk[i][t].w};
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < g.N && !(mk[e] > 0.f)) v[e] = 0.f;
+                            for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] : 0.f;
+                        } else {
+                            const float *me = reinterpret_cast<const float *>(g.mask) + row * g.ldm + col;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (col + e < g.N && !(me[e] > 0.f)) v[e] = 0.f;
+                        }
                     }
                     if (g.rscale) {
-                        const float rs = g.rscale[row];
+                        if (!EARLY) rs[i][t] = g.rscale[row];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] *= rs;
+                        for (int e = 0; e < 4; ++e) v[e] *= rs[i][t];
                     }
                 }
                 if (whole) {
@@ -1498,6 +1534,36 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    // what the epilogue reads, asked for before the operands (clamped places): four columns per thread and pass
+    constexpr int PASSES = TN;                       // of 256 threads x 4 columns over 32 rows
+    const int er = threadIdx.x / (TN * 8), ec = 4 * (threadIdx.x % (TN * 8)), ER = 256 / (TN * 8);
+    float *part = second ? s.part2 : g.part;
+    char *C = second ? s.C2 : g.C;
+    const int64_t ldc = second ? s.ldc2 : g.ldc;
+    const float *rscale = second ? s.rscale2 : g.rscale;
+    float e_c[PASSES][4], e_b[4], e_m[PASSES][4], e_s[PASSES];
+    auto fetch_epilogue = [&]() __attribute__((always_inline)) {
+        if (part) return;                            // uniform over the grid, as are the conditions below
+        auto ccol = [&](int e) { return n0 + ec + e < g.N ? n0 + ec + e : g.N - 1; };
+        auto crow = [&](int p) { return m0 + er + p * ER < M ? m0 + er + p * ER : M - 1; };
+        if (g.bias)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) e_b[e] = g.bias[ccol(e)];
+        if (g.accumulate)
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) e_c[p][e] = epilogue_load(C, crow(p) * ldc + ccol(e), g.out_bf16);
+        if (g.mask)
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) e_m[p][e] = epilogue_load(g.mask, crow(p) * g.ldm + ccol(e), g.mask_bf16);
+        if (rscale)
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) e_s[p] = rscale[crow(p)];
+    };
+    if constexpr (A_KC) fetch_epilogue();            // (the others, which hold more operands, mostly write parts)
     // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway.  However long a split is, a thread
     // adds no more than the 16 .. 32 terms of a step in fp32; its running sum and those of the workgroup are doubles.
     const bool sums = !A_KC && !B_KC && g.colpart && by == 0 && !second;      // uniform over the workgroup
@@ -1557,45 +1623,36 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     if (sums)
         for (int c = threadIdx.x; c < TN * 32; c += 256)
             if (n0 + c < g.N) g.colpart[bz * g.N + n0 + c] = static_cast<float>((bred[0][c] + bred[1][c]) + (bred[2][c] + bred[3][c]));
-    float *part = second ? s.part2 : g.part;
-    char *C = second ? s.C2 : g.C;
-    const int64_t ldc = second ? s.ldc2 : g.ldc;
-    const float *rscale = second ? s.rscale2 : g.rscale;
-    // four columns per thread
-    for (int i = threadIdx.x; i < 32 * TN * 8; i += 256) {
-        const int r = i / (TN * 8), c4 = i % (TN * 8);
-        const int64_t orow = m0 + r, ocol = n0 + 4 * c4;
+    if constexpr (!A_KC) fetch_epilogue();
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int r = er + p * ER;
+        const int64_t orow = m0 + r, ocol = n0 + ec;
         if (orow >= M || ocol >= g.N) continue;
         float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float4 q = *reinterpret_cast<const float4 *>(&red[w][r][4 * c4]);
+            const float4 q = *reinterpret_cast<const float4 *>(&red[w][r][ec]);
             v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
         }
-        const int nv = g.N - ocol < 4 ? static_cast<int>(g.N - ocol) : 4;
-        if (part) {
-            float *o = part + (bz * M + orow) * g.N + ocol;
-            for (int e = 0; e < nv; ++e) o[e] = v[e];
-            continue;
-        }
-        for (int e = 0; e < nv; ++e) {
-            const int64_t at = orow * ldc + ocol + e;
-            float x = v[e];
-            if (g.accumulate)
-                x += g.out_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(C)[at]) << 16)
-                                : reinterpret_cast<const float *>(C)[at];
-            if (g.bias) x += g.bias[ocol + e];
-            if (g.relu) x = x > 0.f ? x : 0.f;
-            if (g.mask) {
-                const int64_t am = orow * g.ldm + ocol + e;
-                const float mv = g.mask_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(g.mask)[am]) << 16)
-                                             : reinterpret_cast<const float *>(g.mask)[am];
-                if (!(mv > 0.f)) x = 0.f;
+        if (!part) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (g.accumulate) v[e] += e_c[p][e];
+                if (g.bias) v[e] += e_b[e];
+                if (g.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                if (g.mask) v[e] = e_m[p][e] > 0.f ? v[e] : 0.f;
+                if (rscale) v[e] *= e_s[p];
             }
-            if (rscale) x *= rscale[orow];
-            if (g.out_bf16) reinterpret_cast<uint16_t *>(C)[at] = static_cast<uint16_t>(f32_to_bf16_rne(x));
-            else reinterpret_cast<float *>(C)[at] = x;
         }
+        float *o = part ? part + (bz * M + orow) * g.N + ocol : reinterpret_cast<float *>(C) + orow * ldc + ocol;
+        uint16_t *ob = reinterpret_cast<uint16_t *>(C) + orow * ldc + ocol;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (ocol + e < g.N) {
+                if (!part && g.out_bf16) ob[e] = static_cast<uint16_t>(f32_to_bf16_rne(v[e]));
+                else o[e] = v[e];
+            }
     }
 }
 
