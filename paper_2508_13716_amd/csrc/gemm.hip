@@ -1228,6 +1228,241 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmArgs g,
     }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The same product for many rows and a small weight matrix (at most 256 columns and 256 k, the sum of two products among them), where
+// a tile's life of a few steps leaves gemm_split_kernel waiting for its first operands and its last stores.  A workgroup walks tiles of
+// 32 rows and all its life holds the three pieces of its weights in registers: a wave 32 columns and 128 k (96 registers, so that two
+// waves share a SIMD; one wave per SIMD with 192 or 384 of them was no faster than gemm_split_kernel: 306 k x 256 x 256 243 us either
+// way).  Above 128 k the waves halve the reduction between them (KH = 2), exchange half of their partial tiles through LDS and store
+// half of the rows each.  Rows of A are fetched two tiles ahead and cut behind the matrix instructions (cut after them: 1-2 % slower);
+// LDS holds A's pieces, one tile being stored while the other is multiplied: one barrier per tile.  Units of 16 bytes
+// S[k / 128][piece][k / 8][row], a plane one unit longer than 32 rows: the units that 8 lanes store lie 4 banks apart.
+// As in gemm_bf16_stream_kernel the operands are exchanged, every tile issues the same loads and stores unconditionally (those
+// beyond the matrix are dropped by the buffer's bounds) and the last row's tile comes apart.
+// us, in a 306 k-vertex GraphSAGE epoch, gemm_split_kernel -> here: sum of two products of 100 k 244 -> 205, masked sum of two of 47 k 206
+// -> 126 (5.9 TB/s: memory), 256 x 256 246 -> 204 (1.2 PFLOP/s of bf16 work); error against fp64 2.4e-7 -> 1.7e-7 (shorter chains).
+constexpr int split_stream_slots(int NS, int KH) { return KH == 1 ? NS : 2 * NS / KH; }     // 32 x 32 parts of C on their way through LDS
+constexpr int split_stream_lds(int NS, int KH) { return 2 * KH * 3 * 16 * 33 * 16 + split_stream_slots(NS, KH) * 32 * 36 * 4 + NS / KH * 128; }
+constexpr int split_stream_held(int NS, int KH) { return NS == 4 && KH == 1 ? 2 : 1; }       // workgroups per compute unit
+
+template <int NS, int KH, bool DUAL, bool MASK>
+__global__ __launch_bounds__(NS * 64, split_stream_held(NS, KH) * NS / 4) void gemm_split_stream_kernel(GemmArgs g, const uint16_t *Wt, uint32_t ku_total, uint32_t n_pad) {
+    constexpr int CG = NS / KH, PLANE = 33, BUF = KH * 3 * 16 * PLANE * 16, CP = 36, NT = NS * 64;
+    constexpr int RPP = NT / (16 * KH), NR = 32 / RPP;  // rows of A per pass, units of a thread in a tile
+    constexpr int NP = 4 / KH;                          // a lane's 16-byte pieces of C in a tile
+    __shared__ __attribute__((aligned(16))) char smem[split_stream_lds(NS, KH)];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cg = wave % CG, kh = wave / CG;           // the wave's columns and part of the reduction
+    const int l32 = lane & 31, half = lane >> 5;
+    const int n0 = static_cast<int>(blockIdx.y) * (CG * 32);
+    float *slot0 = reinterpret_cast<float *>(smem + 2 * BUF) + cg * 32 * CP;
+    float *bias = reinterpret_cast<float *>(smem + 2 * BUF + split_stream_slots(NS, KH) * 32 * CP * 4);
+    const int64_t full = (g.M - 1) / 32;                // tiles before the one that holds the last row
+
+    for (int c = tid; c < CG * 32; c += NT) bias[c] = (g.bias && n0 + c < g.N) ? g.bias[n0 + c] : 0.f;
+    bf16x8 w[3][8];     // (a wave beyond the last column of the image holds its last columns: never stored)
+    {
+        const uint32_t col = n0 + cg * 32, n = col + 32 <= n_pad ? col : n_pad - 32;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const uint32_t u = 16 * kh + 2 * s;
+                uint4 x = make_uint4(0u, 0u, 0u, 0u);
+                if (u < ku_total)                       // (whole steps of 32 k: uniform)
+                    x = *reinterpret_cast<const uint4 *>(Wt + ((static_cast<size_t>(p) * ku_total + u + half) * n_pad + n + l32) * 8);
+                w[p][s] = __builtin_bit_cast(bf16x8, x);
+            }
+    }
+    // the thread's unit of 8 k (rows r0, r0 + RPP ..): where it starts in tile 0, bytes from tile to tile, elements that exist
+    const int v = tid % (16 * KH), r0 = tid / (16 * KH);
+    const bool second = DUAL && 8 * v >= g.K1p;
+    const int kk = second ? 8 * v - static_cast<int>(g.K1p) : 8 * v;
+    const int64_t ld = second ? g.lda2 : g.lda;
+    const int have = static_cast<int>(second ? g.K - g.K1p : DUAL ? g.K1 : g.K) - kk;
+    const char *src = (second ? g.A2 : g.A) + (r0 * ld + (have > 0 ? kk : 0)) * 4;      // (units beyond the width read the first one and are cleared)
+    const uint32_t tb = static_cast<uint32_t>(ld) * 128, at1 = have > 4 ? 16 : 0;
+    const bool ragged = DUAL || g.K < 128 * KH;
+    typedef float4 Rows[2 * NR];
+    auto load = [&](int64_t t, Rows &r) __attribute__((always_inline)) {
+        const char *p = src + static_cast<uint64_t>(static_cast<uint32_t>(t < full ? t : full - 1)) * tb;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            r[2 * q] = *reinterpret_cast<const float4 *>(p + q * (tb / NR));
+            r[2 * q + 1] = *reinterpret_cast<const float4 *>(p + (q * (tb / NR) + at1));
+        }
+    };
+    auto load_last = [&](Rows &r) __attribute__((always_inline)) {            // the rows that exist, no further than their width
+        const int rows = static_cast<int>(g.M - full * 32);
+        const char *p = src + full * tb;
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int n = r0 + RPP * q < rows ? have - 4 * h : 0;
+                r[2 * q + h] = load4<false>(p + q * (tb / NR), 4 * h, n < 4 ? n : 4, 1);
+            }
+    };
+    auto clear = [&](Rows &r) __attribute__((always_inline)) {                // what lies beyond the width
+        if (ragged)
+#pragma unroll
+            for (int q = 0; q < 2 * NR; ++q) {
+                const int n = have - 4 * (q & 1);
+                r[q] = make_float4(n > 0 ? r[q].x : 0.f, n > 1 ? r[q].y : 0.f, n > 2 ? r[q].z : 0.f, n > 3 ? r[q].w : 0.f);
+            }
+    };
+    auto put = [&](Rows &r, char *As) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            const float x[8] = {r[2 * q].x, r[2 * q].y, r[2 * q].z, r[2 * q].w, r[2 * q + 1].x, r[2 * q + 1].y, r[2 * q + 1].z, r[2 * q + 1].w};
+            uint32_t u[4][3];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) split3_pair(x[2 * e], x[2 * e + 1], u[e]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<uint4 *>(As + (((v / 16 * 3 + p) * 16 + v % 16) * PLANE + r0 + RPP * q) * 16) =
+                    make_uint4(u[0][p], u[1][p], u[2][p], u[3][p]);
+        }
+    };
+    // the lane's pieces of its wave's part of the result: columns col0 .. col0 + 3 of rows cr, cr + 8 ..
+    const int cr = 16 * kh + lane / 8, c4 = 4 * (lane % 8), col0 = n0 + cg * 32 + c4;
+    const uint32_t ldc4 = static_cast<uint32_t>(g.ldc) * 4, ldm4 = static_cast<uint32_t>(g.ldm) * 4;
+    const bool whole = col0 + 4 <= g.N;
+    const bool cut = g.N % 4 != 0;                      // a group of four columns ends inside the matrix (uniform)
+    auto finish = [&](float x, float b) __attribute__((always_inline)) {
+        x += b;
+        return g.relu && !(x > 0.f) ? 0.f : x;
+    };
+
+    // rows: of the tile that exist; buf: the stage (and, for KH = 2, the slot) it uses; next: the rows that are cut meanwhile, into the
+    // other stage, and then replaced by those of tile t_next, where there are more
+    auto tile = [&](int64_t t, int rows, int buf, auto more, Rows &next, int64_t t_next) __attribute__((always_inline)) {
+        const char *As = smem + buf * BUF + kh * 3 * 16 * PLANE * 16;
+        float *slot = slot0 + (KH == 1 ? 0 : buf * CG * 32 * CP);
+        float4 mk[NP];
+        float rs[NP];
+        if constexpr (MASK) {
+            const char *mbase = g.mask + t * 32 * g.ldm * 4;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int row = cr + 8 * p < rows ? cr + 8 * p : rows - 1;
+                mk[p] = *reinterpret_cast<const float4 *>(mbase + (static_cast<uint32_t>(row) * ldm4 + (whole ? 4u * col0 : 0u)));
+            }
+        }
+        if (g.rscale)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) rs[p] = g.rscale[t * 32 + (cr + 8 * p < rows ? cr + 8 * p : rows - 1)];
+        constexpr bool MORE = decltype(more)::value;
+        if constexpr (MORE) clear(next);
+        floatx16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            bf16x8 x[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                x[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(As + ((p * 16 + 2 * s + half) * PLANE + l32) * 16));
+            // the six piece products, smallest first
+#define CG_PIECES(PA_, PB_) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[PB_][s], x[PA_], acc, 0, 0, 0);
+            CG_PIECES(2, 0) CG_PIECES(0, 2) CG_PIECES(1, 1) CG_PIECES(1, 0) CG_PIECES(0, 1) CG_PIECES(0, 0)
+#undef CG_PIECES
+        }
+        if constexpr (MORE) put(next, smem + (buf ^ 1) * BUF);
+        // the operands of one unit ahead of the matrix instructions, no more (the registers are the weights'); from the second unit on
+        // the next rows are cut behind them, a few vector instructions each
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s < 7) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+            for (int m = 0; m < 6; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (MORE && s > 0) __builtin_amdgcn_sched_group_barrier(0x002, NR == 1 ? 2 : 4, 0);
+            }
+            if (MORE && s > 0) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MORE) load(t_next, next);
+        // registers 4 q ..: columns 8 q + 4 half .. of row l32.  KH = 2: first the rows that the other wave of these columns stores
+        float4 *at = reinterpret_cast<float4 *>(&slot[l32 * CP + 4 * half]);
+        if (KH == 1 || l32 / 16 != kh)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) at[2 * q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+        if constexpr (KH == 2) {
+            __syncthreads();
+            if (l32 / 16 == kh)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 o = at[2 * q];
+                    at[2 * q] = make_float4(acc[4 * q] + o.x, acc[4 * q + 1] + o.y, acc[4 * q + 2] + o.z, acc[4 * q + 3] + o.w);
+                }
+        }
+        __builtin_amdgcn_wave_barrier();
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.C + t * 32 * g.ldc * 4, 0, 0x7fffffff, 0x00027000);
+        const float4 b4 = *reinterpret_cast<const float4 *>(&bias[cg * 32 + c4]);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            float4 x = *reinterpret_cast<const float4 *>(&slot[(cr + 8 * p) * CP + c4]);
+            x = make_float4(finish(x.x, b4.x), finish(x.y, b4.y), finish(x.z, b4.z), finish(x.w, b4.w));
+            if constexpr (MASK)
+                x = make_float4(mk[p].x > 0.f ? x.x : 0.f, mk[p].y > 0.f ? x.y : 0.f, mk[p].z > 0.f ? x.z : 0.f, mk[p].w > 0.f ? x.w : 0.f);
+            if (g.rscale) x = make_float4(x.x * rs[p], x.y * rs[p], x.z * rs[p], x.w * rs[p]);
+            const uint32_t off = cr + 8 * p < rows && whole ? (cr + 8 * p) * ldc4 + 4u * col0 : 0xfffffff0u;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rsrc, off, 0, 2);
+        }
+        if (cut) {
+#pragma unroll 1
+            for (int e = 0; e < 4 * NP; ++e) {
+                const int row = cr + 8 * (e / 4), col = col0 + e % 4;
+                const bool in = !whole && row < rows && col < g.N;
+                float x = finish(slot[row * CP + c4 + e % 4], bias[cg * 32 + c4 + e % 4]);
+                if constexpr (MASK) {
+                    if (in && !(*reinterpret_cast<const float *>(g.mask + ((t * 32 + row) * g.ldm + col) * 4) > 0.f)) x = 0.f;
+                }
+                if (g.rscale && in) x *= g.rscale[t * 32 + row];
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rsrc, in ? row * ldc4 + 4u * col : 0xfffffff0u, 0, 0);
+            }
+        }
+        if constexpr (KH == 1) __syncthreads();
+    };
+    // as many dropped stores as the tiles before would have issued, so that the waits of the loop can allow for them
+    auto dropped = [&](uint32_t at) __attribute__((always_inline)) {
+        auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.C, 0, 0x7fffffff, 0x00027000);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, at + 16 * p, 0, 2);
+    };
+    Rows ra, rb;
+    const int64_t step = gridDim.x;
+    int64_t t = blockIdx.x;
+    if (t < full) {                                      // uniform over the workgroup
+        load(t, ra);
+        load(t + step, rb);
+        dropped(0xffffff00u);
+        clear(ra);
+        put(ra, smem);
+        load(t + 2 * step, ra);
+        dropped(0xffffff40u);
+        __syncthreads();
+        for (; t + step < full; t += 2 * step) {         // (one way out: the waits are counted over every path)
+            tile(t, 32, 0, std::true_type{}, rb, t + 3 * step);
+            tile(t + step, 32, 1, std::true_type{}, ra, t + 4 * step);
+        }
+        if (t < full) {
+            tile(t, 32, 0, std::false_type{}, ra, 0);
+            t += step;
+        }
+        __syncthreads();                                 // stages and slots are free
+    }
+    if (t == full) {                                     // the tile with the last row (t went through every residue: one workgroup's)
+        load_last(ra);
+        put(ra, smem);
+        __syncthreads();
+        tile(t, static_cast<int>(g.M - full * 32), 0, std::false_type{}, ra, 0);
+    }
+}
+
 // The weight gradient with eight waves on a 128 x BN tile (BN = 128: 2 x 4 waves, each a 64 x 32 part; BN = 64: 4 x 2,
 // each 32 x 32): half the staging and at most half the accumulators per thread of the four-wave form, so that four
 // waves share a SIMD and one wave's cutting and LDS traffic run beside another's matrix instructions.  Waves 0-3 stage
@@ -2195,6 +2430,34 @@ static void launch_split_tiles(bool trans, const GemmArgs &g, int bn, dim3 grid,
     }
 }
 
+template <int NS, int KH>
+static void launch_split_stream_cfg(const GemmArgs &g, const uint16_t *Wt, uint32_t ku_total, uint32_t n_pad, hipStream_t st) {
+    const int64_t gy = (g.N + NS / KH * 32 - 1) / (NS / KH * 32);
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>((g.M + 31) / 32, NUM_CU * split_stream_held(NS, KH) / gy)), static_cast<unsigned>(gy)), block(NS * 64);
+#define CG_FORM(D_, M_) if (!!g.A2 == D_ && !!g.mask == M_) \
+        hipLaunchKernelGGL((gemm_split_stream_kernel<NS, KH, D_, M_>), grid, block, 0, st, g, Wt, ku_total, n_pad);
+    CG_FORM(false, false) CG_FORM(false, true) CG_FORM(true, false) CG_FORM(true, true)
+#undef CG_FORM
+}
+
+// gemm_split_stream_kernel where it applies (plain product or sum of two, weights cut into Wt): rows that start on 16 bytes, weights that
+// eight waves hold, more than 64 columns (306 k x 47 x 256 125 us here, 99 in 64-column tiles), and rows for every workgroup.
+// us, gemm_split_kernel -> here: 12800 x 256 x 256 21.9 -> 19.2, 14000 x 256 x 100 15.8 -> 13.1, 26000 x 128 x 128 15.2 -> 13.5, 20000 x 256
+// x 256 31.0 -> 23.4, 180 k x 128 x 128 56.7 -> 40.8, 306 k x 256 x 100 193 -> 123, x 47 with mask 255 -> 126, x 256 341 -> 307 and with
+// mask 353 -> 264; where k falls just above 128 the two are level (70 k x 256 x 200 69.8 / 70.2, 306 k x 100 x 256 152 / 154).
+static bool launch_split_stream(const GemmArgs &g, const uint16_t *Wt, int64_t ku_total, int64_t n_pad, hipStream_t st) {
+    const bool rows16 = g.a_vec && aligned16(g.A) && aligned16(g.C) && g.ldc % 4 == 0 && (!g.mask || (aligned16(g.mask) && g.ldm % 4 == 0)) &&
+                        (!g.A2 || (aligned16(g.A2) && g.lda2 % 4 == 0));
+    if (!rows16 || g.accumulate || g.part || g.out_bf16 || g.K > 256 || g.N <= 64 || g.N > 256 || g.M < 12288 ||
+        g.lda >= (1 << 22) || g.lda2 >= (1 << 22) || g.ldc >= (1 << 22) || g.ldm >= (1 << 22))
+        return false;
+    const uint32_t ku = static_cast<uint32_t>(ku_total), np = static_cast<uint32_t>(n_pad);
+    if (g.K > 128) launch_split_stream_cfg<8, 2>(g, Wt, ku, np, st);
+    else if (g.N > 128) launch_split_stream_cfg<8, 1>(g, Wt, ku, np, st);
+    else launch_split_stream_cfg<4, 1>(g, Wt, ku, np, st);
+    return true;
+}
+
 template <bool BF16, bool A_KC, bool B_KC>
 static void launch_tiles(const GemmArgs &g, int bn, dim3 grid, hipStream_t st) {
     if (bn == 64) hipLaunchKernelGGL((gemm_kernel<BF16, A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
@@ -2380,7 +2643,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
             hipLaunchKernelGGL(split_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0,
                                stream, static_cast<const float *>(B), ldb, bkc ? 1 : 0, K, N, static_cast<uint16_t *>(ws), n_pad,
                                ku_total);
-            launch_split_tiles(false, g, bn, grid, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream);
+            if (!launch_split_stream(g, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream))
+                launch_split_tiles(false, g, bn, grid, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream);
         }
     } else if (stream_path) {
         const int64_t n_pad = split_rows(N), ku_total = 2 * stream_units(K);
@@ -2575,7 +2839,8 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
                        static_cast<const float *>(W), ldw, trans_b ? 1 : 0, K1, N, static_cast<uint16_t *>(ws), n_pad, ku_total,
                        static_cast<const float *>(W2), ldw2, K1p, K2);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
-    if (bn == 64)
+    if (launch_split_stream(g, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream)) {
+    } else if (bn == 64)
         hipLaunchKernelGGL((gemm_split_kernel<128, 64, 4, true>), grid, dim3(256), 0, stream, g, static_cast<const uint16_t *>(ws),
                            ku_total, n_pad);
     else

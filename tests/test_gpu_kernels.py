@@ -729,6 +729,41 @@ def test_layer_narrow_weight_gradients_exact(env, n, f_in, f_out):
     assert torch.equal(db.double(), dh.double().sum(0))
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(24609, 128, 128), (24608, 65, 7), (24640, 100, 129), (20000, 132, 200), (16399, 256, 256), (50001, 255, 47),
+                                   (12288, 200, 256), (12321, 256, 255), (12352, 196, 128), (49183, 64, 256), (49153, 47, 130), (50000, 1, 200)])
+def test_gemm_f32_many_rows_exact(env, tb, M, N, K):
+    """fp32 products of many rows in three bf16 pieces (weights held in registers where 64 x 64 tiles do not fit the chip at once, up to
+    256 columns and 256 k): the last tile of rows whole, short and of one row, K around a unit and around 128 and 256, N not a multiple of
+    four and of a wave's 32; with and without bias, ReLU and mask.  Sums of integers that need two and three pieces but fit 24 bits: equality.  Padding of
+    every operand is NaN and C's own stays as it is."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    mk = lambda r, c, m: torch.randint(-m, m + 1, (r, c), generator=gen, device="cuda").float()  # noqa: E731
+    A = mk(M, K, 511)                                                   # 9 bits and a sign: two pieces
+    W = mk(*((N, K) if tb else (K, N)), 20)
+    bias, mask = mk(1, N, 70000)[0].contiguous(), mk(M, N, 1)
+    pad = lambda x: torch.nn.functional.pad(x, (0, -x.shape[1] % 4 + 4), value=float("nan")).contiguous()  # noqa: E731
+    Ad, Wd, Md = pad(A), pad(W), pad(mask)
+    Ad[3, 0] = A[3, 0] = 2.0 ** 17 - 1                                  # 17 bits: three pieces
+    plain = A.double() @ (W.T if tb else W).double()
+    assert float(plain.abs().max()) < 2 ** 24 - 70000
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    ldc = (N + 3) // 4 * 4 + 4
+    for use_bias, relu, use_mask in ((False, 0, False), (True, 1, False), (False, 0, True)):
+        say(f"gemm f32 many rows tb={tb} {M}x{N}x{K} bias={use_bias} relu={relu} mask={use_mask}")
+        Cd = torch.full((M, ldc), 2.0, device="cuda")
+        B.gemm(0, tb, M, N, K, Ad, Ad.shape[1], Wd, Wd.shape[1], Cd, ldc, B.F32, bias=bias if use_bias else None, relu=relu,
+               relu_mask=Md if use_mask else None, ldm=Md.shape[1] if use_mask else 0, ws=ws, ws_bytes=wsb, f32_product=B.F32_PRODUCT_SPLIT)
+        torch.cuda.synchronize()
+        ref = plain + bias.double() if use_bias else plain
+        ref = ref.clamp(min=0) if relu else ref
+        ref = ref * (mask > 0) if use_mask else ref
+        assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
@@ -916,6 +951,14 @@ def test_bf16_products_do_not_depend_on_the_fp32_form(env, order):
     a, b, c = (sage_layer(env, "bf16", f, order=order) for f in forms)
     for k in a:
         assert torch.equal(a[k], b[k]) and torch.equal(a[k], c[k]), k
+
+
+@pytest.mark.parametrize("n,f_in,f_out", [(30017, 47, 100), (30016, 100, 256), (30001, 64, 130), (50017, 100, 47), (30000, 130, 72)])
+def test_layer_sum_of_two_split_products(env, n, f_in, f_out):
+    """The two forward products of a GraphSAGE layer in one launch, columns of the two operands meeting inside, at and beyond the 128 k of
+    a wave: within 2e-6 of the fp32 instruction's (2-norm; each form lies within 4e-7 of fp64 at these widths)."""
+    spl, nat = (sage_layer(env, "f32", f, n=n, f_in=f_in, f_out=f_out)["h"].double() for f in (env["B"].F32_PRODUCT_SPLIT, env["B"].F32_PRODUCT_NATIVE))
+    assert float((spl - nat).norm()) <= 2e-6 * float(nat.norm())
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
