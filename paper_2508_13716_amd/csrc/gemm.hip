@@ -2208,14 +2208,24 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, con
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int64_t total = g.part ? g.M * g.N : 0;       // (no partials: only the column sums are left to add)
     int64_t t = static_cast<int64_t>(blockIdx.x) * 32 + tx;
-    const int64_t c_blocks = (total + 31) / 32;
-    if (static_cast<int64_t>(blockIdx.x) >= c_blocks) {     // the workgroups behind C's: column sums, in double precision
+    // column sums, in double precision, by the first workgroups: few, and with the longest chains (behind C's, and with a load at a time,
+    // they ended the launch by themselves: 256 x 256 of 384 parts 32 us, 128 x 256 of 768 parts 42; 20 without them)
+    const int64_t d_blocks = colsum ? (g.N + 31) / 32 : 0;
+    if (static_cast<int64_t>(blockIdx.x) < d_blocks) {
         if (blockIdx.y != 0) return;
         __shared__ double dred[8][32];
-        t -= c_blocks * 32;
         double d = 0.0;
-        if (t < g.N)
-            for (int z = ty; z < S; z += 8) d += static_cast<double>(g.colpart[static_cast<int64_t>(z) * g.N + t]);
+        if (t < g.N) {
+            int z = ty;
+            for (; z + 120 < S; z += 128) {
+                float q[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) q[u] = g.colpart[static_cast<int64_t>(z + 8 * u) * g.N + t];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) d += static_cast<double>(q[u]);
+            }
+            for (; z < S; z += 8) d += static_cast<double>(g.colpart[static_cast<int64_t>(z) * g.N + t]);
+        }
         dred[ty][tx] = d;
         __syncthreads();
         if (ty != 0 || t >= g.N) return;
@@ -2224,6 +2234,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g, int S, con
         colsum[t] = static_cast<float>(d);
         return;
     }
+    t -= d_blocks * 32;
     float v = 0.f;
     if (t < total) {
         int z = ty;
