@@ -1703,7 +1703,7 @@ __device__ __forceinline__ void small_load(const char *p, int64_t step, int64_t 
 constexpr int SMALL_UNITS = 4;      // units per batch
 template <bool BF16> constexpr int SMALL_UNIT_K = BF16 ? 16 : 8;
 
-template <bool BF16, bool A_KC, bool B_KC, int TN>
+template <bool BF16, bool A_KC, bool B_KC, int TN, bool HOLD>
 __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     constexpr int ES = BF16 ? 2 : 4, UK = SMALL_UNIT_K<BF16>, HK = UK / 2, UB = SMALL_UNITS;
     constexpr int PITCH = TN * 32 + 4;
@@ -1769,9 +1769,12 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-    // what the epilogue reads, asked for before the operands (clamped places): four columns per thread and pass
+    // what the epilogue reads (clamped places): four columns per thread and pass, asked for ahead of the operands (HOLD), else ahead of
+    // the exchange through LDS (A_KC) or behind it (reductions over vertices, which mostly write parts)
     constexpr int PASSES = TN;                       // of 256 threads x 4 columns over 32 rows
-    const int er = threadIdx.x / (TN * 8), ec = 4 * (threadIdx.x % (TN * 8)), ER = 256 / (TN * 8);
+    int tid = threadIdx.x;
+    if (A_KC && !HOLD) asm("" : "+v"(tid));          // (what follows from it is not worth a register in the loop)
+    const int er = tid / (TN * 8), ec = 4 * (tid % (TN * 8)), ER = 256 / (TN * 8);
     float *part = second ? s.part2 : g.part;
     char *C = second ? s.C2 : g.C;
     const int64_t ldc = second ? s.ldc2 : g.ldc;
@@ -1798,7 +1801,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) e_s[p] = rscale[crow(p)];
     };
-    if constexpr (A_KC) fetch_epilogue();            // (the others, which hold more operands, mostly write parts)
+    if constexpr (HOLD) fetch_epilogue();
     // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway.  However long a split is, a thread
     // adds no more than the 16 .. 32 terms of a step in fp32; its running sum and those of the workgroup are doubles.
     const bool sums = !A_KC && !B_KC && g.colpart && by == 0 && !second;      // uniform over the workgroup
@@ -1842,6 +1845,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
                 }
             }
     }
+    if constexpr (A_KC && !HOLD) fetch_epilogue();
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -2509,14 +2513,25 @@ static void launch_stream(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad,
 }
 
 // (bf16 operands take the small kernel in reductions over vertices only, see small_product)
+// Epilogue operands held through the loop cost A W of at most 32 columns a wave per SIMD (30000 x 20 x 8 6.4 -> 8.5 us, 20000 x 32 x 100
+// 6.6 -> 7.1), and A W^T of more than 32 one of three: worth it while two workgroups per compute unit are all there are (masked, 4096 x
+// 256 x 112 10.6 held, 11.5 not), not where a third holds the rest of them (10000 x 128 x 100, 626 workgroups, 16.0 held, 12.5 not;
+// with more workgroups or k it is held again: 7000 x 200 x 128, 876 of them, 15.1 held, 15.9 not; 20000 x 41 x 300 24.8, 28.3).
 static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
-#define CG_SMALL_CASE(BF, AK, BK_)                                                                                             \
-    if (bf16 == BF && akc == AK && bkc == BK_) {                                                                               \
-        if (tn == 1) hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, 1>), grid, dim3(256), 0, st, s);                       \
-        else hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, 2>), grid, dim3(256), 0, st, s);                               \
+#define CG_SMALL_CASE(BF, AK, BK_, TN_, HOLD_)                                                                                 \
+    if (bf16 == BF && akc == AK && bkc == BK_ && tn == TN_)                                                                    \
+        hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, TN_, HOLD_>), grid, dim3(256), 0, st, s);
+    CG_SMALL_CASE(false, true, false, 1, false) CG_SMALL_CASE(false, true, false, 2, true) CG_SMALL_CASE(false, true, true, 1, true)
+    const int64_t n_wg = static_cast<int64_t>(grid.x) * grid.y;
+    if (n_wg > 2 * NUM_CU && n_wg <= 3 * NUM_CU && s.g.K + (s.dual ? s.K2 : 0) <= 256) {
+        CG_SMALL_CASE(false, true, true, 2, false)
+    } else {
+        CG_SMALL_CASE(false, true, true, 2, true)
     }
-    CG_SMALL_CASE(false, true, false) CG_SMALL_CASE(false, true, true) CG_SMALL_CASE(false, false, false) CG_SMALL_CASE(false, false, true)
-    CG_SMALL_CASE(true, false, false) CG_SMALL_CASE(true, false, true)
+    CG_SMALL_CASE(false, false, false, 1, false) CG_SMALL_CASE(false, false, false, 2, false)
+    CG_SMALL_CASE(false, false, true, 1, false) CG_SMALL_CASE(false, false, true, 2, false)
+    CG_SMALL_CASE(true, false, false, 1, false) CG_SMALL_CASE(true, false, false, 2, false)
+    CG_SMALL_CASE(true, false, true, 1, false) CG_SMALL_CASE(true, false, true, 2, false)
 #undef CG_SMALL_CASE
 }
 

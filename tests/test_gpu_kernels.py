@@ -764,6 +764,40 @@ def test_gemm_f32_many_rows_exact(env, tb, M, N, K):
         assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1000, 30, 40), (4095, 130, 72), (10_001, 100, 100), (16_500, 41, 256), (20_000, 41, 300), (13_001, 70, 300), (30_001, 100, 100),
+                                   (30_017, 130, 300), (60_001, 47, 24), (60_001, 64, 100), (60_001, 201, 32), (50_001, 100, 20)])
+def test_gemm_f32_epilogues_exact(env, tb, M, N, K):
+    """C (+)= A W with bias, ReLU and mask on every kernel of the fp32 path, in both forms of the product: epilogue operands asked for
+    ahead of the loop or behind it (two and three workgroups per compute unit), staged tiles of 64 and 128 columns that accumulate over
+    one step of the reduction and over more, ragged last rows and columns.  Sums of integers that fit 24 bits: equality.  Padding of
+    every operand is NaN and C's own stays as it is."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    mk = lambda r, c, m: torch.randint(-m, m + 1, (r, c), generator=gen, device="cuda").float()  # noqa: E731
+    A, W, C0, mask, bias = mk(M, K, 511), mk(*((N, K) if tb else (K, N)), 20), mk(M, N, 70000), mk(M, N, 1), mk(1, N, 70000)[0].contiguous()
+    plain = A.double() @ (W.T if tb else W).double()
+    assert float(plain.abs().max()) < 2 ** 24 - 140000
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+    for mult in (4, 1):                                                 # whole vectors, or the bare width plus one
+        pad = lambda x: torch.nn.functional.pad(x, (0, -x.shape[1] % mult + mult), value=float("nan")).contiguous()  # noqa: E731
+        Ad, Wd, Md = pad(A), pad(W), pad(mask)
+        for form in (B.F32_PRODUCT_NATIVE, B.F32_PRODUCT_SPLIT):
+            for acc, use_bias, relu, use_mask in ((1, False, 0, False), (0, False, 0, True), (1, True, 1, True), (0, True, 1, False)):
+                say(f"gemm f32 epilogue tb={tb} {M}x{N}x{K} pitch {mult} form={form} accumulate={acc} bias={use_bias} mask={use_mask}")
+                Cd = pad(C0)
+                B.gemm(0, tb, M, N, K, Ad, Ad.shape[1], Wd, Wd.shape[1], Cd, Cd.shape[1], B.F32, accumulate=acc, bias=bias if use_bias else None,
+                       relu=relu, relu_mask=Md if use_mask else None, ldm=Md.shape[1] if use_mask else 0, ws=ws, ws_bytes=wsb, f32_product=form)
+                torch.cuda.synchronize()
+                ref = plain + C0 if acc else plain
+                ref = ref + bias.double() if use_bias else ref
+                ref = ref.clamp(min=0) if relu else ref
+                ref = ref * (mask > 0) if use_mask else ref
+                assert torch.equal(Cd[:, :N].double(), ref) and Cd[:, N:].isnan().all()
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_gemm_f32_split_product(env, ta, tb):
     """fp32 operands cut into three bf16 pieces and multiplied on the bf16 matrix cores.  (1) With one operand a signed
