@@ -2455,15 +2455,32 @@ static void launch_split_stream_cfg(const GemmArgs &g, const uint16_t *Wt, uint3
 #undef CG_FORM
 }
 
-// gemm_split_stream_kernel where it applies (plain product or sum of two, weights cut into Wt): rows that start on 16 bytes, weights that
-// eight waves hold, more than 64 columns (306 k x 47 x 256 125 us here, 99 in 64-column tiles), and rows for every workgroup.
-// us, gemm_split_kernel -> here: 12800 x 256 x 256 21.9 -> 19.2, 14000 x 256 x 100 15.8 -> 13.1, 26000 x 128 x 128 15.2 -> 13.5, 20000 x 256
-// x 256 31.0 -> 23.4, 180 k x 128 x 128 56.7 -> 40.8, 306 k x 256 x 100 193 -> 123, x 47 with mask 255 -> 126, x 256 341 -> 307 and with
-// mask 353 -> 264; where k falls just above 128 the two are level (70 k x 256 x 200 69.8 / 70.2, 306 k x 100 x 256 152 / 154).
+// Which products of more than 64 columns (306 k x 47 x 256 125 us there, 99 in 64-column tiles) gemm_split_stream_kernel takes; M rows in
+// all, K: both operands of a sum, the first padded to whole steps.  Its time goes by 128 and 256 k, that of gemm_split_kernel by steps of 32
+// and by full rounds of its tiles over the chip.  us alone, gemm_split_kernel -> here, M x N x K:
+// - up to 32 k without a mask it is level or slower: 306000 x 128 x 16 44 -> 53 (masked x 32 100 -> 78); from there to 128 k 0.65 to 1 of
+//   the time: 306000 x 128 x 40 62 -> 55, x 128 94 -> 75, x 256 x 128 174 -> 116, 26000 x 128 x 128 15.2 -> 13.5;
+// - 129 to 192 k it multiplies zeros as well: 306000 x 128 x 160 106 -> 120, x 132 x 160 161 -> 202, x 256 x 192 213 -> 226; so only where the tiles'
+//   last round leaves more than a quarter of their time idle: 20000 x 200 x 192 25.2 -> 21.6, 33000 x 256 x 160 36 -> 36, masked 70000 x 100 x 192 46 -> 34;
+// - above, 0.8 to 1: 306000 x 256 x 256 265 -> 238 (masked 361 -> 245), x 200 248 -> 237; but as before for the seven whole steps of 224 k (130000 x 160 x 224
+//   1.08, masked less), and for one incomplete round of 128 columns (26000 x 68 x 256 1.04, x 96 x 192 1.09);
+// - columns that are no whole groups of four cost it a second pass over them: 306000 x 66 x 160 95 -> 139, x 121 x 160 0.75 as fast; it still
+//   gains where the tiles leave time idle, most of its waves' 32 columns are there and few k are zero: 70000 x 121 x 100 33 -> 29, masked 42 -> 32.
+static bool split_stream_pays(int64_t M, int64_t N, int64_t K, bool masked) {
+    if (N <= 64 || N > 256 || K > 256 || M < 12288) return false;
+    const int64_t tiles = (M + 127) / 128 * ((N + 127) / 128);
+    const bool idle = tiles * 4 <= (tiles + NUM_CU - 1) / NUM_CU * NUM_CU * 3;
+    if (N % 4 != 0) return idle && N % 32 > 16 && K >= 96 && K <= 128;
+    if (K <= 128) return K > 32 || masked;
+    if (K <= 192 || (K == 224 && !masked)) return idle;
+    return tiles > NUM_CU || N > 128 || idle;
+}
+
+// weights cut into Wt; false where its rows do not start on 16 bytes, or it does not pay
 static bool launch_split_stream(const GemmArgs &g, const uint16_t *Wt, int64_t ku_total, int64_t n_pad, hipStream_t st) {
     const bool rows16 = g.a_vec && aligned16(g.A) && aligned16(g.C) && g.ldc % 4 == 0 && (!g.mask || (aligned16(g.mask) && g.ldm % 4 == 0)) &&
                         (!g.A2 || (aligned16(g.A2) && g.lda2 % 4 == 0));
-    if (!rows16 || g.accumulate || g.part || g.out_bf16 || g.K > 256 || g.N <= 64 || g.N > 256 || g.M < 12288 ||
+    if (!rows16 || g.accumulate || g.part || g.out_bf16 || !split_stream_pays(g.M, g.N, g.K, g.mask != nullptr) ||
         g.lda >= (1 << 22) || g.lda2 >= (1 << 22) || g.ldc >= (1 << 22) || g.ldm >= (1 << 22))
         return false;
     const uint32_t ku = static_cast<uint32_t>(ku_total), np = static_cast<uint32_t>(n_pad);

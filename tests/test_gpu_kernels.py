@@ -731,7 +731,8 @@ def test_layer_narrow_weight_gradients_exact(env, n, f_in, f_out):
 
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(24609, 128, 128), (24608, 65, 7), (24640, 100, 129), (20000, 132, 200), (16399, 256, 256), (50001, 255, 47),
-                                   (12288, 200, 256), (12321, 256, 255), (12352, 196, 128), (49183, 64, 256), (49153, 47, 130), (50000, 1, 200)])
+                                   (12288, 200, 256), (12321, 256, 255), (12352, 196, 128), (49183, 64, 256), (49153, 47, 130), (50000, 1, 200),
+                                   (70_001, 121, 100), (70_016, 125, 128), (33_025, 255, 127), (20_011, 200, 161), (70_001, 100, 192), (45_057, 96, 129)])
 def test_gemm_f32_many_rows_exact(env, tb, M, N, K):
     """fp32 products of many rows in three bf16 pieces (weights held in registers where 64 x 64 tiles do not fit the chip at once, up to
     256 columns and 256 k): the last tile of rows whole, short and of one row, K around a unit and around 128 and 256, N not a multiple of
@@ -762,6 +763,33 @@ def test_gemm_f32_many_rows_exact(env, tb, M, N, K):
         ref = ref.clamp(min=0) if relu else ref
         ref = ref * (mask > 0) if use_mask else ref
         assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("M,N,K,streamed", [(26_000, 128, 129, 0), (30_000, 128, 160, 0), (30_000, 100, 192, 0), (70_000, 256, 176, 0), (60_000, 132, 224, 0),
+                                            (26_000, 96, 256, 0), (30_000, 122, 256, 0), (20_000, 200, 160, 1), (70_000, 100, 192, 1), (70_000, 200, 256, 1),
+                                            (33_000, 128, 200, 1)])
+def test_gemm_f32_reductions_of_129_to_256_in_one_chain_or_two(env, M, N, K, streamed):
+    """Which of the two kernels for many rows forms a product in three bf16 pieces: above 128 k the one that keeps the weights in registers
+    adds two chains, the tiled one, which also takes results whose rows do not start on 16 bytes, a single one.  So the results of
+    aligned and unaligned rows are the same bits where the tiled kernel takes both (it is the faster one there), and differ somewhere
+    where the other does."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    pad = lambda w: (w + 3) // 4 * 4  # noqa: E731
+    A, W = torch.randn(M, pad(K), generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    got = []
+    for ldc in (pad(N), pad(N) + 1):
+        say(f"gemm f32 chains {M}x{N}x{K} pitch {ldc}")
+        C = torch.zeros(M, ldc, device="cuda")
+        B.gemm(0, 0, M, N, K, A, A.shape[1], W, N, C, ldc, B.F32, ws=ws, ws_bytes=wsb, f32_product=B.F32_PRODUCT_SPLIT)
+        torch.cuda.synchronize()
+        got.append(C[:, :N])
+    ref = A[:, :K].double() @ W.double()
+    assert all(float((c - ref).norm()) <= 4e-7 * float(ref.norm()) for c in got)
+    assert torch.equal(*got) == (not streamed)
 
 
 @pytest.mark.parametrize("tb", [0, 1])
