@@ -848,10 +848,11 @@ __global__ __launch_bounds__(NS * 64, std::max(1, stream_held(KS, NS) * NS / 4))
     const int cr = tid / (NS * 4), cc = 8 * (tid % (NS * 4));
     const uint32_t ldc2 = static_cast<uint32_t>(g.ldc) * 2, ldm2 = static_cast<uint32_t>(g.ldm) * 2;
     const bool whole = n0 + cc + 8 <= g.N;
-    const bool cut = n0 + NS * 32 > g.N && g.N % 8 != 0;                      // a group of eight columns ends inside the matrix (uniform)
+    const bool cut = !MASK && n0 + NS * 32 > g.N && g.N % 8 != 0;             // a group of eight columns ends inside the matrix (uniform; see bf16_stream_rows)
 
     // mid: what becomes of the A registers between the products and the barrier
     auto tile = [&](int64_t t, int rows, int buf, auto mid) __attribute__((always_inline)) {
+        if constexpr (MASK) asm("" : "+s"(t));         // (addresses per tile: pointers carried from tile to tile take registers that the weights need)
         const char *As = smem + buf * A_BYTES;
         uint16_t *Cs = reinterpret_cast<uint16_t *>(smem + 2 * A_BYTES + buf * C_BYTES);
         const int64_t m0 = t * 32;
@@ -902,15 +903,11 @@ __global__ __launch_bounds__(NS * 64, std::max(1, stream_held(KS, NS) * NS / 4))
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc, at, 0, 2);
         }
         if (cut) {
-            auto msrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(g.mask) + (m0 * g.ldm + n0) * 2, 0, 0x7fffffff, 0x00027000);
 #pragma unroll 1
             for (int e = 0; e < 16; ++e) {
                 const int row = cr + 2 * (e & 8), col = cc + (e & 7);
                 const bool in = !whole && row < rows && n0 + col < g.N;
-                uint16_t x = Cs[row * CPITCH + col];
-                if constexpr (MASK)
-                    if (!positive_bf16(__builtin_amdgcn_raw_buffer_load_b16(msrc, in ? row * ldm2 + 2u * col : 0xfffffff0u, 0, 0))) x = 0;
-                __builtin_amdgcn_raw_buffer_store_b16(x, rsrc, in ? row * ldc2 + 2u * col : 0xfffffff0u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b16(Cs[row * CPITCH + col], rsrc, in ? row * ldc2 + 2u * col : 0xfffffff0u, 0, 0);
             }
         }
     };
@@ -2512,6 +2509,50 @@ static void launch_bf16_tiles(const GemmArgs &g, int bn, bool bm64, dim3 grid, h
 // Units of 16 k that a wave of gemm_bf16_stream_kernel holds, or 0 where it does not apply
 static int stream_units(int64_t K) { return K <= 0 || K > 512 ? 0 : K <= 128 ? 8 : K <= 256 ? 16 : 32; }
 
+// Which products of more than 64 columns (980 k x 47 x 128 104 us there, 91 in tiles; x 256 146 / 149) gemm_bf16_stream_kernel takes: from how
+// many rows on, or a negative number where never.  Its time goes by 128, 256 and 512 k and by 128 columns (up to there) or 256; the tiles
+// (64 rows while they are few) waste less of both, and need no load of weights per workgroup, but read rows that end inside eight k
+// element by element.  So it depends on the reduction (up to 64, 128, 256, below 400 and up to 512; whole eights or not), on whether three
+// quarters of its columns are there, on the mask, which the tiles read as well as it does, and, above 128 columns, on the size of the result
+// rather than on its rows.  Columns that are no whole eights cost it a second pass over them.  A sweep of both kernels (17600 sizes, 16 k to
+// 980 k rows, 66 to 1000 columns, 6 to 512 k) took 0.81 of the tiles' time by these lines, 0.86 with it wherever it applies and 0.81 with the
+// faster one each time.  us, tiles -> here, rows x columns x k:
+//   at most 128 columns: 16384 x 72 x 64 6.2 -> 6.6, 25000 x 96 x 64 0.91; 16384 x 128 x 128 0.86; 100000 x 72 x 264 28 -> 36; 100000 x 128 x 448 0.93
+//   masked: 33000 x 72 x 32 1.11, 50000 x 72 x 32 1.02; 33000 x 128 x 128 0.88; 100000 x 96 x 400 36 -> 39
+//   full: 16384 x 256 x 256 12.6 -> 10.7, 980000 x 256 x 256 322 -> 195; masked 25000 x 256 x 256 1.15, 66000 x 256 x 256 0.9, 16384 x 512 x 128 0.75
+//   not full: 16384 x 160 x 160 1.18, 33000 x 160 x 160 0.97; masked 50000 x 320 x 160 26 -> 31, 100000 x 160 x 160 0.64
+//   ragged: 100000 x 66 x 320 1.64, 50000 x 300 x 32 1.35, masked 50000 x 300 x 8 2.1; but 33000 x 250 x 100 0.69, 100000 x 132 x 128 38 -> 26
+static int64_t bf16_stream_rows(int64_t N, int64_t K, bool masked) {
+    constexpr int64_t Mi = int64_t(1) << 20;
+    if (N <= 64 || !stream_units(K)) return -1;
+    const bool wide = N > 128, full = 3 * ((N + 255) / 256 * 256) < 4 * N, odd = K % 8 != 0;
+    const int band = K <= 64 ? 0 : K <= 128 ? 1 : K <= 256 ? 2 : K < 400 ? 3 : 4;
+    if (!wide) {
+        if (band == 3) return -1;
+        if (N % 8 != 0) return masked || !odd || band == 4 ? -1 : band == 2 ? 49152 : 24576;
+        if (masked) return band == 4 ? 65536 : band == 1 || (band == 2 && !odd) ? 24576 : 49152;
+        return band == 4 && odd ? 49152 : band == 0 || (band == 2 && odd) ? 24576 : 16384;
+    }
+    int64_t result;                     // elements
+    if (N % 8 != 0) {
+        if (masked || (!odd && (band == 0 || band == 3))) return -1;
+        if (full) result = band == 1 || band == 4 || (odd && band != 3) ? 0 : 8 * Mi;
+        else result = band == 4 || (odd && (band == 1 || band == 2)) ? 4 * Mi : band == 3 ? 8 * Mi : 12 * Mi;
+    } else if (!masked) {
+        result = full || band == 1 || band == 4 ? 0 : 4 * Mi;
+    } else if (band == 1 || band == 4 || (odd && band == 0)) {
+        result = full ? 0 : 4 * Mi;
+    } else {
+        result = odd ? 8 * Mi : full && band != 2 ? 7 * Mi : band == 0 ? 12 * Mi : 13 * Mi;
+    }
+    return std::max<int64_t>(16384, (result + N - 1) / N);
+}
+
+static bool bf16_stream_pays(int64_t M, int64_t N, int64_t K, bool masked) {
+    const int64_t rows = bf16_stream_rows(N, K, masked);
+    return rows > 0 && M >= rows;
+}
+
 template <int KS, int NS>
 static void launch_stream_cfg(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad, hipStream_t st) {
     constexpr int HELD = NUM_CU * stream_held(KS, NS);
@@ -2656,10 +2697,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
     g.c_staged = half_path && g.out_bf16 && !g.part && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0 &&
                  (!relu_mask || (aligned16(relu_mask) && (ldm * 2) % 16 == 0));
-    // gemm_bf16_stream_kernel from about one tile per workgroup on, where the load of W into registers is paid back (us against the
-    // tiled kernel, 10000 x 256 x 128 9.7 / 8.0, 20000 x 256 x 256 11.8 / 14.2, 30000 x 256 x 256 13.3 / 18.5, 60000 x 128 x 128 10.1 /
-    // 14.2), and above 64 columns (980 k x 47 x 128 104 / 91, 980 k x 47 x 256 146 / 149)
-    const bool stream_path = g.c_staged && !trans_a && stream_units(K) && N > 64 && M >= 16384 && ws &&
+    const bool stream_path = g.c_staged && !trans_a && bf16_stream_pays(M, N, K, relu_mask != nullptr) && ws &&
                              ws_bytes >= static_cast<size_t>(split_rows(N)) * stream_units(K) * 32 && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;

@@ -645,7 +645,8 @@ def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
 
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(16384, 128, 128), (16385, 65, 7), (16415, 100, 129), (20000, 130, 200), (16399, 256, 256), (50001, 257, 47),
-                                   (16386, 300, 256), (17003, 200, 257), (16384, 72, 511), (16417, 256, 512), (16383, 256, 64), (16390, 256, 520)])
+                                   (16386, 300, 256), (17003, 200, 257), (16384, 72, 511), (16417, 256, 512), (16383, 256, 64), (16390, 256, 520),
+                                   (30_000, 128, 128), (30_001, 72, 96), (25_009, 66, 100), (70_017, 160, 257), (60_031, 256, 256), (33_001, 250, 200), (49_185, 100, 129)])
 def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
     """bf16 products of many rows whose result is stored as bf16 (weights held in registers from 16384 rows on): the last tile of
     rows whole, short and of one row, K around a unit and around 128, 256 and 512, N not a multiple of eight, of a wave's 32 and of a
@@ -674,6 +675,36 @@ def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
         ref = ref.clamp(min=0) if relu else ref
         ref = ref * (mask > 0) if use_mask else ref
         assert torch.equal(Cd[:, :N].float(), ref) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("M,N,K,mask,streamed", [(20_000, 72, 64, 0, 0), (25_000, 72, 64, 0, 1), (30_000, 120, 248, 1, 1), (20_000, 120, 248, 1, 0), (50_000, 96, 320, 0, 0),
+                                                 (50_000, 96, 448, 0, 1), (50_000, 66, 200, 0, 0), (25_000, 66, 100, 0, 1), (50_000, 100, 128, 1, 0), (16_384, 256, 160, 0, 1),
+                                                 (16_384, 160, 160, 0, 0), (30_000, 160, 160, 0, 1), (50_000, 160, 160, 1, 0), (90_000, 160, 160, 1, 1), (40_000, 248, 248, 1, 0),
+                                                 (60_000, 248, 248, 1, 1), (16_384, 504, 120, 1, 1), (50_000, 300, 64, 0, 0), (50_000, 250, 200, 0, 1), (50_000, 250, 200, 1, 0),
+                                                 (16_383, 248, 200, 0, 0), (100_000, 64, 128, 0, 0)])
+def test_gemm_bf16_many_rows_route(env, M, N, K, mask, streamed):
+    """Which bf16 products of many rows keep their weights in registers and which run in tiles, from the image of the weights left in the
+    workspace, at sizes where each is the faster one; the result of either against float64 (one rounding, 2^-8 of a value at most, and
+    sums in float: 2^-9 in the 2-norm)."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    pad = lambda x: torch.nn.functional.pad(x.bfloat16(), (0, -x.shape[1] % 8)).contiguous()  # noqa: E731
+    A, W, Md = (pad(torch.randn(r, c, generator=gen, device="cuda")) for r, c in ((M, K), (K, N), (M, N)))
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    C = torch.zeros(M, Md.shape[1], dtype=torch.bfloat16, device="cuda")
+    say(f"gemm bf16 route {M}x{N}x{K} mask={mask}")
+    B.gemm(0, 0, M, N, K, A, A.shape[1], W, W.shape[1], C, C.shape[1], B.BF16, relu_mask=Md if mask else None, ldm=Md.shape[1] if mask else 0, ws=ws, ws_bytes=wsb)
+    torch.cuda.synchronize()
+    units = 8 if K <= 128 else 16 if K <= 256 else 32
+    tiled = N * -(-K // 8) * 16                                         # the weights as the tiles read them, at most
+    image = -(-N // 128) * 128 * units * 32
+    assert tiled < image <= wsb
+    assert bool((ws[tiled:image] != 0xA5).any()) == bool(streamed)
+    ref = A[:, :K].double() @ W[:, :N].double()
+    ref = ref * (Md[:, :N] > 0) if mask else ref
+    assert float((C[:, :N].double() - ref).norm()) <= 2.0 ** -9 * float(ref.norm())
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 16384), (3, 7, 16385), (64, 16, 16387), (100, 17, 20003), (127, 32, 16447), (128, 33, 16449), (130, 41, 30001),
