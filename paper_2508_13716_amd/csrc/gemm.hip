@@ -2315,6 +2315,12 @@ static size_t split_b_bytes(int64_t N, int64_t K) {
     return align_up(static_cast<size_t>(3) * split_rows(N) * split_ld(K) * sizeof(uint16_t), 256);
 }
 
+// Units of 16 k that a wave of gemm_bf16_stream_kernel holds, or 0 where it does not apply; its image of the weights
+static int stream_units(int64_t K) { return K <= 0 || K > 512 ? 0 : K <= 128 ? 8 : K <= 256 ? 16 : 32; }
+static size_t stream_b_bytes(int64_t N, int64_t K) {
+    return N > 64 ? static_cast<size_t>(split_rows(N)) * stream_units(K) * 16 * sizeof(uint16_t) : 0;
+}
+
 static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches = 1);
 static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk);
 
@@ -2335,8 +2341,8 @@ size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
             s_max = std::max(s_max, z);
         }
     if (trans_a) b += align_up(static_cast<size_t>(s_max) * N * sizeof(float), 256);
-    // room to lay a weight matrix out for the bf16 kernel (bf16 operands) or as its three planes (fp32 operands)
-    if (!trans_a) b = std::max(b, std::max(transposed_b_bytes(N, K), split_b_bytes(N, K)));
+    // room to lay a weight matrix out for the bf16 kernels (bf16 operands) or as its three planes (fp32 operands)
+    if (!trans_a) b = std::max({b, transposed_b_bytes(N, K), split_b_bytes(N, K), stream_b_bytes(N, K)});
     return b;
 }
 
@@ -2505,9 +2511,6 @@ static void launch_bf16_tiles(const GemmArgs &g, int bn, bool bm64, dim3 grid, h
     if (bn == 64) hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 64>), grid, dim3(256), 0, st, g);
     else hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, 128, 128>), grid, dim3(256), 0, st, g);
 }
-
-// Units of 16 k that a wave of gemm_bf16_stream_kernel holds, or 0 where it does not apply
-static int stream_units(int64_t K) { return K <= 0 || K > 512 ? 0 : K <= 128 ? 8 : K <= 256 ? 16 : 32; }
 
 // Which products of more than 64 columns (980 k x 47 x 128 104 us there, 91 in tiles; x 256 146 / 149) gemm_bf16_stream_kernel takes: from how
 // many rows on, or a negative number where never.  Its time goes by 128, 256 and 512 k and by 128 columns (up to there) or 256; the tiles
@@ -2698,7 +2701,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     g.c_staged = half_path && g.out_bf16 && !g.part && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0 &&
                  (!relu_mask || (aligned16(relu_mask) && (ldm * 2) % 16 == 0));
     const bool stream_path = g.c_staged && !trans_a && bf16_stream_pays(M, N, K, relu_mask != nullptr) && ws &&
-                             ws_bytes >= static_cast<size_t>(split_rows(N)) * stream_units(K) * 32 && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
+                             ws_bytes >= stream_b_bytes(N, K) && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
     if (narrow) {

@@ -646,7 +646,8 @@ def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(16384, 128, 128), (16385, 65, 7), (16415, 100, 129), (20000, 130, 200), (16399, 256, 256), (50001, 257, 47),
                                    (16386, 300, 256), (17003, 200, 257), (16384, 72, 511), (16417, 256, 512), (16383, 256, 64), (16390, 256, 520),
-                                   (30_000, 128, 128), (30_001, 72, 96), (25_009, 66, 100), (70_017, 160, 257), (60_031, 256, 256), (33_001, 250, 200), (49_185, 100, 129)])
+                                   (30_000, 128, 128), (30_001, 72, 96), (25_009, 66, 100), (70_017, 160, 257), (60_031, 256, 256), (33_001, 250, 200), (49_185, 100, 129),
+                                   (24_577, 65, 7), (16_417, 256, 16), (24_600, 72, 17), (16_400, 200, 32)])
 def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
     """bf16 products of many rows whose result is stored as bf16 (weights held in registers from 16384 rows on): the last tile of
     rows whole, short and of one row, K around a unit and around 128, 256 and 512, N not a multiple of eight, of a wave's 32 and of a
@@ -681,10 +682,11 @@ def test_gemm_bf16_many_rows_exact(env, tb, M, N, K):
                                                  (50_000, 96, 448, 0, 1), (50_000, 66, 200, 0, 0), (25_000, 66, 100, 0, 1), (50_000, 100, 128, 1, 0), (16_384, 256, 160, 0, 1),
                                                  (16_384, 160, 160, 0, 0), (30_000, 160, 160, 0, 1), (50_000, 160, 160, 1, 0), (90_000, 160, 160, 1, 1), (40_000, 248, 248, 1, 0),
                                                  (60_000, 248, 248, 1, 1), (16_384, 504, 120, 1, 1), (50_000, 300, 64, 0, 0), (50_000, 250, 200, 0, 1), (50_000, 250, 200, 1, 0),
-                                                 (16_383, 248, 200, 0, 0), (100_000, 64, 128, 0, 0)])
+                                                 (16_383, 248, 200, 0, 0), (100_000, 64, 128, 0, 0),
+                                                 (30_000, 65, 7, 0, 1), (30_000, 72, 16, 0, 1), (20_000, 256, 24, 0, 1), (20_000, 200, 32, 0, 1), (70_000, 128, 7, 1, 1)])
 def test_gemm_bf16_many_rows_route(env, M, N, K, mask, streamed):
     """Which bf16 products of many rows keep their weights in registers and which run in tiles, from the image of the weights left in the
-    workspace, at sizes where each is the faster one; the result of either against float64 (one rounding, 2^-8 of a value at most, and
+    workspace, at sizes where each is the faster one and with the workspace that was asked for; the result of either against float64 (one rounding, 2^-8 of a value at most, and
     sums in float: 2^-9 in the 2-norm)."""
     torch, B = env["torch"], env["B"]
     gen = torch.Generator(device="cuda")
