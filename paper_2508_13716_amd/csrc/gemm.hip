@@ -2321,6 +2321,8 @@ static size_t stream_b_bytes(int64_t N, int64_t K) {
     return N > 64 ? static_cast<size_t>(split_rows(N)) * stream_units(K) * 16 * sizeof(uint16_t) : 0;
 }
 
+constexpr int64_t NARROW_K = 16384;         // see narrow_product
+static size_t narrow_ws_bytes(int64_t M, int64_t N, int64_t K);
 static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches = 1);
 static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk);
 
@@ -2341,6 +2343,7 @@ size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
             s_max = std::max(s_max, z);
         }
     if (trans_a) b += align_up(static_cast<size_t>(s_max) * N * sizeof(float), 256);
+    if (trans_a && N <= 64 && K >= NARROW_K) b = std::max(b, narrow_ws_bytes(M, N, K));
     // room to lay a weight matrix out for the bf16 kernels (bf16 operands) or as its three planes (fp32 operands)
     if (!trans_a) b = std::max({b, transposed_b_bytes(N, K), split_b_bytes(N, K), stream_b_bytes(N, K)});
     return b;
@@ -2404,23 +2407,33 @@ static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t
 }
 
 // Which reductions over vertices take gemm_narrow_kernel: those of 16384 vertices and more.  us, gemm_small_kernel (up to 2^31
-// multiply-adds) or gemm_kernel -> here: 128 x 32 x 21557 13.7 -> 13.0, 50 x 41 x 21557 17.8 -> 13.9, 128 x 47 x 50000 26 -> 18, 256 x
-// 41 x 180000 97 -> 57, 602 x 41 x 60000 88 -> 52, 200 x 16 x 250000 66 -> 42, 256 x 47 x 306000 164 -> 100 (3.7 TB/s), 602 x 64 x
-// 250000 276 -> 219; below, where few batches leave most of the time to the start: 100 x 64 x 9973 12.9 -> 13.2, 128 x 64 x 8192
-// 11.2 -> 14.2, 64 x 7 x 9973 10.0 -> 9.9.
+// multiply-adds) or gemm_kernel -> here: 50 x 41 x 22000 18.5 -> 11.4, 128 x 47 x 60000 27.7 -> 17.9, 256 x 41 x 180000 99 -> 54, 602 x 41 x
+// 60000 90 -> 51, 256 x 47 x 306000 164 -> 100 (3.7 TB/s), 602 x 64 x 180000 205 -> 155; below, where few batches leave most of the time
+// to the start: 100 x 64 x 9973 12.9 -> 13.2, 128 x 64 x 8192 11.2 -> 14.2, 64 x 7 x 9973 10.0 -> 9.9.  At most 32 rows fill a quarter of its tile: with more than 16 columns that costs it more than the
+// loads above 2^18 vertices (32 x 24 x 600000 44 -> 61, 16 x 64 x 600000 65 -> 97; 16 x 64 x 180000 37 -> 35).
 static bool narrow_product(int dtype, int mode, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K) {
-    return dtype == CAPGNN_F32 && trans_a && !trans_b && N <= 64 && mode != CAPGNN_F32_PRODUCT_SPLIT && K >= 16384;
+    return dtype == CAPGNN_F32 && trans_a && !trans_b && N <= 64 && mode != CAPGNN_F32_PRODUCT_SPLIT && K >= NARROW_K &&
+           !(M <= 32 && N > 16 && K > (1 << 18));
 }
 
-// Its splits: the workgroups that the chip holds (two or three per compute unit), each wave with NARROW_AHEAD batches at least, in eights, as far as
-// the workspace goes (0: not even one split)
-static int narrow_splits(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
-    const int64_t gy = (M + 127) / 128;
-    int64_t s = std::min<int64_t>((N <= 32 ? 3 : 2) * NUM_CU / gy, K / 64);
-    if (s > 8) s = s / 8 * 8;
-    s = std::max<int64_t>(s, 1);
-    const size_t one = static_cast<size_t>(M * N + N) * sizeof(float) + 256;
-    return static_cast<int>(std::min<int64_t>(s, static_cast<int64_t>(ws_bytes / one)));
+// Its splits: as many as make one workgroup per compute unit, or two where a split is longer than 1024 vertices, in eights.  Between the
+// two some compute units have twice the work of others (256 x 64 x 40000 with 256 workgroups 23.5 us, 320 33.4, 512 27.2), and
+// the more splits the more parts to add up.
+static int narrow_splits(int64_t M, int64_t K) {
+    const int64_t gy = (M + 127) / 128, s = (gy * K > (int64_t(1) << 18) ? 2 : 1) * NUM_CU / gy;
+    return static_cast<int>(std::max<int64_t>(s > 8 ? s / 8 * 8 : s, 1));
+}
+
+static size_t narrow_ws_bytes(int64_t M, int64_t N, int64_t K) {
+    const size_t s = static_cast<size_t>(narrow_splits(M, K));
+    return align_up(s * M * N * sizeof(float), 256) + align_up(s * N * sizeof(float), 256);
+}
+
+// as far as the workspace goes (0: not even one split)
+static int narrow_fit(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+    const size_t one = static_cast<size_t>(M * N + N) * sizeof(float);
+    return ws_bytes >= narrow_ws_bytes(M, N, K) ? narrow_splits(M, K)
+                                                : static_cast<int>(std::min<int64_t>(narrow_splits(M, K), ws_bytes > 512 ? static_cast<int64_t>((ws_bytes - 512) / one) : 0));
 }
 
 // AUTO: smaller products stay on the fp32 instruction (the caller is told the limit), and so do weight gradients at most 64
@@ -2647,10 +2660,10 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         small_path = false;
         S = choose_split(trans_a, M, N, K, bm, bn, bk, true);
     }
-    const bool narrow = narrow_product(dtype, mode, trans_a, trans_b, M, N, K) && ws && narrow_splits(M, N, K, ws_bytes) > 0;
+    const bool narrow = narrow_product(dtype, mode, trans_a, trans_b, M, N, K) && ws && narrow_fit(M, N, K, ws_bytes) > 0;
     if (narrow) {
         small_path = false;
-        S = narrow_splits(M, N, K, ws_bytes);
+        S = narrow_fit(M, N, K, ws_bytes);
         bn = 64;
     }
     if (small_path) {
@@ -2779,8 +2792,8 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
     // two narrow reductions over vertices
     const size_t half_ws = ws_bytes / 2 / 256 * 256;
-    const int narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K)
-                           ? narrow_splits(g.M, g.N, g.K, half_ws) : 0;
+    const bool narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K) &&
+                        narrow_fit(g.M, g.N, g.K, half_ws) > 0;
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     // the three-piece form on the terms of launch_gemm and launch_gemm_dual
     const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&
@@ -2792,11 +2805,11 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     int tn = 2, S = 1;
     g.k_chunk = Ksum;
     if (narrow) {
-        S = narrow;
+        S = narrow_fit(g.M, g.N, g.K, half_ws);
         g.k_chunk = ((g.K + S - 1) / S + 15) / 16 * 16;
         g.part = static_cast<float *>(ws);
         s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + half_ws);
-        if (colsum) g.colpart = g.part + static_cast<size_t>(S) * g.M * g.N;
+        if (colsum) g.colpart = g.part + align_up(static_cast<size_t>(S) * g.M * g.N * sizeof(float), 256) / sizeof(float);
     } else if (small) small_geometry(bf, trans_a, g.M, g.N, g.K, &tn, &S, &g.k_chunk);
     if (s.dual && S > 1) return CAPGNN_OK;           // a sum is formed by the waves of one workgroup
     if (narrow) {

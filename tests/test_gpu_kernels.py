@@ -736,6 +736,26 @@ def test_gemm_f32_narrow_vertex_reduction_exact(env, M, N, K):
             assert torch.equal(Cd[:, :N].double(), want) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(64, 41, 20_000), (128, 47, 250_000), (128, 24, 300_000), (256, 64, 40_000), (264, 20, 30_000), (300, 41, 200_000), (602, 64, 16_384)])
+def test_gemm_f32_narrow_vertex_reduction_fills_the_chip_evenly(env, M, N, K):
+    """With the workspace that was asked for, a narrow X^T G is cut into as many parts as make one workgroup per compute unit, or two where
+    the parts are long, and no number between: counted in the parts left in the workspace.  Small integers: equality."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    A, G = (torch.randint(-3, 4, (K, w), generator=gen, device="cuda").float() for w in (M, N))
+    wsb = B.gemm_workspace_bytes(1, M, N, K)
+    ws = torch.full((wsb // 4,), float("nan"), device="cuda")
+    C = torch.zeros(M, N, device="cuda")
+    say(f"gemm narrow X^T G parts {M}x{N}x{K}")
+    B.gemm(1, 0, M, N, K, A, M, G, N, C, N, B.F32, ws=ws, ws_bytes=wsb)
+    torch.cuda.synchronize()
+    tiles, per_cu = -(-M // 128), 2 if K * -(-M // 128) > 1 << 18 else 1
+    most = 256 * per_cu // tiles
+    assert int((~ws.isnan()).sum()) == M * N * (most // 8 * 8 if most > 8 else most)
+    assert torch.equal(C.double(), A.double().T @ G.double())
+
+
 @pytest.mark.parametrize("n,f_in,f_out", [(16384, 100, 41), (20001, 130, 64), (40000, 64, 8)])
 def test_layer_narrow_weight_gradients_exact(env, n, f_in, f_out):
     """Both weight gradients and the bias gradient of a GraphSAGE layer with at most 64 outputs, over 16384 vertices and more, one entry
