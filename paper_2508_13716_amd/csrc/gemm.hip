@@ -2429,13 +2429,6 @@ static size_t narrow_ws_bytes(int64_t M, int64_t N, int64_t K) {
     return align_up(s * M * N * sizeof(float), 256) + align_up(s * N * sizeof(float), 256);
 }
 
-// as far as the workspace goes (0: not even one split)
-static int narrow_fit(int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
-    const size_t one = static_cast<size_t>(M * N + N) * sizeof(float);
-    return ws_bytes >= narrow_ws_bytes(M, N, K) ? narrow_splits(M, K)
-                                                : static_cast<int>(std::min<int64_t>(narrow_splits(M, K), ws_bytes > 512 ? static_cast<int64_t>((ws_bytes - 512) / one) : 0));
-}
-
 // AUTO: smaller products stay on the fp32 instruction (the caller is told the limit), and so do weight gradients at most 64
 // columns wide (half of the threads that stage their operands would idle; measured slower)
 static bool split_form(int mode, int trans_a, int64_t M, int64_t N, int64_t K) {
@@ -2660,10 +2653,10 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         small_path = false;
         S = choose_split(trans_a, M, N, K, bm, bn, bk, true);
     }
-    const bool narrow = narrow_product(dtype, mode, trans_a, trans_b, M, N, K) && ws && narrow_fit(M, N, K, ws_bytes) > 0;
+    const bool narrow = narrow_product(dtype, mode, trans_a, trans_b, M, N, K) && ws && ws_bytes >= narrow_ws_bytes(M, N, K);
     if (narrow) {
         small_path = false;
-        S = narrow_fit(M, N, K, ws_bytes);
+        S = narrow_splits(M, K);
         bn = 64;
     }
     if (small_path) {
@@ -2793,7 +2786,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     // two narrow reductions over vertices
     const size_t half_ws = ws_bytes / 2 / 256 * 256;
     const bool narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K) &&
-                        narrow_fit(g.M, g.N, g.K, half_ws) > 0;
+                        half_ws >= narrow_ws_bytes(g.M, g.N, g.K);
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     // the three-piece form on the terms of launch_gemm and launch_gemm_dual
     const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&
@@ -2805,7 +2798,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     int tn = 2, S = 1;
     g.k_chunk = Ksum;
     if (narrow) {
-        S = narrow_fit(g.M, g.N, g.K, half_ws);
+        S = narrow_splits(g.M, g.K);
         g.k_chunk = ((g.K + S - 1) / S + 15) / 16 * 16;
         g.part = static_cast<float *>(ws);
         s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + half_ws);

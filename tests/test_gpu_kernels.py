@@ -713,8 +713,9 @@ def test_gemm_bf16_many_rows_route(env, M, N, K, mask, streamed):
                                    (257, 48, 16400), (602, 49, 17000), (255, 64, 65537)])
 def test_gemm_f32_narrow_vertex_reduction_exact(env, M, N, K):
     """X^T G in float with at most 64 columns over 16384 vertices and more: tiles of 16 columns and of 128 rows whole and ragged, K around
-    batches and splits, rows aligned and not, workspace as asked for and for two splits only, accumulating and with bias and ReLU.
-    Small integers (sums below 2^24): equality.  Padding is NaN; the last rows end with the allocation."""
+    batches and splits, rows aligned and not, accumulating and with bias and ReLU; with less than the workspace asked for, the splits of
+    the staged kernel (one for every 16 steps of 16, and no more than fill the chip six times), and with room for two splits
+    CAPGNN_ENOMEM, C untouched.  Small integers (sums below 2^24): equality.  Padding is NaN; the last rows end with the allocation."""
     torch, B = env["torch"], env["B"]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M + N + K)
@@ -725,12 +726,20 @@ def test_gemm_f32_narrow_vertex_reduction_exact(env, M, N, K):
     for pad in (0, 1, 4):
         flat = lambda x: torch.cat([torch.nn.functional.pad(x[:-1], (0, pad), value=float("nan")).reshape(-1), x[-1]])  # noqa: E731
         Ad, Gd = flat(A), flat(G)
-        for room, accumulate, relu in ((wsb, 0, 0), (wsb, 1, 1), (2 * (M * N + N) * 4 + 512, 0, 0)):
+        least = min(1536 // -(-M // 128), K // 256) * M * N * 4
+        for room, accumulate, relu in ((wsb, 0, 0), (wsb, 1, 1), (least, 0, 0), (2 * M * N * 4, 0, 0)):
             say(f"gemm narrow X^T G {M}x{N}x{K} pad={pad} workspace={room} accumulate={accumulate}")
             ws = torch.empty(room, dtype=torch.uint8, device="cuda")
             Cd = torch.full((M, N + 3), 2.0, device="cuda")
-            B.gemm(1, 0, M, N, K, Ad, M + pad, Gd, N + pad, Cd, N + 3, B.F32, accumulate=accumulate, bias=bias if relu else None, relu=relu,
-                   ws=ws, ws_bytes=room)
+            call = lambda: B.gemm(1, 0, M, N, K, Ad, M + pad, Gd, N + pad, Cd, N + 3, B.F32, accumulate=accumulate, bias=bias if relu else None,  # noqa: E731
+                                  relu=relu, ws=ws, ws_bytes=room)
+            if room == 2 * M * N * 4:
+                with pytest.raises(B.CapgnnError) as e:
+                    call()
+                torch.cuda.synchronize()
+                assert e.value.code == B.ENOMEM and (Cd == 2.0).all()
+                continue
+            call()
             torch.cuda.synchronize()
             want = (ref + 2.0 + bias).clamp(min=0) if accumulate else ref
             assert torch.equal(Cd[:, :N].double(), want) and (Cd[:, N:] == 2.0).all()
