@@ -505,8 +505,13 @@ typedef struct {
  *   c: NULL iff n_halo == 0.  labels/mask: device.  logits: device float [n_loc x f_out(L-1)] dense, or NULL.
  *   dW[l], dW_self[l], dbias[l]: device float buffers per layer (dW_self[l] NULL for GCN).
  *   loss_out: host float*, written after a stream synchronisation (the only forced sync);
- *   times: NULL, or filled from HIP events recorded on the streams the kernels run on (adds a sync).
- *   ws: capgnn_epoch_workspace_bytes(); side_stream may be NULL (then everything runs on `stream`).
+ *   times: NULL, or filled from HIP events recorded on the streams the kernels run on (adds a sync).  A timed epoch runs
+ *     stage by stage, so that each record holds its own work: sums over the parts of a weight gradient count as combine,
+ *     those of the loss as loss, other_ms holds passes over a gradient alone and the update.  An epoch without times may
+ *     copy the halo rows of all layers in one launch at its start, and leave those sums and the update to one at its end;
+ *     its results are the same bits.
+ *   ws: capgnn_epoch_workspace_bytes() (at most 64 MiB of it for parts of weight gradients kept to the epoch's end);
+ *     side_stream may be NULL (then everything runs on `stream`).
  * Errors: EINVAL, ENOMEM (workspace too small), EUNSUPPORTED, EHIP. */
 size_t capgnn_epoch_workspace_bytes(const capgnn_graph *g, const capgnn_cache *c,
                                     const capgnn_layer *layers, int L);

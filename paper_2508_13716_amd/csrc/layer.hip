@@ -672,7 +672,8 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
     int cur = 0;
     BwdFusion fuse;
     FinishList finish;
-    FinishList *later = gradients_apart(layers, L, dW, dW_self, dbias) ? &finish : nullptr;
+    // (a timed epoch adds up every stage's sums in that stage)
+    FinishList *later = !g_rec.on && gradients_apart(layers, L, dW, dW_self, dbias) ? &finish : nullptr;
     {
         Scope s(CAPGNN_K_LOSS, L - 1, 0, st);
         // a bf16 model gets the gradient in fp32 first (the bias gradient is summed before rounding)

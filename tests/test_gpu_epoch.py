@@ -517,6 +517,44 @@ def test_epoch_gradient_rows_outside_the_loss_are_skipped(env, kind, dtype, n, c
         assert err <= (1e-5 if dtype == "f32" else 2.0 ** -9) if share else not dw.any()
 
 
+@pytest.mark.parametrize("kind,dtype,lr", [("sage", "f32", 0.0), ("sage", "f32", 0.1), ("gcn", "f32", 0.0), ("gcn", "bf16", 0.0)])
+def test_timed_epoch_keeps_every_stage_its_own_work(env, kind, dtype, lr):
+    """The records of a timed epoch whose weight gradients are sums over parts: one loss record, forward and backward products for every
+    layer; GraphSAGE, which needs no pass over a gradient alone, has an elementwise record where there is an update and no other.  Results are
+    the same bits as those of an epoch without times, which leaves the sums to its end."""
+    torch, B = env["torch"], env["B"]
+    rng = np.random.default_rng(5)
+    n, dims, L = 3001, (40, 32, 24, 7), 3
+    dt, code = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    mk = lambda *s: (torch.randn(*s, generator=gen, device="cuda") / 5).to(dt)  # noqa: E731
+    g = B.Graph(n, 0, np.arange(0, 4 * n + 1, 4, dtype=np.int64), rng.integers(0, n, 4 * n).astype(np.int32), np.full(n, 0.25, np.float32), None)
+    w, w_self = [mk(a, b) for a, b in zip(dims, dims[1:])], [mk(a, b) for a, b in zip(dims, dims[1:])]
+    b = [torch.randn(d, generator=gen, device="cuda") for d in dims[1:]]
+    x, labels = mk(n, dims[0]), torch.randint(0, dims[-1], (n,), generator=gen, device="cuda", dtype=torch.int32)
+    order = B.AGG_FIRST if kind == "sage" else B.XFORM_FIRST
+    sage = kind == "sage"
+    start = [t.clone() for t in w + w_self + b]
+    outs = []
+    for timed in (False, True):
+        say(f"timed epoch {kind} {dtype} lr={lr} timed={timed}")
+        for t, s in zip(w + w_self + b, start): t.copy_(s)
+        layers = [B.make_layer(B.SAGE_MEAN if sage else B.GCN, dims[l], dims[l + 1], B.ACT_RELU if l < L - 1 else B.ACT_NONE, code, w[l],
+                               w_self[l] if sage else None, b[l], order, out_f32=int(l == L - 1 and dtype == "bf16")) for l in range(L)]
+        ws = torch.empty(B.epoch_workspace_bytes(g, None, layers), dtype=torch.uint8, device="cuda")
+        dw, ds = ([torch.zeros(a, c, device="cuda") for a, c in zip(dims, dims[1:])] for _ in range(2))
+        db, logits = [torch.zeros(d, device="cuda") for d in dims[1:]], torch.zeros(n, dims[-1], device="cuda")
+        loss, times = B.epoch(g, None, layers, x, dims[0], labels, None, 0.0, logits, dw, ds if sage else None, db, lr, ws, ws.numel(), want_times=timed)
+        outs.append([*(t.clone() for t in dw + ds + db + w + w_self + b + [logits]), torch.tensor(loss)])
+    kinds = [(r["kind"], r["layer"], r["backward"]) for r in times["records"]]
+    assert kinds.count(("loss", L - 1, 0)) == 1
+    assert all((k, l, bw) in kinds for l in range(L) for k, bw in (("gemm", 0), ("gemm", 1)))
+    passes = [k for k in kinds if k[0] == "elementwise"]
+    if sage: assert passes == ([("elementwise", 0, 1)] if lr else []) and (times["other_ms"] > 0) == bool(lr)
+    assert all(torch.equal(p, q) for p, q in zip(*outs))
+
+
 @pytest.mark.parametrize("recorded", [False, True])
 @pytest.mark.parametrize("L,shared", [(2, "none"), (3, "dw"), (3, "bias"), (16, "none"), (16, "dw")])
 def test_epoch_end_adds_up_every_gradient(env, L, shared, recorded):
