@@ -517,6 +517,44 @@ def test_epoch_gradient_rows_outside_the_loss_are_skipped(env, kind, dtype, n, c
         assert err <= (1e-5 if dtype == "f32" else 2.0 ** -9) if share else not dw.any()
 
 
+@pytest.mark.parametrize("n,hidden,classes", [(30_017, 100, 47), (30_016, 200, 47), (30_001, 200, 121), (66_001, 125, 47), (30_017, 130, 41), (30_017, 255, 100)])
+def test_epoch_masked_sum_of_two_split_products(env, n, hidden, classes):
+    """The input gradient of a transform-first GraphSAGE layer under the ReLU of the layer below, one launch over both weight matrices with the
+    mask in its epilogue: with the weights in registers (one and two waves to a reduction, whole and ragged groups of columns) and in
+    tiles.  Self loops only, so the lower layer's gradients are x^T (dZ (W + W_self)^T masked) and its column sums: each column against
+    float64 with the epoch's own hidden layer and logits, 2e-6 of the largest (sums of up to 66000 terms in splits of 200 and a few float
+    roundings before them; 2e-7 measured)."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + hidden)
+    mk = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+    f_in = 24
+    g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.ones(n, np.float32), None)
+    x, w, w_self = mk(n, f_in), [mk(f_in, hidden) / 5, mk(hidden, classes) / 10], [mk(f_in, hidden) / 5, mk(hidden, classes) / 10]
+    b = [mk(hidden) / 5, mk(classes) / 5]
+    layers = [B.make_layer(B.SAGE_MEAN, f_in, hidden, B.ACT_RELU, B.F32, w[0], w_self[0], b[0], B.AGG_FIRST, f32_product=B.F32_PRODUCT_SPLIT),
+              B.make_layer(B.SAGE_MEAN, hidden, classes, B.ACT_NONE, B.F32, w[1], w_self[1], b[1], B.XFORM_FIRST, f32_product=B.F32_PRODUCT_SPLIT)]
+    labels = torch.randint(0, classes, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    dw, ds, db = ([torch.zeros_like(t) for t in v] for v in (w, w_self, b))
+    logits = torch.zeros(n, classes, device="cuda")
+    ws = torch.empty(B.epoch_workspace_bytes(g, None, layers), dtype=torch.uint8, device="cuda")
+    say(f"masked sum of two products {n} {hidden} {classes}")
+    B.epoch(g, None, layers, x, f_in, labels, None, 0.0, logits, dw, ds, db, 0.0, ws, ws.numel())
+    torch.cuda.synchronize()
+    at, ld = B.epoch_activation(g, None, layers, 0, ws)
+    at -= ws.data_ptr()
+    h = ws[at:at + 4 * n * ld].view(torch.float32).view(n, ld)[:, :hidden]
+    assert float((h.double() - (x.double() @ (w[0] + w_self[0]).double() + b[0].double()).clamp(min=0)).norm()) <= 1e-6 * float(h.double().norm())
+    dz = torch.softmax(logits.double(), 1)
+    dz[torch.arange(n, device="cuda"), labels.long()] -= 1
+    dz0 = (dz / n) @ (w[1].double() + w_self[1].double()).T * (h > 0)
+    for got, ref in ((dw[0], x.double().T @ dz0), (ds[0], x.double().T @ dz0), (db[0], dz0.sum(0))):
+        e = float((got.double() - ref).abs().max() / ref.abs().max())
+        say(f"   {e:.2e}")
+        assert e <= 2e-6
+    g.close()
+
+
 @pytest.mark.parametrize("kind,dtype,lr", [("sage", "f32", 0.0), ("sage", "f32", 0.1), ("gcn", "f32", 0.0), ("gcn", "bf16", 0.0)])
 def test_timed_epoch_keeps_every_stage_its_own_work(env, kind, dtype, lr):
     """The records of a timed epoch whose weight gradients are sums over parts: one loss record, forward and backward products for every

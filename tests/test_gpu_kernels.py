@@ -1125,11 +1125,12 @@ def test_layer_bwd_with_one_buffer_for_both_weight_gradients(env, dtype, n):
 
 
 @pytest.mark.parametrize("order", [1, 2])
-@pytest.mark.parametrize("n,f_in,f_out", [(50_000, 40, 60), (17_000, 150, 130), (50_000, 61, 37)])
+@pytest.mark.parametrize("n,f_in,f_out", [(50_000, 40, 60), (17_000, 150, 130), (50_000, 61, 37), (60_001, 100, 47), (30_017, 200, 121), (70_001, 100, 256),
+                                          (66_001, 125, 47)])
 def test_sage_layer_products_over_two_weight_matrices(env, order, n, f_in, f_out):
-    """The sum of a GraphSAGE layer's two products as one launch of gemm_split_kernel over both weight matrices, 64 and 128 columns wide
-    (more than 768 tiles of 64 x 64): the forward product of the AGG_FIRST order and the input gradient of XFORM_FIRST, with widths that
-    fill their last step of 32 and that do not.  Self loops only, so both products read the layer's input itself.  Distance from float64
+    """The sum of a GraphSAGE layer's two products as one launch over both weight matrices, in tiles 64 and 128 columns wide and with the
+    weights in registers (more than 768 tiles of 64 x 64): the forward product of the AGG_FIRST order and the input gradient of
+    XFORM_FIRST, with widths that fill their last step of 32, their last group of four columns, and that do not.  Self loops only, so both products read the layer's input itself.  Distance from float64
     no more than four times that of the fp32 instruction plus 2^-23 (see test_gemm_f32_split_product)."""
     torch, B = env["torch"], env["B"]
     gen = torch.Generator(device="cuda")
@@ -1153,6 +1154,38 @@ def test_sage_layer_products_over_two_weight_matrices(env, order, n, f_in, f_out
     say(f"two weight matrices n={n} {f_in}-{f_out} order={order}: {err}")
     for k in ("h", "dx"):
         assert err[k, B.F32_PRODUCT_SPLIT] <= 4.0 * err[k, B.F32_PRODUCT_NATIVE] + 2.0 ** -23 and err[k, B.F32_PRODUCT_NATIVE] <= TOL_F32
+    g.close()
+
+
+@pytest.mark.parametrize("n,f_in,f_out", [(60_001, 47, 100), (30_017, 100, 128), (66_001, 125, 100), (30_017, 130, 300), (20_011, 200, 256), (9001, 40, 30)])
+def test_layer_input_gradient_with_scaled_rows(env, n, f_in, f_out):
+    """The input gradient of a GCN layer in the AGG_FIRST order, whose product dZ W^T multiplies each row by its scale: in tiles of 64 and 128
+    columns, with the weights in registers (whole and ragged groups of columns) and small.  One entry per row.  Distance from float64 no
+    more than four times that of the fp32 instruction plus 2^-23 (see test_gemm_f32_split_product)."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + f_in)
+    mk = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+    rng = np.random.default_rng(n)
+    col, r, c = rng.permutation(n).astype(np.int32), rng.uniform(0.5, 2, n).astype(np.float32), rng.uniform(0.5, 2, n).astype(np.float32)
+    g = B.Graph(n, 0, np.arange(n + 1, dtype=np.int64), col, r, c)
+    pad = lambda x: torch.nn.functional.pad(x, (0, -x.shape[1] % 4)).contiguous()  # noqa: E731
+    x, dh, w = pad(mk(n, f_in)), pad(mk(n, f_out)), mk(f_in, f_out)
+    at, rd, cd = (torch.from_numpy(v).cuda() for v in (col.astype(np.int64), r, c))
+    ref = torch.zeros(n, f_in, dtype=torch.float64, device="cuda")
+    ref[at] = (dh[:, :f_out].double() @ w.double().T) * rd.double()[:, None] * cd.double()[at][:, None]
+    err = {}
+    for form in (B.F32_PRODUCT_NATIVE, B.F32_PRODUCT_SPLIT):
+        l = B.make_layer(B.GCN, f_in, f_out, B.ACT_NONE, B.F32, w, None, None, B.AGG_FIRST, f32_product=form)
+        size = B.layer_workspace_bytes(g, l)
+        ws, saved = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty(B.layer_saved_bytes(g, l) + 256, dtype=torch.uint8, device="cuda")
+        h, dx = torch.zeros_like(dh), torch.zeros_like(x)
+        say(f"layer input gradient with scaled rows {n} {f_in}-{f_out} form={form}")
+        B.layer_fwd(g, l, x, x.shape[1], h, h.shape[1], saved, ws, size)
+        B.layer_bwd(g, l, x, x.shape[1], h, h.shape[1], saved, dh.clone(), dh.shape[1], None, None, None, dx, dx.shape[1], 0, ws, size)
+        torch.cuda.synchronize()
+        err[form] = ((dx[:, :f_in].double() - ref).abs().max() / ref.abs().max()).item()
+    assert err[B.F32_PRODUCT_SPLIT] <= 4.0 * err[B.F32_PRODUCT_NATIVE] + 2.0 ** -23 and err[B.F32_PRODUCT_NATIVE] <= TOL_F32
     g.close()
 
 
