@@ -1769,9 +1769,14 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     // what the epilogue reads (clamped places): four columns per thread and pass, asked for ahead of the operands (HOLD), else ahead of
     // the exchange through LDS (A_KC) or behind it (reductions over vertices, which mostly write parts)
     constexpr int PASSES = TN;                       // of 256 threads x 4 columns over 32 rows
-    int tid = threadIdx.x;
-    if (A_KC && !HOLD) asm("" : "+v"(tid));          // (what follows from it is not worth a register in the loop)
-    const int er = tid / (TN * 8), ec = 4 * (tid % (TN * 8)), ER = 256 / (TN * 8);
+    constexpr int ER = 256 / (TN * 8);
+    int er = threadIdx.x / (TN * 8), ec = 4 * (threadIdx.x % (TN * 8));
+    if constexpr (A_KC && !HOLD) {                   // (not worth registers in the loop)
+        int tid = threadIdx.x;
+        asm("" : "+v"(tid));
+        er = tid / (TN * 8);
+        ec = 4 * (tid % (TN * 8));
+    }
     float *part = second ? s.part2 : g.part;
     char *C = second ? s.C2 : g.C;
     const int64_t ldc = second ? s.ldc2 : g.ldc;
@@ -2580,16 +2585,22 @@ static void launch_stream(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad,
 }
 
 // (bf16 operands take the small kernel in reductions over vertices only, see small_product)
-// Epilogue operands held through the loop cost A W of at most 32 columns a wave per SIMD (30000 x 20 x 8 6.4 -> 8.5 us, 20000 x 32 x 100
-// 6.6 -> 7.1), and A W^T of more than 32 one of three: worth it while two workgroups per compute unit are all there are (masked, 4096 x
-// 256 x 112 10.6 held, 11.5 not), not where a third holds the rest of them (10000 x 128 x 100, 626 workgroups, 16.0 held, 12.5 not;
-// with more workgroups or k it is held again: 7000 x 200 x 128, 876 of them, 15.1 held, 15.9 not; 20000 x 41 x 300 24.8, 28.3).
+// Epilogue operands held through the loop cost A W of at most 32 columns one of four waves per SIMD, and A W^T of more than 32 one of three:
+// worth it while the workgroups that are left are all there are (A W: 15000 x 32 x 200, 469 workgroups, 9.0 us held, 9.5 not; masked A W^T:
+// 4096 x 256 x 112 10.6 held, 11.5 not), not where one more per compute unit holds the rest of them (30000 x 20 x 8, 938, 8.5 held, 6.4 not;
+// 10000 x 128 x 100 by W^T, 626, 16.0 held, 12.5 not; with more workgroups or k that one holds again: 7000 x 200 x 128, 876 of them, 15.1
+// held, 15.9 not; 20000 x 41 x 300 24.8, 28.3).
 static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
 #define CG_SMALL_CASE(BF, AK, BK_, TN_, HOLD_)                                                                                 \
     if (bf16 == BF && akc == AK && bkc == BK_ && tn == TN_)                                                                    \
         hipLaunchKernelGGL((gemm_small_kernel<BF, AK, BK_, TN_, HOLD_>), grid, dim3(256), 0, st, s);
-    CG_SMALL_CASE(false, true, false, 1, false) CG_SMALL_CASE(false, true, false, 2, true) CG_SMALL_CASE(false, true, true, 1, true)
+    CG_SMALL_CASE(false, true, false, 2, true) CG_SMALL_CASE(false, true, true, 1, true)
     const int64_t n_wg = static_cast<int64_t>(grid.x) * grid.y;
+    if (n_wg > 3 * NUM_CU) {
+        CG_SMALL_CASE(false, true, false, 1, false)
+    } else {
+        CG_SMALL_CASE(false, true, false, 1, true)
+    }
     if (n_wg > 2 * NUM_CU && n_wg <= 3 * NUM_CU && s.g.K + (s.dual ? s.K2 : 0) <= 256) {
         CG_SMALL_CASE(false, true, true, 2, false)
     } else {

@@ -855,7 +855,7 @@ def test_gemm_f32_reductions_of_129_to_256_in_one_chain_or_two(env, M, N, K, str
 
 
 @pytest.mark.parametrize("tb", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(1000, 30, 40), (4095, 130, 72), (10_001, 100, 100), (16_500, 41, 256), (20_000, 41, 300), (13_001, 70, 300), (30_001, 100, 100),
+@pytest.mark.parametrize("M,N,K", [(1000, 30, 40), (4095, 130, 72), (10_001, 100, 100), (16_500, 41, 256), (30_001, 32, 20), (20_000, 41, 300), (13_001, 70, 300), (30_001, 100, 100),
                                    (30_017, 130, 300), (60_001, 47, 24), (60_001, 64, 100), (60_001, 201, 32), (50_001, 100, 20)])
 def test_gemm_f32_epilogues_exact(env, tb, M, N, K):
     """C (+)= A W with bias, ReLU and mask on every kernel of the fp32 path, in both forms of the product: epilogue operands asked for
