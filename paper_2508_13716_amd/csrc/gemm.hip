@@ -1700,8 +1700,10 @@ __device__ __forceinline__ void small_load(const char *p, int64_t step, int64_t 
 constexpr int SMALL_UNITS = 4;      // units per batch
 template <bool BF16> constexpr int SMALL_UNIT_K = BF16 ? 16 : 8;
 
+// HOLD: epilogue operands held through the loop; in reductions over vertices, which hold none, registers for two waves per SIMD
+// (see launch_small)
 template <bool BF16, bool A_KC, bool B_KC, int TN, bool HOLD>
-__global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
+__global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(SmallGemmArgs s) {
     constexpr int ES = BF16 ? 2 : 4, UK = SMALL_UNIT_K<BF16>, HK = UK / 2, UB = SMALL_UNITS;
     constexpr int PITCH = TN * 32 + 4;
     __shared__ __attribute__((aligned(16))) float red[4][32][PITCH];
@@ -1767,7 +1769,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
     // what the epilogue reads (clamped places): four columns per thread and pass, asked for ahead of the operands (HOLD), else ahead of
-    // the exchange through LDS (A_KC) or behind it (reductions over vertices, which mostly write parts)
+    // the exchange through LDS; reductions over vertices, which mostly write parts, ask for it element by element (see below)
     constexpr int PASSES = TN;                       // of 256 threads x 4 columns over 32 rows
     constexpr int ER = 256 / (TN * 8);
     int er = threadIdx.x / (TN * 8), ec = 4 * (threadIdx.x % (TN * 8));
@@ -1803,7 +1805,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) e_s[p] = rscale[crow(p)];
     };
-    if constexpr (HOLD) fetch_epilogue();
+    if constexpr (A_KC && HOLD) fetch_epilogue();
     // column sums of B: the bias gradient rides on the weight gradient that reads dZ anyway.  However long a split is, a thread
     // adds no more than the 16 .. 32 terms of a step in fp32; its running sum and those of the workgroup are doubles.
     const bool sums = !A_KC && !B_KC && g.colpart && by == 0 && !second;      // uniform over the workgroup
@@ -1864,7 +1866,39 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(SmallGemmArgs s) {
     if (sums)
         for (int c = threadIdx.x; c < TN * 32; c += 256)
             if (n0 + c < g.N) g.colpart[bz * g.N + n0 + c] = static_cast<float>((bred[0][c] + bred[1][c]) + (bred[2][c] + bred[3][c]));
-    if constexpr (!A_KC) fetch_epilogue();
+    if constexpr (!A_KC) {
+        // four columns per thread, in an epilogue of its own: the pass below changes how the compiler orders the loads and waits of these
+        // kernels' loops (bf16 weight gradients: 602 x 32 x 30000 45.9 us by it, 24.8 so; pairs of 100 x 200 x 66498 62, 50)
+        for (int i = threadIdx.x; i < 32 * TN * 8; i += 256) {
+            const int r = i / (TN * 8), c4 = i % (TN * 8);
+            const int64_t orow = m0 + r, ocol = n0 + 4 * c4;
+            if (orow >= M || ocol >= g.N) continue;
+            float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float4 q = *reinterpret_cast<const float4 *>(&red[w][r][4 * c4]);
+                v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
+            }
+            const int nv = g.N - ocol < 4 ? static_cast<int>(g.N - ocol) : 4;
+            if (part) {
+                float *o = part + (bz * M + orow) * g.N + ocol;
+                for (int e = 0; e < nv; ++e) o[e] = v[e];
+                continue;
+            }
+            for (int e = 0; e < nv; ++e) {
+                const int64_t at = orow * ldc + ocol + e;
+                float x = v[e];
+                if (g.accumulate) x += epilogue_load(C, at, g.out_bf16);
+                if (g.bias) x += g.bias[ocol + e];
+                if (g.relu) x = x > 0.f ? x : 0.f;
+                if (g.mask && !(epilogue_load(g.mask, orow * g.ldm + ocol + e, g.mask_bf16) > 0.f)) x = 0.f;
+                if (rscale) x *= rscale[orow];
+                if (g.out_bf16) reinterpret_cast<uint16_t *>(C)[at] = static_cast<uint16_t>(f32_to_bf16_rne(x));
+                else reinterpret_cast<float *>(C)[at] = x;
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         const int r = er + p * ER;
@@ -2590,6 +2624,10 @@ static void launch_stream(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad,
 // 4096 x 256 x 112 10.6 held, 11.5 not), not where one more per compute unit holds the rest of them (30000 x 20 x 8, 938, 8.5 held, 6.4 not;
 // 10000 x 128 x 100 by W^T, 626, 16.0 held, 12.5 not; with more workgroups or k that one holds again: 7000 x 200 x 128, 876 of them, 15.1
 // held, 15.9 not; 20000 x 41 x 300 24.8, 28.3).
+// bf16 reductions of at most 32 columns: registers for two waves per SIMD while X is small and its workgroups are more than the compute units
+// or their chains long (us, one wave and two: 200 x 32 x 12000 16.5, 12.3; 602 x 5 x 5000 15.3, 11.1; 16 x 32 x 66000 17.1, 11.1; equal at
+// 512 x 32 x 5000), one beyond (602 x 32 x 30000 24.5, 46.2; 602 x 5 x 150000 92, 294) and where a few workgroups make short chains (in a
+// layer, with column sums, 128 x 31 x 1469 7.5, 11.4).
 static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid, hipStream_t st) {
 #define CG_SMALL_CASE(BF, AK, BK_, TN_, HOLD_)                                                                                 \
     if (bf16 == BF && akc == AK && bkc == BK_ && tn == TN_)                                                                    \
@@ -2608,7 +2646,12 @@ static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, 
     }
     CG_SMALL_CASE(false, false, false, 1, false) CG_SMALL_CASE(false, false, false, 2, false)
     CG_SMALL_CASE(false, false, true, 1, false) CG_SMALL_CASE(false, false, true, 2, false)
-    CG_SMALL_CASE(true, false, false, 1, false) CG_SMALL_CASE(true, false, false, 2, false)
+    if (s.g.M * s.g.K * grid.y <= (int64_t(1) << 23) && (n_wg > NUM_CU || s.g.K >= (1 << 14))) {
+        CG_SMALL_CASE(true, false, false, 1, true)
+    } else {
+        CG_SMALL_CASE(true, false, false, 1, false)
+    }
+    CG_SMALL_CASE(true, false, false, 2, false)
     CG_SMALL_CASE(true, false, true, 1, false) CG_SMALL_CASE(true, false, true, 2, false)
 #undef CG_SMALL_CASE
 }

@@ -549,6 +549,34 @@ def test_gemm_bf16_matrix_core_path(env, ta, tb):
             assert (got[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(16, 32, 16383), (16, 32, 16384), (1, 1, 16391), (33, 5, 20001), (256, 31, 5000), (289, 31, 5000), (300, 7, 2049),
+                                   (256, 32, 32768), (257, 32, 32768), (602, 3, 14001)])
+def test_gemm_bf16_reductions_of_at_most_32_columns_exact(env, M, N, K):
+    """Weight gradients on both sides of each line between the forms for one and for two waves per SIMD: the length of the chains, workgroups
+    and compute units, the size of X; alone and added to what C holds.  Small integers: every sum is an integer below 2^24
+    (9 * 32768 + 2), so each form gives it exactly, and gives the same on a second call."""
+    torch, B, H = env["torch"], env["B"], env["H"]
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-3, 4, (K, M)).astype(np.float32)
+    G = rng.integers(-3, 4, (K, N)).astype(np.float32)
+    ref = A.T.astype(np.float64) @ G.astype(np.float64)
+    st = lambda x: synth.f32_to_bf16_rne(x).reshape(x.shape)
+    lda, ldg, ldc = synth.pad_to(M, 8), synth.pad_to(N, 8), N + 3
+    Ad, Gd = H.padded_matrix(st(A), lda), H.padded_matrix(st(G), ldg)
+    Ad[:, M:] = float("nan")
+    Gd[:, N:] = float("nan")
+    wsb = B.gemm_workspace_bytes(1, M, N, K)
+    ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+    for acc in (0, 1, 0):
+        Cd = torch.full((M, ldc), 2.0, dtype=torch.float32, device="cuda")
+        say(f"gemm bf16 reduction {M}x{N}x{K} accumulate={acc}")
+        B.gemm(1, 0, M, N, K, Ad, lda, Gd, ldg, Cd, ldc, B.BF16, out_f32=1, accumulate=acc, ws=ws, ws_bytes=wsb)
+        torch.cuda.synchronize()
+        got = Cd.cpu().numpy()
+        assert np.array_equal(got[:, :N].astype(np.float64), ref + 2.0 * acc)
+        assert (got[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_gemm_size_classes_exact(env, dtype, ta, tb):
