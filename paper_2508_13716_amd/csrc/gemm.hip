@@ -1229,15 +1229,14 @@ __global__ __launch_bounds__(NW * 64, NW / 2) void gemm_split_kernel(GemmArgs g,
 // The same product for many rows and a small weight matrix (at most 256 columns and 256 k, the sum of two products among them), where
 // a tile's life of a few steps leaves gemm_split_kernel waiting for its first operands and its last stores.  A workgroup walks tiles of
 // 32 rows and all its life holds the three pieces of its weights in registers: a wave 32 columns and 128 k (96 registers, so that two
-// waves share a SIMD; one wave per SIMD with 192 or 384 of them was no faster than gemm_split_kernel: 306 k x 256 x 256 243 us either
-// way).  Above 128 k the waves halve the reduction between them (KH = 2), exchange half of their partial tiles through LDS and store
+// waves share a SIMD; one wave per SIMD with 192 or 384 of them was no faster than gemm_split_kernel).  Above 128 k the waves halve the reduction between them (KH = 2), exchange half of their partial tiles through LDS and store
 // half of the rows each.  Rows of A are fetched two tiles ahead and cut behind the matrix instructions (cut after them: 1-2 % slower);
 // LDS holds A's pieces, one tile being stored while the other is multiplied: one barrier per tile.  Units of 16 bytes
 // S[k / 128][piece][k / 8][row], a plane one unit longer than 32 rows: the units that 8 lanes store lie 4 banks apart.
 // As in gemm_bf16_stream_kernel the operands are exchanged, every tile issues the same loads and stores unconditionally (those
 // beyond the matrix are dropped by the buffer's bounds) and the last row's tile comes apart.
 // us, in a 306 k-vertex GraphSAGE epoch, gemm_split_kernel -> here: sum of two products of 100 k 244 -> 205, masked sum of two of 47 k 206
-// -> 126 (5.9 TB/s: memory), 256 x 256 246 -> 204 (1.2 PFLOP/s of bf16 work); error against fp64 2.4e-7 -> 1.7e-7 (shorter chains).
+// -> 126 (5.9 TB/s: memory), 256 x 256 246 -> 204 (1.2 PFLOP/s of bf16 work; a single product alone 265 -> 238, see split_stream_pays); error against fp64 2.4e-7 -> 1.7e-7 (shorter chains).
 constexpr int split_stream_slots(int NS, int KH) { return KH == 1 ? NS : 2 * NS / KH; }     // 32 x 32 parts of C on their way through LDS
 constexpr int split_stream_lds(int NS, int KH) { return 2 * KH * 3 * 16 * 33 * 16 + split_stream_slots(NS, KH) * 32 * 36 * 4 + NS / KH * 128; }
 constexpr int split_stream_held(int NS, int KH) { return NS == 4 && KH == 1 ? 2 : 1; }       // workgroups per compute unit
@@ -2402,7 +2401,8 @@ constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piec
 // Reductions over vertices (trans_a), whose other kernels stage tiles through LDS step by step: about as far as the small kernel is
 // the faster one for every M, with the splits of small_geometry (us small / other, M x N at 2^e multiply-adds, medians over five
 // placements of the operands).  fp32, N > 64, up to 2^28.46: 200 x 256 14 / 20 at 2^27, 602 x 256 22 / 26 at 2^28, 100 x 256 23 / 23
-// and 602 x 256 26 / 23 at 2^28.4.  fp32, N <= 64 (the other kernel half idle), up to 2^31: 100 x 41 81 / 86 at 2^30, 200 x 41 124 /
+// and 602 x 256 26 / 23 at 2^28.4.  fp32, N <= 64 (the other kernel half idle), up to 2^31, where gemm_narrow_kernel does not take them
+// (see narrow_product: shorter reductions, little workspace, few rows and very many vertices): 100 x 41 81 / 86 at 2^30, 200 x 41 124 /
 // 130, 320 x 64 79 / 81, 602 x 41 118 / 111, 512 x 64 70 / 63 at 2^31, 602 x 41 232 / 197 at 2^32.  bf16, N > 64, up to 2^30.46:
 // 200 x 256 21 / 26, 602 x 256 28 / 27, 100 x 100 31 / 33 at 2^30.  bf16, 32 < N <= 64, up to 2^32: 200 x 41 42 / 57, 602 x 64 30 / 32
 // at 2^31, 512 x 64 44 / 51, 602 x 41 69 / 64 at 2^32.  bf16, N <= 32, up to 2^30: 100 x 16 60 / 83, 602 x 16 54 / 51 at 2^30, 320 x 16
