@@ -102,6 +102,16 @@ __device__ __forceinline__ float epilogue_load(const char *p, int64_t at, int bf
     return bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(p)[at]) << 16) : reinterpret_cast<const float *>(p)[at];
 }
 
+// an element of the product with the whole epilogue (the sum with C included), as it is stored
+__device__ __forceinline__ float epilogue_value(const GemmArgs &g, int64_t row, int64_t col, float v) {
+    if (g.accumulate) v += epilogue_load(g.C, row * g.ldc + col, g.out_bf16);
+    if (g.bias) v += g.bias[col];
+    if (g.relu) v = v > 0.f ? v : 0.f;
+    if (g.mask && !(epilogue_load(g.mask, row * g.ldm + col, g.mask_bf16) > 0.f)) v = 0.f;
+    if (g.rscale) v *= g.rscale[row];
+    return v;
+}
+
 // Writes one wave's TM x TN grid of 32x32 accumulator tiles (top-left corner (row0, col0)) with the epilogue.
 // D layout of the 32x32 MFMAs: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
 template <int TM, int TN>
@@ -122,18 +132,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&a
                     g.part[(static_cast<int64_t>(bz) * g.M + row) * g.N + col] = v;
                     continue;
                 }
-                if (g.accumulate) {
-                    v += g.out_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(g.C)[row * g.ldc + col]) << 16)
-                                    : reinterpret_cast<const float *>(g.C)[row * g.ldc + col];
-                }
-                if (g.bias) v += g.bias[col];
-                if (g.relu) v = v > 0.f ? v : 0.f;
-                if (g.mask) {
-                    const float mv = g.mask_bf16 ? __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t *>(g.mask)[row * g.ldm + col]) << 16)
-                                                 : reinterpret_cast<const float *>(g.mask)[row * g.ldm + col];
-                    if (!(mv > 0.f)) v = 0.f;
-                }
-                if (g.rscale) v *= g.rscale[row];
+                v = epilogue_value(g, row, col, v);
                 if (g.out_bf16) reinterpret_cast<uint16_t *>(g.C)[row * g.ldc + col] = static_cast<uint16_t>(f32_to_bf16_rne(v));
                 else reinterpret_cast<float *>(g.C)[row * g.ldc + col] = v;
             }
@@ -1093,17 +1092,6 @@ struct SplitPlaneLoader {
     }
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// LDS image of an operand stored across the reduction index (both of X^T G): 8-byte units (piece, k / 4, column), a
-// plane of bt columns per (piece, k / 4).  A staging thread holds four neighbouring columns (32 bytes) and stores them
-// as two 16-byte halves; eight neighbouring lanes are 32 bytes apart, so every second group of four lanes swaps its
-// halves and one store covers all the banks.  col_slot() is where a column ends up.
-struct ColUnits8 {
-    static constexpr int bytes(int bt) { return 3 * 8 * bt * 8; }
-    static __device__ __forceinline__ int col_slot(int col) { return col ^ ((col >> 3) & 2); }
-};
-
 // C = A B (or A B^T) with A stored along the reduction index; the second operand comes cut into units (Wt: ku_total
 // units along k per piece, n_pad rows).  NW waves: four (2 x 2) or, on a 128 x 128 tile, eight (2 x 4, each a 64 x 32
 // part: half the staging and half the accumulators per thread, four waves per SIMD).
@@ -1459,186 +1447,228 @@ __global__ __launch_bounds__(NS * 64, split_stream_held(NS, KH) * NS / 4) void g
     }
 }
 
-// The weight gradient with eight waves on a 128 x BN tile (BN = 128: 2 x 4 waves, each a 64 x 32 part; BN = 64: 4 x 2,
-// each 32 x 32): half the staging and at most half the accumulators per thread of the four-wave form, so that four
-// waves share a SIMD and one wave's cutting and LDS traffic run beside another's matrix instructions.  Waves 0-3 stage
-// the first operand's tile, waves 4-7 the second's; LDS image as in gemm_split_kernel<true, ...>: 8-byte units
-// (piece, k / 4, column), columns placed by ColUnits8::col_slot.
-struct SplitColLoader {
-    f32x4 r[4];                     // one block of 4 k x 4 columns per thread
-    const f32x4 *pf;
-    const char *base;
-    int64_t ld, t0, T;
-    char *s;
-    int bt, kb, tq;                 // tile width; the thread's k-block and column group
-    bool idle;                      // a 64-column second tile leaves half of its waves without work
-    uint2 pk[4][3];                 // [column][piece], four k each
+// The weight gradient X^T G in three pieces: both operands are stored across the reduction index (vertices), and nothing is staged.  A
+// wave holds 128 x (TB * 32) results (TB = 4: all 256 accumulation registers) and loads both operands as the matrix instruction wants
+// them: a lane eight vertices of one column, each load two rows of 32 columns.  It cuts the next operands between the matrix
+// instructions, a pair of numbers behind every third of them, and asks for the numbers of the step after as soon as a pair is cut: no
+// LDS, no barrier, one wave per SIMD with one step (16 KB) on its way.  The four waves of a workgroup take quarters of its vertices and add
+// their results through LDS, in wave order, when a part ends: parts are as many as make the chains of fp32 additions no longer than one per
+// split of the other kernels (choose_split), if longer than COLS_CHAIN (256 x 256 x 306000, error against fp64: one part 1.13e-6, two 8.2e-7,
+// tiles staged through LDS 9.3e-7; a part more costs about 10 us there).
+// Rows beyond the end of a wave's vertices are dropped by the buffer's bounds (zeros); columns beyond the operand's width only reach
+// results that are not stored.  No alignment is asked for.  PMC at 256 x 256 x 306000: matrix cores busy 73 % of the time, at 1.76 GHz.
+// us with the sum over parts, eight-wave tiles of 128 x 128 staged through LDS -> here: 256 x 256 x 306000 281 -> 217, 100 x 256 x
+// 306000 188 -> 133, 602 x 256 x 180000 420 -> 298, 100 x 256 x 70001 53 -> 35, 602 x 200 x 30000 102 -> 60, 2000 x 1000 x 1000 135 -> 32.
+constexpr int COLS_CHAIN = 512;
+constexpr int COLS_PITCH = 72;      // floats per row of 64 results on their way through LDS (four rows further = other half of the banks)
 
-    __device__ __forceinline__ void init(const GemmArgs &g, int64_t m0, int64_t n0, int bm, int bn, char *As, char *Bs, int tid) {
-        const bool second = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;        // uniform over the wave
-        base = second ? g.B : g.A;
-        ld = second ? g.ldb : g.lda;
-        t0 = second ? n0 : m0;
-        T = second ? g.N : g.M;
-        s = second ? Bs : As;
-        bt = second ? bn : bm;
-        const int tt = tid & 255, cpr = bt / 4;
-        kb = tt / cpr; tq = tt % cpr;
-        idle = kb >= 8;
-    }
-
-    __device__ __forceinline__ void fetch(int64_t k0, int64_t k_end, int vec) {
-        if (idle) return;
-        const int64_t t = t0 + 4 * tq;
-        const int ncol = static_cast<int>(T - t < 4 ? T - t : 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t k = k0 + 4 * kb + j;
-            const float4 v = load4<false>(base, k * ld + t, k < k_end ? ncol : 0, vec);
-            r[j] = f32x4{v.x, v.y, v.z, v.w};
-        }
-    }
-
-    __device__ __forceinline__ void fast_begin(int64_t k0) {
-        pf = reinterpret_cast<const f32x4 *>(base + ((k0 + 4 * kb) * ld + t0 + 4 * tq) * 4);
-    }
-
-    // the check-free path runs only when rows are whole 16-byte vectors
-    __device__ __forceinline__ void fetch_fast() {
-        if (idle) return;
-        const int64_t ld4 = ld / 4;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r[j] = pf[j * ld4];
-        pf += SBK * ld4;
-    }
-
-    __device__ __forceinline__ void cut() {
-        if (idle) return;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            uint32_t lo[3], hi[3];
-            split3_pair(r[0][c], r[1][c], lo);
-            split3_pair(r[2][c], r[3][c], hi);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) pk[c][p] = make_uint2(lo[p], hi[p]);
-        }
-    }
-
-    __device__ __forceinline__ void put() const {
-        if (idle) return;
-        const int sw = ((tq >> 2) & 1) * 16;       // see ColUnits8
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            char *dst = s + (((p * 8 + kb) * bt) + 4 * tq) * 8;
-            *reinterpret_cast<uint4 *>(dst + sw) = make_uint4(pk[0][p].x, pk[0][p].y, pk[1][p].x, pk[1][p].y);
-            *reinterpret_cast<uint4 *>(dst + 16 - sw) = make_uint4(pk[2][p].x, pk[2][p].y, pk[3][p].x, pk[3][p].y);
-        }
-    }
-};
-
-template <int BN>
-// (second launch bound: waves per SIMD; two workgroups of eight waves per compute unit need four)
-__global__ __launch_bounds__(512, BN == 128 ? 4 : 2) void gemm_split_trans_kernel(GemmArgs g) {
-    static_assert(BN == 128 || BN == 64, "tile widths");
-    constexpr int BM = 128;
-    constexpr int WAVES_N = BN / 32, WAVES_M = 8 / WAVES_N;     // every wave one 32-column strip
-    constexpr int WM = BM / WAVES_M, WN = 32, TM = WM / 32;
-    constexpr int A_BYTES = ColUnits8::bytes(BM), B_BYTES = ColUnits8::bytes(BN);
-    __shared__ __attribute__((aligned(16))) char smem[A_BYTES + B_BYTES];
-    char *As = smem, *Bs = smem + A_BYTES;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+template <int TB, bool SUMS>
+__global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(GemmArgs g, int parts) {
+    constexpr int TA = 4;
+    __shared__ __attribute__((aligned(16))) float red[4][TA][32 * COLS_PITCH];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     int bx, by, bz;
-    if (!tile_coords(g, &bx, &by, &bz)) return;      // uniform over the workgroup
-    const int64_t m0 = static_cast<int64_t>(by) * BM;
-    const int64_t n0 = static_cast<int64_t>(bx) * BN;
-    const int64_t k_begin = static_cast<int64_t>(bz) * g.k_chunk;
-    const int64_t k_end = (k_begin + g.k_chunk < g.K) ? k_begin + g.k_chunk : g.K;
-
-    floatx16 acc[TM][1];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.f;
-
-    SplitColLoader lc;
-    const int64_t nk = (k_end > k_begin) ? (k_end - k_begin + SBK - 1) / SBK : 0;
-    const int64_t nk_full = (k_end > k_begin) ? (k_end - k_begin) / SBK : 0;
-    // uniform over the workgroup: every row / column of the tile exists and vector loads are allowed
-    const bool interior = m0 + BM <= g.M && n0 + BN <= g.N && g.a_vec && g.b_vec;
-    const int both_vec = g.a_vec && g.b_vec;
-    lc.init(g, m0, n0, BM, BN, As, Bs, tid);
-    if (nk > 0) {
-        lc.fetch(k_begin, k_end, both_vec);
-        lc.cut();
-        lc.put();
-        if (interior) lc.fast_begin(k_begin + SBK);
+    if (g.S < NUM_XCD) {                                // too few splits for every L2 domain to have one: the tiles go to all of them
+        const int tile = static_cast<int>(blockIdx.x) % (g.gx * g.gy);
+        bz = static_cast<int>(blockIdx.x) / (g.gx * g.gy);
+        bx = tile % g.gx;
+        by = tile / g.gx;
+    } else if (!tile_coords(g, &bx, &by, &bz)) {
+        return;                                         // uniform over the workgroup
     }
-    // column sums of B (see gemm_small_kernel): waves 4-7 stage it, a thread's block of a step is four k of four columns
-    const bool sums = g.colpart && by == 0;
-    double bsum[4] = {0.0, 0.0, 0.0, 0.0};
-    auto add_b = [&]() __attribute__((always_inline)) {
-        if (lc.idle) return;
-        const f32x4 t = (lc.r[0] + lc.r[1]) + (lc.r[2] + lc.r[3]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bsum[e] += static_cast<double>(t[e]);
+    const int64_t m0 = static_cast<int64_t>(by) * (TA * 32), n0 = static_cast<int64_t>(bx) * (TB * 32);
+    // the wave's vertices: `parts` stretches of g.k_chunk (a multiple of 32) one after the other
+    const int64_t k_begin = (static_cast<int64_t>(bz) * 4 + wave) * parts * g.k_chunk;
+    const int64_t k_have = g.K - k_begin < parts * g.k_chunk ? g.K - k_begin : parts * g.k_chunk;
+    const int n_rows = k_have > 0 ? static_cast<int>(k_have) : 0;
+    const int lda = static_cast<int>(g.lda) * 4, ldb = static_cast<int>(g.ldb) * 4;         // bytes
+    const int width_a = static_cast<int>(g.M - m0 < TA * 32 ? g.M - m0 : TA * 32) * 4, width_b = static_cast<int>(g.N - n0 < TB * 32 ? g.N - n0 : TB * 32) * 4;
+    const char *pa = g.A + (n_rows > 0 ? k_begin * lda + m0 * 4 : 0), *pb = g.B + (n_rows > 0 ? k_begin * ldb + n0 * 4 : 0);
+    // the 16 rows from the wave's row `row` on, as many as there are
+    auto rows16 = [&](const char *p, int ld, int row, int width) __attribute__((always_inline)) {
+        const int n = n_rows - row < 16 ? n_rows - row : 16;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), 0, n > 0 ? (n - 1) * ld + width : 0, 0x00027000);
     };
-    if (sums && nk > 0) add_b();
-    __syncthreads();
-    const int slot_b = ColUnits8::col_slot(wn * WN + l32);
-    auto products = [&]() {
+    uint32_t oa[8], ob[8];
 #pragma unroll
-        for (int ks = 0; ks < SBK / 16; ++ks) {
-            bf16x8 a[3][TM], b[3];
+    for (int j = 0; j < 8; ++j) {
+        oa[j] = static_cast<uint32_t>(half * 8 + j) * lda + l32 * 4;
+        ob[j] = static_cast<uint32_t>(half * 8 + j) * ldb + l32 * 4;
+    }
+    float ra[TA][8], rb[TB][8];                     // numbers of the step after next (ra[1 ..]: of the next)
+    u32x4 ap[2][3], bp[2][TB][3];                   // pieces: of this tile of 32 rows and the next, of this step's columns and the next's
+    floatx16 acc[TA][TB];
+    double bsum[TB] = {};                           // SUMS: sums of the lane's columns of G
+    float tsum = 0.f;
+    auto load2 = [&](auto rsrc, const uint32_t (&o)[8], int tile, int e, float (&r)[8]) __attribute__((always_inline)) {
+        r[2 * e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o[2 * e] + tile * 128, 0, 0));
+        r[2 * e + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o[2 * e + 1] + tile * 128, 0, 0));
+    };
+    auto cut2 = [&](const float (&r)[8], int e, u32x4 (&p)[3]) __attribute__((always_inline)) {
+        uint32_t u[3];
+        split3_pair(r[2 * e], r[2 * e + 1], u);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
+        for (int x = 0; x < 3; ++x) p[x][e] = u[x];
+    };
+    auto add_b = [&](int j, int e) __attribute__((always_inline)) {     // a step's eight numbers in fp32, the running sum a double
+        if constexpr (SUMS) {
+            const float t = rb[j][2 * e] + rb[j][2 * e + 1];
+            tsum = e == 0 ? t : tsum + t;
+            if (e == 3) bsum[j] += static_cast<double>(tsum);
+        }
+    };
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const int slot = ColUnits8::col_slot(wm * WM + i * 32 + l32);
-                    const uint2 v0 = *reinterpret_cast<const uint2 *>(As + ((p * 8 + 4 * ks + 2 * half) * BM + slot) * 8);
-                    const uint2 v1 = *reinterpret_cast<const uint2 *>(As + ((p * 8 + 4 * ks + 2 * half + 1) * BM + slot) * 8);
-                    a[p][i] = __builtin_bit_cast(bf16x8, make_uint4(v0.x, v0.y, v1.x, v1.y));
-                }
-                const uint2 w0 = *reinterpret_cast<const uint2 *>(Bs + ((p * 8 + 4 * ks + 2 * half) * BN + slot_b) * 8);
-                const uint2 w1 = *reinterpret_cast<const uint2 *>(Bs + ((p * 8 + 4 * ks + 2 * half + 1) * BN + slot_b) * 8);
-                b[p] = __builtin_bit_cast(bf16x8, make_uint4(w0.x, w0.y, w1.x, w1.y));
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear();
+    {
+        auto sa = rows16(pa, lda, 0, width_a), sb = rows16(pb, ldb, 0, width_b);
+        auto sa1 = rows16(pa + 16 * lda, lda, 16, width_a), sb1 = rows16(pb + 16 * ldb, ldb, 16, width_b);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) load2(sa, oa, 0, e, ra[0]);
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) load2(sb, ob, j, e, rb[j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cut2(ra[0], e, ap[0]);
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                cut2(rb[j], e, bp[0][j]);
+                add_b(j, e);
             }
-            // the six piece products, smallest first
-#define CG_PIECES_T(PA_, PB_)                                                                                                 \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                                           \
-        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA_][i], b[PB_], acc[i][0], 0, 0, 0);
-            CG_PIECES_T(2, 0) CG_PIECES_T(0, 2) CG_PIECES_T(1, 1) CG_PIECES_T(1, 0) CG_PIECES_T(0, 1) CG_PIECES_T(0, 0)
-#undef CG_PIECES_T
-        }
-    };
-    for (int64_t kt = 0; kt + 1 < nk; ++kt) {
-        if (interior && kt + 1 < nk_full) lc.fetch_fast();
-        else lc.fetch(k_begin + (kt + 1) * SBK, k_end, both_vec);
-        products();
-        __syncthreads();            // every wave has read this step's operands
-        if (sums) add_b();
-        lc.cut();
-        lc.put();
-        __syncthreads();
-    }
-    if (nk > 0) products();
-    if (sums) {
-        __syncthreads();            // the operand tiles are free: [8][BN] partial sums
-        double (*bred)[BN] = reinterpret_cast<double (*)[BN]>(smem);
-        static_assert(8 * BN * sizeof(double) <= A_BYTES + B_BYTES, "the partial sums must fit the operand tiles");
-        if (tid >= 256 && !lc.idle)
+        // in the order in which the loop asks for them: its waits are counted over both ways in
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bred[lc.kb][4 * lc.tq + e] = bsum[e];
-        __syncthreads();
-        if (tid < BN && n0 + tid < g.N) {
-            double t = 0.0;
-            for (int y = 0; y < 8; ++y) t += bred[y][tid];
-            g.colpart[bz * g.N + n0 + tid] = static_cast<float>(t);
-        }
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < TA) load2(sa, oa, i + 1, e, ra[(i + 1) % TA]);
+                else load2(sa1, oa, 0, e, ra[0]);
+                if (i < TB) load2(sb1, ob, i, e, rb[i]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    store_tile<TM, 1>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
+    int row = 0;
+    auto step = [&](auto parity) __attribute__((always_inline)) {
+        constexpr int P = decltype(parity)::value;
+        pa += 16 * lda;
+        pb += 16 * ldb;
+        auto sa1 = rows16(pa, lda, row + 16, width_a), sa2 = rows16(pa + 16 * lda, lda, row + 32, width_a), sb2 = rows16(pb + 16 * ldb, ldb, row + 32, width_b);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TA; ++i) {
+            const int c = i & 1, ni = (i + 1) % TA, j2 = i % TB;
+            const int groups = i < TB ? 8 : 4;          // pairs that are cut meanwhile: of the next 32 rows, and of 32 of the next step's columns
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q >= groups) continue;
+                const int e = groups == 8 ? q / 2 : q, first = 6 * TB * q / groups, last = 6 * TB * (q + 1) / groups;
+#pragma unroll
+                for (int m = 0; m < 6 * TB; ++m) {
+                    if (m < first || m >= last) continue;
+                    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};       // the six piece products, smallest first
+                    acc[i][m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ap[c][PA[m / TB]]),
+                                                                             __builtin_bit_cast(bf16x8, bp[P][m % TB][PB[m / TB]]), acc[i][m % TB], 0, 0, 0);
+                }
+                if (groups == 4 || q % 2 == 0) {
+                    cut2(ra[ni], e, ap[c ^ 1]);
+                    if (i + 1 < TA) load2(sa1, oa, ni, e, ra[ni]);
+                    else load2(sa2, oa, ni, e, ra[ni]);
+                } else {
+                    cut2(rb[j2], e, bp[P ^ 1][j2]);
+                    add_b(j2, e);
+                    load2(sb2, ob, j2, e, rb[j2]);
+                }
+#pragma unroll
+                for (int m = 0; m < 6 * TB; ++m) {
+                    if (m < first || m >= last) continue;
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                // one matrix instruction
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                // vector instructions behind it
+                    if (m > first) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0); // a load
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        row += 16;
+    };
+    static_assert(TA % 2 == 0 && TB <= TA, "a tile of columns is cut beside a tile of rows");
+    for (int part = 0; part < parts; ++part) {
+        const int end = static_cast<int>((part + 1) * g.k_chunk);
+        while (row < end && row < n_rows) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        const int z = bz * parts + part;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));        // what follows from it is formed here: held through the loop it takes registers that are not there
+        const int c32 = ln & 31, hf = ln >> 5;
+        if constexpr (SUMS) {
+            // (what the steps ahead have added belongs to the next part: the parts' sums are added up all the same)
+            double (*bred)[TB * 32] = reinterpret_cast<double (*)[TB * 32]>(&red[0][0][0]);
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                bred[2 * wave + hf][j * 32 + c32] = bsum[j];
+                bsum[j] = 0.0;
+            }
+            __syncthreads();
+            const int col = 64 * wave + ln;
+            if (by == 0 && col < TB * 32 && n0 + col < g.N) {
+                double t = 0.0;
+                for (int y = 0; y < 8; ++y) t += bred[y][col];
+                g.colpart[z * g.N + n0 + col] = static_cast<float>(t);
+            }
+            __syncthreads();
+        }
+        // 64 columns at a time: the four waves' results side by side, then each wave adds up and stores 32 rows of them
+#pragma unroll
+        for (int h = 0; h < TB / 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[wave][i][(8 * (r >> 2) + 4 * hf + (r & 3)) * COLS_PITCH + j * 32 + c32] = acc[i][2 * h + j][r];
+            __syncthreads();
+            const int64_t col = n0 + h * 64 + 4 * (ln % 16);
+            const bool vec = g.part ? g.N % 4 == 0 && reinterpret_cast<uintptr_t>(g.part) % 16 == 0
+                                    : g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(g.C) % 16 == 0;
+#pragma unroll 1
+            for (int p = 0; p < 8; ++p) {
+                const int lr = 4 * p + ln / 16;
+                const int64_t at = m0 + wave * 32 + lr;
+                float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float4 x = *reinterpret_cast<const float4 *>(&red[w][wave][lr * COLS_PITCH + 4 * (ln % 16)]);
+                    v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+                }
+                if (at >= g.M || col >= g.N) continue;
+                float *dst = g.part ? g.part + (static_cast<int64_t>(z) * g.M + at) * g.N + col : reinterpret_cast<float *>(g.C) + at * g.ldc + col;
+                if (!g.part)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) v[e] = epilogue_value(g, at, col + e, v[e]);
+                if (vec && col + 4 <= g.N) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) dst[e] = v[e];
+                }
+            }
+            __syncthreads();
+        }
+        clear();
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1937,6 +1967,7 @@ __global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(
 // at a time, NARROW_AHEAD batches ahead, and multiplies; the four waves of a workgroup take turns at the k of its split and are summed
 // through LDS in wave order, splits by gemm_reduce_kernel.  Rows need no alignment.
 constexpr int NARROW_AHEAD = 4;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
 
 // A pair of problems of one shape (A2, B2, part2) runs as the second row of the grid.
@@ -2481,16 +2512,46 @@ static bool split_sum(int mode, int trans_b, int64_t M, int64_t N, int64_t K1, i
     return split_form(mode, 0, M, N, K1 + K2);
 }
 
-// tiles 64 columns wide keep four waves; 128-column tiles run eight (both forms of the product)
-static void launch_split_tiles(bool trans, const GemmArgs &g, int bn, dim3 grid, const uint16_t *Wt, int64_t ku_total,
-                               int64_t n_pad, hipStream_t st) {
-    if (trans) {
-        if (bn == 64) hipLaunchKernelGGL(gemm_split_trans_kernel<64>, grid, dim3(512), 0, st, g);
-        else hipLaunchKernelGGL(gemm_split_trans_kernel<128>, grid, dim3(512), 0, st, g);
-    } else {
-        if (bn == 64) hipLaunchKernelGGL((gemm_split_kernel<128, 64>), grid, dim3(256), 0, st, g, Wt, ku_total, n_pad);
-        else hipLaunchKernelGGL((gemm_split_kernel<128, 128, 8>), grid, dim3(512), 0, st, g, Wt, ku_total, n_pad);
+// tiles 64 columns wide keep four waves; 128-column tiles run eight
+static void launch_split_tiles(const GemmArgs &g, int bn, dim3 grid, const uint16_t *Wt, int64_t ku_total, int64_t n_pad, hipStream_t st) {
+    if (bn == 64) hipLaunchKernelGGL((gemm_split_kernel<128, 64>), grid, dim3(256), 0, st, g, Wt, ku_total, n_pad);
+    else hipLaunchKernelGGL((gemm_split_kernel<128, 128, 8>), grid, dim3(512), 0, st, g, Wt, ku_total, n_pad);
+}
+
+// gemm_split_cols_kernel: column tiles of 32 in a workgroup's tile, reduction splits (workgroups per tile), parts of each, vertices of a
+// wave in a part.  At most `most` partial results.  A step of 16 vertices takes a wave 2.4 us with 128 columns and 1.45 us with 64, a
+// workgroup's start and end 11 and 8 us (256 x 256 by 40000 and 306000, 100 x 256 by 70001 and 306000), a compute unit holds one workgroup,
+// and the tiles of a split share an L2 domain, so the splits come in eights where they are that many.  So 128 columns but for short
+// reductions and for columns that fill half of the last tile: us with the better splits, 128 and 64 columns: 256 x 256 x 306000 189, 218;
+// 602 x 200 x 30000 57, 65; 256 x 256 x 40000 36.0, 35.5; 128 x 128 x 100000 30.1, 27.5; 97 x 131 x 50001 29.5, 25.4.
+struct ColsPlan { int tb, S, parts; int64_t chunk; };
+static ColsPlan cols_plan(int64_t M, int64_t N, int64_t K, int most) {
+    ColsPlan best{4, 1, 1, (K + 127) / 128 * 32};
+    double best_us = 1e30;
+    for (int tb : {4, 2}) {
+        const int64_t tiles = (M + 127) / 128 * ((N + tb * 32 - 1) / (tb * 32)), held = NUM_CU / NUM_XCD;
+        for (int S = 1; S <= most && S <= 2 * NUM_CU; S += S < 8 ? 1 : 8) {
+            const int64_t per_domain = S < NUM_XCD ? (S * tiles + NUM_XCD - 1) / NUM_XCD : S / NUM_XCD * tiles, steps = (K + 64 * S - 1) / (64 * S);
+            const double us = (per_domain + held - 1) / held * (steps * (tb == 4 ? 2.4 : 1.45) + (tb == 4 ? 11.0 : 8.0)) +
+                              (S > 1 ? 1.6e-6 * static_cast<double>(S) * M * N : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best.tb = tb;
+                best.S = S;
+            }
+        }
     }
+    const int64_t wave = (K + 4 * best.S - 1) / (4 * best.S);
+    best.parts = static_cast<int>(std::max<int64_t>(std::min<int64_t>((wave + COLS_CHAIN - 1) / COLS_CHAIN, (most + 4 * best.S - 1) / (4 * best.S)), 1));
+    best.chunk = ((wave + best.parts - 1) / best.parts + 31) / 32 * 32;
+    return best;
+}
+
+static void launch_split_cols(const GemmArgs &g, const ColsPlan &p, dim3 grid, hipStream_t st) {
+#define CG_COLS(TB_, SUMS_) if (p.tb == TB_ && !!g.colpart == SUMS_) \
+        hipLaunchKernelGGL((gemm_split_cols_kernel<TB_, SUMS_>), grid, dim3(256), 0, st, g, p.parts);
+    CG_COLS(4, false) CG_COLS(4, true) CG_COLS(2, false) CG_COLS(2, true)
+#undef CG_COLS
 }
 
 template <int NS, int KH>
@@ -2693,7 +2754,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     // fp32 operands as three bf16 pieces each (see gemm_split_kernel)
     const int mode = f32_product;
     const bool split_path = dtype == CAPGNN_F32 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
-                            (trans_a || (ws && ws_bytes >= split_b_bytes(N, K)));
+                            (trans_a ? K < (int64_t(1) << 31) && lda < (1 << 24) && ldb < (1 << 24) : ws && ws_bytes >= split_b_bytes(N, K));
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
     const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
     bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
@@ -2717,7 +2778,17 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         bm = 32;
         bn = 32 * tn;
     }
-    const bool mid_path = !small_path && mid;
+    const bool mid_path = !small_path && mid, cols_path = trans_a && split_path && !small_path && !narrow;
+    ColsPlan cols{};
+    int grid_S = S;         // reduction splits as workgroups (S: as partial results)
+    if (cols_path) {
+        if (S > 1 && (!ws || ws_bytes < static_cast<size_t>(S) * M * N * sizeof(float)))
+            CG_FAIL(CAPGNN_ENOMEM, "gemm: workspace of %zu bytes needed, %zu given", static_cast<size_t>(S) * M * N * sizeof(float), ws_bytes);
+        cols = cols_plan(M, N, K, S);
+        grid_S = cols.S;
+        S = cols.S * cols.parts;
+        bn = 32 * cols.tb;
+    }
     if (mid_path || (half_path && !trans_a && tiles128 <= 1280)) bm = bn = 64;
     GemmArgs g;
     g.M = M; g.N = N; g.K = K;
@@ -2742,6 +2813,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         g.k_chunk = (steps + S - 1) / S * bk;
     }
     if (small_path) g.k_chunk = small_chunk;
+    if (cols_path) g.k_chunk = cols.chunk;
     if (narrow) {
         g.part = static_cast<float *>(ws);
         g.k_chunk = ((K + S - 1) / S + 15) / 16 * 16;      // (the last splits may be empty: zeros)
@@ -2754,10 +2826,12 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         g.colpart = reinterpret_cast<float *>(static_cast<char *>(ws) + at);
     }
     const int64_t gy = (M + bm - 1) / bm, gx = (N + bn - 1) / bn;
-    const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
+    if (!cols_path) grid_S = S;
+    const int64_t n_wg = cols_path && grid_S < NUM_XCD ? gx * gy * grid_S
+                         : grid_S > 1 ? NUM_XCD * ((grid_S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     if (n_wg >= (int64_t(1) << 31) || gx >= (int64_t(1) << 24) || gy >= (int64_t(1) << 30))
         CG_FAIL(CAPGNN_EINVAL, "gemm: %lld x %lld tiles exceed the grid", (long long)gy, (long long)gx);
-    g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
+    g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = grid_S;
     g.c_staged = half_path && g.out_bf16 && !g.part && !g.accumulate && !g.rscale && aligned16(C) && (ldc * 2) % 16 == 0 &&
                  (!relu_mask || (aligned16(relu_mask) && (ldm * 2) % 16 == 0));
     const bool stream_path = g.c_staged && !trans_a && bf16_stream_pays(M, N, K, relu_mask != nullptr) && ws &&
@@ -2781,14 +2855,14 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, sm);
     } else if (split_path) {
         if (trans_a) {
-            launch_split_tiles(true, g, bn, grid, nullptr, 0, 0, stream);
+            launch_split_cols(g, cols, grid, stream);
         } else {
             const int64_t n_pad = split_rows(N), ku_total = split_ld(K) / 8;
             hipLaunchKernelGGL(split_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0,
                                stream, static_cast<const float *>(B), ldb, bkc ? 1 : 0, K, N, static_cast<uint16_t *>(ws), n_pad,
                                ku_total);
             if (!launch_split_stream(g, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream))
-                launch_split_tiles(false, g, bn, grid, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream);
+                launch_split_tiles(g, bn, grid, static_cast<const uint16_t *>(ws), ku_total, n_pad, stream);
         }
     } else if (stream_path) {
         const int64_t n_pad = split_rows(N), ku_total = 2 * stream_units(K);

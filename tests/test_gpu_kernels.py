@@ -976,6 +976,67 @@ def test_gemm_f32_split_product(env, ta, tb):
         B.gemm(0, 0, 1, 1, 1, one, 1, one, 1, one, 1, B.F32, f32_product=7)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (127, 65, 15), (128, 64, 16), (129, 128, 17), (33, 129, 47), (130, 192, 64), (128, 128, 65), (257, 200, 600), (96, 256, 2049),
+                                   (602, 100, 5000), (64, 41, 20_001), (300, 130, 38_401), (100, 256, 70_001), (128, 128, 300_000), (700, 600, 1600)])
+def test_gemm_f32_split_vertex_reduction_exact(env, M, N, K):
+    """X^T G in three bf16 pieces: tiles of 128 rows and of 64 and 128 columns whole and ragged, K around a step of 16, the two steps of a loop
+    and the four waves of a workgroup, one split and many, one part of a split and several (300 000); rows aligned and not; with the workspace
+    that was asked for, with as little as the call accepts, and, where there is one split, with the whole epilogue.  Integers of nine bits by
+    -1, 0 and 1 (sums below 2^24): equality.  Padding is NaN; the last rows end with the allocation."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    A = torch.randint(-400, 401, (K, M), generator=gen, device="cuda").float()
+    G = torch.randint(-1, 2, (K, N), generator=gen, device="cuda").float()
+    ref = A.double().T @ G.double()
+    assert float(ref.abs().max()) < 2 ** 24
+    bias = torch.randint(-9, 9, (N,), generator=gen, device="cuda").float()
+    splits = min(1536 // (-(-M // 128) * -(-N // (64 if N <= 64 else 128))), K // 512)
+    least = splits * M * N * 4 if splits > 1 else 0
+    for pad in (0, 1, 4):
+        flat = lambda x: torch.cat([torch.nn.functional.pad(x[:-1], (0, pad), value=float("nan")).reshape(-1), x[-1]])  # noqa: E731
+        Ad, Gd = flat(A), flat(G)
+        for room, full in ((B.gemm_workspace_bytes(1, M, N, K), 0), (least, 0), (least, 1)):
+            say(f"gemm split X^T G {M}x{N}x{K} pad={pad} workspace={room} epilogue={full}")
+            ws = torch.empty(max(room, 1), dtype=torch.uint8, device="cuda")
+            Cd = torch.full((M, N + 3), 2.0, device="cuda")
+            B.gemm(1, 0, M, N, K, Ad, M + pad, Gd, N + pad, Cd, N + 3, B.F32, accumulate=full, bias=bias if full else None, relu=full, ws=ws,
+                   ws_bytes=room, f32_product=B.F32_PRODUCT_SPLIT)
+            torch.cuda.synchronize()
+            want = (ref + 2.0 + bias).clamp(min=0) if full else ref
+            assert torch.equal(Cd[:, :N].double(), want) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("n,dims", [(100_000, (40, 100, 70)), (30_011, (130, 121, 9))])
+def test_epoch_bias_gradient_of_split_weight_gradients(env, n, dims):
+    """The hidden layer's bias gradient, whose columns the three-piece X^T G sums on its way (64 and 128 columns of a workgroup), on a graph of
+    self loops.  Against fp64: each dZ is off by a few fp32 roundings of its terms, the sum by less than 1e-6 of the sum of their magnitudes."""
+    torch, B = env["torch"], env["B"]
+    assert n * dims[0] * dims[1] >= 1.375 * 2 ** 28
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    g = B.Graph(n, 0, np.arange(0, n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.ones(n, np.float32), np.ones(n, np.float32))
+    x = torch.randn(n, dims[0], generator=gen, device="cuda")
+    w = [torch.randn(a, b, generator=gen, device="cuda") / a ** 0.5 for a, b in zip(dims, dims[1:])]
+    b = [0.1 * torch.randn(d, generator=gen, device="cuda") for d in dims[1:]]
+    labels = torch.randint(0, dims[-1], (n,), generator=gen, device="cuda", dtype=torch.int32)
+    dw, db = [torch.zeros_like(t) for t in w], [torch.zeros_like(t) for t in b]
+    layers = [B.make_layer(B.GCN, a, c, act, B.F32, w[i], None, b[i], B.AGG_FIRST)
+              for i, (a, c, act) in enumerate(zip(dims, dims[1:], (B.ACT_RELU, B.ACT_NONE)))]
+    wsb = B.epoch_workspace_bytes(g, None, layers)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    logits = torch.zeros(n, dims[-1], device="cuda")
+    say(f"bias gradient beside a three-piece weight gradient n={n} {dims}")
+    B.epoch(g, None, layers, x, dims[0], labels, None, 0.0, logits, dw, None, db, 0.0, ws, wsb, None, None, want_loss=False)
+    torch.cuda.synchronize()
+    h = (x.double() @ w[0].double() + b[0].double()).clamp(min=0)
+    p = torch.softmax(h @ w[1].double() + b[1].double(), 1)
+    p[torch.arange(n, device="cuda"), labels.long()] -= 1.0
+    dz = (p / n) @ w[1].double().T * (h > 0)
+    assert ((db[0].double() - dz.sum(0)).abs() <= 1e-6 * dz.abs().sum(0)).all()
+    assert ((dw[0].double() - x.double().T @ dz).abs() <= 2e-6 * (x.abs().double().T @ dz.abs())).all()
+
+
 @pytest.mark.parametrize("tb", [0, 1])
 def test_gemm_f32_auto_form_is_the_documented_one(env, tb):
     """AUTO is the fp32 instruction below 2^28 multiply-adds and without a workspace, the three-piece form from there on: bit for bit
