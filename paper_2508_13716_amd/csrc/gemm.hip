@@ -488,9 +488,7 @@ constexpr int HPAD = 8;            // bf16 elements of row padding
 // position (in elements) of 16-byte chunk `chunk` (0..3) inside LDS row `row`
 __device__ __forceinline__ int chunk_pos(int row, int chunk) { return 8 * (chunk ^ ((row >> 3) & 3)); }
 
-// TOFF: first thread of the workgroup that works on this tile when the operand needs the transposing path
-// (that path keeps (HBK/4) * (BT/8) threads busy; the two operands of X^T G take disjoint thread ranges).
-template <bool KC, int BT, int TOFF>
+template <bool KC, int BT>
 struct HalfTileLoader {
     static constexpr int NLD = KC ? BT * HBK / 8 / 256 : 4;   // 16-byte chunks per thread
     static constexpr int NTH = (HBK / 4) * (BT / 8);          // threads of the transposing path
@@ -521,8 +519,8 @@ struct HalfTileLoader {
                 r[q] = load8(base, t * ld + k, nv);
             }
         } else {
-            const int tt = tid - TOFF;
-            if (tt < 0 || tt >= NTH) return;
+            const int tt = tid;
+            if (tt >= NTH) return;
             constexpr int CPR = BT / 8;
             const int kb = tt / CPR, tq = tt % CPR;       // four k starting at 4*kb, eight columns starting at 8*tq
             const int64_t t = t0 + 8 * tq;
@@ -568,8 +566,8 @@ struct HalfTileLoader {
                 *reinterpret_cast<uint4 *>(&s[row][chunk_pos(row, kq)]) = r[q];
             }
         } else {
-            const int tt = tid - TOFF;
-            if (tt < 0 || tt >= NTH) return;
+            const int tt = tid;
+            if (tt >= NTH) return;
             constexpr int CPR = BT / 8;
             const int kb = tt / CPR, tq = tt % CPR;
             const uint32_t w[4][4] = {{r[0].x, r[0].y, r[0].z, r[0].w}, {r[1].x, r[1].y, r[1].z, r[1].w},
@@ -600,9 +598,9 @@ __device__ __forceinline__ uint4 keep_positive(uint4 v, uint4 m) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// (second launch bound: X^T G on full tiles keeps three workgroups per compute unit beside its column sums)
+// (X^T G, both of whose operands are stored across the reduction index, has gemm_bf16_cols_kernel)
 template <bool A_KC, bool B_KC, int BM, int BN>
-__global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int LDSROW = HBK + HPAD;
@@ -631,8 +629,8 @@ __global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    HalfTileLoader<A_KC, BM, 0> la;
-    HalfTileLoader<B_KC, BN, A_KC ? 0 : 128> lb;     // when both operands are transposed they split the threads
+    HalfTileLoader<A_KC, BM> la;
+    HalfTileLoader<B_KC, BN> lb;
     la.k_rows = g.K; lb.k_rows = g.K;
     const int64_t nk = (k_end > k_begin) ? (k_end - k_begin + HBK - 1) / HBK : 0;
     if (nk > 0) {
@@ -651,27 +649,6 @@ __global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm
             lb.fast_begin(g.B, g.ldb, n0, k_begin + HBK, tid);
         }
     }
-    // column sums of B (see gemm_small_kernel): a staging thread's four rows of a step cover the same eight columns
-    constexpr bool SUMS = !A_KC && !B_KC;
-    const bool sums = SUMS && g.colpart && by == 0;
-    double bsum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    auto add_b = [&]() __attribute__((always_inline)) {
-        if constexpr (SUMS) {
-            float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t w[4] = {lb.r[q].x, lb.r[q].y, lb.r[q].z, lb.r[q].w};
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    t[2 * d] += __uint_as_float(w[d] << 16);
-                    t[2 * d + 1] += __uint_as_float(w[d] & 0xffff0000u);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bsum[e] += static_cast<double>(t[e]);
-        }
-    };
-    if (sums && nk > 0) add_b();
     __syncthreads();
     for (int64_t kt = 0; kt < nk; ++kt) {
         const int buf = static_cast<int>(kt & 1);
@@ -710,29 +687,10 @@ __global__ __launch_bounds__(256, !A_KC && !B_KC && BN == 128 ? 3 : 1) void gemm
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
         if (more) {
-            if (sums) add_b();
             la.stash(As[buf ^ 1], tid);
             lb.stash(Bs[buf ^ 1], tid);
         }
         __syncthreads();
-    }
-    if constexpr (SUMS) {
-        if (sums) {     // threads 128 .. 128 + NTH of the workgroup stage B: [HBK / 4][BN] partial sums
-            double (*bred)[BN] = reinterpret_cast<double (*)[BN]>(smem);
-            static_assert(HBK / 4 * BN * sizeof(double) <= sizeof(smem), "the partial sums must fit the operand tiles");
-            constexpr int CPR = BN / 8;
-            const int tt = tid - 128;
-            if (tt >= 0 && tt < (HBK / 4) * CPR)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) bred[tt / CPR][8 * (tt % CPR) + e] = bsum[e];
-            __syncthreads();
-            if (tid < BN && n0 + tid < g.N) {
-                double t = 0.0;
-                for (int y = 0; y < HBK / 4; ++y) t += bred[y][tid];
-                g.colpart[bz * g.N + n0 + tid] = static_cast<float>(t);
-            }
-            __syncthreads();
-        }
     }
     if (!g.c_staged) {
         store_tile<TM, TN>(g, acc, m0 + wm * WM, n0 + wn * WN, l32, half, bz);
@@ -827,7 +785,7 @@ __global__ __launch_bounds__(NS * 64, std::max(1, stream_held(KS, NS) * NS / 4))
 #pragma unroll
         for (int q = 0; q < NLD; ++q) {
             const int row = r0 + q * RPP;
-            r[q] = HalfTileLoader<true, 128, 0>::load8(g.A, (full * 32 + row) * g.lda + 8 * v, row < rows ? (have < 8 ? have : 8) : 0);
+            r[q] = HalfTileLoader<true, 128>::load8(g.A, (full * 32 + row) * g.lda + 8 * v, row < rows ? (have < 8 ? have : 8) : 0);
         }
     };
     auto put = [&](Rows &r, char *As) __attribute__((always_inline)) {
@@ -1447,6 +1405,20 @@ __global__ __launch_bounds__(NS * 64, split_stream_held(NS, KH) * NS / 4) void g
     }
 }
 
+// what the kernels for two products in one launch are told
+struct SmallGemmArgs {
+    GemmArgs g;                     // tile grid, sizes, epilogue; A2 / lda2 / K1 not used
+    // second product of a sum C = A B + A2 B2 (dual), or second problem of the same shape C2 = A2 B2 (pair)
+    const char *A2; int64_t lda2;
+    const char *B2; int64_t ldb2;
+    char *C2; int64_t ldc2;
+    float *part2;
+    const float *rscale2;
+    int64_t K2;                     // of the dual form
+    int64_t M2;                     // rows of the second problem
+    int dual;
+};
+
 // The weight gradient X^T G in three pieces: both operands are stored across the reduction index (vertices), and nothing is staged.  A
 // wave holds 128 x (TB * 32) results (TB = 4: all 256 accumulation registers) and loads both operands as the matrix instruction wants
 // them: a lane eight vertices of one column, each load two rows of 32 columns.  It cuts the next operands between the matrix
@@ -1463,7 +1435,11 @@ constexpr int COLS_CHAIN = 512;
 constexpr int COLS_PITCH = 72;      // floats per row of 64 results on their way through LDS (four rows further = other half of the banks)
 
 template <int TB, bool SUMS>
-__global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(GemmArgs g, int parts) {
+__global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(SmallGemmArgs p2, int parts) {
+    GemmArgs g = p2.g;
+    if (blockIdx.y != 0) {                              // the second of a pair: another first operand, the same G
+        g.A = p2.A2; g.lda = p2.lda2; g.C = p2.C2; g.ldc = p2.ldc2; g.part = p2.part2;
+    }
     constexpr int TA = 4;
     __shared__ __attribute__((aligned(16))) float red[4][TA][32 * COLS_PITCH];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1621,7 +1597,7 @@ __global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(GemmArgs g, int
             }
             __syncthreads();
             const int col = 64 * wave + ln;
-            if (by == 0 && col < TB * 32 && n0 + col < g.N) {
+            if (by == 0 && blockIdx.y == 0 && col < TB * 32 && n0 + col < g.N) {
                 double t = 0.0;
                 for (int y = 0; y < 8; ++y) t += bred[y][col];
                 g.colpart[z * g.N + n0 + col] = static_cast<float>(t);
@@ -1671,6 +1647,220 @@ __global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(GemmArgs g, int
     }
 }
 
+// X^T G of bf16 operands in the same manner, bound by memory: a wave's 128 x (TB * 32) results, four (TB) columns of a vertex per lane and
+// load, so tile i of 32 rows holds the columns 4 r + i of X; eight vertices of a column come together by byte permutes.  Three steps of 16
+// vertices (8 KB each) are on their way while one is multiplied.  The waves of all splits take steps in turn, so that what is read at any
+// time is one stretch of the operands (a stretch per wave: 256 x 256 x 980000 241 us instead of 228, 128 x 256 167 instead of 152).  Rows start on
+// 16 bytes; a last row that ends inside a group of four columns is read apart, column by column.
+// us with the sum over parts, tiles staged through LDS or gemm_small_kernel -> here: 256 x 256 x 980000 320 -> 228 (4.6 TB/s), 128 x 256 x 980000 191 -> 152, 256 x 47 x
+// 980000 146 -> 112, 389 x 200 x 98712 84 -> 61, 602 x 256 x 30000 47 -> 32, 200 x 2 x 98712 29 -> 19, 100 x 16 x 250000 41 -> 21.
+template <int TB, bool SUMS>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_cols_kernel(SmallGemmArgs p2, int parts) {
+    GemmArgs g = p2.g;
+    if (blockIdx.y != 0) {                              // the second of a pair: another first operand, the same G
+        g.A = p2.A2; g.lda = p2.lda2; g.C = p2.C2; g.ldc = p2.ldc2; g.part = p2.part2;
+    }
+    constexpr int TA = 4, AHEAD = 4, CP = TB * 32 + 4;         // steps held, floats per row of the wave's results on their way through LDS
+    constexpr int WB = TB / 2;                                 // dwords of a lane's columns of G
+    __shared__ __attribute__((aligned(16))) float red[4][64 * CP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    int bx, by, bz;
+    if (g.S < NUM_XCD) {                                // too few splits for every L2 domain to have one: the tiles go to all of them
+        const int tile = static_cast<int>(blockIdx.x) % (g.gx * g.gy);
+        bz = static_cast<int>(blockIdx.x) / (g.gx * g.gy);
+        bx = tile % g.gx;
+        by = tile / g.gx;
+    } else if (!tile_coords(g, &bx, &by, &bz)) {
+        return;                                         // uniform over the workgroup
+    }
+    const int64_t m0 = static_cast<int64_t>(by) * (TA * 32), n0 = static_cast<int64_t>(bx) * (TB * 32);
+    const bool ragged = (g.M | g.N) % 4 != 0;           // the matrices' last row is read apart
+    const int64_t k_all = ragged ? g.K - 1 : g.K;
+    const int k_first = (bz * 4 + wave) * 16, k_step = 64 * g.S, n_all = static_cast<int>(k_all);
+    const int lda = static_cast<int>(g.lda) * 2, ldb = static_cast<int>(g.ldb) * 2;         // bytes
+    const int left_a = static_cast<int>(g.M - m0 < TA * 32 ? g.M - m0 : TA * 32), left_b = static_cast<int>(g.N - n0 < TB * 32 ? g.N - n0 : TB * 32);
+    const int width_a = (left_a + 3) / 4 * 8, width_b = (left_b + 3) / 4 * 8;
+    const char *pa = g.A + (static_cast<int64_t>(k_first) * lda + m0 * 2), *pb = g.B + (static_cast<int64_t>(k_first) * ldb + n0 * 2);
+    auto rows16 = [&](const char *p, int ld, int row, int width) __attribute__((always_inline)) {
+        const int n = n_all - row < 16 ? n_all - row : 16;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), 0, n > 0 ? (n - 1) * ld + width : 0, 0x00027000);
+    };
+    uint32_t oa[8], ob[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        oa[j] = static_cast<uint32_t>(half * 8 + j) * lda + l32 * 8;
+        ob[j] = static_cast<uint32_t>(half * 8 + j) * ldb + l32 * (2 * TB);
+    }
+    struct Raw { uint32_t a[8][2], b[8][WB]; };
+    Raw raw[AHEAD];
+    u32x4 oa4[2][TA], ob4[2][TB];                       // operands of this step and the next
+    floatx16 acc[TA][TB];
+    double bsum[TB] = {};
+    int row = k_first;                                        // of the step that is asked for next
+    auto ask = [&](Raw &r) __attribute__((always_inline)) {
+        auto sa = rows16(pa, lda, row, width_a), sb = rows16(pb, ldb, row, width_b);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(sa, oa[j], 0, 0));
+            r.a[j][0] = v.x; r.a[j][1] = v.y;
+            if constexpr (WB == 2) {
+                const u32x2 w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(sb, ob[j], 0, 0));
+                r.b[j][0] = w.x; r.b[j][WB - 1] = w.y;
+            } else {
+                r.b[j][0] = __builtin_amdgcn_raw_buffer_load_b32(sb, ob[j], 0, 0);
+            }
+        }
+        pa += static_cast<int64_t>(k_step) * lda;
+        pb += static_cast<int64_t>(k_step) * ldb;
+        row += k_step;
+    };
+    // eight vertices of each of the lane's columns
+    auto turn = [&](const Raw &r, u32x4 (&a)[TA], u32x4 (&b)[TB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+                a[i][e] = __builtin_amdgcn_perm(r.a[2 * e + 1][i / 2], r.a[2 * e][i / 2], i & 1 ? 0x07060302u : 0x05040100u);
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+                b[j][e] = __builtin_amdgcn_perm(r.b[2 * e + 1][j / 2], r.b[2 * e][j / 2], j & 1 ? 0x07060302u : 0x05040100u);
+        }
+        if constexpr (SUMS) {                           // a step's eight numbers in fp32, the running sum a double
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                float t = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t += __uint_as_float(b[j][e] << 16) + __uint_as_float(b[j][e] & 0xffff0000u);
+                bsum[j] += static_cast<double>(t);
+            }
+        }
+    };
+    auto multiply = [&](const u32x4 (&a)[TA], const u32x4 (&b)[TB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+    };
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear();
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) {
+        ask(raw[p]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    turn(raw[0], oa4[0], ob4[0]);
+    ask(raw[0]);
+    int at = 0;                                         // rows multiplied
+    for (int part = 0; part < parts; ++part) {
+        const int end = static_cast<int>((part + 1) * g.k_chunk);
+        while (at < end) {               // (g.k_chunk: a multiple of AHEAD steps)
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) {
+                multiply(oa4[p & 1], ob4[p & 1]);
+                turn(raw[(p + 1) % AHEAD], oa4[(p & 1) ^ 1], ob4[(p & 1) ^ 1]);
+                ask(raw[(p + 1) % AHEAD]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            at += 16 * AHEAD;
+        }
+        if (ragged && bz == 0 && wave == 0 && part == 0) {
+            Raw r{};
+            const uint16_t *xa = reinterpret_cast<const uint16_t *>(g.A) + (g.K - 1) * g.lda + m0 + 4 * l32;
+            const uint16_t *xb = reinterpret_cast<const uint16_t *>(g.B) + (g.K - 1) * g.ldb + n0 + TB * l32;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (half == 0 && 4 * l32 + e < left_a) r.a[0][e / 2] |= static_cast<uint32_t>(xa[e]) << (16 * (e & 1));
+#pragma unroll
+            for (int e = 0; e < TB; ++e)
+                if (half == 0 && TB * l32 + e < left_b) r.b[0][e / 2] |= static_cast<uint32_t>(xb[e]) << (16 * (e & 1));
+            u32x4 ta[TA], tb[TB];
+            turn(r, ta, tb);
+            multiply(ta, tb);
+        }
+        const int z = bz * parts + part;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));        // what follows from it is formed here: held through the loop it takes registers
+        const int c32 = ln & 31, hf = ln >> 5;
+        if constexpr (SUMS) {
+            // (what the step ahead has added belongs to the next part: the parts' sums are added up all the same)
+            double (*bred)[TB * 32] = reinterpret_cast<double (*)[TB * 32]>(&red[0][0]);
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                bred[2 * wave + hf][TB * c32 + j] = bsum[j];
+                bsum[j] = 0.0;
+            }
+            __syncthreads();
+            const int col = 64 * wave + ln;
+            if (by == 0 && blockIdx.y == 0 && col < TB * 32 && n0 + col < g.N) {
+                double t = 0.0;
+                for (int y = 0; y < 8; ++y) t += bred[y][col];
+                g.colpart[z * g.N + n0 + col] = static_cast<float>(t);
+            }
+            __syncthreads();
+        }
+        // two tiles of 32 rows at a time: the four waves' results side by side, then each wave adds up and stores 16 rows of them
+#pragma unroll
+        for (int h = 0; h < TA / 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float *to = &red[wave][(2 * (8 * (r >> 2) + 4 * hf + (r & 3)) + i) * CP + TB * c32];
+#pragma unroll
+                    for (int j = 0; j < TB; ++j) to[j] = acc[2 * h + i][j][r];
+                }
+            __syncthreads();
+            constexpr int CGS = TB * 8, RPP = 64 / CGS;          // groups of four columns in a row, rows per pass
+            const int64_t col = n0 + 4 * (ln % CGS);
+            const bool vec = g.part ? g.N % 4 == 0 && reinterpret_cast<uintptr_t>(g.part) % 16 == 0
+                                    : g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(g.C) % 16 == 0;
+#pragma unroll 1
+            for (int p = 0; p < 16 / RPP; ++p) {
+                const int lr = 16 * wave + RPP * p + ln / CGS;           // row 2 r + i: column 4 r + 2 h + i of X
+                const int64_t to = m0 + 4 * (lr / 2) + 2 * h + lr % 2;
+                float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float4 x = *reinterpret_cast<const float4 *>(&red[w][lr * CP + 4 * (ln % CGS)]);
+                    v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+                }
+                if (to >= g.M || col >= g.N) continue;
+                if (!g.part) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) v[e] = epilogue_value(g, to, col + e, v[e]);
+                    if (g.out_bf16) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < g.N) reinterpret_cast<uint16_t *>(g.C)[to * g.ldc + col + e] = static_cast<uint16_t>(f32_to_bf16_rne(v[e]));
+                        continue;
+                    }
+                }
+                float *dst = g.part ? g.part + (static_cast<int64_t>(z) * g.M + to) * g.N + col : reinterpret_cast<float *>(g.C) + to * g.ldc + col;
+                if (vec && col + 4 <= g.N) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) dst[e] = v[e];
+                }
+            }
+            __syncthreads();
+        }
+        clear();
+    }
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Small products, whose tiles of 128 rows would leave most of the chip idle and pay a round trip to memory per 16 or 32 k:
 // here a workgroup owns 32 x (TN * 32) outputs, its four waves take quarters of the reduction (or, of a sum of two
@@ -1678,18 +1868,6 @@ __global__ __launch_bounds__(256, 1) void gemm_split_cols_kernel(GemmArgs g, int
 // them from, four units (fp32: 32 k, bf16: 64 k) at a time and one batch ahead: one or two round trips in all.  The four
 // partial tiles are added through LDS in wave order.  No alignment is needed; k may be assigned to the instruction's k slots
 // in any order as long as both operands agree, so a lane takes four (eight) consecutive k of its row.
-struct SmallGemmArgs {
-    GemmArgs g;                     // tile grid, sizes, epilogue; A2 / lda2 / K1 not used
-    // second product of a sum C = A B + A2 B2 (dual), or second problem of the same shape C2 = A2 B2 (pair)
-    const char *A2; int64_t lda2;
-    const char *B2; int64_t ldb2;
-    char *C2; int64_t ldc2;
-    float *part2;
-    const float *rscale2;
-    int64_t K2;                     // of the dual form
-    int64_t M2;                     // rows of the second problem
-    int dual;
-};
 
 // One unit of an operand: 4 fp32 k (of a half wave's 8) or 8 bf16 k (of 16), of one row / column of the result.
 template <bool BF16> struct SmallUnit { float v[4]; };
@@ -2525,15 +2703,16 @@ static void launch_split_tiles(const GemmArgs &g, int bn, dim3 grid, const uint1
 // reductions and for columns that fill half of the last tile: us with the better splits, 128 and 64 columns: 256 x 256 x 306000 189, 218;
 // 602 x 200 x 30000 57, 65; 256 x 256 x 40000 36.0, 35.5; 128 x 128 x 100000 30.1, 27.5; 97 x 131 x 50001 29.5, 25.4.
 struct ColsPlan { int tb, S, parts; int64_t chunk; };
-static ColsPlan cols_plan(int64_t M, int64_t N, int64_t K, int most) {
-    ColsPlan best{4, 1, 1, (K + 127) / 128 * 32};
+static ColsPlan cols_plan(bool bf16, int64_t M, int64_t N, int64_t K, int most, int products = 1) {
+    const int64_t unit = bf16 ? 64 : 32;                // vertices of a wave are whole turns of its loop
+    ColsPlan best{4, 1, 1, 0};
     double best_us = 1e30;
     for (int tb : {4, 2}) {
-        const int64_t tiles = (M + 127) / 128 * ((N + tb * 32 - 1) / (tb * 32)), held = NUM_CU / NUM_XCD;
+        const int64_t tiles = products * ((M + 127) / 128) * ((N + tb * 32 - 1) / (tb * 32)), held = NUM_CU / NUM_XCD;
+        const double step = bf16 ? (tb == 4 ? 0.8 : 0.6) : tb == 4 ? 2.4 : 1.45, ends = bf16 ? (tb == 4 ? 9.0 : 7.0) : tb == 4 ? 11.0 : 8.0;
         for (int S = 1; S <= most && S <= 2 * NUM_CU; S += S < 8 ? 1 : 8) {
             const int64_t per_domain = S < NUM_XCD ? (S * tiles + NUM_XCD - 1) / NUM_XCD : S / NUM_XCD * tiles, steps = (K + 64 * S - 1) / (64 * S);
-            const double us = (per_domain + held - 1) / held * (steps * (tb == 4 ? 2.4 : 1.45) + (tb == 4 ? 11.0 : 8.0)) +
-                              (S > 1 ? 1.6e-6 * static_cast<double>(S) * M * N : 0.0);
+            const double us = (per_domain + held - 1) / held * (steps * step + ends) + (S > 1 ? 1.6e-6 * products * S * M * N : 0.0);
             if (us < best_us) {
                 best_us = us;
                 best.tb = tb;
@@ -2543,15 +2722,42 @@ static ColsPlan cols_plan(int64_t M, int64_t N, int64_t K, int most) {
     }
     const int64_t wave = (K + 4 * best.S - 1) / (4 * best.S);
     best.parts = static_cast<int>(std::max<int64_t>(std::min<int64_t>((wave + COLS_CHAIN - 1) / COLS_CHAIN, (most + 4 * best.S - 1) / (4 * best.S)), 1));
-    best.chunk = ((wave + best.parts - 1) / best.parts + 31) / 32 * 32;
+    best.chunk = ((wave + best.parts - 1) / best.parts + unit - 1) / unit * unit;
     return best;
 }
 
-static void launch_split_cols(const GemmArgs &g, const ColsPlan &p, dim3 grid, hipStream_t st) {
-#define CG_COLS(TB_, SUMS_) if (p.tb == TB_ && !!g.colpart == SUMS_) \
-        hipLaunchKernelGGL((gemm_split_cols_kernel<TB_, SUMS_>), grid, dim3(256), 0, st, g, p.parts);
+// Which of gemm_small_kernel's bf16 reductions over vertices gemm_bf16_cols_kernel takes (it takes all of those that the small kernel leaves): its
+// ends cost 9 us, its tiles are 128 rows high, and it reads faster.  From a sweep of both (550 sizes, M 16 to 602, N 2 to 256, K 1000 to 250000: 0.89
+// of the small kernel's time with the faster one each time), us small -> here, M x N x K:
+// - N <= 64, from 6 M elements of X: 389 x 16 x 20000 20.4 -> 13.8, 100 x 41 x 100000 20.3 -> 17.7, 128 x 32 x 40000 15.5 -> 15.0, 100 x 16 x 40000 14.6 -> 14.4;
+//   not for X that fills less than three quarters of a tile: 50 x 41 x 250000 18.6 -> 20.9, 16 x 64 x 250000 17.2 -> 18.6;
+// - N <= 128, from 2 M elements over 16384 vertices and 4 M below: 128 x 100 x 20000 15.4 -> 14.6, 389 x 100 x 10000 16.9 -> 16.6, 200 x 128 x 10000
+//   14.6 -> 15.3; not 16 x 100 x 250000 19.4 -> 24.5, 50 x 121 x 200000 28 -> 31;
+// - above, from 1 M and 2 M elements: 50 x 256 x 20000 15.3 -> 14.8, 200 x 256 x 10000 17.3 -> 17.3, 200 x 200 x 5000 13.8 -> 14.8; and whenever X has
+//   512 columns and more (the small kernel's tiles fill the chip more than once): 602 x 256 x 1000 22.1 -> 15.5; not 1000 x 600 x 2000 24.5 -> 26.1.
+static bool bf16_cols_pays(int64_t M, int64_t N, int64_t K) {
+    const int64_t x = M * K;
+    if (N <= 64) return M >= 96 && x >= 6000000;
+    if (M <= 32 || (M < 64 && N <= 128 && K >= (1 << 17))) return false;
+    if (N > 128 && N <= 256 && M >= 512) return true;
+    return x >= (int64_t(1) << (20 + (N <= 128) + (K < 16384)));
+}
+
+static void launch_cols(const SmallGemmArgs &s, bool bf16, const ColsPlan &p, dim3 grid, hipStream_t st) {
+#define CG_COLS(TB_, SUMS_) if (p.tb == TB_ && !!s.g.colpart == SUMS_) { \
+        if (bf16) hipLaunchKernelGGL((gemm_bf16_cols_kernel<TB_, SUMS_>), grid, dim3(256), 0, st, s, p.parts); \
+        else hipLaunchKernelGGL((gemm_split_cols_kernel<TB_, SUMS_>), grid, dim3(256), 0, st, s, p.parts); }
     CG_COLS(4, false) CG_COLS(4, true) CG_COLS(2, false) CG_COLS(2, true)
 #undef CG_COLS
+}
+
+// what 32-bit offsets of 16 rows and row numbers reach
+static bool cols_reach(int64_t K, int64_t lda, int64_t ldb) { return K < (int64_t(1) << 30) && lda < (1 << 24) && ldb < (1 << 24); }
+
+// workgroups of one product: tiles times splits, padded to whole rounds of the L2 domains where the splits are dealt to them
+static int64_t cols_grid(const ColsPlan &p, int64_t M, int64_t N) {
+    const int64_t tiles = (M + 127) / 128 * ((N + p.tb * 32 - 1) / (p.tb * 32));
+    return p.S < NUM_XCD ? p.S * tiles : (p.S + NUM_XCD - 1) / NUM_XCD * NUM_XCD * tiles;
 }
 
 template <int NS, int KH>
@@ -2750,14 +2956,17 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const bool b_aligned = aligned16(B) && (ldb * 2) % 16 == 0;
     const bool repack_b = dtype == CAPGNN_BF16 && !trans_a && ws && ws_bytes >= transposed_b_bytes(N, K) &&
                           !(b_aligned && (trans_b || (tiles64 <= 768 && K <= 256)));
-    const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned);
+    const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned) &&
+                           (!trans_a || trans_b || cols_reach(K, lda, ldb));
     // fp32 operands as three bf16 pieces each (see gemm_split_kernel)
     const int mode = f32_product;
     const bool split_path = dtype == CAPGNN_F32 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
-                            (trans_a ? K < (int64_t(1) << 31) && lda < (1 << 24) && ldb < (1 << 24) : ws && ws_bytes >= split_b_bytes(N, K));
+                            (trans_a ? cols_reach(K, lda, ldb) : ws && ws_bytes >= split_b_bytes(N, K));
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
     const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
+    const bool half_cols = half_path && trans_a && !trans_b;
     bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
+    if (half_cols && bf16_cols_pays(M, N, K)) small_path = false;
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
     int S = choose_split(trans_a, M, N, K, bm, bn, bk), tn = 0;
@@ -2778,13 +2987,13 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         bm = 32;
         bn = 32 * tn;
     }
-    const bool mid_path = !small_path && mid, cols_path = trans_a && split_path && !small_path && !narrow;
+    const bool mid_path = !small_path && mid, cols_path = trans_a && !trans_b && (split_path || half_cols) && !small_path && !narrow;
     ColsPlan cols{};
     int grid_S = S;         // reduction splits as workgroups (S: as partial results)
     if (cols_path) {
         if (S > 1 && (!ws || ws_bytes < static_cast<size_t>(S) * M * N * sizeof(float)))
             CG_FAIL(CAPGNN_ENOMEM, "gemm: workspace of %zu bytes needed, %zu given", static_cast<size_t>(S) * M * N * sizeof(float), ws_bytes);
-        cols = cols_plan(M, N, K, S);
+        cols = cols_plan(half_cols, M, N, K, S);
         grid_S = cols.S;
         S = cols.S * cols.parts;
         bn = 32 * cols.tb;
@@ -2827,7 +3036,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     }
     const int64_t gy = (M + bm - 1) / bm, gx = (N + bn - 1) / bn;
     if (!cols_path) grid_S = S;
-    const int64_t n_wg = cols_path && grid_S < NUM_XCD ? gx * gy * grid_S
+    const int64_t n_wg = cols_path ? cols_grid(cols, M, N)
                          : grid_S > 1 ? NUM_XCD * ((grid_S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     if (n_wg >= (int64_t(1) << 31) || gx >= (int64_t(1) << 24) || gy >= (int64_t(1) << 30))
         CG_FAIL(CAPGNN_EINVAL, "gemm: %lld x %lld tiles exceed the grid", (long long)gy, (long long)gx);
@@ -2855,7 +3064,9 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, sm);
     } else if (split_path) {
         if (trans_a) {
-            launch_split_cols(g, cols, grid, stream);
+            SmallGemmArgs sm{};
+            sm.g = g;
+            launch_cols(sm, false, cols, grid, stream);
         } else {
             const int64_t n_pad = split_rows(N), ku_total = split_ld(K) / 8;
             hipLaunchKernelGGL(split_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0,
@@ -2869,6 +3080,10 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         hipLaunchKernelGGL(unit_repack_kernel, dim3(static_cast<unsigned>((ku_total * n_pad * 8 + 255) / 256)), dim3(256), 0, stream,
                            static_cast<const uint16_t *>(B), ldb, bkc ? 1 : 0, K, N, static_cast<uint16_t *>(ws), n_pad, ku_total);
         launch_stream(g, static_cast<const uint16_t *>(ws), static_cast<uint32_t>(n_pad), stream);
+    } else if (cols_path) {
+        SmallGemmArgs sm{};
+        sm.g = g;
+        launch_cols(sm, true, cols, grid, stream);
     } else if (half_path) {
         if (repack_b) {
             const int64_t ldt = (K + 7) / 8 * 8;
@@ -2879,8 +3094,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         }
         if (akc && bkc) launch_bf16_tiles<true, true>(g, bn, bm == 64, grid, stream);
         else if (akc) launch_bf16_tiles<true, false>(g, bn, bm == 64, grid, stream);
-        else if (bkc) launch_bf16_tiles<false, true>(g, bn, bm == 64, grid, stream);
-        else launch_bf16_tiles<false, false>(g, bn, bm == 64, grid, stream);
+        else launch_bf16_tiles<false, true>(g, bn, bm == 64, grid, stream);
     } else {
         const bool bf = dtype == CAPGNN_BF16;
 #define CG_GEMM_CASE(BF, AK, BKC_) if (bf == BF && akc == AK && bkc == BKC_) launch_tiles<BF, AK, BKC_>(g, bn, grid, stream);
@@ -2915,6 +3129,32 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     const size_t half_ws = ws_bytes / 2 / 256 * 256;
     const bool narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K) &&
                         half_ws >= narrow_ws_bytes(g.M, g.N, g.K);
+    // two reductions over vertices with the operands in registers, on the terms of launch_gemm
+    auto rows16 = [](const void *p, int64_t ld) { return aligned16(p) && ld % 8 == 0; };
+    const int most = choose_split(trans_a, g.M, g.N, g.K, 128, g.N <= 64 ? 64 : 128, HBK);
+    const bool cols_pair = pair && trans_a && !trans_b && g.M == s.M2 && ws && !narrow && g.K > 0 && most > 1 && cols_reach(g.K, std::max(g.lda, s.lda2), g.ldb) &&
+                           g.B == s.B2 && g.ldb == s.ldb2 && half_ws >= align_up(static_cast<size_t>(most) * g.M * g.N * sizeof(float), 256) + most * g.N * sizeof(float) &&
+                           (bf ? rows16(g.A, g.lda) && rows16(s.A2, s.lda2) && rows16(g.B, g.ldb) && (!small || bf16_cols_pays(g.M, g.N, g.K))
+                               : !small && split_form(f32_product, 1, g.M, g.N, g.K));
+    if (cols_pair) {
+        const ColsPlan cols = cols_plan(bf, g.M, g.N, g.K, most, 2);
+        const int S = cols.S * cols.parts;
+        g.k_chunk = cols.chunk;
+        if (S > 1) {
+            g.part = static_cast<float *>(ws);
+            s.part2 = reinterpret_cast<float *>(static_cast<char *>(ws) + half_ws);
+        }
+        if (colsum) g.colpart = reinterpret_cast<float *>(static_cast<char *>(ws) + align_up(static_cast<size_t>(S) * g.M * g.N * sizeof(float), 256));
+        g.out_bf16 = bf && !out_f32;
+        g.gx = static_cast<int>((g.N + 32 * cols.tb - 1) / (32 * cols.tb)); g.gy = static_cast<int>((g.M + 127) / 128); g.S = cols.S;
+        launch_cols(s, bf, cols, dim3(static_cast<unsigned>(cols_grid(cols, g.M, g.N)), 2, 1), stream);
+        if ((S > 1 || colsum) && !(later && reduce_later(later, g, S, s.part2, s.C2, s.ldc2, colsum)))
+            hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>((S > 1 ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), 2), dim3(256), 0,
+                               stream, g, S, static_cast<const float *>(s.part2), s.C2, s.ldc2, colsum);
+        CG_HIP(hipGetLastError());
+        *done = true;
+        return CAPGNN_OK;
+    }
     const int64_t tiles64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     // the three-piece form on the terms of launch_gemm and launch_gemm_dual
     const bool split = !bf && !trans_a && ws && ws_bytes >= split_b_bytes(g.N, s.dual ? split_ld(g.K) + s.K2 : g.K) &&

@@ -671,6 +671,67 @@ def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
         assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(512, 129, 1), (513, 200, 15), (602, 256, 17), (515, 131, 63), (512, 132, 65), (520, 250, 257), (601, 255, 1000), (100, 70, 21_001),
+                                   (129, 65, 17_000), (40, 140, 30_011), (128, 256, 300_000), (97, 41, 70_001), (389, 2, 20_003), (130, 64, 50_000), (33, 129, 66_666)])
+def test_gemm_bf16_vertex_reduction_in_registers_exact(env, M, N, K):
+    """X^T G of bf16 operands with aligned rows at sizes that the small kernel leaves: tiles of 128 rows and of 64 and 128 columns whole and
+    ragged, K around a step of 16, the four waves and the four steps of a turn, one split and many, last rows that end inside four columns; with
+    the workspace that was asked for, with as little as the call accepts, and, there, with the whole epilogue, stored as float and as bf16.  Small
+    integers (sums below 2^24, below 2^8 where they are stored as bf16): equality.  Padding is NaN; the last rows end with the allocation."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    A, G = (torch.randint(-3, 4, (K, w), generator=gen, device="cuda").float() for w in (M, N))
+    ref = A.double().T @ G.double()
+    bias = torch.randint(-9, 9, (N,), generator=gen, device="cuda").float()
+    splits = min(1536 // (-(-M // 128) * -(-N // (64 if N <= 64 else 128))), K // 512)
+    least = splits * M * N * 4 if splits > 1 else 0
+    for pad in (0, 8):
+        flat = lambda x: torch.cat([torch.nn.functional.pad(x[:-1], (0, -x.shape[1] % 8 + pad), value=float("nan")).reshape(-1), x[-1]]).bfloat16()  # noqa: E731
+        Ad, Gd = flat(A), flat(G)
+        lda, ldb = (-(-w // 8) * 8 + pad for w in (M, N))
+        for room, full, f32 in ((B.gemm_workspace_bytes(1, M, N, K), 0, 1), (least, 0, 1), (least, 1, 1)) + (((least, 1, 0),) if K < 20 else ()):
+            say(f"gemm bf16 X^T G in registers {M}x{N}x{K} pad={pad} workspace={room} epilogue={full} f32={f32}")
+            ws = torch.empty(max(room, 1), dtype=torch.uint8, device="cuda")
+            Cd = torch.full((M, N + 3), 2.0, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+            B.gemm(1, 0, M, N, K, Ad, lda, Gd, ldb, Cd, N + 3, B.BF16, out_f32=f32, accumulate=full, bias=bias if full else None, relu=full, ws=ws,
+                   ws_bytes=room)
+            torch.cuda.synchronize()
+            want = (ref + 2.0 + bias).clamp(min=0) if full else ref
+            assert torch.equal(Cd[:, :N].double(), want) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,f_in,f_out", [(40_000, 100, 100), (70_001, 131, 200), (20_003, 520, 136), (66_000, 97, 64)])
+def test_layer_pair_of_weight_gradients_in_registers_exact(env, dtype, n, f_in, f_out):
+    """Both weight gradients of a GraphSAGE layer in one launch of the kernels that hold their results in registers (fp32 above 64 columns), and its
+    bias gradient, one entry of weight one per row.  Small integers (sums below 2^24): equality."""
+    torch, B = env["torch"], env["B"]
+    td, dt = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    rng = np.random.default_rng(n)
+    col = rng.integers(0, n, n).astype(np.int32)
+    g = B.Graph(n, 0, np.arange(0, n + 1, dtype=np.int64), col, np.ones(n, np.float32), np.ones(n, np.float32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    ldi, ldo = -(-f_in // 8) * 8, -(-f_out // 8) * 8
+    x, dh = (torch.nn.functional.pad(torch.randint(-3, 4, (n, w), generator=gen, device="cuda").to(td), (0, ld - w)) for w, ld in ((f_in, ldi), (f_out, ldo)))
+    w, w_self = (torch.zeros(f_in, f_out, device="cuda", dtype=td) for _ in range(2))
+    l = B.make_layer(B.SAGE_MEAN, f_in, f_out, B.ACT_NONE, dt, w, w_self, torch.zeros(f_out, device="cuda"), B.AGG_FIRST)
+    saved = torch.empty(B.layer_saved_bytes(g, l), dtype=torch.uint8, device="cuda")
+    wsb = B.layer_workspace_bytes(g, l)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    h = torch.zeros(n, ldo, device="cuda", dtype=td)
+    dw, dws, db = torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_out, device="cuda")
+    say(f"pair of weight gradients {dtype} {n} {f_in}->{f_out}")
+    B.layer_fwd(g, l, x, ldi, h, ldo, saved, ws, wsb, None)
+    B.layer_bwd(g, l, x, ldi, h, ldo, saved, dh.clone(), ldo, dw, dws, db, None, 0, False, ws, wsb, None)
+    torch.cuda.synchronize()
+    X, D = x[:, :f_in].double(), dh[:, :f_out].double()
+    m = X[torch.from_numpy(col).long().cuda()]
+    assert torch.equal(dw.double(), m.T @ D) and torch.equal(dws.double(), X.T @ D)
+    assert torch.equal(db.double(), D.sum(0))
+
+
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(16384, 128, 128), (16385, 65, 7), (16415, 100, 129), (20000, 130, 200), (16399, 256, 256), (50001, 257, 47),
                                    (16386, 300, 256), (17003, 200, 257), (16384, 72, 511), (16417, 256, 512), (16383, 256, 64), (16390, 256, 520),
