@@ -1961,12 +1961,24 @@ __global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(
                 for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, true>(pb[j], sb, ku, k_end, vb, b[u][j]);
             }
         } else {
+            // (a plain product's wave has a batch or little more: its whole units take the whole loads; element by element 10000 x 64 x 64
+            // fp32 by W^T 13.1 us, so 10.3; 6000 x 128 x 128 bf16 9.3, so 6.7)
 #pragma unroll
             for (int u = 0; u < UB; ++u) {
                 const int64_t ku = kb + u * UK + half * HK;
-                small_load<BF16, A_KC, false>(pa, sa, ku, k_end, va, a[u]);
+                if (A_KC && kb + (u + 1) * UK <= k_end) {
+                    small_load<BF16, A_KC, true>(pa, sa, ku, k_end, va, a[u]);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, false>(pb[j], sb, ku, k_end, vb, b[u][j]);
+                    for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, true>(pb[j], sb, ku, k_end, vb, b[u][j]);
+                } else if (A_KC && kb + u * UK >= k_end) {
+                    a[u] = SmallUnit<BF16>{};
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) b[u][j] = SmallUnit<BF16>{};
+                } else {
+                    small_load<BF16, A_KC, false>(pa, sa, ku, k_end, va, a[u]);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) small_load<BF16, B_KC, false>(pb[j], sb, ku, k_end, vb, b[u][j]);
+                }
             }
         }
     };
@@ -2570,7 +2582,7 @@ static size_t stream_b_bytes(int64_t N, int64_t K) {
 
 constexpr int64_t NARROW_K = 16384;         // see narrow_product
 static size_t narrow_ws_bytes(int64_t M, int64_t N, int64_t K);
-static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches = 1);
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches = 1, int trans_b = 0);
 static void small_geometry(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int *tn, int *S, int64_t *k_chunk);
 
 size_t gemm_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) {
@@ -2616,11 +2628,20 @@ constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piec
 // 200 x 256 21 / 26, 602 x 256 28 / 27, 100 x 100 31 / 33 at 2^30.  bf16, 32 < N <= 64, up to 2^32: 200 x 41 42 / 57, 602 x 64 30 / 32
 // at 2^31, 512 x 64 44 / 51, 602 x 41 69 / 64 at 2^32.  bf16, N <= 32, up to 2^30: 100 x 16 60 / 83, 602 x 16 54 / 51 at 2^30, 320 x 16
 // 117 / 95 at 2^31.
-static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches) {
+// Plain bf16 products: from the k on from which its one round trip pays for its loads of W element by element, while its workgroups (32 rows by
+// 32 or 64 columns) are few (a sweep of 726 sizes; us, 64 x 64 tiles with the launch that repacks W where they need it -> small):
+// 12000 x 32 x 64 5.8 -> 5.6, 3000 x 128 x 32 6.0 -> 6.1; 6000 x 128 x 128 7.3 -> 6.5, 12000 x 128 x 128 7.8 -> 9.7; 3000 x 64 x 256 9.8 -> 6.2, 500 x 256 x 602 17.8 -> 8.6; 25000 x 16 x 256 10.7 -> 9.8, 25000 x 32 x 64 6.2 -> 6.7,
+// 12000 x 128 x 389 14.4 -> 13.4.  By W^T (both operands along k) the tiles need no repacking: 12000 x 16 x 256 8.2 -> 7.0, 6000 x 64 x 256 8.0 -> 8.1, 3000 x 32 x 128 6.3 -> 6.4.  Two products in
+// one launch replace two of either.
+static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches, int trans_b) {
     if (K <= 0) return false;
     const double macs = static_cast<double>(M) * N * K;
     if (trans_a) return macs <= (bf16 ? (N <= 32 ? 0x1p30 : N <= 64 ? 0x1p32 : 0x1.6p30) : (N <= 64 ? 0x1p31 : 0x1.6p28));
-    return !bf16 && macs < SPLIT_MIN_MACS && ((M + 31) / 32) * ((N + 31) / 32) <= launches * (1024 + 8 * std::max<int64_t>(K - 50, 0));
+    if (!bf16) return macs < SPLIT_MIN_MACS && ((M + 31) / 32) * ((N + 31) / 32) <= launches * (1024 + 8 * std::max<int64_t>(K - 50, 0));
+    const int64_t n_wg = ((M + 31) / 32) * (N <= 32 ? 1 : (N + 63) / 64);
+    if (launches > 1) return n_wg <= 400;
+    if (trans_b) return N <= 32 && K >= 96 && n_wg <= 400;
+    return K >= 64 && n_wg <= (N <= 32 && K >= 96 ? 800 : 400);
 }
 
 // Tiles and reduction splits of a small product: N tiles of 64 columns (32 where that is all), and for a reduction over
@@ -2885,7 +2906,6 @@ static void launch_stream(const GemmArgs &g, const uint16_t *Wt, uint32_t n_pad,
 #undef CG_STREAM
 }
 
-// (bf16 operands take the small kernel in reductions over vertices only, see small_product)
 // Epilogue operands held through the loop cost A W of at most 32 columns one of four waves per SIMD, and A W^T of more than 32 one of three:
 // worth it while the workgroups that are left are all there are (A W: 15000 x 32 x 200, 469 workgroups, 9.0 us held, 9.5 not; masked A W^T:
 // 4096 x 256 x 112 10.6 held, 11.5 not), not where one more per compute unit holds the rest of them (30000 x 20 x 8, 938, 8.5 held, 6.4 not;
@@ -2919,6 +2939,8 @@ static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, 
         CG_SMALL_CASE(true, false, false, 1, false)
     }
     CG_SMALL_CASE(true, false, false, 2, false)
+    CG_SMALL_CASE(true, true, false, 1, true) CG_SMALL_CASE(true, true, false, 2, true)
+    CG_SMALL_CASE(true, true, true, 1, true) CG_SMALL_CASE(true, true, true, 2, true)
     CG_SMALL_CASE(true, false, true, 1, false) CG_SMALL_CASE(true, false, true, 2, false)
 #undef CG_SMALL_CASE
 }
@@ -2965,7 +2987,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
     const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
     const bool half_cols = half_path && trans_a && !trans_b;
-    bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
+    bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K, 1, trans_b) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
     if (half_cols && bf16_cols_pays(M, N, K)) small_path = false;
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
@@ -2998,7 +3020,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         S = cols.S * cols.parts;
         bn = 32 * cols.tb;
     }
-    if (mid_path || (half_path && !trans_a && tiles128 <= 1280)) bm = bn = 64;
+    if (mid_path || (half_path && !trans_a && !small_path && tiles128 <= 1280)) bm = bn = 64;
     GemmArgs g;
     g.M = M; g.N = N; g.K = K;
     g.A = static_cast<const char *>(A); g.lda = lda;
@@ -3124,7 +3146,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     GemmArgs &g = s.g;
     const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
     const int64_t Ksum = g.K + (s.dual ? s.K2 : 0);       // (the waves of a workgroup share it)
-    const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual ? 2 : 1);
+    const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual || (bf && pair) ? 2 : 1, trans_b);
     // two narrow reductions over vertices
     const size_t half_ws = ws_bytes / 2 / 256 * 256;
     const bool narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K) &&

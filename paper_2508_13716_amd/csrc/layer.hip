@@ -188,13 +188,14 @@ static int layer_fwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     {
         Scope s(CAPGNN_K_GEMM, li, 0, st);
         void *gws = static_cast<char *>(ws) + fwd_t_bytes(g, l, order);
-        if (sage && dt == CAPGNN_F32)
+        const bool pair = sage && (dt == CAPGNN_F32 || !l->out_f32);        // T and H are stored alike
+        if (pair)
             CG_TRY(launch_gemm_pair(0, 0, g->n_cols, g->n_loc, l->f_out, l->f_in, X, ldx, X, ldx, l->W, l->f_out, l->W_self, l->f_out, ws,
                                     ldt, H, ldh, dt, 0, pre ? g->fwd.in_scale : nullptr, gws, fwd_g_bytes(g, l), st, l->f32_product));
         else
             CG_TRY(launch_gemm(0, 0, g->n_cols, l->f_out, l->f_in, X, ldx, l->W, l->f_out, ws, ldt, dt, 0, 0, nullptr, 0,
                                nullptr, 0, gws, fwd_g_bytes(g, l), st, pre ? g->fwd.in_scale : nullptr, l->f32_product));
-        if (sage && dt != CAPGNN_F32)
+        if (sage && !pair)
             CG_TRY(launch_gemm(0, 0, g->n_loc, l->f_out, l->f_in, X, ldx, l->W_self, l->f_out, H, ldh, dt, l->out_f32, 0,
                                nullptr, 0, nullptr, 0, gws, fwd_g_bytes(g, l), st, nullptr, l->f32_product));
     }

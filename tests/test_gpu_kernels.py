@@ -671,6 +671,35 @@ def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
         assert torch.equal(Cd[:, :N].double(), ref) and (Cd[:, N:] == 2.0).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 3, 64), (33, 32, 65), (97, 17, 111), (64, 33, 112), (31, 64, 127), (100, 130, 128), (65, 200, 144), (40, 64, 160), (129, 31, 191), (70, 47, 200),
+                                   (500, 5, 255), (33, 65, 257), (96, 100, 384), (45, 256, 602)])
+def test_gemm_small_plain_partial_batches_exact(env, dtype, tb, M, N, K):
+    """Plain products of the small kernel whose waves have whole units, parts of a unit and none beside one another (K around units of 8 and 16 and
+    the 128 and 256 of a batch of four waves); rows aligned and not; with the whole epilogue.  Small integers: equality."""
+    torch, B = env["torch"], env["B"]
+    td, dt = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    mk = lambda r, c: torch.randint(-2, 3, (r, c), generator=gen, device="cuda").float()  # noqa: E731
+    A, W, mask, bias = mk(M, K), mk(*((N, K) if tb else (K, N))), mk(M, N), mk(1, N)[0].contiguous()
+    ref = A.double() @ (W.T if tb else W).double()
+    for pad in (0, 1, 8):
+        wide = lambda x: torch.nn.functional.pad(x, (0, (-x.shape[1] % 8 if pad == 8 else 0) + pad), value=float("nan")).to(td).contiguous()  # noqa: E731
+        Ad, Wd, Md = wide(A), wide(W), wide(mask)
+        wsb = B.gemm_workspace_bytes(0, M, N, K)
+        ws = torch.empty(max(wsb, 1), dtype=torch.uint8, device="cuda")
+        for full in (0, 1):
+            say(f"gemm small plain {dtype} tb={tb} {M}x{N}x{K} pad={pad} epilogue={full}")
+            Cd = torch.full((M, N + 3), 2.0, device="cuda")
+            B.gemm(0, tb, M, N, K, Ad, Ad.shape[1], Wd, Wd.shape[1], Cd, N + 3, dt, out_f32=1, accumulate=full, bias=bias if full else None, relu=full,
+                   relu_mask=Md if full and dtype == "f32" else None, ldm=Md.shape[1] if full and dtype == "f32" else 0, ws=ws, ws_bytes=wsb)
+            torch.cuda.synchronize()
+            want = (ref + 2.0 + bias).clamp(min=0) * ((mask > 0) if dtype == "f32" else 1) if full else ref
+            assert torch.equal(Cd[:, :N].double(), want.double()) and (Cd[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(512, 129, 1), (513, 200, 15), (602, 256, 17), (515, 131, 63), (512, 132, 65), (520, 250, 257), (601, 255, 1000), (100, 70, 21_001),
                                    (129, 65, 17_000), (40, 140, 30_011), (128, 256, 300_000), (97, 41, 70_001), (389, 2, 20_003), (130, 64, 50_000), (33, 129, 66_666)])
 def test_gemm_bf16_vertex_reduction_in_registers_exact(env, M, N, K):
