@@ -207,23 +207,29 @@ bool spmm_uses_live(const SpOp &op, int F, int64_t ldx);
 int launch_spmm(const SpOp &op, bool restrict_sub, const void *X, int64_t ldx, void *Y, int64_t ldy, int F,
                 int dtype, const SpmmEpilogue &ep, hipStream_t stream);
 
+// Products that do not wait for one another, collected between begin (the calling thread's batch, emptied) and launch (gemm.hip)
+struct SmallBatch;
+SmallBatch *small_batch_begin();
+int launch_small_batch(SmallBatch *b, hipStream_t stream);
+
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
                 hipStream_t stream, const float *row_scale = nullptr,    // row_scale: C[i,:] *= row_scale[i] at the very end (fp32 C)
                 int f32_product = CAPGNN_F32_PRODUCT_AUTO,
                 float *colsum = nullptr,                                 // [N] column sums of B (trans_a && !trans_b only)
-                FinishList *later = nullptr);                            // takes the sum over splits, whose parts stay in ws, if it can
+                FinishList *later = nullptr,                             // takes the sum over splits, whose parts stay in ws, if it can
+                SmallBatch *batch = nullptr);                            // may take the product: it runs with launch_small_batch
 // C = A op(W) + A2 op(W2) (+ bias, ReLU), one launch where a kernel forms the sum, else the two launches it replaces
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
                      const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product,
-                     const void *relu_mask = nullptr, int64_t ldm = 0);
+                     const void *relu_mask = nullptr, int64_t ldm = 0, SmallBatch *batch = nullptr);
 // C = op(A) op(B) (rows scaled) and C2 = op(A2) op(B2), one launch for small and middling sizes
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product, float *colsum = nullptr, FinishList *later = nullptr);
+                     int f32_product, float *colsum = nullptr, FinishList *later = nullptr, SmallBatch *batch = nullptr);
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K);
 // scratch that lets launch_gemm_dual run as one launch
 size_t gemm_dual_ws_bytes(int64_t N, int64_t K1, int64_t K2);

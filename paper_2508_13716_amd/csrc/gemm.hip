@@ -42,8 +42,7 @@ struct GemmArgs {
 // chosen so that workgroups that read the same operand data share a domain and follow one another there: the
 // tiles of one reduction split (they read the same slab of both operands), or the tiles along N of one row
 // block (they read the same rows of A).  Returns false for the padding workgroups at the end of the grid.
-__device__ __forceinline__ bool tile_coords(const GemmArgs &g, int *bx, int *by, int *bz) {
-    const int64_t b = blockIdx.x;
+__device__ __forceinline__ bool tile_coords(const GemmArgs &g, int64_t b, int *bx, int *by, int *bz) {
     const int xcd = static_cast<int>(b % NUM_XCD);
     const int64_t seq = b / NUM_XCD;
     if (g.S > 1) {
@@ -59,6 +58,7 @@ __device__ __forceinline__ bool tile_coords(const GemmArgs &g, int *bx, int *by,
     *by = static_cast<int>(y);
     return y < g.gy;
 }
+__device__ __forceinline__ bool tile_coords(const GemmArgs &g, int *bx, int *by, int *bz) { return tile_coords(g, blockIdx.x, bx, by, bz); }
 
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     uint32_t u = __float_as_uint(f);
@@ -1909,17 +1909,23 @@ template <bool BF16> constexpr int SMALL_UNIT_K = BF16 ? 16 : 8;
 
 // HOLD: epilogue operands held through the loop; in reductions over vertices, which hold none, registers for two waves per SIMD
 // (see launch_small)
+// (LDS of a workgroup: the four partial tiles, and the partial column sums)
+template <int TN> struct SmallShared {
+    static constexpr int PITCH = TN * 32 + 4;
+    float red[4][32][PITCH];
+    double bred[4][TN * 32];
+};
+
 template <bool BF16, bool A_KC, bool B_KC, int TN, bool HOLD>
-__global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(SmallGemmArgs s) {
+__device__ __forceinline__ void small_tile(const SmallGemmArgs &s, SmallShared<TN> &lds, int64_t block, bool second) {
     constexpr int ES = BF16 ? 2 : 4, UK = SMALL_UNIT_K<BF16>, HK = UK / 2, UB = SMALL_UNITS;
-    constexpr int PITCH = TN * 32 + 4;
-    __shared__ __attribute__((aligned(16))) float red[4][32][PITCH];
+    auto &red = lds.red;
+    auto &bred = lds.bred;
     const GemmArgs &g = s.g;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     int bx, by, bz;
-    if (!tile_coords(g, &bx, &by, &bz)) return;      // uniform over the workgroup
-    const bool second = blockIdx.y != 0;             // pair: the other problem
+    if (!tile_coords(g, block, &bx, &by, &bz)) return;      // uniform over the workgroup; second: the other problem of a pair
     const int64_t M = second ? s.M2 : g.M;
     const int64_t m0 = static_cast<int64_t>(by) * 32, n0 = static_cast<int64_t>(bx) * (TN * 32);
     // the wave's operands and its range of the reduction
@@ -2073,7 +2079,6 @@ __global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * half + (r & 3)][j * 32 + l32] = acc[j][r];
-    __shared__ double bred[4][TN * 32];
     if (sums) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -2148,6 +2153,28 @@ __global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(
                 else o[e] = v[e];
             }
     }
+}
+
+template <bool BF16, bool A_KC, bool B_KC, int TN, bool HOLD>
+__global__ __launch_bounds__(256, !A_KC && HOLD ? 2 : 1) void gemm_small_kernel(SmallGemmArgs s) {
+    __shared__ __attribute__((aligned(16))) SmallShared<TN> lds;
+    small_tile<BF16, A_KC, B_KC, TN, HOLD>(s, lds, blockIdx.x, blockIdx.y != 0);
+}
+
+// The products of a layer's backward pass that do not wait for one another, the weight gradients X^T G (column tiles of TW) and the input gradient
+// G W^T (TX), in one launch: each alone leaves most of the chip idle and costs a launch.  Task i has the workgroups [first[i], first[i + 1]), the
+// two problems of a pair one after the other.
+struct SmallBatchArgs {
+    SmallGemmArgs task[3];
+    int first[4], nx[3], plain[3];
+};
+template <bool BF16, int TW, int TX>
+__global__ __launch_bounds__(256, 2) void gemm_small_batch_kernel(SmallBatchArgs b) {
+    __shared__ __attribute__((aligned(16))) union { SmallShared<TW> w; SmallShared<TX> x; } lds;
+    const int wg = blockIdx.x, i = wg < b.first[1] ? 0 : wg < b.first[2] ? 1 : 2;
+    const int at = wg - b.first[i], second = at >= b.nx[i];
+    if (b.plain[i]) small_tile<BF16, true, true, TX, true>(b.task[i], lds.x, at - second * b.nx[i], second != 0);
+    else small_tile<BF16, false, false, TW, BF16 && TW == 1>(b.task[i], lds.w, at - second * b.nx[i], second != 0);
 }
 
 // Reductions over vertices with a narrow second operand, C = A^T B, A [K x M] and B [K x N <= 64] in float, on the fp32 instruction
@@ -2945,6 +2972,60 @@ static void launch_small(const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, 
 #undef CG_SMALL_CASE
 }
 
+// Products of a layer's backward pass that wait for one launch (see gemm_small_batch_kernel)
+struct SmallBatch {
+    SmallBatchArgs args{};
+    dim3 grid[3];
+    bool bf16 = false;
+    int count = 0, tw = 0, tx = 0;
+};
+
+// Takes a product where it fits: weight gradients of one width and one input gradient, each with what the chip holds of workgroups at most, and
+// short reductions (bf16 ones of at most 32 columns only where the form for two waves per SIMD is due, see launch_small)
+static bool batch_small(SmallBatch *b, const SmallGemmArgs &s, bool bf16, bool akc, bool bkc, int tn, dim3 grid) {
+    if (!b || b->count == 3 || akc != bkc || (b->count && b->bf16 != bf16) || static_cast<int64_t>(grid.x) * grid.y > 2 * NUM_CU) return false;
+    if (akc ? b->tx != 0 : (b->tw != 0 && b->tw != tn) || s.g.K > 32768 ||
+                           (bf16 && tn == 1 && !(s.g.M * s.g.K * grid.y <= (int64_t(1) << 23) && (static_cast<int64_t>(grid.x) * grid.y > NUM_CU || s.g.K >= (1 << 14)))))
+        return false;
+    const int i = b->count++;
+    b->bf16 = bf16;
+    (akc ? b->tx : b->tw) = tn;
+    b->args.task[i] = s;
+    b->args.nx[i] = static_cast<int>(grid.x);
+    b->args.plain[i] = akc;
+    b->grid[i] = grid;
+    return true;
+}
+
+int launch_small_batch(SmallBatch *b, hipStream_t st) {
+    if (b->count == 1) {
+        launch_small(b->args.task[0], b->bf16, b->args.plain[0], b->args.plain[0], b->args.plain[0] ? b->tx : b->tw, b->grid[0], st);
+    } else if (b->count > 1) {
+        int at = 0;
+        for (int i = 0; i < 3; ++i) {
+            b->args.first[i] = at;
+            if (i < b->count) at += static_cast<int>(b->grid[i].x * b->grid[i].y);
+        }
+        b->args.first[3] = at;
+        const int tw = std::max(b->tw, 1), tx = std::max(b->tx, 1);
+#define CG_BATCH(BF_, TW_, TX_) if (b->bf16 == BF_ && tw == TW_ && tx == TX_) \
+        hipLaunchKernelGGL((gemm_small_batch_kernel<BF_, TW_, TX_>), dim3(static_cast<unsigned>(at)), dim3(256), 0, st, b->args);
+        CG_BATCH(false, 1, 1) CG_BATCH(false, 1, 2) CG_BATCH(false, 2, 1) CG_BATCH(false, 2, 2)
+        CG_BATCH(true, 1, 1) CG_BATCH(true, 1, 2) CG_BATCH(true, 2, 1) CG_BATCH(true, 2, 2)
+#undef CG_BATCH
+    }
+    b->count = b->tw = b->tx = 0;
+    CG_HIP(hipGetLastError());
+    return CAPGNN_OK;
+}
+
+// the calling thread's, empty
+SmallBatch *small_batch_begin() {
+    thread_local SmallBatch b;
+    b.count = b.tw = b.tx = 0;
+    return &b;
+}
+
 static void launch_narrow(const SmallGemmArgs &s, dim3 grid, hipStream_t st) {
     if (s.g.N <= 16) hipLaunchKernelGGL(gemm_narrow_kernel<1>, grid, dim3(256), 0, st, s);
     else if (s.g.N <= 32) hipLaunchKernelGGL(gemm_narrow_kernel<2>, grid, dim3(256), 0, st, s);
@@ -2955,7 +3036,7 @@ static void launch_narrow(const SmallGemmArgs &s, dim3 grid, hipStream_t st) {
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
-                hipStream_t stream, const float *row_scale, int f32_product, float *colsum, FinishList *later) {
+                hipStream_t stream, const float *row_scale, int f32_product, float *colsum, FinishList *later, SmallBatch *batch) {
     if (colsum && (!trans_a || trans_b)) CG_FAIL(CAPGNN_EINVAL, "gemm: column sums are formed by X^T G alone");
     if (dtype != CAPGNN_F32 && dtype != CAPGNN_BF16) CG_FAIL(CAPGNN_EINVAL, "gemm: unknown dtype %d", dtype);
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
@@ -3069,6 +3150,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
                              ws_bytes >= stream_b_bytes(N, K) && lda < (1 << 22) && ldc < (1 << 22) && ldm < (1 << 22);
     dim3 grid(static_cast<unsigned>(n_wg), 1, 1);
     bool akc = !trans_a, bkc = trans_b != 0;
+    // nothing follows the product here: its parts, if any, are added up later
+    const bool parts = S > 1 || colsum || narrow, alone = !parts || (later && reduce_later(later, g, S, nullptr, nullptr, 0, colsum));
     if (narrow) {
         SmallGemmArgs sm{};
         sm.g = g;
@@ -3077,7 +3160,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         SmallGemmArgs sm{};
         sm.g = g;
         sm.M2 = M;
-        launch_small(sm, dtype == CAPGNN_BF16, akc, bkc, tn, grid, stream);
+        if (!(alone && batch_small(batch, sm, dtype == CAPGNN_BF16, akc, bkc, tn, grid))) launch_small(sm, dtype == CAPGNN_BF16, akc, bkc, tn, grid, stream);
     } else if (mid_path) {
         SmallGemmArgs sm{};
         sm.g = g;
@@ -3127,7 +3210,7 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 #undef CG_GEMM_CASE
     }
     CG_HIP(hipGetLastError());
-    if ((S > 1 || colsum || narrow) && !(later && reduce_later(later, g, S, nullptr, nullptr, 0, colsum))) {
+    if (!alone) {
         const int64_t blocks = (S > 1 || narrow ? (M * N + 31) / 32 : 0) + (colsum ? (N + 31) / 32 : 0);
         hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, g, S,
                            static_cast<const float *>(nullptr), static_cast<char *>(nullptr), int64_t(0), colsum);
@@ -3140,7 +3223,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
 // C = op(A) op(B) and C2 = op(A2) op(B2) of one shape but for the rows (pair).  *done says whether the sizes are such a kernel's;
 // nothing has run otherwise.
 static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, int dtype, int out_f32, void *ws, size_t ws_bytes,
-                            hipStream_t stream, int f32_product, float *colsum, bool *done, FinishList *later = nullptr) {
+                            hipStream_t stream, int f32_product, float *colsum, bool *done, FinishList *later = nullptr,
+                            SmallBatch *batch = nullptr) {
     *done = false;
     SmallGemmArgs s = in;
     GemmArgs &g = s.g;
@@ -3216,11 +3300,13 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     g.gx = static_cast<int>(gx); g.gy = static_cast<int>(gy); g.S = S;
     const int64_t n_wg = S > 1 ? NUM_XCD * ((S + NUM_XCD - 1) / NUM_XCD) * gx * gy : NUM_XCD * ((gy + NUM_XCD - 1) / NUM_XCD) * gx;
     const dim3 grid(static_cast<unsigned>(n_wg), pair ? 2 : 1, 1);
+    const bool alone = !(S > 1 || colsum || narrow) || (later && reduce_later(later, g, S, pair ? s.part2 : nullptr, s.C2, s.ldc2, colsum));
     if (narrow) launch_narrow(s, grid, stream);
+    else if (small && alone && batch_small(batch, s, bf, !trans_a, trans_b != 0, tn, grid)) {}
     else if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
     else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
     else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
-    if ((S > 1 || colsum || narrow) && !(later && reduce_later(later, g, S, pair ? s.part2 : nullptr, s.C2, s.ldc2, colsum)))
+    if (!alone)
         hipLaunchKernelGGL(gemm_reduce_kernel,
                            dim3(static_cast<unsigned>((S > 1 || narrow ? (g.M * g.N + 31) / 32 : 0) + (colsum ? (g.N + 31) / 32 : 0)), pair ? 2 : 1),
                            dim3(256), 0, stream, g, S, static_cast<const float *>(s.part2), s.C2, s.ldc2, colsum);
@@ -3234,7 +3320,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
 int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N, int64_t K, const void *A, int64_t lda, const void *A2,
                      int64_t lda2, const void *B, int64_t ldb, const void *B2, int64_t ldb2, void *C, int64_t ldc, void *C2,
                      int64_t ldc2, int dtype, int out_f32, const float *row_scale, void *ws, size_t ws_bytes, hipStream_t stream,
-                     int f32_product, float *colsum, FinishList *later) {
+                     int f32_product, float *colsum, FinishList *later, SmallBatch *batch) {
     if (M2 > M) CG_FAIL(CAPGNN_EINVAL, "gemm_pair: the second product has more rows");
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
@@ -3251,14 +3337,14 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
     const bool apart = c1 + ((M - 1) * ldc + N) * es_c <= c2 || c2 + ((M2 - 1) * ldc2 + N) * es_c <= c1;
     if (apart && M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
         lda2 >= (trans_a ? M : K) && ldb >= (trans_b ? K : N) && ldb2 >= (trans_b ? K : N))
-        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done, later));
+        CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done, later, batch));
     if (done) return CAPGNN_OK;
     // (parts that are added up later keep half of the workspace each)
     const size_t half = later ? ws_bytes / 2 / 256 * 256 : 0;
     CG_TRY(launch_gemm(trans_a, trans_b, M, N, K, A, lda, B, ldb, C, ldc, dtype, out_f32, 0, nullptr, 0, nullptr, 0, ws,
-                       later ? half : ws_bytes, stream, row_scale, f32_product, colsum, later));
+                       later ? half : ws_bytes, stream, row_scale, f32_product, colsum, later, batch));
     return launch_gemm(trans_a, trans_b, M2, N, K, A2, lda2, B2, ldb2, C2, ldc2, dtype, out_f32, 0, nullptr, 0, nullptr, 0,
-                       ws ? static_cast<char *>(ws) + half : nullptr, ws_bytes - half, stream, nullptr, f32_product, nullptr, later);
+                       ws ? static_cast<char *>(ws) + half : nullptr, ws_bytes - half, stream, nullptr, f32_product, nullptr, later, batch);
 }
 
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return (trans_a ? 2 : 1) * gemm_ws_bytes(trans_a, M, N, K); }
@@ -3271,7 +3357,7 @@ size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
                      const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product, const void *relu_mask,
-                     int64_t ldm) {
+                     int64_t ldm, SmallBatch *batch) {
     if (f32_product != CAPGNN_F32_PRODUCT_AUTO && f32_product != CAPGNN_F32_PRODUCT_NATIVE && f32_product != CAPGNN_F32_PRODUCT_SPLIT)
         CG_FAIL(CAPGNN_EINVAL, "gemm: unknown form of the fp32 product %d", f32_product);
     const bool sane = M > 0 && N > 0 && K1 > 0 && K2 > 0 && A && A2 && W && W2 && C && lda >= K1 && lda2 >= K2 &&
@@ -3290,7 +3376,7 @@ int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *
         s.g.K = K1; s.K2 = K2; s.dual = 1; s.M2 = M;
         s.A2 = static_cast<const char *>(A2); s.lda2 = lda2; s.B2 = static_cast<const char *>(W2); s.ldb2 = ldw2;
         bool done = false;
-        CG_TRY(launch_two_small(s, 0, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, nullptr, &done));
+        CG_TRY(launch_two_small(s, 0, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, nullptr, &done, nullptr, batch));
         if (done) return CAPGNN_OK;
     }
     const int64_t K1p = split_ld(K1 > 0 ? K1 : 0), K = K1p + K2;

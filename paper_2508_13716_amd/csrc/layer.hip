@@ -298,6 +298,8 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     const size_t w_half = later && sage ? fuse.later_bytes / 2 / 256 * 256 : 0;
     void *ws_w[2] = {later ? fuse.later_ws : ws_gemm, later ? fuse.later_ws + w_half : ws_gemm};
     const size_t wb[2] = {later ? (sage ? w_half : fuse.later_bytes) : gw, later ? w_half : gw};
+    // small products of this layer run as one launch: none reads what another writes
+    SmallBatch *batch = fuse.later ? small_batch_begin() : nullptr;
     if (order == CAPGNN_AGG_FIRST) {
         if (!saved) CG_FAIL(CAPGNN_EINVAL, "layer_bwd: saved is NULL");
         const int64_t ldm = pad_ld(g, l->f_in, dt);
@@ -306,22 +308,24 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
             if (sage && dW && dW_self) {
                 CG_TRY(launch_gemm_pair(1, 0, l->f_in, l->f_in, l->f_out, g->n_loc, saved, ldm, X, ldx, dHb, lddhb, dHb, lddhb, dW, l->f_out,
                                         dW_self, l->f_out, dt, 1, nullptr, ws_w[0], later ? fuse.later_bytes : gw, st, l->f32_product,
-                                        gemm_db, later));
+                                        gemm_db, later, batch));
             } else {
                 if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, saved, ldm, dHb, lddhb, dW, l->f_out, dt, 1, 0,
-                                           nullptr, 0, nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, gemm_db, later));
+                                           nullptr, 0, nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, gemm_db, later, batch));
                 if (sage && dW_self)
                     CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0,
-                                       nullptr, 0, nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, nullptr, later));
+                                       nullptr, 0, nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, nullptr, later, batch));
             }
             // dM = dZ W^T; the self term dZ W_self^T goes to dX, where the transposed aggregation of dM is added to it
             if (dX && sage)
                 CG_TRY(launch_gemm_pair(0, 1, g->n_loc, g->n_loc, l->f_in, l->f_out, dHb, lddhb, dHb, lddhb, l->W, l->f_out, l->W_self,
                                         l->f_out, tmp, ldm, dX, lddx, dt, 0, pre_b ? g->bwd.in_scale : nullptr, ws_gemm, gw, st,
-                                        l->f32_product));
+                                        l->f32_product, nullptr, nullptr, batch));
             else if (dX)
                 CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W, l->f_out, tmp, ldm, dt, 0, 0,
-                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, pre_b ? g->bwd.in_scale : nullptr, l->f32_product));
+                                   nullptr, 0, nullptr, 0, ws_gemm, gw, st, pre_b ? g->bwd.in_scale : nullptr, l->f32_product, nullptr, nullptr,
+                                   batch));
+            if (batch) CG_TRY(launch_small_batch(batch, st));
         }
         if (dX) {
             Scope s(CAPGNN_K_SPMM_BWD, li, 1, st);
@@ -346,23 +350,24 @@ static int layer_bwd_impl(const capgnn_graph *g, const capgnn_layer *l, int orde
     }
     Scope s(CAPGNN_K_GEMM, li, 1, st);
     if (dW) CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_cols, X, ldx, tmp, ldt, dW, l->f_out, dt, 1, 0, nullptr, 0,
-                               nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, nullptr, later));
+                               nullptr, 0, ws_w[0], wb[0], st, nullptr, l->f32_product, nullptr, later, batch));
     if (sage && dW_self)
         CG_TRY(launch_gemm(1, 0, l->f_in, l->f_out, g->n_loc, X, ldx, dHb, lddhb, dW_self, l->f_out, dt, 1, 0, nullptr, 0,
-                           nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, gemm_db, later));
+                           nullptr, 0, ws_w[1], wb[1], st, nullptr, l->f32_product, gemm_db, later, batch));
     if (dX) {
         const int64_t rows = need_halo_grad ? g->n_cols : g->n_loc;
         if (sage && !need_halo_grad) {
             CG_TRY(launch_gemm_dual(1, g->n_loc, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX,
-                                    lddx, dt, 0, nullptr, 0, ws_gemm, gw, st, l->f32_product, fuse.dx_mask, fuse.ld_mask));
+                                    lddx, dt, 0, nullptr, 0, ws_gemm, gw, st, l->f32_product, fuse.dx_mask, fuse.ld_mask, batch));
         } else {
             CG_TRY(launch_gemm(0, 1, rows, l->f_in, l->f_out, tmp, ldt, l->W, l->f_out, dX, lddx, dt, 0, 0, nullptr, 0,
-                               fuse.dx_mask, fuse.ld_mask, ws_gemm, gw, st, nullptr, l->f32_product));
+                               fuse.dx_mask, fuse.ld_mask, ws_gemm, gw, st, nullptr, l->f32_product, nullptr, nullptr, sage ? nullptr : batch));
             if (sage)
                 CG_TRY(launch_gemm(0, 1, g->n_loc, l->f_in, l->f_out, dHb, lddhb, l->W_self, l->f_out, dX, lddx, dt, 0, 1,
                                    nullptr, 0, nullptr, 0, ws_gemm, gw, st, nullptr, l->f32_product));
         }
     }
+    if (batch) CG_TRY(launch_small_batch(batch, st));
     return CAPGNN_OK;
 }
 

@@ -593,6 +593,47 @@ def test_timed_epoch_keeps_every_stage_its_own_work(env, kind, dtype, lr):
     assert all(torch.equal(p, q) for p, q in zip(*outs))
 
 
+@pytest.mark.parametrize("kind,dtype", [("gcn", "f32"), ("sage", "f32"), ("gcn", "bf16"), ("sage", "bf16")])
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("n,dims", [(37, (33, 64, 5)), (1003, (100, 32, 70)), (9001, (64, 128, 30, 7)), (33_001, (40, 31, 9))])
+def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dims):
+    """The small weight and input gradients of a layer run as one launch; an epoch that records its stages' times runs them one by one: the same
+    parts, added up in another order (the gradients differ by fp32 rounding of sums of at most 512 parts, random: far below 2e-6).  The last
+    size has reductions too long for the batch."""
+    torch, B = env["torch"], env["B"]
+    sage, bf = kind == "sage", dtype == "bf16"
+    td, dt = (torch.bfloat16, B.BF16) if bf else (torch.float32, B.F32)
+    rng = np.random.default_rng(n)
+    deg = rng.integers(1, 5, n)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    g = B.Graph(n, 0, rowptr, col, (1.0 / deg).astype(np.float32), np.ones(n, np.float32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    mk = lambda a, b: (torch.randn(a, b, generator=gen, device="cuda") / a ** 0.5).to(td)  # noqa: E731
+    ld = -(-dims[0] // 8) * 8
+    x = torch.zeros(n, ld, device="cuda", dtype=td)
+    x[:, :dims[0]] = torch.randn(n, dims[0], generator=gen, device="cuda").to(td)
+    L = len(dims) - 1
+    w, ws_ = ([mk(a, b) for a, b in zip(dims, dims[1:])] for _ in range(2))
+    b = [0.1 * torch.randn(d, generator=gen, device="cuda") for d in dims[1:]]
+    labels = torch.randint(0, dims[-1], (n,), generator=gen, device="cuda", dtype=torch.int32)
+    layers = [B.make_layer(B.SAGE_MEAN if sage else B.GCN, dims[i], dims[i + 1], B.ACT_NONE if i == L - 1 else B.ACT_RELU, dt, w[i], ws_[i] if sage else None,
+                           b[i], order, out_f32=int(bf and i == L - 1)) for i in range(L)]
+    wsb = B.epoch_workspace_bytes(g, None, layers)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    out = []
+    for timed in (False, True):
+        grads = [[torch.full((p, q), 7.0, device="cuda") for p, q in zip(dims, dims[1:])] for _ in range(2)] + [[torch.full((d,), 7.0, device="cuda") for d in dims[1:]]]
+        logits = torch.zeros(n, dims[-1], device="cuda")
+        print(f"small products in one launch {kind} {dtype} order={order} n={n} {dims} timed={timed}", flush=True)
+        B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, wsb, None, None, want_times=timed)
+        torch.cuda.synchronize()
+        out.append([t.double() for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits.double()])
+    for p, q in zip(*out):
+        assert float((p - q).norm()) <= 2e-6 * float(q.norm())
+
+
 @pytest.mark.parametrize("recorded", [False, True])
 @pytest.mark.parametrize("L,shared", [(2, "none"), (3, "dw"), (3, "bias"), (16, "none"), (16, "dw")])
 def test_epoch_end_adds_up_every_gradient(env, L, shared, recorded):
