@@ -2329,6 +2329,183 @@ __global__ __launch_bounds__(256, NT <= 2 ? 3 : 2) void gemm_narrow_kernel(Small
     }
 }
 
+// Plain fp32 products in three pieces whose 64 x 64 tiles are few for the chip or whose reduction is long for its tiles: a workgroup owns one tile and its
+// four waves take quarters of the reduction, each for itself: operands go from memory straight into the registers of the matrix instruction,
+// two steps of 16 k ahead, and are cut there; no barrier until the four partial tiles are added through LDS, in wave order.  Of 32 k a
+// lane takes 16 neighbouring ones of its row, so that the loads that share a line of A follow one another.  Also the sum of two products (DUAL: the
+// steps of the second follow those of the first) and two products of one shape (blockIdx.y, see SmallGemmArgs).  Rows need no alignment.
+template <bool B_KC, bool DUAL>
+__global__ __launch_bounds__(256, 2) void gemm_split_quarters_kernel(SmallGemmArgs p2) {
+    constexpr int TM = 2, TN = 2, PITCH = 68;
+    __shared__ __attribute__((aligned(16))) float red[4][64][PITCH];
+    const GemmArgs &g = p2.g;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, half = lane >> 5;
+    int bx, by, bz;
+    if (!tile_coords(g, &bx, &by, &bz)) return;      // uniform over the workgroup
+    const bool other = !DUAL && blockIdx.y != 0;     // the second of a pair
+    const int64_t M = other ? p2.M2 : g.M;
+    const int64_t m0 = static_cast<int64_t>(by) * 64, n0 = static_cast<int64_t>(bx) * 64;
+    if (m0 >= M) return;
+    struct Side { const char *a, *b; int64_t lda, ldb; bool va, vb; int K; };
+    auto side = [&](bool second) __attribute__((always_inline)) {
+        const char *A = second ? p2.A2 : g.A, *B = second ? p2.B2 : g.B;
+        const int64_t lda = second ? p2.lda2 : g.lda, ldb = second ? p2.ldb2 : g.ldb;
+        return Side{A + m0 * lda * 4, B + (B_KC ? n0 * ldb : n0) * 4, lda, ldb, ((reinterpret_cast<uintptr_t>(A) | static_cast<uintptr_t>(lda * 4)) & 15) == 0,
+                    ((reinterpret_cast<uintptr_t>(B) | static_cast<uintptr_t>(ldb * 4)) & 15) == 0, static_cast<int>(DUAL && second ? p2.K2 : g.K)};
+    };
+    const Side s0 = side(other), s1 = side(true);
+    // rows and columns beyond the matrices repeat the last one: what they give is never stored
+    uint32_t row[TM], col[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) row[i] = static_cast<uint32_t>(M - m0 - 1 < i * 32 + l32 ? M - m0 - 1 : i * 32 + l32);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) col[j] = static_cast<uint32_t>(g.N - n0 - 1 < j * 32 + l32 ? g.N - n0 - 1 : j * 32 + l32);
+    const int steps0 = (s0.K + 15) / 16, steps = steps0 + (DUAL ? (s1.K + 15) / 16 : 0), per = (steps + 7) / 8 * 2;
+    const int t_end = steps < (wave + 1) * per ? steps : (wave + 1) * per;
+    struct Raw { float a[TM][8], b[TN][8]; };
+    // step t: 16 k of 32 that both halves of the wave share in pairs of steps, or the last ones
+    auto ask = [&](int t, Raw &r) __attribute__((always_inline)) {
+        const bool second = DUAL && t >= steps0;
+        const Side &s = DUAL && second ? s1 : s0;
+        if (second) t -= steps0;
+        const uint32_t lda = static_cast<uint32_t>(s.lda), ldb = static_cast<uint32_t>(s.ldb);
+        if (t < s.K / 32 * 2) {
+            const int k0 = t / 2 * 32 + (t & 1) * 8;
+            const char *a = s.a + k0 * 4, *b = s.b + (B_KC ? static_cast<int64_t>(k0) * 4 : k0 * s.ldb * 4);
+            auto along = [&](const char *q, bool vec, float (&x)[8]) __attribute__((always_inline)) {
+                if (vec) {
+                    const float4 u = reinterpret_cast<const float4 *>(q)[0], v = reinterpret_cast<const float4 *>(q)[1];
+                    x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w; x[4] = v.x; x[5] = v.y; x[6] = v.z; x[7] = v.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = reinterpret_cast<const float *>(q)[e];
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < TM; ++i) along(a + (row[i] * lda + 16u * half) * 4u, s.va, r.a[i]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (B_KC) {
+                    along(b + (col[j] * ldb + 16u * half) * 4u, s.vb, r.b[j]);
+                } else {
+                    const char *q = b + (16u * half * ldb + col[j]) * 4u;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) r.b[j][e] = *reinterpret_cast<const float *>(q + static_cast<int64_t>(e) * s.ldb * 4);
+                }
+            }
+        } else {
+            const int k0 = s.K / 32 * 32 + (t - s.K / 32 * 2) * 16 + half * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool in = k0 + e < s.K;
+#pragma unroll
+                for (int i = 0; i < TM; ++i) r.a[i][e] = in ? *reinterpret_cast<const float *>(s.a + (row[i] * s.lda + k0 + e) * 4) : 0.f;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    r.b[j][e] = in ? *reinterpret_cast<const float *>(s.b + (B_KC ? col[j] * s.ldb + k0 + e : (k0 + e) * s.ldb + col[j]) * 4) : 0.f;
+            }
+        }
+    };
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    auto multiply = [&](int t, Raw &r) __attribute__((always_inline)) {
+        u32x4 a[TM][3], b[TN][3];
+        auto cut = [&](const float (&x)[8], u32x4 (&p)[3]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t u[3];
+                split3_pair(x[2 * e], x[2 * e + 1], u);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) p[q][e] = u[q];
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < TM; ++i) cut(r.a[i], a[i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) cut(r.b[j], b[j]);
+        if (t + 2 < t_end) ask(t + 2, r);
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};       // the six piece products, smallest first
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][PA[q]]), __builtin_bit_cast(bf16x8, b[j][PB[q]]),
+                                                                        acc[i][j], 0, 0, 0);
+    };
+    {
+        Raw x, y;
+        int t = wave * per;
+        if (t < t_end) ask(t, x);
+        if (t + 1 < t_end) ask(t + 1, y);
+        for (; t < t_end; t += 2) {
+            multiply(t, x);
+            if (t + 1 < t_end) multiply(t + 1, y);
+        }
+    }
+    // four columns of rows 16 wave + lane / 16 + 4 p: the epilogue's operands, ahead of the exchange
+    char *C = other ? p2.C2 : g.C;
+    const int64_t ldc = other ? p2.ldc2 : g.ldc;
+    const float *rscale = other ? p2.rscale2 : g.rscale;
+    const int c4 = 4 * (lane % 16);
+    auto crow = [&](int p) { const int64_t r = m0 + 16 * wave + lane / 16 + 4 * p; return r < M ? r : M - 1; };
+    auto ccol = [&](int e) { return n0 + c4 + e < g.N ? n0 + c4 + e : g.N - 1; };
+    float e_b[4], e_c[4][4], e_m[4][4], e_s[4];
+    if (g.bias)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) e_b[e] = g.bias[ccol(e)];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if (g.accumulate)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) e_c[p][e] = reinterpret_cast<const float *>(C)[crow(p) * ldc + ccol(e)];
+        if (g.mask)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) e_m[p][e] = reinterpret_cast<const float *>(g.mask)[crow(p) * g.ldm + ccol(e)];
+        if (rscale) e_s[p] = rscale[crow(p)];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[wave][i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)][j * 32 + l32] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int lr = 16 * wave + lane / 16 + 4 * p;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float4 x = *reinterpret_cast<const float4 *>(&red[w][lr][c4]);
+            v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (g.accumulate) v[e] += e_c[p][e];
+            if (g.bias) v[e] += e_b[e];
+            if (g.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
+            if (g.mask) v[e] = e_m[p][e] > 0.f ? v[e] : 0.f;
+            if (rscale) v[e] *= e_s[p];
+        }
+        if (m0 + lr >= M) continue;
+        float *out = reinterpret_cast<float *>(C) + (m0 + lr) * ldc + n0 + c4;
+        if (n0 + c4 + 4 <= g.N && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0) {
+            *reinterpret_cast<float4 *>(out) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n0 + c4 + e < g.N) out[e] = v[e];
+        }
+    }
+}
+
 // Plain fp32 products of middling size (the 128-row tiles of gemm_split_kernel would not fill the chip): 64 x 64 tiles with
 // four waves, a 32 x 32 part each.  Both operands are cut here, the second one as well, which saves the launch that cuts a
 // weight matrix beforehand (4-5 us, a third of such a product).  Two LDS buffers and operands fetched two steps ahead: one
@@ -2791,6 +2968,17 @@ static bool bf16_cols_pays(int64_t M, int64_t N, int64_t K) {
     return x >= (int64_t(1) << (20 + (N <= 128) + (K < 16384)));
 }
 
+// Which three-piece products of middling size gemm_split_quarters_kernel takes: those whose 64 x 64 tiles are two per compute unit at most, or three
+// with a long reduction; by W^T, whose rows it reads in 16-byte pieces, fewer.  us, gemm_split_mid_kernel -> here, M x N x K (280 sizes): 4096 x 256 x 602 27.4 ->
+// 17.0, 8820 x 64 x 602 28.3 -> 15.5, 15000 x 128 x 256 17.1 -> 15.0, 21557 x 64 x 256 17.7 -> 14.1, 30000 x 64 x 389 25.9 -> 22.4, 8820 x 256 x 389 28.7 -> 26.6, 21557 x 128 x 256 21.0 ->
+// 19.8, x 128 x 128 14.0 -> 13.9; not 15000 x 256 x 256 18.9 -> 24.1.  By W^T: 4096 x 256 x 256 17.0 -> 13.8, 21557 x 64 x 200 20.0 -> 17.7; not 8820 x 128 x
+// 256 19.6 -> 21.3, 21557 x 128 x 128 17.8 -> 20.8.
+static bool quarters_pay(int64_t M, int64_t N, int64_t K, int trans_b) {
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+    if (trans_b) return tiles <= 256 || (tiles <= 480 && K <= 224);
+    return tiles <= 512 || (tiles <= 768 && K >= 256);
+}
+
 static void launch_cols(const SmallGemmArgs &s, bool bf16, const ColsPlan &p, dim3 grid, hipStream_t st) {
 #define CG_COLS(TB_, SUMS_) if (p.tb == TB_ && !!s.g.colpart == SUMS_) { \
         if (bf16) hipLaunchKernelGGL((gemm_bf16_cols_kernel<TB_, SUMS_>), grid, dim3(256), 0, st, s, p.parts); \
@@ -3033,6 +3221,13 @@ static void launch_narrow(const SmallGemmArgs &s, dim3 grid, hipStream_t st) {
     else hipLaunchKernelGGL(gemm_narrow_kernel<4>, grid, dim3(256), 0, st, s);
 }
 
+static void launch_quarters(const SmallGemmArgs &s, bool bkc, dim3 grid, hipStream_t st) {
+    if (bkc && s.dual) hipLaunchKernelGGL((gemm_split_quarters_kernel<true, true>), grid, dim3(256), 0, st, s);
+    else if (bkc) hipLaunchKernelGGL((gemm_split_quarters_kernel<true, false>), grid, dim3(256), 0, st, s);
+    else if (s.dual) hipLaunchKernelGGL((gemm_split_quarters_kernel<false, true>), grid, dim3(256), 0, st, s);
+    else hipLaunchKernelGGL((gemm_split_quarters_kernel<false, false>), grid, dim3(256), 0, st, s);
+}
+
 int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 const void *B, int64_t ldb, void *C, int64_t ldc, int dtype, int out_f32, int accumulate,
                 const float *bias, int relu, const void *relu_mask, int64_t ldm, void *ws, size_t ws_bytes,
@@ -3066,7 +3261,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const bool split_path = dtype == CAPGNN_F32 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
                             (trans_a ? cols_reach(K, lda, ldb) : ws && ws_bytes >= split_b_bytes(N, K));
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
-    const bool mid = split_path && !trans_a && K > 0 && tiles64 <= 768 && lda < (1 << 22) && ldb < (1 << 22);
+    const bool mid_reach = split_path && !trans_a && K > 0 && K < (1 << 30) && lda < (1 << 22) && ldb < (1 << 22);
+    const bool mid = mid_reach && tiles64 <= 768, quarters = mid && quarters_pay(M, N, K, trans_b);
     const bool half_cols = half_path && trans_a && !trans_b;
     bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K, 1, trans_b) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
     if (half_cols && bf16_cols_pays(M, N, K)) small_path = false;
@@ -3165,7 +3361,8 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
         SmallGemmArgs sm{};
         sm.g = g;
         sm.M2 = M;
-        if (bkc) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, sm);
+        if (quarters) launch_quarters(sm, bkc, grid, stream);
+        else if (bkc) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, sm);
         else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, sm);
     } else if (split_path) {
         if (trans_a) {
@@ -3304,6 +3501,7 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     if (narrow) launch_narrow(s, grid, stream);
     else if (small && alone && batch_small(batch, s, bf, !trans_a, trans_b != 0, tn, grid)) {}
     else if (small) launch_small(s, bf, !trans_a, trans_b != 0, tn, grid, stream);
+    else if (quarters_pay(pair ? g.M + s.M2 : g.M, g.N, Ksum, trans_b)) launch_quarters(s, trans_b != 0, grid, stream);
     else if (trans_b) hipLaunchKernelGGL(gemm_split_mid_kernel<true>, grid, dim3(256), 0, stream, s);
     else hipLaunchKernelGGL(gemm_split_mid_kernel<false>, grid, dim3(256), 0, stream, s);
     if (!alone)

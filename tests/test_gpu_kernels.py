@@ -1066,6 +1066,35 @@ def test_gemm_f32_split_product(env, ta, tb):
         B.gemm(0, 0, 1, 1, 1, one, 1, one, 1, one, 1, B.F32, f32_product=7)
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (63, 65, 15), (64, 64, 16), (65, 63, 31), (130, 128, 32), (257, 41, 33), (64, 200, 47), (300, 130, 127), (1000, 100, 128), (129, 64, 129),
+                                   (4097, 200, 200), (2000, 256, 602), (21_557, 128, 257)])
+def test_gemm_f32_split_quarters_exact(env, tb, M, N, K):
+    """Three-piece products of few 64 x 64 tiles, whose four waves take quarters of the reduction: tiles whole and ragged, K around a step of 16, a pair
+    of them and the eight of four waves; rows aligned and not; with the whole epilogue.  Integers of nine bits by -1, 0 and 1 (sums below
+    2^24): equality.  Padding is NaN; the last rows end with the allocation."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    A = torch.randint(-400, 401, (M, K), generator=gen, device="cuda").float()
+    W = torch.randint(-1, 2, (N, K) if tb else (K, N), generator=gen, device="cuda").float()
+    mask, bias = torch.randint(-1, 2, (M, N), generator=gen, device="cuda").float(), torch.randint(-9, 9, (N,), generator=gen, device="cuda").float()
+    ref = A.double() @ (W.T if tb else W).double()
+    wsb = B.gemm_workspace_bytes(0, M, N, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for pad in (0, 1, 4):
+        flat = lambda x: torch.cat([torch.nn.functional.pad(x[:-1], (0, pad), value=float("nan")).reshape(-1), x[-1]])  # noqa: E731
+        Ad, Wd, Md = flat(A), flat(W), flat(mask)
+        for full in (0, 1):
+            say(f"gemm split quarters tb={tb} {M}x{N}x{K} pad={pad} epilogue={full}")
+            Cd = torch.full((M, N + pad), 2.0, device="cuda")
+            B.gemm(0, tb, M, N, K, Ad, K + pad, Wd, W.shape[1] + pad, Cd, N + pad, B.F32, accumulate=full, bias=bias if full else None, relu=full,
+                   relu_mask=Md if full else None, ldm=N + pad if full else 0, ws=ws, ws_bytes=wsb, f32_product=B.F32_PRODUCT_SPLIT)
+            torch.cuda.synchronize()
+            want = (ref + 2.0 + bias).clamp(min=0) * (mask > 0) if full else ref
+            assert torch.equal(Cd[:, :N].double(), want.double()) and (Cd[:, N:] == 2.0).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (127, 65, 15), (128, 64, 16), (129, 128, 17), (33, 129, 47), (130, 192, 64), (128, 128, 65), (257, 200, 600), (96, 256, 2049),
                                    (602, 100, 5000), (64, 41, 20_001), (300, 130, 38_401), (100, 256, 70_001), (128, 128, 300_000), (700, 600, 1600)])
 def test_gemm_f32_split_vertex_reduction_exact(env, M, N, K):
