@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdarg.h>
+#include <atomic>
 #include <vector>
 
 #include "../../include/capgnn.h"
@@ -116,6 +117,10 @@ struct capgnn_graph {
     uint32_t flags = 0;
     capgnn::SpOp fwd, bwd;
     std::vector<void *> dev_allocs;
+    // pinned words in which an epoch's last kernel leaves the loss for the host, one cache line per epoch under way (bit i of `taken`: line i)
+    static constexpr int LOSS_LINES = 16, LOSS_STRIDE = 32;
+    float *loss_host = nullptr, *loss_dev = nullptr;
+    mutable std::atomic<unsigned> taken{0};
 };
 
 struct capgnn_cache {

@@ -348,6 +348,15 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
                           n_loc, &bh) && (rc = upload_blocked(g, bh, &b)))
             return fail(rc);
     }
+    // (without pinned memory the loss is copied)
+    if (hipHostMalloc(reinterpret_cast<void **>(&g->loss_host), capgnn_graph::LOSS_LINES * capgnn_graph::LOSS_STRIDE * sizeof(float)) != hipSuccess) {
+        g->loss_host = nullptr;
+        (void)hipGetLastError();
+    } else if (hipHostGetDevicePointer(reinterpret_cast<void **>(&g->loss_dev), g->loss_host, 0) != hipSuccess) {
+        (void)hipHostFree(g->loss_host);
+        g->loss_host = nullptr;
+        (void)hipGetLastError();
+    }
     if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess) {
         set_error("graph_create: stream synchronisation failed");
         return fail(CAPGNN_EHIP);
@@ -359,6 +368,7 @@ extern "C" int capgnn_graph_create(capgnn_graph **out, int64_t n_loc, int64_t n_
 extern "C" int capgnn_graph_destroy(capgnn_graph *g) {
     if (!g) return CAPGNN_OK;
     for (void *p : g->dev_allocs) (void)hipFree(p);
+    if (g->loss_host) (void)hipHostFree(g->loss_host);
     delete g;
     return CAPGNN_OK;
 }
