@@ -410,18 +410,19 @@ __global__ __launch_bounds__(64, NV < 3 ? (BF16 && LPR < 64 ? 5 : 6) : 1) void s
 // of cut rows and the kernel that adds them would be, and the long rows where the caller brought no scratch for pieces.
 template <int NV> constexpr int ROW_WAVES = NV == 1 ? 16 : 4;
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
-__global__ __launch_bounds__(64 * ROW_WAVES<NV>) void spmm_rows_kernel(SpmmArgs a, const RowItem *cut, int n_cut, int64_t n_waves) {
+__global__ __launch_bounds__(64 * ROW_WAVES<NV>) void spmm_rows_kernel(SpmmArgs a, const RowItem *cut, int n_cut, const RowItem *whole,
+                                                                          int n_rows, int64_t n_waves) {
     constexpr int U = (NV == 1) ? 8 : 4;
     constexpr int PASS = LPR * E * NV;
     constexpr int NW = ROW_WAVES<NV>;
     __shared__ float red[NW - 1][NV * E][LPR];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (static_cast<int>(blockIdx.x) >= n_cut) {
-        const int64_t w = static_cast<int64_t>(blockIdx.x - n_cut) * NW + wave;
+    if (static_cast<int>(blockIdx.x) >= n_rows) {
+        const int64_t w = static_cast<int64_t>(blockIdx.x - n_rows) * NW + wave;
         if (w < n_waves) wave_items<BF16, OBF16, W, E, LPR, NV>(a, w, lane);
         return;
     }
-    const RowItem it = cut[blockIdx.x];
+    const RowItem it = static_cast<int>(blockIdx.x) < n_cut ? cut[blockIdx.x] : whole[blockIdx.x - n_cut];
     const uint32_t end = it.beg + it.cnt, per = (it.cnt + NW - 1) / NW;
     const uint32_t e0 = wave * per < it.cnt ? it.beg + wave * per : end, e1 = end - e0 < per ? end : e0 + per;
     for (int pass = 0; pass < a.F_lim; pass += PASS) {
@@ -921,6 +922,24 @@ static bool rows_in_one_launch(int64_t nnz, int64_t longest, int64_t row_bytes, 
     return nnz <= ROWS_NNZ && row_us <= 5.0 + static_cast<double>(nnz) * row_bytes / 8.5e6;
 }
 
+// Rows below the cut that a launch of spmm_rows_kernel gives a workgroup each as well: a wave takes about a microsecond for a
+// trip (its gathers under way at once), so those of at least two trips and of a quarter of what the launch's bytes need at 8.5 TB/s,
+// while they and the cut rows are no more than the compute units.  40 k entries x 128 floats: launch 12.4 -> 10.0 us, the epoch
+// of two layers 63.6 -> 59.3; 420 k entries x 50 and 128 floats: epoch 202 -> 195; 14 k entries x 128 floats 22.3 -> 20.8.  Without the
+// second bound 200 k entries x 128 floats lost 2 us; with a lane group's 128 entries per trip (32 bf16 features) and rows of
+// 32 entries in workgroups of their own, 100 k entries lost 5 us a launch.  Graphs without cut rows keep single-wave workgroups
+// (490 k entries of 98 k short rows: an epoch 304 -> 332 us in workgroups of sixteen).
+static int64_t middling_rows(const ItemList &list, int64_t nnz, int64_t row_bytes, int trip) {
+    const double trips = std::max(2.0, 0.25 * static_cast<double>(nnz) * row_bytes / 8.5e6);
+    int64_t rows = 0;
+    for (int t = 1024; t >= 32 && t >= trips * trip; t /= 2) {
+        const int64_t m = list.first_below(t) - list.n_pieces;
+        if (list.n_cut + m > NUM_CU) break;
+        rows = m;
+    }
+    return rows;
+}
+
 // pieces: the caller brought scratch for the pieces of the cut rows
 template <bool BF16, bool OBF16, bool W, int E, int LPR, int NV>
 static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz, hipStream_t st) {
@@ -931,12 +950,18 @@ static int launch_cfg(SpmmArgs a, const ItemList &list, bool pieces, int64_t nnz
     const bool long_rows = nnz >= CROWDED_ROW * list.n_items && row_bytes >= CROWDED_BYTES;
     const bool one_launch = list.n_cut > 0 && (pieces ? rows_in_one_launch(nnz, list.longest, row_bytes, NW) : nnz <= ROWS_NNZ);
     pieces = pieces && !one_launch;
-    if (!pieces) { a.items += list.n_pieces; a.n_items -= list.n_pieces; a.n_wave -= list.n_pieces; a.n_pieces = 0; }
+    const int64_t middling = one_launch ? middling_rows(list, nnz, row_bytes, G * (NV == 1 ? 8 : 4)) : 0;
+    const RowItem *const whole = list.items + list.n_pieces;
+    const int64_t rows = pieces ? 0 : list.n_cut + middling;        // given a workgroup each
+    if (!pieces) {
+        const int64_t skip = list.n_pieces + middling;
+        a.items += skip; a.n_items -= skip; a.n_wave = std::max<int64_t>(a.n_wave - skip, 0); a.n_pieces = 0;
+    }
     const int64_t waves = a.n_wave + (a.n_items - a.n_wave + G - 1) / G;
-    if (!pieces && list.n_cut > 0)
+    if (rows > 0)
         hipLaunchKernelGGL((spmm_rows_kernel<BF16, OBF16, W, E, LPR, NV>),
-                           dim3(static_cast<unsigned>(list.n_cut + (one_launch ? (waves + NW - 1) / NW : 0))), dim3(64 * NW), 0, st, a,
-                           list.cut, static_cast<int>(list.n_cut), waves);
+                           dim3(static_cast<unsigned>(rows + (one_launch ? (waves + NW - 1) / NW : 0))), dim3(64 * NW), 0, st, a,
+                           list.cut, static_cast<int>(list.n_cut), whole, static_cast<int>(rows), waves);
     if (!one_launch && waves > 0) {
         bool done = false;
         if constexpr (!BF16 && E > 1 && LPR > 4) {

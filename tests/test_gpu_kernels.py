@@ -221,6 +221,37 @@ def test_spmm_row_length_classes_exact(env, fill, scratch):
             g.close()
 
 
+@pytest.mark.parametrize("n40,n70", [(179, 60), (180, 60), (10, 240), (10, 241)])
+def test_spmm_middling_rows_of_a_small_graph_exact(env, n40, n70):
+    """Rows below the cut that a small graph's one launch gives workgroups of their own, up to 256 with the cut rows (16 here): both
+    classes at the limit, the lower one a row beyond it, only the upper one, neither.  Small integers: equality."""
+    torch, B, H, O, orc = env["torch"], env["B"], env["H"], env["O"], env["orc"]
+    rng = np.random.default_rng(n40 + n70)
+    lens = rng.permutation([130] * 15 + [700] + [70] * n70 + [40] * n40 + [33, 31, 5, 0] + [9] * 300)
+    n_loc, n_halo = len(lens), 100
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = rng.integers(0, n_loc + n_halo, rowptr[-1]).astype(np.int32)
+    val = rng.integers(-1, 2, rowptr[-1]).astype(np.float32)
+    for F, ld, vals in [(5, 8, False), (41, 41, True), (64, 64, False), (128, 128, True), (250, 256, False), (700, 700, True)]:
+        X = rng.integers(-2, 3, (n_loc + n_halo, F)).astype(np.float32)
+        og = orc.Graph(n_loc, n_loc + n_halo, rowptr, col, np.ones(n_loc), np.ones(n_loc + n_halo), val.astype(np.float64) if vals else None)
+        ref = orc.spmm_fwd(og, X.astype(np.float64))
+        for dt in (B.F32, B.BF16):
+            say(f"spmm middling rows n40={n40} n70={n70} F={F} dtype={dt}")
+            g = B.Graph(n_loc, n_halo, rowptr, col, None, None, val if vals else None)
+            Xd = H.padded_matrix(X if dt == B.F32 else synth.f32_to_bf16_rne(X).reshape(X.shape), ld)
+            wsb = B.spmm_workspace_bytes(g, F, dt)
+            for ws in (torch.empty(wsb, dtype=torch.uint8, device="cuda"), None):
+                Yd = torch.full((n_loc, ld), 7.0, dtype=Xd.dtype, device="cuda")
+                B.spmm_fwd(g, Xd, ld, Yd, ld, F, dt, ws=ws, ws_bytes=wsb if ws is not None else 0)
+                torch.cuda.synchronize()
+                Y = O.widen(H.dev_to_np(Yd))
+                want = ref if dt == B.F32 else synth.bf16_to_f32(synth.f32_to_bf16_rne(ref.astype(np.float32))).reshape(ref.shape)
+                assert np.array_equal(Y[:, :F], want), (F, dt)
+                assert (Y[:, F:] == 7.0).all()
+            g.close()
+
+
 @pytest.mark.parametrize("scratch", [True, False])
 @pytest.mark.parametrize("hub,others", [(500_000, 350_000), (60_000, 90_000), (2_100, 6_000)])
 def test_spmm_hub_of_a_small_graph_exact(env, hub, others, scratch):
