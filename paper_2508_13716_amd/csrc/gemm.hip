@@ -7,7 +7,8 @@
 // current one (register prefetch + two LDS buffers, one barrier per k-step).  bf16 operands are
 // widened to fp32 while they are staged.  The vertex-dimension reduction of the weight gradient
 // (trans_a) is split over workgroups; partial tiles go to the workspace and are summed in a fixed
-// order by a second kernel, which also applies the epilogue.
+// order by a second kernel, which also applies the epilogue.  Small products, narrow or long reductions over vertices and
+// products of many rows have kernels of their own below, most of which read their operands straight into registers.
 #include "common.h"
 
 #include <algorithm>
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 // the reduction index contiguous (S[row][k], 32 k per step = four 16-byte chunks, rows padded to 80 bytes; the
 // chunk position is XOR-ed with bits of the row so that neither the operand reads nor the transposing stores pile
 // up on a few banks).  An operand stored with the reduction index contiguous is moved with 16-byte loads and
-// stores.  One stored the other way (the vertex dimension of the weight gradient X^T G) is loaded 16 bytes along
+// stores.  One stored the other way is loaded 16 bytes along
 // its rows, four consecutive k per thread, transposed in registers (byte permutes pair up the values of two k)
 // and stored as 8-byte pieces: no 2-byte LDS traffic.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -916,9 +917,8 @@ __global__ __launch_bounds__(NS * 64, std::max(1, stream_held(KS, NS) * NS / 4))
 // 16-byte read, consecutive lanes read consecutive units; a plane is 32 bytes longer than a power of two so that the
 // 8-byte staging stores of 16 consecutive lanes, 2 rows x 4 units x 2 halves, cover 128 consecutive bytes of banks);
 // the weight matrix of a plain product is cut once, by split_repack_kernel, into the same units in global memory and
-// only copied here; an operand stored across the reduction index (both operands of X^T G) is transposed in registers
-// and kept in 8-byte units S[piece][k / 4][row], which makes both the staging stores (32 bytes per thread and piece)
-// and the operand reads (two 8-byte reads) run over consecutive LDS addresses.
+// only copied here.  Both operands of X^T G are stored across the reduction index: gemm_split_cols_kernel reads
+// them straight into registers instead.
 constexpr int SBK = 32;
 
 // x = piece 0 + piece 1 + piece 2 exactly, for two numbers at once; p[i] holds piece i of x0 in its low half and of
