@@ -924,11 +924,12 @@ static bool rows_in_one_launch(int64_t nnz, int64_t longest, int64_t row_bytes, 
 
 // Rows below the cut that a launch of spmm_rows_kernel gives a workgroup each as well: a wave takes about a microsecond for a
 // trip (its gathers under way at once), so those of at least two trips and of a quarter of what the launch's bytes need at 8.5 TB/s,
-// while they and the cut rows are no more than the compute units.  40 k entries x 128 floats: launch 12.4 -> 10.0 us, the epoch
-// of two layers 63.6 -> 59.3; 420 k entries x 50 and 128 floats: epoch 202 -> 195; 14 k entries x 128 floats 22.3 -> 20.8.  Without the
-// second bound 200 k entries x 128 floats lost 2 us; with a lane group's 128 entries per trip (32 bf16 features) and rows of
-// 32 entries in workgroups of their own, 100 k entries lost 5 us a launch.  Graphs without cut rows keep single-wave workgroups
-// (490 k entries of 98 k short rows: an epoch 304 -> 332 us in workgroups of sixteen).
+// while they and the cut rows are no more than the compute units.  us: 40 k entries x 128 floats 12.3 -> 7.3, the epoch of two
+// layers around it 63.6 -> 59.3; an epoch of 420 k entries (50 and 128 floats) 202 -> 195; forward and backward of 77 k entries
+// x 80 floats 22.3 -> 20.9.  With half of that time as the second bound the 420 k entries gain nothing, without one an epoch of
+// 200 k entries x 128 floats goes 286 -> 288.  Trips of a wave matter: 32 bf16 features take 128 entries per trip, and rows of 32
+// entries in workgroups of their own cost an epoch of 100 k such entries 109 -> 129.  Graphs without cut rows keep single-wave
+// workgroups (490 k entries of 98 k short rows: an epoch 304 -> 332 in workgroups of sixteen).
 static int64_t middling_rows(const ItemList &list, int64_t nnz, int64_t row_bytes, int trip) {
     const double trips = std::max(2.0, 0.25 * static_cast<double>(nnz) * row_bytes / 8.5e6);
     int64_t rows = 0;
