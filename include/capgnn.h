@@ -424,6 +424,8 @@ int capgnn_layer_order(const capgnn_graph *g, const capgnn_layer *l, int need_dx
 
 /* Forward: H = act(A_hat X W + bias)            (GCN, proof of Lemma 2)
  *          H = act(X_loc W_self + mean_agg(X) W + bias)   (GraphSAGE-mean)
+ * A CAPGNN_BF16 GraphSAGE layer first stores X_loc W_self as H (rounded, unless out_f32), then adds the neighbour term to what it
+ * stored; capgnn_layer_bwd forms dX from the self term and the transposed aggregation likewise.  The same for every number of rows.
  * X: device [n_cols x ldx] = [local rows; halo rows]; H: device [n_loc x ldh].
  * saved: device buffer of capgnn_layer_saved_bytes() that layer_bwd needs (the aggregated input
  * for AGG_FIRST; nothing for XFORM_FIRST). */

@@ -2835,8 +2835,8 @@ constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piec
 // Plain bf16 products: from the k on from which its one round trip pays for its loads of W element by element, while its workgroups (32 rows by
 // 32 or 64 columns) are few (a sweep of 726 sizes; us, 64 x 64 tiles with the launch that repacks W where they need it -> small):
 // 12000 x 32 x 64 5.8 -> 5.6, 3000 x 128 x 32 6.0 -> 6.1; 6000 x 128 x 128 7.3 -> 6.5, 12000 x 128 x 128 7.8 -> 9.7; 3000 x 64 x 256 9.8 -> 6.2, 500 x 256 x 602 17.8 -> 8.6; 25000 x 16 x 256 10.7 -> 9.8, 25000 x 32 x 64 6.2 -> 6.7,
-// 12000 x 128 x 389 14.4 -> 13.4.  By W^T (both operands along k) the tiles need no repacking: 12000 x 16 x 256 8.2 -> 7.0, 6000 x 64 x 256 8.0 -> 8.1, 3000 x 32 x 128 6.3 -> 6.4.  Two products in
-// one launch replace two of either.
+// 12000 x 128 x 389 14.4 -> 13.4.  By W^T (both operands along k) the tiles need no repacking: 12000 x 16 x 256 8.2 -> 7.0, 6000 x 64 x 256 8.0 -> 8.1, 3000 x 32 x 128 6.3 -> 6.4.  Two products of
+// one shape in one launch replace two of either.
 static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches, int trans_b) {
     if (K <= 0) return false;
     const double macs = static_cast<double>(M) * N * K;
@@ -3427,7 +3427,8 @@ static int launch_two_small(const SmallGemmArgs &in, int trans_a, int trans_b, i
     GemmArgs &g = s.g;
     const bool bf = dtype == CAPGNN_BF16, pair = s.C2 != nullptr;
     const int64_t Ksum = g.K + (s.dual ? s.K2 : 0);       // (the waves of a workgroup share it)
-    const bool small = (bf || f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual || (bf && pair) ? 2 : 1, trans_b);
+    // (a bf16 sum is two launches at every size: see launch_gemm_dual)
+    const bool small = (bf ? !s.dual : f32_product != CAPGNN_F32_PRODUCT_SPLIT) && small_product(bf, trans_a, g.M, g.N, Ksum, s.dual || bf ? 2 : 1, trans_b);
     // two narrow reductions over vertices
     const size_t half_ws = ws_bytes / 2 / 256 * 256;
     const bool narrow = pair && g.M == s.M2 && ws && narrow_product(dtype, f32_product, trans_a, trans_b, g.M, g.N, g.K) &&
@@ -3548,10 +3549,12 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
 size_t gemm_pair_ws_bytes(int trans_a, int64_t M, int64_t N, int64_t K) { return (trans_a ? 2 : 1) * gemm_ws_bytes(trans_a, M, N, K); }
 
 // C = A op(W) + A2 op(W2) (+ bias, ReLU): the two products of a GraphSAGE layer (neighbour term and self term), or of its input
-// gradient, into one result.  Small and middling sizes, and fp32 operands in the three-piece form, run as ONE launch, whose
+// gradient, into one result.  fp32 operands of small and middling sizes, and in the three-piece form, run as ONE launch, whose
 // reduction walks both first operands, so C is written once and never read back; every other case is the two launches it
-// replaces (A2 W2 first, then A W accumulated on top with the epilogue).  A [M x K1], A2 [M x K2] row-major; W [K1 x N],
-// W2 [K2 x N], or their transposes when trans_b.
+// replaces (A2 W2 first, then A W accumulated on top with the epilogue).  bf16 operands are always two: A2 W2 is rounded as it is
+// stored, at every number of rows alike.  One launch for few rows, rounding once, moved the gradients of layers of 1000 to 4000 vertices by 2
+// to 5 % of their norm (pre-activations near zero change sides).  A [M x K1], A2 [M x K2] row-major; W [K1 x N], W2 [K2 x N], or
+// their transposes when trans_b.
 int launch_gemm_dual(int trans_b, int64_t M, int64_t N, int64_t K1, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t K2,
                      const void *A2, int64_t lda2, const void *W2, int64_t ldw2, void *C, int64_t ldc, int dtype, int out_f32,
                      const float *bias, int relu, void *ws, size_t ws_bytes, hipStream_t stream, int f32_product, const void *relu_mask,

@@ -1396,6 +1396,48 @@ def test_sage_layer_products_over_two_weight_matrices(env, order, n, f_in, f_out
     g.close()
 
 
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("n,f_in,f_out", [(37, 40, 30), (1003, 100, 64), (3001, 130, 200), (6400, 64, 128), (12_800, 96, 64), (12_801, 96, 64), (33_001, 64, 72)])
+def test_bf16_sage_layer_rounds_as_two_launches_exact(env, order, n, f_in, f_out):
+    """A bf16 GraphSAGE layer stores its self product, rounded, and adds the neighbour product to what it stored, at every number of rows: in the
+    AGG_FIRST order forward, in XFORM_FIRST backward; the other direction rounds both terms and adds in the aggregation.  Small integers, whose
+    sums are exact in float (below 2^24) and whose stored values are not in bf16 (beyond 2^8): equality with the same roundings."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + f_in + order)
+    mk = lambda r, c: torch.randint(-8, 9, (r, c), generator=gen, device="cuda").double()  # noqa: E731
+    rne = lambda t: t.float().bfloat16().double()  # noqa: E731
+    bf = lambda t: torch.nn.functional.pad(t.bfloat16(), (0, -t.shape[1] % 8)).contiguous()  # noqa: E731
+    col = torch.randint(0, n, (n,), generator=gen, device="cuda")
+    g = B.Graph(n, 0, np.arange(0, n + 1, dtype=np.int64), col.int().cpu().numpy(), np.ones(n, np.float32), np.ones(n, np.float32))
+    x, dh, w, w_self, bias = mk(n, f_in), mk(n, f_out), mk(f_in, f_out), mk(f_in, f_out), mk(1, f_out)[0]
+    summed = lambda t: torch.zeros_like(t).index_add_(0, col, t)  # noqa: E731
+    if order == B.AGG_FIRST:
+        h = rne(x[col] @ w + rne(x @ w_self) + bias)
+        dx = rne(summed(rne(dh @ w.T)) + rne(dh @ w_self.T))
+        dw = x[col].T @ dh
+    else:
+        back = summed(dh)                    # (a few terms of at most 8: bf16 holds it)
+        h = rne(rne(x @ w)[col] + rne(x @ w_self) + bias)
+        dx = rne(back @ w.T + rne(dh @ w_self.T))
+        dw = x.T @ back
+    assert n < 1000 or not torch.equal(h, rne((x[col] @ w) + x @ w_self + bias))
+    xb, db, wb, wb_self, bias = bf(x), bf(dh), w.bfloat16(), w_self.bfloat16(), bias.float()       # (the layer keeps pointers)
+    l = B.make_layer(B.SAGE_MEAN, f_in, f_out, B.ACT_NONE, B.BF16, wb, wb_self, bias, order)
+    ldi, ldo = xb.shape[1], db.shape[1]
+    size = B.layer_workspace_bytes(g, l)
+    ws, saved = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty(B.layer_saved_bytes(g, l) + 256, dtype=torch.uint8, device="cuda")
+    hd, dxd = torch.zeros(n, ldo, dtype=torch.bfloat16, device="cuda"), torch.zeros(n, ldi, dtype=torch.bfloat16, device="cuda")
+    dwd, dwsd, dbd = torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_in, f_out, device="cuda"), torch.zeros(f_out, device="cuda")
+    say(f"bf16 GraphSAGE layer's roundings order={order} n={n} {f_in}-{f_out}")
+    B.layer_fwd(g, l, xb, ldi, hd, ldo, saved, ws, size)
+    B.layer_bwd(g, l, xb, ldi, hd, ldo, saved, db.clone(), ldo, dwd, dwsd, dbd, dxd, ldi, 0, ws, size)
+    torch.cuda.synchronize()
+    assert torch.equal(hd[:, :f_out].double(), h) and torch.equal(dxd[:, :f_in].double(), dx)
+    assert torch.equal(dwd.double(), dw) and torch.equal(dwsd.double(), x.T @ dh) and torch.equal(dbd.double(), dh.sum(0))
+    g.close()
+
+
 @pytest.mark.parametrize("n,f_in,f_out", [(60_001, 47, 100), (30_017, 100, 128), (66_001, 125, 100), (30_017, 130, 300), (20_011, 200, 256), (9001, 40, 30)])
 def test_layer_input_gradient_with_scaled_rows(env, n, f_in, f_out):
     """The input gradient of a GCN layer in the AGG_FIRST order, whose product dZ W^T multiplies each row by its scale: in tiles of 64 and 128
