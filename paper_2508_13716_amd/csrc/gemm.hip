@@ -1675,7 +1675,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_cols_kernel(SmallGemmArgs p2
         return;                                         // uniform over the workgroup
     }
     const int64_t m0 = static_cast<int64_t>(by) * (TA * 32), n0 = static_cast<int64_t>(bx) * (TB * 32);
-    const bool ragged = (g.M | g.N) % 4 != 0;           // the matrices' last row is read apart
+    const bool ragged = (g.M | g.N) % 4 != 0;           // the matrices' last row (there is one: g.K > 0) is read apart
     const int64_t k_all = ragged ? g.K - 1 : g.K;
     const int k_first = (bz * 4 + wave) * 16, k_step = 64 * g.S, n_all = static_cast<int>(k_all);
     const int lda = static_cast<int>(g.lda) * 2, ldb = static_cast<int>(g.ldb) * 2;         // bytes
@@ -3254,14 +3254,15 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const bool b_aligned = aligned16(B) && (ldb * 2) % 16 == 0;
     const bool repack_b = dtype == CAPGNN_BF16 && !trans_a && ws && ws_bytes >= transposed_b_bytes(N, K) &&
                           !(b_aligned && (trans_b || (tiles64 <= 768 && K <= 256)));
-    const bool half_path = dtype == CAPGNN_BF16 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned) &&
+    // An empty reduction, which leaves the epilogue of zeros, is gemm_kernel's: it does no step and reads neither operand.
+    const bool half_path = dtype == CAPGNN_BF16 && K > 0 && aligned16(A) && (lda * 2) % 16 == 0 && (repack_b || b_aligned) &&
                            (!trans_a || trans_b || cols_reach(K, lda, ldb));
     // fp32 operands as three bf16 pieces each (see gemm_split_kernel)
     const int mode = f32_product;
-    const bool split_path = dtype == CAPGNN_F32 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
+    const bool split_path = dtype == CAPGNN_F32 && K > 0 && !(trans_a && trans_b) && split_form(mode, trans_a, M, N, K) &&
                             (trans_a ? cols_reach(K, lda, ldb) : ws && ws_bytes >= split_b_bytes(N, K));
     // gemm_split_mid_kernel while its tiles fit the chip at once (three workgroups per compute unit)
-    const bool mid_reach = split_path && !trans_a && K > 0 && K < (1 << 30) && lda < (1 << 22) && ldb < (1 << 22);
+    const bool mid_reach = split_path && !trans_a && K < (1 << 30) && lda < (1 << 22) && ldb < (1 << 22);
     const bool mid = mid_reach && tiles64 <= 768, quarters = mid && quarters_pay(M, N, K, trans_b);
     const bool half_cols = half_path && trans_a && !trans_b;
     bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K, 1, trans_b) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);

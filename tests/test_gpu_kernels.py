@@ -762,6 +762,54 @@ def test_gemm_bf16_vertex_reduction_in_registers_exact(env, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N", [(1, 1), (40, 32), (130, 47), (512, 129), (602, 256)])
+def test_gemm_empty_reduction_is_the_epilogue_of_zeros(env, dtype, ta, tb, M, N):
+    """K = 0, rows aligned and not, columns whole groups of four and not, every form of the fp32 product: zeros, with the epilogue where one is
+    asked for.  Operands are rows of infinities around the empty matrices' addresses: none of them may be read."""
+    torch, B = env["torch"], env["B"]
+    td, dt = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    bias, mask = torch.arange(N, device="cuda").float() - 3.0, torch.randint(-1, 2, (M, N), device="cuda").to(td)
+    for pad in (8, 9):
+        lda, ldb = -(-(M if ta else 1) // 8) * 8 + pad, -(-(N if not tb else 1) // 8) * 8 + pad
+        A, W = (torch.full((4 * max(M, N) * ld + 8 * ld,), float("inf"), device="cuda").to(td)[4 * ld:] for ld in (lda, ldb))
+        wsb = B.gemm_workspace_bytes(ta, M, N, 0)
+        ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+        for full, form, f32 in ((0, 0, 1), (1, 0, 1), (1, 0, 0)) + (((1, 1, 1), (1, 2, 1)) if dtype == "f32" else ()):
+            say(f"gemm empty reduction {dtype} ta={ta} tb={tb} {M}x{N} pad={pad} epilogue={full} form={form} f32={f32}")
+            Cd = torch.full((M, N + 3), 2.0, device="cuda", dtype=td if not f32 else torch.float32)
+            B.gemm(ta, tb, M, N, 0, A, lda, W, ldb, Cd, N + 3, dt, out_f32=f32, accumulate=full, bias=bias if full else None, relu=full,
+                   relu_mask=mask if full else None, ldm=N if full else 0, ws=ws, ws_bytes=wsb, f32_product=form)
+            torch.cuda.synchronize()
+            want = (2.0 + bias).clamp(min=0).expand(M, N) * (mask > 0) if full else torch.zeros(M, N, device="cuda")
+            assert torch.equal(Cd[:, :N].double(), want.to(Cd.dtype).double()) and (Cd[:, N:] == 2.0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["gcn", "sage"])
+@pytest.mark.parametrize("f_in,f_out", [(602, 47), (33, 130), (64, 64)])
+def test_layer_gradients_of_a_partition_without_local_rows_are_zero(env, dtype, kind, f_in, f_out):
+    """AGG_FIRST on a partition of halo rows alone: weight and bias gradients are empty sums."""
+    torch, B = env["torch"], env["B"]
+    td, dt = (torch.bfloat16, B.BF16) if dtype == "bf16" else (torch.float32, B.F32)
+    sage = kind == "sage"
+    g = B.Graph(0, 5, np.zeros(1, np.int64), np.zeros(0, np.int32), np.ones(0, np.float32), np.ones(5, np.float32))
+    ldi, ldo = -(-f_in // 8) * 8, -(-f_out // 8) * 8
+    big = lambda r, c: torch.full((r, c), float("inf"), device="cuda").to(td)  # noqa: E731
+    x, h, dh, w, w_self, bias = big(5, ldi), big(4, ldo), big(4, ldo), big(f_in, f_out), big(f_in, f_out), torch.zeros(f_out, device="cuda")
+    l = B.make_layer(B.SAGE_MEAN if sage else B.GCN, f_in, f_out, B.ACT_RELU, dt, w, w_self if sage else None, bias, B.AGG_FIRST)
+    wsb = B.layer_workspace_bytes(g, l)
+    saved, ws = big(8, ldi), torch.empty(max(wsb, 256), dtype=torch.uint8, device="cuda")
+    dw, dws, db = torch.full((f_in, f_out), 7.0, device="cuda"), torch.full((f_in, f_out), 7.0, device="cuda"), torch.full((f_out,), 7.0, device="cuda")
+    say(f"layer without local rows {kind} {dtype} {f_in}-{f_out}")
+    B.layer_fwd(g, l, x, ldi, h, ldo, saved, ws, wsb)
+    B.layer_bwd(g, l, x, ldi, h, ldo, saved, dh, ldo, dw, dws if sage else None, db, None, 0, 0, ws, wsb)
+    torch.cuda.synchronize()
+    assert not dw.any() and not db.any() and not (sage and dws.any())
+    g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n,f_in,f_out", [(40_000, 100, 100), (70_001, 131, 200), (20_003, 520, 136), (66_000, 97, 64)])
 def test_layer_pair_of_weight_gradients_in_registers_exact(env, dtype, n, f_in, f_out):
     """Both weight gradients of a GraphSAGE layer in one launch of the kernels that hold their results in registers (fp32 above 64 columns), and its
