@@ -3266,7 +3266,12 @@ int launch_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const
     const bool mid = mid_reach && tiles64 <= 768, quarters = mid && quarters_pay(M, N, K, trans_b);
     const bool half_cols = half_path && trans_a && !trans_b;
     bool small_path = small_product(dtype == CAPGNN_BF16, trans_a, M, N, K, 1, trans_b) && !(split_path && mode == CAPGNN_F32_PRODUCT_SPLIT);
-    if (half_cols && bf16_cols_pays(M, N, K)) small_path = false;
+    if (half_cols && small_path && bf16_cols_pays(M, N, K)) {
+        // (with too little room for the parts of these splits, there may be enough for the fewer of the small kernel)
+        const size_t s = choose_split(trans_a, M, N, K, bm, bn, HBK), parts = s > 1 ? s * M * N * sizeof(float) : 0;
+        const size_t need = colsum ? align_up(parts, 256) + s * N * sizeof(float) : parts;
+        small_path = need > 0 && (!ws || ws_bytes < need);
+    }
     const int bk = (half_path || split_path) ? HBK : BK;
     static_assert(SBK == HBK, "the two bf16 kernels step through K alike");
     int S = choose_split(trans_a, M, N, K, bm, bn, bk), tn = 0;

@@ -679,6 +679,35 @@ def test_gemm_vertex_reduction_with_little_workspace(env, dtype, tb):
             assert (got == 2.0).all() if room < need else np.array_equal(got.astype(np.float64), ref), (M, N, K, room)
 
 
+@pytest.mark.parametrize("M,N,K,parts", [(128, 256, 40_000, 32), (256, 256, 20_000, 16), (389, 16, 20_000, 39), (100, 41, 100_000, 121), (512, 200, 1000, 0)])
+def test_gemm_bf16_aligned_vertex_reduction_with_little_workspace(env, M, N, K, parts):
+    """X^T G of bf16 operands with aligned rows, which runs in registers with the workspace that the query names: with less, the small kernel's fewer
+    splits, or the registers' at 16 steps of 32 each, down to the parts of the fewer of both; with four bytes less CAPGNN_ENOMEM, C
+    untouched.  Small integers: exact with any number of splits."""
+    torch, B = env["torch"], env["B"]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+    lda, ldb = -(-M // 8) * 8, -(-N // 8) * 8
+    A, G = (torch.randint(-3, 4, (K, w), generator=gen, device="cuda") for w in (lda, ldb))
+    ref = A[:, :M].double().T @ G[:, :N].double()
+    A, G = A.bfloat16(), G.bfloat16()
+    fine = min(1536 // (-(-M // 128) * -(-N // (64 if N <= 64 else 128))), K // 512) * M * N * 4
+    rooms = {parts * M * N * 4, (parts + 1) * M * N * 4, fine, B.gemm_workspace_bytes(1, M, N, K)}
+    for room in sorted(rooms) + ([parts * M * N * 4 - 4, 0] if parts else []):
+        say(f"gemm bf16 X^T G {M}x{N}x{K}: {room} bytes of workspace")
+        ws = torch.empty(room, dtype=torch.uint8, device="cuda") if room else None
+        Cd = torch.full((M, N), 2.0, device="cuda")
+        call = lambda: B.gemm(1, 0, M, N, K, A, lda, G, ldb, Cd, N, B.BF16, out_f32=1, ws=ws, ws_bytes=room)  # noqa: E731
+        if room < parts * M * N * 4:
+            with pytest.raises(B.CapgnnError) as e:
+                call()
+            assert e.value.code == B.ENOMEM
+        else:
+            call()
+        torch.cuda.synchronize()
+        assert (Cd == 2.0).all() if room < parts * M * N * 4 else torch.equal(Cd.double(), ref), room
+
+
 @pytest.mark.parametrize("ta,tb,M,N,K", [(0, 0, 164_001, 47, 40), (0, 1, 164_001, 64, 72), (0, 0, 82_100, 130, 24), (0, 1, 82_100, 200, 33), (1, 0, 513, 64, 131_100),
                                          (1, 1, 600, 41, 180_001), (1, 0, 300, 130, 38_400), (1, 1, 257, 250, 25_000)])
 def test_gemm_bf16_full_size_tiles_exact(env, ta, tb, M, N, K):
