@@ -548,9 +548,11 @@ static bool gradients_apart(const capgnn_layer *layers, int L, float **dW, float
 
 // A line of the graph's pinned memory for the loss of one epoch, while the epoch is under way.  A copy of the loss to the caller's own memory,
 // which is not pinned, costs a launch and a wait of its own: 21557-vertex multi-label epoch 225 -> 202 us.
+// An epoch that fails after its last kernel was asked for keeps its line for good: the kernel may yet write there.
 struct LossLine {
     const capgnn_graph *g;
     int i = -1;
+    bool asked = false;             // a kernel that writes the line may be on its way
     explicit LossLine(const capgnn_graph *graph) : g(graph) {}
     bool take() {
         if (!g->loss_host) return false;
@@ -562,7 +564,7 @@ struct LossLine {
         i = -1;
         return false;
     }
-    ~LossLine() { if (i >= 0) g->taken.fetch_and(~(1u << i)); }
+    ~LossLine() { if (i >= 0 && !asked) g->taken.fetch_and(~(1u << i)); }
     float *dev() const { return g->loss_dev + i * capgnn_graph::LOSS_STRIDE; }
     float host() const { return *static_cast<const volatile float *>(g->loss_host + i * capgnn_graph::LOSS_STRIDE); }
 };
@@ -759,6 +761,7 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
     if (loss_copy && !finish.count) CG_HIP(hipMemcpyAsync(loss_copy, loss_dev, sizeof(float), hipMemcpyDeviceToDevice, st));
     if (finish.count || sgd.count) {
         Scope s(CAPGNN_K_ELEMENTWISE, 0, 1, st);
+        line.asked = true;
         CG_TRY(launch_finish(&finish, &sgd, lr, st));
     }
     if (capture && has_miss && side != st) {
@@ -770,6 +773,7 @@ static int epoch_impl(const capgnn_graph *g, capgnn_cache *c, const capgnn_layer
     if (loss_out) {
         if (line.i < 0) CG_HIP(hipMemcpyAsync(loss_out, loss_dev, sizeof(float), hipMemcpyDeviceToHost, st));
         CG_HIP(hipStreamSynchronize(st));
+        line.asked = false;
         if (line.i >= 0) *loss_out = line.host();
     }
     if (times) {

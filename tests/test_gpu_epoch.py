@@ -634,6 +634,50 @@ def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dim
         assert float((p - q).norm()) <= 2e-6 * float(q.norm())
 
 
+def test_epochs_of_one_graph_in_many_threads_return_their_own_loss(env):
+    """Twenty threads, each with a stream, workspace, labels and results of its own, run epochs of one graph at the same time: more than the graph has
+    pinned lines for their losses, so some come by a copy.  Each epoch returns the loss of its own labels, the one that it returned alone."""
+    import threading
+    torch, B = env["torch"], env["B"]
+    n, dims, T, reps = 20_011, (64, 32, 9), 20, 6
+    rng = np.random.default_rng(5)
+    deg = rng.integers(1, 9, n)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    g = B.Graph(n, 0, rowptr, rng.integers(0, n, rowptr[-1]).astype(np.int32), (1.0 / deg).astype(np.float32), np.ones(n, np.float32))
+    x = torch.randn(n, dims[0], device="cuda")
+    w, b = [torch.randn(p, q, device="cuda") / p ** 0.5 for p, q in zip(dims, dims[1:])], [0.1 * torch.randn(q, device="cuda") for q in dims[1:]]
+    layers = [B.make_layer(B.GCN, dims[i], dims[i + 1], B.ACT_NONE if i else B.ACT_RELU, B.F32, w[i], None, b[i]) for i in range(2)]
+    size = B.epoch_workspace_bytes(g, None, layers)
+    own = [dict(labels=torch.randint(0, 2 + t % 8, (n,), device="cuda", dtype=torch.int32), ws=torch.empty(size, dtype=torch.uint8, device="cuda"),
+                dw=[torch.zeros_like(m) for m in w], db=[torch.zeros_like(m) for m in b], logits=torch.zeros(n, dims[-1], device="cuda"), st=torch.cuda.Stream())
+           for t in range(T)]
+    torch.cuda.synchronize()
+    run = lambda o: B.epoch(g, None, layers, x, dims[0], o["labels"], None, 0.0, o["logits"], o["dw"], None, o["db"], 0.0, o["ws"], size, o["st"])[0]  # noqa: E731
+    alone = []
+    for t, o in enumerate(own):
+        alone.append(run(o))
+        ref = float(torch.nn.functional.cross_entropy(o["logits"].double(), o["labels"].long()))
+        assert abs(alone[-1] - ref) <= 1e-5 * ref, (t, alone[-1], ref)       # a mean of 20 k terms, each a few fp32 roundings
+        o["first"] = [m.clone() for m in o["dw"] + o["db"]]
+    assert len(set(alone)) == T
+    torch.cuda.synchronize()
+    say(f"{T} threads, {reps} epochs each")
+    got, start = [[] for _ in range(T)], threading.Barrier(T)
+
+    def work(t):
+        start.wait()
+        for _ in range(reps): got[t].append(run(own[t]))
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(T)]
+    for t in threads: t.start()
+    for t in threads: t.join()
+    torch.cuda.synchronize()
+    assert got == [[a] * reps for a in alone]
+    assert all(torch.equal(p, q) for o in own for p, q in zip(o["dw"] + o["db"], o["first"]))
+    assert run(own[0]) == alone[0]
+    g.close()
+
+
 @pytest.mark.parametrize("recorded", [False, True])
 @pytest.mark.parametrize("L,shared", [(2, "none"), (3, "dw"), (3, "bias"), (16, "none"), (16, "dw")])
 def test_epoch_end_adds_up_every_gradient(env, L, shared, recorded):
