@@ -599,7 +599,9 @@ def test_timed_epoch_keeps_every_stage_its_own_work(env, kind, dtype, lr):
 def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dims):
     """The small weight and input gradients of a layer run as one launch; an epoch that records its stages' times runs them one by one: the same
     parts, added up in another order (the gradients differ by fp32 rounding of sums of at most 512 parts, random: far below 2e-6).  The last
-    size has reductions too long for the batch."""
+    size has reductions too long for the batch.  The loss reaches the host by the last kernel in the one, by a copy in the other.  Both agree with
+    float64 as far as pre-activations within rounding of zero let them: one that changes sides moves a gradient by up to 1e-3 (fp32), and
+    bf16 roundings through three layers by up to 6e-2; a product taken for another is off by 1."""
     torch, B = env["torch"], env["B"]
     sage, bf = kind == "sage", dtype == "bf16"
     td, dt = (torch.bfloat16, B.BF16) if bf else (torch.float32, B.F32)
@@ -627,11 +629,24 @@ def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dim
         grads = [[torch.full((p, q), 7.0, device="cuda") for p, q in zip(dims, dims[1:])] for _ in range(2)] + [[torch.full((d,), 7.0, device="cuda") for d in dims[1:]]]
         logits = torch.zeros(n, dims[-1], device="cuda")
         print(f"small products in one launch {kind} {dtype} order={order} n={n} {dims} timed={timed}", flush=True)
-        B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, wsb, None, None, want_times=timed)
+        loss, _ = B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, wsb, None, None,
+                          want_times=timed)
         torch.cuda.synchronize()
-        out.append([t.double() for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits.double()])
+        out.append([t.double() for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits.double(), torch.tensor(loss).double().cuda()])
     for p, q in zip(*out):
         assert float((p - q).norm()) <= 2e-6 * float(q.norm())
+    dst, src = torch.arange(n, device="cuda").repeat_interleave(torch.from_numpy(deg).cuda()), torch.from_numpy(col).cuda().long()
+    leaf = [[t.detach().double().requires_grad_() for t in part] for part in (w, ws_, b)]
+    h = x[:, :dims[0]].double()
+    for i in range(L):
+        m = torch.zeros_like(h).index_add(0, dst, h[src] / torch.from_numpy(deg).cuda()[dst].double()[:, None])
+        z = m @ leaf[0][i] + leaf[2][i] + (h @ leaf[1][i] if sage else 0)
+        h = z.clamp(min=0) if i < L - 1 else z
+    ref_loss = torch.nn.functional.cross_entropy(z, labels.long())
+    ref_loss.backward()
+    ref = [t.grad for part in (leaf if sage else [leaf[0], leaf[2]]) for t in part] + [z.detach(), ref_loss.detach()]
+    err = [float((p - q).norm() / q.norm()) for p, q in zip(out[0], ref)]
+    assert max(err) <= (6e-2 if bf else 1e-3), err
 
 
 def test_epochs_of_one_graph_in_many_threads_return_their_own_loss(env):
