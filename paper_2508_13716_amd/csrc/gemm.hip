@@ -3540,7 +3540,8 @@ int launch_gemm_pair(int trans_a, int trans_b, int64_t M, int64_t M2, int64_t N,
     const int64_t es_c = (dtype == CAPGNN_BF16 && !out_f32) ? 2 : 4;
     const uintptr_t c1 = reinterpret_cast<uintptr_t>(C), c2 = reinterpret_cast<uintptr_t>(C2);
     const bool apart = c1 + ((M - 1) * ldc + N) * es_c <= c2 || c2 + ((M2 - 1) * ldc2 + N) * es_c <= c1;
-    if (apart && M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
+    // (the sum over splits scales both results alike, and row_scale is the first one's)
+    if (apart && !(trans_a && row_scale) && M2 > 0 && N > 0 && A && A2 && B && B2 && C && C2 && ldc >= N && ldc2 >= N && lda >= (trans_a ? M : K) &&
         lda2 >= (trans_a ? M : K) && ldb >= (trans_b ? K : N) && ldb2 >= (trans_b ? K : N))
         CG_TRY(launch_two_small(s, trans_a, trans_b, dtype, out_f32, ws, ws_bytes, stream, f32_product, colsum, &done, later, batch));
     if (done) return CAPGNN_OK;
