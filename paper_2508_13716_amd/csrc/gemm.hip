@@ -2833,10 +2833,11 @@ constexpr int64_t SPLIT_MIN_MACS = int64_t(1) << 28;     // AUTO: the three-piec
 // at 2^31, 512 x 64 44 / 51, 602 x 41 69 / 64 at 2^32.  bf16, N <= 32, up to 2^30: 100 x 16 60 / 83, 602 x 16 54 / 51 at 2^30, 320 x 16
 // 117 / 95 at 2^31.
 // Plain bf16 products: from the k on from which its one round trip pays for its loads of W element by element, while its workgroups (32 rows by
-// 32 or 64 columns) are few (a sweep of 726 sizes; us, 64 x 64 tiles with the launch that repacks W where they need it -> small):
-// 12000 x 32 x 64 5.8 -> 5.6, 3000 x 128 x 32 6.0 -> 6.1; 6000 x 128 x 128 7.3 -> 6.5, 12000 x 128 x 128 7.8 -> 9.7; 3000 x 64 x 256 9.8 -> 6.2, 500 x 256 x 602 17.8 -> 8.6; 25000 x 16 x 256 10.7 -> 9.8, 25000 x 32 x 64 6.2 -> 6.7,
-// 12000 x 128 x 389 14.4 -> 13.4.  By W^T (both operands along k) the tiles need no repacking: 12000 x 16 x 256 8.2 -> 7.0, 6000 x 64 x 256 8.0 -> 8.1, 3000 x 32 x 128 6.3 -> 6.4.  Two products of
-// one shape in one launch replace two of either.
+// 32 or 64 columns) are few (a sweep of 726 sizes; us, 64 x 64 tiles with the launch that repacks W where they need it / small):
+// - taken: 12000 x 32 x 64 5.8 / 5.6, 6000 x 128 x 128 7.3 / 6.5, 3000 x 64 x 256 9.8 / 6.2, 500 x 256 x 602 17.8 / 8.6, 25000 x 16 x 256 10.7 / 9.8;
+// - left: 3000 x 128 x 32 6.0 / 6.1, 12000 x 128 x 128 7.8 / 9.7, 25000 x 32 x 64 6.2 / 6.7, and, by the same line, 12000 x 128 x 389 14.4 / 13.4.
+// By W^T (both operands along k) the tiles need no repacking: taken 12000 x 16 x 256 8.2 / 7.0, 3000 x 32 x 128 6.3 / 6.4, left 6000 x 64 x 256
+// 8.0 / 8.1.  Two products of one shape in one launch replace two of either.
 static bool small_product(bool bf16, int trans_a, int64_t M, int64_t N, int64_t K, int launches, int trans_b) {
     if (K <= 0) return false;
     const double macs = static_cast<double>(M) * N * K;
@@ -2954,12 +2955,14 @@ static ColsPlan cols_plan(bool bf16, int64_t M, int64_t N, int64_t K, int most, 
 // Which of gemm_small_kernel's bf16 reductions over vertices gemm_bf16_cols_kernel takes (it takes all of those that the small kernel leaves): its
 // ends cost 9 us, its tiles are 128 rows high, and it reads faster.  From a sweep of both (550 sizes, M 16 to 602, N 2 to 256, K 1000 to 250000: 0.89
 // of the small kernel's time with the faster one each time), us small -> here, M x N x K:
-// - N <= 64, from 6 M elements of X: 389 x 16 x 20000 20.4 -> 13.8, 100 x 41 x 100000 20.3 -> 17.7, 128 x 32 x 40000 15.5 -> 15.0, 100 x 16 x 40000 14.6 -> 14.4;
-//   not for X that fills less than three quarters of a tile: 50 x 41 x 250000 18.6 -> 20.9, 16 x 64 x 250000 17.2 -> 18.6;
-// - N <= 128, from 2 M elements over 16384 vertices and 4 M below: 128 x 100 x 20000 15.4 -> 14.6, 389 x 100 x 10000 16.9 -> 16.6, 200 x 128 x 10000
-//   14.6 -> 15.3; not 16 x 100 x 250000 19.4 -> 24.5, 50 x 121 x 200000 28 -> 31;
-// - above, from 1 M and 2 M elements: 50 x 256 x 20000 15.3 -> 14.8, 200 x 256 x 10000 17.3 -> 17.3, 200 x 200 x 5000 13.8 -> 14.8; and whenever X has
-//   512 columns and more (the small kernel's tiles fill the chip more than once): 602 x 256 x 1000 22.1 -> 15.5; not 1000 x 600 x 2000 24.5 -> 26.1.
+// - N <= 64, from 6 M elements of X: 389 x 16 x 20000 20.4 -> 13.8, 100 x 41 x 100000 20.3 -> 17.7; below that little is left (128 x 32 x 40000
+//   15.5, here 15.0; 100 x 16 x 40000 14.6, 14.4), and not for X that fills less than three quarters of a tile: 50 x 41 x 250000 18.6, here 20.9,
+//   16 x 64 x 250000 17.2, 18.6;
+// - N <= 128, from 2^21 elements over 16384 vertices and 2^22 below: 128 x 100 x 20000 15.4 -> 14.6; left are 389 x 100 x 10000 16.9, here 16.6,
+//   200 x 128 x 10000 14.6, 15.3, and, with few columns of X, 16 x 100 x 250000 19.4, 24.5, 50 x 121 x 200000 28, 31;
+// - above, from 2^20 and 2^21 elements, left 50 x 256 x 20000 15.3, here 14.8, 200 x 256 x 10000 17.3, 17.3, 200 x 200 x 5000 13.8, 14.8, 1000 x 600
+//   x 2000 24.5, 26.1; and whenever X has 512 columns and more with N <= 256 (the small kernel's tiles fill the chip more than once):
+//   602 x 256 x 1000 22.1 -> 15.5.
 static bool bf16_cols_pays(int64_t M, int64_t N, int64_t K) {
     const int64_t x = M * K;
     if (N <= 64) return M >= 96 && x >= 6000000;
@@ -2971,8 +2974,8 @@ static bool bf16_cols_pays(int64_t M, int64_t N, int64_t K) {
 // Which three-piece products of middling size gemm_split_quarters_kernel takes: those whose 64 x 64 tiles are two per compute unit at most, or three
 // with a long reduction; by W^T, whose rows it reads in 16-byte pieces, fewer.  us, gemm_split_mid_kernel -> here, M x N x K (280 sizes): 4096 x 256 x 602 27.4 ->
 // 17.0, 8820 x 64 x 602 28.3 -> 15.5, 15000 x 128 x 256 17.1 -> 15.0, 21557 x 64 x 256 17.7 -> 14.1, 30000 x 64 x 389 25.9 -> 22.4, 8820 x 256 x 389 28.7 -> 26.6, 21557 x 128 x 256 21.0 ->
-// 19.8, x 128 x 128 14.0 -> 13.9; not 15000 x 256 x 256 18.9 -> 24.1.  By W^T: 4096 x 256 x 256 17.0 -> 13.8, 21557 x 64 x 200 20.0 -> 17.7; not 8820 x 128 x
-// 256 19.6 -> 21.3, 21557 x 128 x 128 17.8 -> 20.8.
+// 19.8; not 21557 x 128 x 128 14.0, here 13.9, nor 15000 x 256 x 256 18.9, 24.1.  By W^T: 4096 x 256 x 256 17.0 -> 13.8, 21557 x 64 x 200 20.0 -> 17.7; not 8820 x 128 x
+// 256 19.6, here 21.3, nor 21557 x 128 x 128 17.8, 20.8.
 static bool quarters_pay(int64_t M, int64_t N, int64_t K, int trans_b) {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
     if (trans_b) return tiles <= 256 || (tiles <= 480 && K <= 224);
