@@ -599,9 +599,7 @@ def test_timed_epoch_keeps_every_stage_its_own_work(env, kind, dtype, lr):
 def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dims):
     """The small weight and input gradients of a layer run as one launch; an epoch that records its stages' times runs them one by one: the same
     parts, added up in another order (the gradients differ by fp32 rounding of sums of at most 512 parts, random: far below 2e-6).  The last
-    size has reductions too long for the batch.  The loss reaches the host by the last kernel in the one, by a copy in the other.  Both agree with
-    float64 as far as pre-activations within rounding of zero let them: one that changes sides moves a gradient by up to 1e-3 (fp32), and
-    bf16 roundings through three layers by up to 6e-2; a product taken for another is off by 1."""
+    size has reductions too long for the batch."""
     torch, B = env["torch"], env["B"]
     sage, bf = kind == "sage", dtype == "bf16"
     td, dt = (torch.bfloat16, B.BF16) if bf else (torch.float32, B.F32)
@@ -629,14 +627,43 @@ def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dim
         grads = [[torch.full((p, q), 7.0, device="cuda") for p, q in zip(dims, dims[1:])] for _ in range(2)] + [[torch.full((d,), 7.0, device="cuda") for d in dims[1:]]]
         logits = torch.zeros(n, dims[-1], device="cuda")
         print(f"small products in one launch {kind} {dtype} order={order} n={n} {dims} timed={timed}", flush=True)
-        loss, _ = B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, wsb, None, None,
-                          want_times=timed)
+        B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, wsb, None, None, want_times=timed)
         torch.cuda.synchronize()
-        out.append([t.double() for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits.double(), torch.tensor(loss).double().cuda()])
+        out.append([t.double() for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits.double()])
     for p, q in zip(*out):
         assert float((p - q).norm()) <= 2e-6 * float(q.norm())
+
+
+@pytest.mark.parametrize("kind,dtype", [("gcn", "f32"), ("sage", "f32"), ("gcn", "bf16"), ("sage", "bf16")])
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("n,dims", [(1003, (100, 32, 70)), (9001, (64, 128, 30, 7))])
+def test_epoch_of_small_products_against_float64(env, kind, dtype, order, n, dims):
+    """An untimed epoch, whose layers run their small products as one launch and whose loss reaches the host by the last kernel, and a timed one,
+    whose loss is copied: losses alike, and both, with gradients and logits, as float64 has them as far as pre-activations within rounding
+    of zero let them: one that changes sides moves a gradient by up to 1e-3 (fp32), bf16 roundings through three layers by up to 6e-2; a
+    product taken for another is off by 1."""
+    torch, B = env["torch"], env["B"]
+    sage, bf, L = kind == "sage", dtype == "bf16", len(dims) - 1
+    td, dt = (torch.bfloat16, B.BF16) if bf else (torch.float32, B.F32)
+    rng = np.random.default_rng(n)
+    deg = rng.integers(1, 5, n)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = rng.integers(0, n, rowptr[-1]).astype(np.int32)
+    g = B.Graph(n, 0, rowptr, col, (1.0 / deg).astype(np.float32), np.ones(n, np.float32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    ld = -(-dims[0] // 8) * 8
+    x = torch.zeros(n, ld, device="cuda", dtype=td)
+    x[:, :dims[0]] = torch.randn(n, dims[0], generator=gen, device="cuda").to(td)
+    w, w_self = ([(torch.randn(p, q, generator=gen, device="cuda") / p ** 0.5).to(td) for p, q in zip(dims, dims[1:])] for _ in range(2))
+    b = [0.1 * torch.randn(d, generator=gen, device="cuda") for d in dims[1:]]
+    labels = torch.randint(0, dims[-1], (n,), generator=gen, device="cuda", dtype=torch.int32)
+    layers = [B.make_layer(B.SAGE_MEAN if sage else B.GCN, dims[i], dims[i + 1], B.ACT_NONE if i == L - 1 else B.ACT_RELU, dt, w[i],
+                           w_self[i] if sage else None, b[i], order, out_f32=int(bf and i == L - 1)) for i in range(L)]
+    size = B.epoch_workspace_bytes(g, None, layers)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
     dst, src = torch.arange(n, device="cuda").repeat_interleave(torch.from_numpy(deg).cuda()), torch.from_numpy(col).cuda().long()
-    leaf = [[t.detach().double().requires_grad_() for t in part] for part in (w, ws_, b)]
+    leaf = [[t.detach().double().requires_grad_() for t in part] for part in (w, w_self, b)]
     h = x[:, :dims[0]].double()
     for i in range(L):
         m = torch.zeros_like(h).index_add(0, dst, h[src] / torch.from_numpy(deg).cuda()[dst].double()[:, None])
@@ -644,9 +671,20 @@ def test_small_products_of_a_layer_in_one_launch(env, kind, dtype, order, n, dim
         h = z.clamp(min=0) if i < L - 1 else z
     ref_loss = torch.nn.functional.cross_entropy(z, labels.long())
     ref_loss.backward()
-    ref = [t.grad for part in (leaf if sage else [leaf[0], leaf[2]]) for t in part] + [z.detach(), ref_loss.detach()]
-    err = [float((p - q).norm() / q.norm()) for p, q in zip(out[0], ref)]
-    assert max(err) <= (6e-2 if bf else 1e-3), err
+    ref = [t.grad for part in (leaf if sage else [leaf[0], leaf[2]]) for t in part] + [z.detach()]
+    losses, bound = [], 6e-2 if bf else 1e-3
+    for timed in (False, True):
+        grads = [[torch.full((p, q), 7.0, device="cuda") for p, q in zip(dims, dims[1:])] for _ in range(2)] + [[torch.full((d,), 7.0, device="cuda") for d in dims[1:]]]
+        logits = torch.zeros(n, dims[-1], device="cuda")
+        say(f"epoch of small products against float64 {kind} {dtype} order={order} n={n} {dims} timed={timed}")
+        losses.append(B.epoch(g, None, layers, x, ld, labels, None, 0.0, logits, grads[0], grads[1] if sage else None, grads[2], 0.0, ws, size, None, None,
+                              want_times=timed)[0])
+        torch.cuda.synchronize()
+        got = [t for part in (grads if sage else [grads[0], grads[2]]) for t in part] + [logits]
+        err = [float((p.double() - q).norm() / q.norm()) for p, q in zip(got, ref)]
+        assert max(err) <= bound and abs(losses[-1] - float(ref_loss)) <= bound * float(ref_loss), (err, losses)
+    assert abs(losses[0] - losses[1]) <= 2e-6 * losses[1]
+    g.close()
 
 
 def test_epochs_of_one_graph_in_many_threads_return_their_own_loss(env):
